@@ -615,54 +615,53 @@ __device__ __forceinline__ void prologue(const __bf16* __restrict__ k, const __b
                             [&](int s) { return s < ROT_SLOTS ? pos_lane : pos_of_slot(s); }, qf);
 }
 
-// Write the wave's 32 x D accumulator as rows: stage O^T through LDS (64 channels at a time) so that every
-// global store instruction writes whole contiguous row segments.
-//   PARTIAL = false: out[orow][:] = bf16(O / l)          PARTIAL = true: ws_o[prow][:] = fp16(O / l)
+// Write the wave's 32 x D accumulator as rows, straight from registers.
+//   PARTIAL = false: out[dst_row][:] = bf16(O / l)       PARTIAL = true: ws_o[dst_row][:] = fp16(O / l)
 // A partial is normalised by its own denominator, so it is a convex combination of V rows and fp16 (11 bits,
 // 8 times finer than the bf16 result) holds it; the merge weighs it with l again.
+// Lanes c and c + 32 hold alternate groups of four channels of row c.  Two swaps of the vector unit give each of them
+// eight neighbouring channels, so a lane stores 16 bytes and a row receives 32 contiguous bytes per instruction; the L2
+// puts the pieces of a line together.  An epilogue is pure latency at the end of a workgroup, so what counts is how
+// short its dependent chain is: staging the rows through LDS for whole-line stores, with two lane permutes per four rows,
+// took 2.4 us of the 12.4 us of a workgroup that walks five key tiles; without it the request over 8 x 512 rows went
+// from 25.6 to 24.1 us, 64 x 512 offline tokens from 296 to 284 us.  64-byte pieces (one more swap) measured no better.
 template <int D, bool PARTIAL>
-__device__ __forceinline__ void store_rows(const Acc<D>& acc, float l_tot, bool valid, int64_t dst_row, void* dst,
-                                           LDS_AS char* wave_buf, int lane)
+__device__ __forceinline__ void store_rows(const Acc<D>& acc, float l_tot, bool valid, int64_t dst_row, void* dst, int lane)
 {
-    constexpr int STRIDE = 64 * 4 + 16; // bytes per staged row: 64 floats + pad
-    const int c = lane & 31, h = lane >> 5;
+    const int h = lane >> 5;
     const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
-    const int r_in = lane >> 4, c4 = lane & 15;
+    auto pack = [&](int db, int q4, int i) { // channels 32 db + 8 q4 + 4 h + 2 i, + 1
+        const float x = acc.o[db][4 * q4 + 2 * i] * inv, y = acc.o[db][4 * q4 + 2 * i + 1] * inv;
+        if (PARTIAL) {
+            f16x2 t;
+            t[0] = (_Float16)x;
+            t[1] = (_Float16)y;
+            return __builtin_bit_cast(uint32_t, t);
+        }
+        bf16x2 t;
+        t[0] = (__bf16)x;
+        t[1] = (__bf16)y;
+        return __builtin_bit_cast(uint32_t, t);
+    };
+    char* row = (char*)dst + (dst_row * D + 8 * h) * 2;
 #pragma unroll
-    for (int half = 0; half < D / 64; ++half) {
+    for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-        for (int dbl = 0; dbl < 2; ++dbl)
+        for (int p = 0; p < 2; ++p) {
+            u32x4 w;
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int db = 2 * half + dbl;
-                f32x4 x;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] = acc.o[db][4 * q4 + e] * inv;
-                *(LDS_AS f32x4*)(wave_buf + c * STRIDE + (32 * dbl + 8 * q4 + 4 * h) * 4) = x;
+            for (int i = 0; i < 2; ++i) {
+                // lanes below 32 keep group 2 p of both halves, lanes from 32 on group 2 p + 1
+                const auto r = __builtin_amdgcn_permlane32_swap(pack(db, 2 * p, i), pack(db, 2 * p + 1, i), false, false);
+                w[i] = r[0];
+                w[2 + i] = r[1];
             }
-        // 4 rows per instruction: lane -> (row 4 rr + lane / 16, channels 4 (lane % 16) .. +3 of this half)
-#pragma unroll
-        for (int rr = 0; rr < 8; ++rr) {
-            const int row = 4 * rr + r_in;
-            const f32x4 x = *(LDS_AS const f32x4*)(wave_buf + row * STRIDE + c4 * 16);
-            const int64_t drow = __shfl(dst_row, row);       // row's owner lane is lane `row` (c == row, h == 0)
-            const int ok = __shfl((int)valid, row);
-            if (ok) {
-                if (PARTIAL) {
-                    f16x4 y;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) y[e] = (_Float16)x[e];
-                    // written once and read once, by the merge kernel: a streaming store (0.7 us less at 6 MB of partials)
-                    __builtin_nontemporal_store(y, (f16x4*)((_Float16*)dst + drow * D + 64 * half + 4 * c4));
-                } else {
-                    bf16x4 y;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) y[e] = (__bf16)x[e];
-                    *(bf16x4*)((__bf16*)dst + drow * D + 64 * half + 4 * c4) = y;
-                }
+            if (valid) {
+                // ordinary stores, partials too: a streaming store would send the 32-byte pieces on before the L2 has
+                // put a line together (8 x 512 rows, 64 query tokens: 25.3 us against 24.1)
+                *(u32x4*)(row + (32 * db + 16 * p) * 2) = w;
             }
         }
-    }
 }
 
 // ---- step 6: query prefill over the assembled cache -------------------------------------------------------------
@@ -727,14 +726,12 @@ __global__ __launch_bounds__(64 * NW, 2) void prefix_attn_kernel(const TrPrefixA
     attn_tiles<D, NW, NS, AUX>((const __bf16*)a.k, (const __bf16*)a.v, w, rc, qf, sd.kv_row0 + n_doc + first_tok, sd.kv_row0, smem, acc);
 
     const float l_tot = acc.l + __shfl_xor(acc.l, 32);
-    __builtin_amdgcn_s_barrier(); // all waves are done with the K/V stages; reuse them as store staging
-    LDS_AS char* wave_buf = smem + wave * (32 * (64 * 4 + 16));
     if (sd.n_split == 1) {
-        store_rows<D, false>(acc, l_tot, rc.valid, (int64_t)rc.orow, a.out, wave_buf, lane);
+        store_rows<D, false>(acc, l_tot, rc.valid, (int64_t)rc.orow, a.out, lane);
     } else {
         const int rows_s = sd.n_q * g;
         const int64_t prow = (int64_t)sd.ws_row0 + (int64_t)(split * a.n_kv_heads + kvh) * rows_s + tok_local * g + rl % g;
-        store_rows<D, true>(acc, l_tot, rc.valid, prow, a.ws_o, wave_buf, lane);
+        store_rows<D, true>(acc, l_tot, rc.valid, prow, a.ws_o, lane);
         // a split in which the row saw no key reports m = -inf so that the merge ignores it
         if (rc.valid && h == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(l_tot > 0.0f ? acc.mref : -INFINITY, l_tot);
     }
@@ -907,14 +904,12 @@ __global__ __launch_bounds__(64 * GATHER_NW, 2) void gather_attn_kernel(const Tr
     }
 
     const float l_tot = acc.l + __shfl_xor(acc.l, 32);
-    __builtin_amdgcn_s_barrier(); // all waves are done with the K/V stages; reuse them as store staging
-    LDS_AS char* wave_buf = smem + wave * (32 * (64 * 4 + 16));
     if (a.n_split == 1) {
-        store_rows<D, false>(acc, l_tot, rc.valid, (int64_t)rc.orow, a.out, wave_buf, lane);
+        store_rows<D, false>(acc, l_tot, rc.valid, (int64_t)rc.orow, a.out, lane);
     } else {
         const int rows_s = a.n_q * g;
         const int64_t prow = (int64_t)(split * a.n_kv_heads + kvh) * rows_s + tok_local * g + rl % g;
-        store_rows<D, true>(acc, l_tot, rc.valid, prow, a.ws_o, wave_buf, lane);
+        store_rows<D, true>(acc, l_tot, rc.valid, prow, a.ws_o, lane);
         if (rc.valid && h == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(l_tot > 0.0f ? acc.mref : -INFINITY, l_tot);
     }
 }
@@ -1291,23 +1286,19 @@ __global__ __launch_bounds__(64 * NW, 2) void blockdiag_attn_kernel(const TrBloc
     attn_tiles<D, NW, NS>((const __bf16*)a.k, (const __bf16*)a.v, w, rc, qf, t_first, lo_last, smem, acc);
 
     const float l_tot = acc.l + __shfl_xor(acc.l, 32);
-    __builtin_amdgcn_s_barrier();
-    LDS_AS char* wave_buf = smem + wave * (32 * (64 * 4 + 16));
     if (sg.n_split == 1) {
-        store_rows<D, false>(acc, l_tot, rc.valid, (int64_t)rc.orow, a.out, wave_buf, lane);
+        store_rows<D, false>(acc, l_tot, rc.valid, (int64_t)rc.orow, a.out, lane);
     } else { // the layout the merge kernel reads: [split][KV head][token of the segment x group]
         const int64_t rows_s = (int64_t)sg.n_tok * g;
         const int64_t prow = (int64_t)sg.ws_row0 + ((int64_t)split * a.n_kv_heads + kvh) * rows_s + (int64_t)(t - sg.tok0) * g + rl % g;
-        store_rows<D, true>(acc, l_tot, rc.valid, prow, a.ws_o, wave_buf, lane);
+        store_rows<D, true>(acc, l_tot, rc.valid, prow, a.ws_o, lane);
         if (rc.valid && lane < 32) *(float2*)(a.ws_ml + prow * 2) = make_float2(l_tot > 0.0f ? acc.mref : -INFINITY, l_tot);
     }
 }
 
 template <int D, int NW, int NS> constexpr int smem_bytes()
 {
-    constexpr int stages = NS * Geo<D>::STAGE_BYTES;
-    constexpr int staging = NW * 32 * (64 * 4 + 16);
-    return stages > staging ? stages : staging;
+    return NS * Geo<D>::STAGE_BYTES;
 }
 
 template <int D, int NW, int NS, bool HALF, int AUX = 0>
@@ -1340,8 +1331,7 @@ template <int D, bool HALF>
 int launch_gather(const TrGatherArgs& a, hipStream_t s)
 {
     auto kern = gather_attn_kernel<D, HALF>;
-    constexpr int staging = GATHER_NW * 32 * (64 * 4 + 16);
-    constexpr int lds = gather_lds_bytes<D>() > staging ? gather_lds_bytes<D>() : staging;
+    constexpr int lds = gather_lds_bytes<D>();
     static std::atomic<uint64_t> configured{0};
     if (int rc = tr_raise_lds_limit((const void*)kern, lds, &configured)) return rc;
     hipLaunchKernelGGL(kern, dim3(a.n_items), dim3(64 * GATHER_NW), lds, s, a);

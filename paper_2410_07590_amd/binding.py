@@ -1,8 +1,9 @@
-"""ctypes binding of libturborag_hip.so - same names as include/turborag.h, argument marshalling only.
+"""Binding of libturborag_hip.so - same names as include/turborag.h, argument marshalling only.
 
 Every step of the hot path runs in the library's HIP kernels.  torch is used for device
-memory and for the current stream handle; nothing here computes.  If the library is missing
-the import fails loudly: there is no fallback path.
+memory and for the current stream handle; nothing here computes.  The calls that enqueue work
+are marshalled by the extension module _tr_host (csrc/py_host.cpp), the others by ctypes.  If
+either is missing the first use fails loudly: there is no fallback path.
 """
 import ctypes as C
 import os
@@ -46,6 +47,7 @@ class TurboRagError(RuntimeError):
 
 
 _lib = None
+_ext = None   # the extension module, once it is bound to _lib's entry points
 
 
 def lib_path():
@@ -54,10 +56,11 @@ def lib_path():
 
 def lib():
     """Load the in-tree library (it must have been built: __graft_entry__.build() or `python -m ...build`)."""
-    global _lib
+    global _lib, _ext
     if _lib is None:
-        if not os.path.exists(_build.LIB):
-            raise RuntimeError("libturborag_hip.so is not built; run `python -m paper_2410_07590_amd.build`")
+        if not os.path.exists(_build.LIB) or not os.path.exists(_build.HOST):
+            raise RuntimeError("libturborag_hip.so or _tr_host.so is not built; run `python -m paper_2410_07590_amd.build`")
+        from . import _tr_host
         L = C.CDLL(_build.LIB)
         L.tr_last_error.restype = C.c_char_p
         for name in ("tr_prefill_attn_workspace_size", "tr_prefill_attn_batched_workspace_size",
@@ -66,8 +69,16 @@ def lib():
                      "tr_linear_workspace_size", "tr_prefill_attn_static_scratch_bytes",
                      "tr_probe_mfma_loop_sink_bytes"):
             getattr(L, name).restype = C.c_size_t
-        _lib = L
+        _tr_host.bind({name: C.cast(getattr(L, name), C.c_void_p).value for name in EXPORTS}, TurboRagError,
+                      getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None))
+        _ext, _lib = _tr_host, L
     return _lib
+
+
+def _native():
+    if _lib is None:
+        lib()
+    return _ext
 
 
 def _check(rc):
@@ -140,62 +151,32 @@ def tr_store_create(shape, k_store, v_store, chunk_row_start):
 
 def tr_plan(store, chunk_ids, pos_mode, want_pos_ids=True):
     """Returns (offsets int64[n+1], pos_ids int32[n_doc] or None)."""
-    ids, ids_p = _host(chunk_ids, np.int32)
-    offsets = np.zeros(ids.size + 1, np.int64)
-    _check(lib().tr_plan(store.handle, ids_p, C.c_int32(ids.size), C.c_int32(pos_mode),
-                         offsets.ctypes.data_as(C.c_void_p), None, C.c_int64(0)))
-    if not want_pos_ids:
-        return offsets, None
-    pos = np.zeros(int(offsets[-1]), np.int32)
-    _check(lib().tr_plan(store.handle, ids_p, C.c_int32(ids.size), C.c_int32(pos_mode),
-                         offsets.ctypes.data_as(C.c_void_p), pos.ctypes.data_as(C.c_void_p), C.c_int64(pos.size)))
-    return offsets, pos
+    return _native().plan(store, chunk_ids, pos_mode, want_pos_ids)
 
 
 def tr_kv_assemble(store, chunk_ids, offsets, pos_mode, out_k, out_v, stream=None):
-    ids, ids_p = _host(chunk_ids, np.int32)
-    off, off_p = _host(offsets, np.int64)
-    _check(lib().tr_kv_assemble(store.handle, ids_p, off_p, C.c_int32(ids.size), C.c_int32(pos_mode),
-                                _dev(out_k), _dev(out_v), C.c_int64(out_k.shape[0]), _stream(stream)))
+    _native().kv_assemble(store, chunk_ids, offsets, pos_mode, out_k, out_v, stream)
 
 
 def tr_kv_assemble_raw(store, chunk_ids, offsets, pos_mode, out_k, out_v, stream=None):
     """`store` holds un-rotated keys; every key is turned once, at its position id."""
-    ids, ids_p = _host(chunk_ids, np.int32)
-    off, off_p = _host(offsets, np.int64)
-    _check(lib().tr_kv_assemble_raw(store.handle, ids_p, off_p, C.c_int32(ids.size), C.c_int32(pos_mode),
-                                    _dev(out_k), _dev(out_v), C.c_int64(out_k.shape[0]), _stream(stream)))
+    _native().kv_assemble_raw(store, chunk_ids, offsets, pos_mode, out_k, out_v, stream)
 
 
 def tr_kv_assemble_batched(store, chunk_ids, cu_chunks, pos_modes, cache_row_start, out_k, out_v, stream=None):
-    ids, ids_p = _host(chunk_ids, np.int32)
-    cu, cu_p = _host(cu_chunks, np.int32)
-    pm, pm_p = _host(pos_modes, np.int32)
-    rs, rs_p = _host(cache_row_start, np.int64)
-    _check(lib().tr_kv_assemble_batched(store.handle, ids_p, cu_p, pm_p, rs_p, C.c_int32(pm.size),
-                                        _dev(out_k), _dev(out_v), C.c_int64(out_k.shape[0]), _stream(stream)))
+    _native().kv_assemble_batched(store, chunk_ids, cu_chunks, pos_modes, cache_row_start, out_k, out_v, stream)
 
 
 def tr_kv_append(shape, k_new, v_new, q_pos, cache_k, cache_v, dst_row, stream=None):
-    _check(lib().tr_kv_append(C.byref(shape), _dev(k_new), _dev(v_new), _dev(q_pos), C.c_int32(k_new.shape[0]),
-                              _dev(cache_k), _dev(cache_v), C.c_int64(dst_row), C.c_int64(cache_k.shape[0]),
-                              _stream(stream)))
+    _native().kv_append(shape, k_new, v_new, q_pos, cache_k, cache_v, dst_row, stream)
 
 
 def tr_kv_assemble_append(store, chunk_ids, offsets, pos_mode, k_new, v_new, q_pos, out_k, out_v, stream=None):
-    ids, ids_p = _host(chunk_ids, np.int32)
-    off, off_p = _host(offsets, np.int64)
-    _check(lib().tr_kv_assemble_append(store.handle, ids_p, off_p, C.c_int32(ids.size), C.c_int32(pos_mode), _dev(k_new), _dev(v_new),
-                                       _dev(q_pos), C.c_int32(k_new.shape[0]), _dev(out_k), _dev(out_v), C.c_int64(out_k.shape[0]),
-                                       _stream(stream)))
+    _native().kv_assemble_append(store, chunk_ids, offsets, pos_mode, k_new, v_new, q_pos, out_k, out_v, stream)
 
 
 def tr_kv_append_batched(shape, k_new, v_new, q_pos, cu_q, cache_row_start, cache_k, cache_v, stream=None):
-    cu, cu_p = _host(cu_q, np.int32)
-    rs, rs_p = _host(cache_row_start, np.int64)
-    _check(lib().tr_kv_append_batched(C.byref(shape), _dev(k_new), _dev(v_new), _dev(q_pos), cu_p, rs_p,
-                                      C.c_int32(cu.size - 1), _dev(cache_k), _dev(cache_v),
-                                      C.c_int64(cache_k.shape[0]), _stream(stream)))
+    _native().kv_append_batched(shape, k_new, v_new, q_pos, cu_q, cache_row_start, cache_k, cache_v, stream)
 
 
 def tr_prefill_attn_workspace_size(shape, n_q, kv_len):
@@ -203,9 +184,7 @@ def tr_prefill_attn_workspace_size(shape, n_q, kv_len):
 
 
 def tr_prefill_attn(shape, q, k, v, q_pos, kv_len, out, workspace=None, stream=None):
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().tr_prefill_attn(C.byref(shape), _dev(q), _dev(k), _dev(v), _dev(q_pos), C.c_int32(q.shape[0]),
-                                 C.c_int64(kv_len), _dev(out), _dev(workspace), C.c_size_t(ws_bytes), _stream(stream)))
+    _native().prefill_attn(shape, q, k, v, q_pos, kv_len, out, workspace, stream)
 
 
 def tr_prefill_attn_static_scratch_bytes():
@@ -214,8 +193,7 @@ def tr_prefill_attn_static_scratch_bytes():
 
 def tr_prefill_attn_static(shape, q, k, v, q_pos, kv_len, out, stream=None):
     """tr_prefill_attn with the library's own static scratch array instead of a workspace (no device allocation)."""
-    _check(lib().tr_prefill_attn_static(C.byref(shape), _dev(q), _dev(k), _dev(v), _dev(q_pos), C.c_int32(q.shape[0]),
-                                        C.c_int64(kv_len), _dev(out), _stream(stream)))
+    _native().prefill_attn_static(shape, q, k, v, q_pos, kv_len, out, stream)
 
 
 def tr_set_tuning(name, value):
@@ -241,12 +219,7 @@ def tr_prefill_attn_batched_workspace_size(shape, cu_q, cache_row_start):
 
 
 def tr_prefill_attn_batched(shape, q, k, v, q_pos, cu_q, cache_row_start, out, workspace=None, stream=None):
-    cu, cu_p = _host(cu_q, np.int32)
-    rs, rs_p = _host(cache_row_start, np.int64)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().tr_prefill_attn_batched(C.byref(shape), _dev(q), _dev(k), _dev(v), _dev(q_pos), cu_p, rs_p,
-                                         C.c_int32(cu.size - 1), _dev(out), _dev(workspace), C.c_size_t(ws_bytes),
-                                         _stream(stream)))
+    _native().prefill_attn_batched(shape, q, k, v, q_pos, cu_q, cache_row_start, out, workspace, stream)
 
 
 def tr_prefill_attn_gather_workspace_size(store, chunk_ids, offsets, pos_mode, n_q):
@@ -257,12 +230,7 @@ def tr_prefill_attn_gather_workspace_size(store, chunk_ids, offsets, pos_mode, n
 
 
 def tr_prefill_attn_gather(store, chunk_ids, offsets, pos_mode, q, cache_k, cache_v, q_pos, out, workspace=None, stream=None):
-    ids, ids_p = _host(chunk_ids, np.int32)
-    off, off_p = _host(offsets, np.int64)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().tr_prefill_attn_gather(store.handle, ids_p, off_p, C.c_int32(ids.size), C.c_int32(pos_mode), _dev(q), _dev(cache_k),
-                                        _dev(cache_v), _dev(q_pos), C.c_int32(q.shape[0]), C.c_int64(cache_k.shape[0]), _dev(out),
-                                        _dev(workspace), C.c_size_t(ws_bytes), _stream(stream)))
+    _native().prefill_attn_gather(store, chunk_ids, offsets, pos_mode, q, cache_k, cache_v, q_pos, out, workspace, stream)
 
 
 def tr_decode_attn_workspace_size(shape, cache_row_start):
@@ -271,10 +239,7 @@ def tr_decode_attn_workspace_size(shape, cache_row_start):
 
 
 def tr_decode_attn(shape, q, k, v, q_pos, cache_row_start, out, workspace=None, stream=None):
-    rs, rs_p = _host(cache_row_start, np.int64)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().tr_decode_attn(C.byref(shape), _dev(q), _dev(k), _dev(v), _dev(q_pos), rs_p, C.c_int32(rs.size - 1),
-                                _dev(out), _dev(workspace), C.c_size_t(ws_bytes), _stream(stream)))
+    _native().decode_attn(shape, q, k, v, q_pos, cache_row_start, out, workspace, stream)
 
 
 def tr_chunk_prefill_attn_workspace_size(shape, total_tokens, max_chunk_len):
@@ -282,11 +247,7 @@ def tr_chunk_prefill_attn_workspace_size(shape, total_tokens, max_chunk_len):
 
 
 def tr_chunk_prefill_attn(shape, q, k, v, cu_chunk_lens, n_chunks, max_chunk_len, out, k_rot_out, workspace, stream=None):
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().tr_chunk_prefill_attn(C.byref(shape), _dev(q), _dev(k), _dev(v), _dev(cu_chunk_lens),
-                                       C.c_int32(n_chunks), C.c_int64(q.shape[0]), C.c_int32(max_chunk_len),
-                                       _dev(out), _dev(k_rot_out), _dev(workspace), C.c_size_t(ws_bytes),
-                                       _stream(stream)))
+    _native().chunk_prefill_attn(shape, q, k, v, cu_chunk_lens, n_chunks, max_chunk_len, out, k_rot_out, workspace, stream)
 
 
 def tr_sequence_plan(chunk_lens, n_tail, pos_mode, tail_start=-1):
@@ -309,11 +270,7 @@ def tr_sequence_prefill_attn_workspace_size(shape, seg_start_host, total_tokens)
 
 def tr_sequence_prefill_attn(shape, q, k, v, seg_start, pos, out, k_rot_out, seg_start_host=None, workspace=None, stream=None):
     """seg_start_host: the host array tr_sequence_plan returned (lets the library cut long key ranges into pieces)."""
-    h = None if seg_start_host is None else np.ascontiguousarray(seg_start_host, dtype=np.int32)
-    hp = C.c_void_p(0) if h is None else h.ctypes.data_as(C.c_void_p)
-    _check(lib().tr_sequence_prefill_attn(C.byref(shape), _dev(q), _dev(k), _dev(v), _dev(seg_start), _dev(pos), hp,
-                                          C.c_int64(q.shape[0]), _dev(out), _dev(k_rot_out), _dev(workspace),
-                                          C.c_size_t(0 if workspace is None else workspace.numel()), _stream(stream)))
+    _native().sequence_prefill_attn(shape, q, k, v, seg_start, pos, out, k_rot_out, seg_start_host, workspace, stream)
 
 
 def _features(n_features):
@@ -330,14 +287,7 @@ def tr_linear(x, w, y, workspace=None, stream=None):
     """y[j][M, N_j] = x[M, K] @ w[j][N_j, K]^T, bf16, at most 128 rows of x.  w, y: one tensor each, or lists of up to four
     that share x."""
     ws_, ys_ = (list(w), list(y)) if isinstance(w, (list, tuple)) else ([w], [y])
-    M, K = x.shape
-    for wj, yj in zip(ws_, ys_):
-        assert wj.shape[1] == K and yj.numel() == M * wj.shape[0]
-    f, fp = _features([wj.shape[0] for wj in ws_])
-    wp = (C.c_void_p * len(ws_))(*[_dev(t) for t in ws_])
-    yp = (C.c_void_p * len(ys_))(*[_dev(t) for t in ys_])
-    _check(lib().tr_linear(_dev(x), C.c_int32(M), C.c_int32(K), C.c_int32(len(ws_)), wp, yp, fp, _dev(workspace),
-                           C.c_size_t(0 if workspace is None else workspace.numel()), _stream(stream)))
+    _native().linear(x, ws_, ys_, workspace, stream)
 
 
 def workspace(nbytes, device="cuda"):

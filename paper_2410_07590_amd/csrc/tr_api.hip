@@ -100,8 +100,15 @@ int tr_check_shape(const tr_shape* s)
 
 void tr_fill_theta(const tr_shape* s, double* theta)
 {
-    for (int m = 0; m < 64; ++m) theta[m] = 0.0;
-    for (int m = 0; m < s->head_dim / 2; ++m) theta[m] = pow(s->rope_base, -2.0 * (double)m / (double)s->head_dim);
+    // every call needs the table and a process meets one or two (base, head_dim): 64 powers are 2 us of host time
+    static thread_local double base = 0.0, table[64];
+    static thread_local int32_t head_dim = 0;
+    if (base != s->rope_base || head_dim != s->head_dim) {
+        for (int m = 0; m < 64; ++m) table[m] = m < s->head_dim / 2 ? pow(s->rope_base, -2.0 * (double)m / (double)s->head_dim) : 0.0;
+        base = s->rope_base;
+        head_dim = s->head_dim;
+    }
+    memcpy(theta, table, sizeof table);
 }
 
 static const int64_t ROW_LIMIT = ((int64_t)1 << 31) - 1;

@@ -1,0 +1,35 @@
+"""The extension module behind the binding: what it accepts, converts and refuses (CPU: nothing is enqueued)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2410_07590_amd import binding as B
+
+
+@pytest.fixture(scope="module")
+def store():
+    B.lib()
+    sh = B.make_shape(4, 4, 64, "f32", 1e4)
+    sh_store = B.Store(sh, None, None, [0, 0, 0])  # two empty chunks: no memory is behind it
+    return sh_store
+
+
+@pytest.mark.parametrize("ids", [[1, 0, 1], (1, 0, 1), np.array([1, 0, 1], np.int64), np.array([1, 9, 0, 9, 1, 9], np.int32)[::2],
+                                 np.array([1.0, 0.0, 1.0]), torch.tensor([1, 0, 1])])
+def test_host_arrays_are_converted_as_numpy_does(store, ids):
+    offsets, pos = B.tr_plan(store, ids, B.TR_POS_REORDERED)
+    assert offsets.dtype == np.int64 and offsets.tolist() == [0, 0, 0, 0]
+    assert pos.dtype == np.int32 and pos.size == 0
+    assert B.tr_plan(store, ids, np.int32(0), want_pos_ids=False)[1] is None
+
+
+def test_library_errors_and_wrong_arguments(store):
+    with pytest.raises(B.TurboRagError) as e:
+        B.tr_plan(store, [2], B.TR_POS_REORDERED)
+    assert e.value.code == B.TR_ERR_BAD_CHUNK_ID and "chunk_ids[0]" in str(e.value)
+    with pytest.raises(AssertionError):  # a host tensor where device memory is expected
+        B.tr_kv_append(store.shape, torch.zeros(1, 4, 64), None, None, None, None, 0, stream=0)
+    with pytest.raises(TypeError):
+        B.tr_kv_append(store.shape, "k", None, None, None, None, 0, stream=0)
+    with pytest.raises(AttributeError):
+        B.tr_plan(None, [0], B.TR_POS_REORDERED)

@@ -1,0 +1,35 @@
+"""fp32 attention at the edges of its key batches (32 groups of 8 keys at head_dim 64, 16 at 128, a quarter of that when there
+are many rows) and on both sides of the rule that chooses the waves per row, against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2410_07590_amd import synth
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("head_dim,n_doc,n_q,layout", [
+    (64, 1, 1, 0),        # two keys: all groups but two are empty
+    (64, 253, 4, 1),      # rows that see 254 .. 257 keys, the batch being 256
+    (64, 600, 3, 0),      # a remainder in the third batch
+    (128, 125, 5, 0),     # 126 .. 130 keys, the batch being 128
+    (128, 300, 2, 1),
+    (64, 61, 1030, 0),    # 4 x 1030 rows: two waves per row, 62 .. 1091 keys in batches of 64
+    (128, 30, 513, 1),    # one row block above the rule's line (4 x 513 rows), batches of 32 keys
+])
+def test_f32_attention_edges(head_dim, n_doc, n_q, layout):
+    from paper_2410_07590_amd import binding as B
+    sh = synth.Shape(4, 2, head_dim, "f32", 1e4, layout)
+    rng = np.random.Generator(np.random.PCG64([31, head_dim, n_doc, n_q]))
+    row_start = np.array([0, n_doc], np.int64)
+
+    def draw(n, heads):
+        return synth.normal_tensor(rng, (n, heads, head_dim), sh.torch_dtype)
+
+    store = synth.Store(draw(n_doc, 2), draw(n_doc, 2), row_start)
+    sd = B.Store(H.gpu_shape(B, sh), store.k.cuda(), store.v.cuda(), row_start)
+    req = synth.Request(np.array([0], np.int32), synth.POS_REORDERED, n_q, draw(n_q, 4), draw(n_q, 2), draw(n_q, 2),
+                        (n_doc + np.arange(n_q)).astype(np.int32), n_doc, [n_doc])
+    rows = None if n_q < 100 else np.linspace(0, n_q - 1, 40).astype(int)
+    H.check_request(B, sh, store, sd, req, rows=rows, k_mismatch_frac=1e-4)

@@ -233,7 +233,7 @@ int launch_runs(const tr_store* store, const std::vector<CopyRun>& runs, void* o
         if (tail && i == runs.size()) { // last launch carries the append
             a.app = *tail;
             a.app.first_block = blocks;
-            blocks += (int)(((int64_t)tail->n_q * (sh->head_dim / 2) + 255) / 256);
+            blocks += (int)(((int64_t)tail->n_q + TR_APPEND_TOKENS_PER_BLOCK - 1) / TR_APPEND_TOKENS_PER_BLOCK);
         }
         int rc = tr_launch_assemble(a, sh->dtype, blocks, stream);
         if (rc) return rc;
@@ -341,7 +341,7 @@ int launch_append(const tr_shape* shape, const void* k_new, const void* v_new, c
     while (i < descs.size()) {
         int n = 0, tokens = 0;
         while (i < descs.size() && n < TR_MAX_APPEND_DESC) {
-            if (descs[i].n_q > 0) { a.desc[n++] = descs[i]; tokens += descs[i].n_q; }
+            if (descs[i].n_q > 0) { a.tok0[n] = tokens; a.desc[n++] = descs[i]; tokens += descs[i].n_q; }
             ++i;
         }
         a.n_desc = n;
@@ -417,7 +417,7 @@ extern "C" int tr_kv_assemble_append(const tr_store* store, const int32_t* chunk
     tail.n_q = n_q;
     tail.dst_row0 = (int32_t)off;
     tail.first_block = 0;
-    tail.n_kv_heads = store->shape.n_kv_heads;
+    tail.pad_ = 0;
     return launch_runs(store, runs, out_k, out_v, (hipStream_t)stream, &tail);
     });
 }
@@ -464,7 +464,7 @@ extern "C" int tr_kv_assemble_raw(const tr_store* store, const int32_t* chunk_id
     const int rc = request_runs("tr_kv_assemble_raw", store, chunk_ids, offsets, n_chunks, pos_mode, out_k, out_v, out_capacity_rows, &runs);
     if (rc) return rc;
     // every row is a token whose key is turned once, at its position id (the run's first id plus the row's index):
-    // the arithmetic of the query append, one thread per (row, channel pair)
+    // the arithmetic of the query append, one wave per row
     std::vector<TrAppendDesc> d;
     d.reserve(runs.size());
     for (const CopyRun& r : runs) {

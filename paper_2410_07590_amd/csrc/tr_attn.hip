@@ -114,6 +114,18 @@ template <bool MAX> __device__ __forceinline__ int wave_reduce_i(int v)
 __device__ __forceinline__ int wave_max_i(int v) { return wave_reduce_i<true>(v); }
 __device__ __forceinline__ int wave_min_i(int v) { return wave_reduce_i<false>(v); }
 
+// Index of the last of n ascending entries that is <= x, for a wave-uniform x >= first(0): every lane looks at its own
+// entry and a ballot counts.  One trip to the argument block, where a search takes one for every step, some hundred
+// nanoseconds each, before a workgroup knows what to load (64 decode requests: six).  Every lane must be active.
+template <class First> __device__ __forceinline__ int last_not_above(int n, int x, First first)
+{
+    if (n == 1) return 0;
+    const int lane = threadIdx.x & 63;
+    int count = 0;
+    for (int i0 = 0; i0 < n; i0 += 64) count += __popcll(__ballot(i0 + lane < n && first(min(i0 + lane, n - 1)) <= x));
+    return count - 1;
+}
+
 // ---- rotated queries (Eq. 3 at the token's position id) -------------------------------------------------------
 // Lane (c = lane & 31, h = lane >> 5) ends up holding Q'[row c][16 ks + 8 h .. +7] for ks < D/16, scaled by
 // log2(e)/sqrt(d) before its single rounding to bf16.  Angles are reduced in fp64 to [-1/2, 1/2] revolutions and
@@ -674,12 +686,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefix_attn_kernel(const TrPrefixA
     extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
     LDS_AS char* smem = (LDS_AS char*)smem_raw;
     const int item = xcd_remap(blockIdx.x, a.n_items);
-    int lo = 0, hi = a.n_seq - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (a.seq[mid].item0 <= item) lo = mid; else hi = mid - 1;
-    }
-    const TrSeqDesc sd = a.seq[lo];
+    const TrSeqDesc sd = a.seq[last_not_above(a.n_seq, item, [&](int i) { return a.seq[i].item0; })];
     const int local = item - sd.item0;
     const int tile = local % sd.n_tiles;
     const int rest = local / sd.n_tiles;
@@ -782,8 +789,7 @@ __global__ __launch_bounds__(64 * GATHER_NW, 2) void gather_attn_kernel(const Tr
     int g1 = min(g0 + a.tiles_per_split, a.n_tiles_total);
     g1 = min(g1, a.seg[tail].tile0 + last_tok / KT + 1);
     const int n_tiles = g1 > g0 ? g1 - g0 : 0;
-    int s_issue = 0;
-    while (s_issue + 1 < a.n_seg && a.seg[s_issue + 1].tile0 <= g0) ++s_issue;
+    int s_issue = last_not_above(a.n_seg, g0, [&](int i) { return a.seg[i].tile0; });
     int s_comp = s_issue;
 
     const int64_t row_elems = (int64_t)a.n_kv_heads * D;
@@ -934,12 +940,7 @@ __global__ __launch_bounds__(64 * SHORT_NW, 1) void short_attn_kernel(const TrPr
     extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
     LDS_AS char* smem = (LDS_AS char*)smem_raw;
     const int item = xcd_remap(blockIdx.x, a.n_items);
-    int lo = 0, hi = a.n_seq - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (a.seq[mid].item0 <= item) lo = mid; else hi = mid - 1;
-    }
-    const TrSeqDesc sd = a.seq[lo];
+    const TrSeqDesc sd = a.seq[last_not_above(a.n_seq, item, [&](int i) { return a.seq[i].item0; })];
     const int local = item - sd.item0;
     const int tile = local % sd.n_tiles;
     const int rest = local / sd.n_tiles;
@@ -1115,15 +1116,17 @@ __global__ __launch_bounds__(256) void combine_kernel(const TrPrefixArgs a, int 
     constexpr int CPLN = D / LPR;               // channels per lane: 4 or 2
     const int lane_r = threadIdx.x & 31;
     const int64_t R = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
-    if (R >= total_rows) return;
     const int tq = a.seq[0].q_row0 + (int)(R / a.n_q_heads);
     const int hq = (int)(R % a.n_q_heads);
-    int lo = 0, hi = a.n_seq - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (a.seq[mid].q_row0 <= tq) lo = mid; else hi = mid - 1;
+    int sq = 0;
+    if (a.n_seq > 1) { // the wave's two rows may belong to two requests
+        auto first = [&](int i) { return a.seq[i].q_row0; };
+        const int s0 = last_not_above(a.n_seq, __builtin_amdgcn_readlane(tq, 0), first);
+        const int s1 = last_not_above(a.n_seq, __builtin_amdgcn_readlane(tq, 32), first);
+        sq = (threadIdx.x & 32) ? s1 : s0;
     }
-    const TrSeqDesc sd = a.seq[lo];
+    if (R >= total_rows) return;
+    const TrSeqDesc sd = a.seq[sq];
     if (sd.n_split == 1) return;
     const int g = a.group;
     const int kvh = hq / g;
@@ -1207,12 +1210,7 @@ __global__ __launch_bounds__(64 * NW, 2) void blockdiag_attn_kernel(const TrBloc
     const int item = xcd_remap(blockIdx.x, a.items_per_head * a.n_kv_heads);
     const int kvh = item / a.items_per_head;
     const int j = item % a.items_per_head;
-    int slo = 0, shi = a.n_seg - 1;
-    while (slo < shi) {
-        const int mid = (slo + shi + 1) >> 1;
-        if (a.seg[mid].item0 <= j) slo = mid; else shi = mid - 1;
-    }
-    const TrBdSeg sg = a.seg[slo];
+    const TrBdSeg sg = a.seg[last_not_above(a.n_seg, j, [&](int i) { return a.seg[i].item0; })];
     // last row tiles first: under a causal mask they walk the most keys (a query behind the documents walks all of
     // them), so they must not be the ones that start last
     const int tile = sg.tile_hi - (j - sg.item0) / sg.n_split;

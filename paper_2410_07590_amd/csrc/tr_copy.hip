@@ -130,99 +130,63 @@ __device__ __forceinline__ uint4 ld_stream(const uint4* p)
     return make_uint4(r[0], r[1], r[2], r[3]);
 }
 
-constexpr int APPEND_MAX_HEADS = 16; // KV heads held in registers at once; more go round the loop again
+// ---- one row of the query append: K' rotated at its position id, V copied, for every KV head -----------------
+// A wave owns a token: lane m computes (cos, sin) of pair m once (the fp64 sincos is by far the longest thing here, so
+// it is done once per pair and token, and the first loads go out before it), parks it in LDS, and the lanes then walk
+// the row in 16-byte units.  64 is a multiple of the units per head, so a lane keeps its unit position, hence its pairs.
+// Nothing is shared between waves, so there is no barrier: the only dependent chain is load, angle, rotate, store.
+// (A thread per pair that walked all heads in 2- or 4-byte pieces took 7.6 us for 21 tokens of 8 heads and 10.8 us for 64
+// requests of one token, 5.3 and 4.7 us as it is here; a thread per unit with an angle for each of its pairs took
+// 15.1 us for 6200 rows of 4 heads, half-split layout, now 12.5 us.)
+constexpr int APPEND_WAVES = TR_APPEND_TOKENS_PER_BLOCK;
+constexpr int APPEND_UNITS = 4;  // 16-byte units of K (and of V) a lane has in flight
 
-// The same for the half-split layout: the pair is (channel m, channel m + d/2) of every head.
-template <int DTYPE>
-__device__ __forceinline__ void append_pair_half(const void* k_new, const void* v_new, int pos, void* cache_k,
-                                                 void* cache_v, int n_kv_heads, int half, double theta_m, int64_t src_row,
-                                                 int64_t dst_row, int m)
-{
-    typedef typename std::conditional<DTYPE == TR_BF16, uint16_t, float>::type Elem;
-    const int d = 2 * half;
-    const Elem* ks = (const Elem*)k_new + src_row * n_kv_heads * d + m;
-    const Elem* vs = (const Elem*)v_new + src_row * n_kv_heads * d + m;
-    Elem* kd = (Elem*)cache_k + dst_row * n_kv_heads * d + m;
-    Elem* vd = (Elem*)cache_v + dst_row * n_kv_heads * d + m;
-    const double angle = (double)pos * theta_m;
-    double sn = 0.0, cn = 1.0;
-    for (int h0 = 0; h0 < n_kv_heads; h0 += APPEND_MAX_HEADS) {
-        Elem ka[APPEND_MAX_HEADS], kb[APPEND_MAX_HEADS], va[APPEND_MAX_HEADS], vb[APPEND_MAX_HEADS];
-#pragma unroll
-        for (int j = 0; j < APPEND_MAX_HEADS; ++j)
-            if (h0 + j < n_kv_heads) {
-                ka[j] = ks[(h0 + j) * d];
-                kb[j] = ks[(h0 + j) * d + half];
-                if (v_new) { va[j] = vs[(h0 + j) * d]; vb[j] = vs[(h0 + j) * d + half]; }
-            }
-        if (h0 == 0) sincos(angle, &sn, &cn);
-#pragma unroll
-        for (int j = 0; j < APPEND_MAX_HEADS; ++j)
-            if (h0 + j < n_kv_heads) {
-                double xa, xb, ya, yb;
-                if constexpr (DTYPE == TR_BF16) {
-                    xa = bf16_bits_to_double(ka[j]);
-                    xb = bf16_bits_to_double(kb[j]);
-                } else {
-                    xa = (double)ka[j];
-                    xb = (double)kb[j];
-                }
-                rotate_pair(xa, xb, cn, sn, ya, yb);
-                if constexpr (DTYPE == TR_BF16) {
-                    kd[(h0 + j) * d] = (uint16_t)double_to_bf16_bits(ya);
-                    kd[(h0 + j) * d + half] = (uint16_t)double_to_bf16_bits(yb);
-                } else {
-                    kd[(h0 + j) * d] = __double2float_rn(ya);
-                    kd[(h0 + j) * d + half] = __double2float_rn(yb);
-                }
-                if (v_new) { vd[(h0 + j) * d] = va[j]; vd[(h0 + j) * d + half] = vb[j]; }
-            }
-    }
-}
-
-// ---- one (token, pair m) of the query append: K' rotated at q_pos, V copied, for every KV head ----------------
-// The angle is shared by all KV heads of the token (the fp64 sincos is by far the longest thing a thread does, so
-// it is done once per thread), and the loads go out before it.
 template <int DTYPE, bool HALF>
-__device__ __forceinline__ void append_pair(const void* k_new, const void* v_new, int pos, void* cache_k,
-                                            void* cache_v, int n_kv_heads, int half, double theta_m, int64_t src_row,
-                                            int64_t dst_row, int m)
+__device__ __forceinline__ void append_token(const void* k_new, const void* v_new, int pos, void* cache_k, void* cache_v, int row_units,
+                                             int head_units, int half_dim, const double* theta, int64_t src_row, int64_t dst_row,
+                                             double2* cs /* LDS, 64 entries of this wave's own */, int lane)
 {
-    if constexpr (HALF) {
-        append_pair_half<DTYPE>(k_new, v_new, pos, cache_k, cache_v, n_kv_heads, half, theta_m, src_row, dst_row, m);
-        return;
-    }
-    typedef typename std::conditional<DTYPE == TR_BF16, uint32_t, float2>::type Pair; // one (even, odd) channel pair
-    const Pair* ks = (const Pair*)k_new + src_row * n_kv_heads * half + m;
-    const Pair* vs = (const Pair*)v_new + src_row * n_kv_heads * half + m;
-    Pair* kd = (Pair*)cache_k + dst_row * n_kv_heads * half + m;
-    Pair* vd = (Pair*)cache_v + dst_row * n_kv_heads * half + m;
-    const double angle = (double)pos * theta_m;
-    double sn = 0.0, cn = 1.0;
-    for (int h0 = 0; h0 < n_kv_heads; h0 += APPEND_MAX_HEADS) {
-        Pair kx[APPEND_MAX_HEADS], vx[APPEND_MAX_HEADS];
+    const uint4* ks = (const uint4*)k_new + src_row * row_units;
+    const uint4* vs = (const uint4*)v_new + src_row * row_units;
+    uint4* kd = (uint4*)cache_k + dst_row * row_units;
+    uint4* vd = (uint4*)cache_v + dst_row * row_units;
+    constexpr int N_CS = HALF ? UnitHalf<DTYPE>::ELEMS : Unit<DTYPE>::PAIRS; // pairs a unit takes part in
+    const int hu = lane % head_units, hmask = head_units >> 1;
+    const bool low = hu < hmask;
+    const int m0 = (HALF && !low ? hu - hmask : hu) * N_CS;
+    double c[N_CS], s[N_CS];
+    for (int u0 = lane; u0 - lane < row_units; u0 += 64 * APPEND_UNITS) { // wave-uniform trip count
+        uint4 kx[APPEND_UNITS], vx[APPEND_UNITS];
 #pragma unroll
-        for (int j = 0; j < APPEND_MAX_HEADS; ++j)
-            if (h0 + j < n_kv_heads) {
-                kx[j] = ks[(h0 + j) * half];
-                if (v_new) vx[j] = vs[(h0 + j) * half];
+        for (int i = 0; i < APPEND_UNITS; ++i)
+            if (u0 + 64 * i < row_units) {
+                kx[i] = ld_stream(ks + u0 + 64 * i);
+                if (v_new) vx[i] = ld_stream(vs + u0 + 64 * i);
             }
-        if (h0 == 0) sincos(angle, &sn, &cn);
+        if (u0 == lane) {
+            if (lane < half_dim) {
+                double sn, cn;
+                sincos((double)pos * theta[lane], &sn, &cn);
+                cs[lane] = make_double2(cn, sn);
+            }
+            // LDS serves a wave's accesses in order; only the compiler has to keep them so
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int j = 0; j < APPEND_MAX_HEADS; ++j)
-            if (h0 + j < n_kv_heads) {
-                double xa, xb, ya, yb;
-                if constexpr (DTYPE == TR_BF16) {
-                    xa = bf16_bits_to_double(kx[j] & 0xffffu);
-                    xb = bf16_bits_to_double(kx[j] >> 16);
-                } else {
-                    xa = (double)kx[j].x;
-                    xb = (double)kx[j].y;
-                }
-                rotate_pair(xa, xb, cn, sn, ya, yb);
-                if constexpr (DTYPE == TR_BF16) kd[(h0 + j) * half] = double_to_bf16_bits(ya) | (double_to_bf16_bits(yb) << 16);
-                else kd[(h0 + j) * half] = make_float2(__double2float_rn(ya), __double2float_rn(yb));
-                if (v_new) vd[(h0 + j) * half] = vx[j]; // v_new == NULL: keys only
+            for (int p = 0; p < N_CS; ++p) {
+                const double2 e = cs[m0 + p];
+                c[p] = e.x;
+                s[p] = e.y;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < APPEND_UNITS; ++i)
+            if (u0 + 64 * i < row_units) { // rows are whole heads, so a lane and its partner's lane are here together
+                uint4 y;
+                if constexpr (HALF) y = UnitHalf<DTYPE>::rotate(kx[i], shfl_xor_u4(kx[i], hmask), low, c, s);
+                else y = Unit<DTYPE>::rotate(kx[i], c, s);
+                kd[u0 + 64 * i] = y;
+                if (v_new) vd[u0 + 64 * i] = vx[i]; // v_new == NULL: keys only
             }
     }
 }
@@ -238,15 +202,15 @@ __device__ __forceinline__ void st_stream(uint4* p, uint4 x) { *p = x; }
 template <int DTYPE, bool HALF>
 __global__ __launch_bounds__(256) void assemble_kernel(const TrAssembleArgs a)
 {
-    __shared__ double cs[64][2];
+    __shared__ double2 cs[64 * APPEND_WAVES]; // a copy block uses the first 64
     const int b = blockIdx.x;
     if (a.app.n_q > 0 && b >= a.app.first_block) {
-        // tail blocks: the request's own query tokens, one thread per (token, pair)
-        const int gid = (b - a.app.first_block) * 256 + (int)threadIdx.x;
-        const int tok = gid / a.half_dim, m = gid % a.half_dim;
+        // tail blocks: the request's own query tokens, one wave each
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        const int tok = (b - a.app.first_block) * APPEND_WAVES + wave;
         if (tok < a.app.n_q)
-            append_pair<DTYPE, HALF>(a.app.k_new, a.app.v_new, a.app.q_pos[tok], a.k_dst, a.v_dst, a.app.n_kv_heads, a.half_dim,
-                                     a.theta[m], tok, (int64_t)a.app.dst_row0 + tok, m);
+            append_token<DTYPE, HALF>(a.app.k_new, a.app.v_new, a.app.q_pos[tok], a.k_dst, a.v_dst, a.row_units, a.head_units,
+                                      a.half_dim, a.theta, tok, (int64_t)a.app.dst_row0 + tok, cs + 64 * wave, threadIdx.x & 63);
         return;
     }
     int lo = 0, hi = a.n_desc - 1;
@@ -285,18 +249,17 @@ __global__ __launch_bounds__(256) void assemble_kernel(const TrAssembleArgs a)
         if (tid < a.half_dim) {
             double sn, cn;
             sincos((double)d.delta * a.theta[tid], &sn, &cn);
-            cs[tid][0] = cn;
-            cs[tid][1] = sn;
+            cs[tid] = make_double2(cn, sn);
         }
         __syncthreads();
         if constexpr (HALF) {
             const int m0 = (low ? hu : hu - hmask) * E;
 #pragma unroll
-            for (int p = 0; p < E; ++p) { c[p] = cs[m0 + p][0]; s[p] = cs[m0 + p][1]; }
+            for (int p = 0; p < E; ++p) { c[p] = cs[m0 + p].x; s[p] = cs[m0 + p].y; }
         } else {
             const int m0 = hu * P;
 #pragma unroll
-            for (int p = 0; p < P; ++p) { c[p] = cs[m0 + p][0]; s[p] = cs[m0 + p][1]; }
+            for (int p = 0; p < P; ++p) { c[p] = cs[m0 + p].x; s[p] = cs[m0 + p].y; }
         }
     }
 
@@ -326,72 +289,34 @@ __global__ __launch_bounds__(256) void assemble_kernel(const TrAssembleArgs a)
 }
 
 // ---- query append: cache rows of the query tokens (K' rotated at q_pos, V copied) -------------------------
-template <int DTYPE, bool HALF>
-__global__ __launch_bounds__(256) void append_kernel(const TrAppendArgs a)
+// Index of the last entry of first[0 .. n) that is <= x, for a wave-uniform x: every lane looks at its own entries and a
+// ballot counts, one trip to the argument block where a search takes one per step (each some hundred nanoseconds, which is
+// what a launch of a few tokens consists of).  first[] ascends and first[0] <= x.
+__device__ __forceinline__ int last_not_above(const int32_t* first, int n, int x, int lane)
 {
-    const int half = a.head_dim >> 1;
-    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int tok = (int)(gid / half), m = (int)(gid % half);
-    if (tok >= a.total_tokens) return;
-    // request that owns packed token `tok` of this launch
-    int r = 0, base = 0;
-    while (r + 1 < a.n_desc && tok >= base + a.desc[r].n_q) { base += a.desc[r].n_q; ++r; }
-    const int i = tok - base;
-    // position id: the caller's, or (raw-store assembly) the run's first position plus the row's index in the run
-    const int pos = a.q_pos ? a.q_pos[a.desc[r].q_row0 + i] : a.desc[r].pos0 + i;
-    append_pair<DTYPE, HALF>(a.k_new, a.v_new, pos, a.cache_k, a.cache_v, a.n_kv_heads, half, a.theta[m],
-                             (int64_t)a.desc[r].q_row0 + i, (int64_t)a.desc[r].dst_row0 + i, m);
+    int count = 0;
+    for (int i0 = 0; i0 < n; i0 += 64) // at most two rounds: TR_MAX_APPEND_DESC entries
+        count += __popcll(__ballot(i0 + lane < n && first[min(i0 + lane, n - 1)] <= x));
+    return count - 1;
 }
 
-// The same rows for launches of many tokens (a store of un-rotated keys assembled at the final position ids, the key
-// rotation of the one-pass sequence call): a thread owns one 16-byte unit of a token, computes the (cos, sin) of the
-// pairs that unit takes part in once, and walks the KV heads with 16-byte accesses, where the kernel above moves one
-// pair (4 bytes) per thread and head.  Same arithmetic, so the same bits.
-constexpr int APPEND_UNITS_HEADS = 8; // KV heads in flight per thread
 template <int DTYPE, bool HALF>
-__global__ __launch_bounds__(256) void append_units_kernel(const TrAppendArgs a)
+__global__ __launch_bounds__(64 * APPEND_WAVES) void append_kernel(const TrAppendArgs a)
 {
-    constexpr int P = Unit<DTYPE>::PAIRS, E = UnitHalf<DTYPE>::ELEMS;
-    constexpr int N_CS = HALF ? E : P; // pairs this thread's unit takes part in
-    const int head_units = a.head_dim * (DTYPE == TR_BF16 ? 2 : 4) / 16; // a power of two, at most 32: a token's units share a wave
-    const int hmask = head_units >> 1;
-    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int tok = (int)(gid / head_units), unit = (int)(gid % head_units);
-    if (tok >= a.total_tokens) return; // whole tokens leave together, so the partner lane of the half-split layout stays
-    int r = 0, base = 0;
-    while (r + 1 < a.n_desc && tok >= base + a.desc[r].n_q) { base += a.desc[r].n_q; ++r; }
-    const int i = tok - base;
-    const int pos = a.q_pos ? a.q_pos[a.desc[r].q_row0 + i] : a.desc[r].pos0 + i;
-    const int64_t row_units = (int64_t)a.n_kv_heads * head_units;
-    const uint4* ks = (const uint4*)a.k_new + ((int64_t)a.desc[r].q_row0 + i) * row_units + unit;
-    const uint4* vs = (const uint4*)a.v_new + ((int64_t)a.desc[r].q_row0 + i) * row_units + unit;
-    uint4* kd = (uint4*)a.cache_k + ((int64_t)a.desc[r].dst_row0 + i) * row_units + unit;
-    uint4* vd = (uint4*)a.cache_v + ((int64_t)a.desc[r].dst_row0 + i) * row_units + unit;
-    const bool low = unit < hmask;
-    const int m0 = HALF ? (low ? unit : unit - hmask) * E : unit * P;
-    double c[N_CS], s[N_CS];
-    for (int h0 = 0; h0 < a.n_kv_heads; h0 += APPEND_UNITS_HEADS) {
-        uint4 kx[APPEND_UNITS_HEADS], vx[APPEND_UNITS_HEADS];
-#pragma unroll
-        for (int j = 0; j < APPEND_UNITS_HEADS; ++j)
-            if (h0 + j < a.n_kv_heads) {
-                kx[j] = ld_stream(ks + (h0 + j) * head_units);
-                if (a.v_new) vx[j] = ld_stream(vs + (h0 + j) * head_units);
-            }
-        if (h0 == 0) { // the loads are on their way while the angles are computed
-#pragma unroll
-            for (int p = 0; p < N_CS; ++p) sincos((double)pos * a.theta[m0 + p], &s[p], &c[p]);
-        }
-#pragma unroll
-        for (int j = 0; j < APPEND_UNITS_HEADS; ++j)
-            if (h0 + j < a.n_kv_heads) {
-                uint4 y;
-                if constexpr (HALF) y = UnitHalf<DTYPE>::rotate(kx[j], shfl_xor_u4(kx[j], hmask), low, c, s);
-                else y = Unit<DTYPE>::rotate(kx[j], c, s);
-                kd[(h0 + j) * head_units] = y;
-                if (a.v_new) vd[(h0 + j) * head_units] = vx[j]; // v_new == NULL: keys only
-            }
-    }
+    __shared__ double2 cs[64 * APPEND_WAVES];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t tok64 = (int64_t)blockIdx.x * APPEND_WAVES + wave;
+    if (tok64 >= a.total_tokens) return;
+    const int tok = (int)tok64;
+    // the run that owns packed token `tok` of this launch
+    const int r = a.n_desc == 1 ? 0 : last_not_above(a.tok0, a.n_desc, tok, lane);
+    const TrAppendDesc d = a.desc[r];
+    const int i = tok - a.tok0[r];
+    // position id: the caller's, or (raw-store assembly) the run's first position plus the row's index in the run
+    const int pos = a.q_pos ? a.q_pos[d.q_row0 + i] : d.pos0 + i;
+    const int head_units = a.head_dim * (DTYPE == TR_BF16 ? 2 : 4) / 16; // a power of two, at most 32
+    append_token<DTYPE, HALF>(a.k_new, a.v_new, pos, a.cache_k, a.cache_v, a.n_kv_heads * head_units, head_units, a.head_dim >> 1,
+                              a.theta, (int64_t)d.q_row0 + i, (int64_t)d.dst_row0 + i, cs + 64 * wave, lane);
 }
 
 // ---- offline key rotation (Sec. 3.4 step 2): K' = R(t - cu[c]) k -------------------------------------------
@@ -477,23 +402,11 @@ int tr_launch_assemble(const TrAssembleArgs& a, int dtype, int n_blocks, hipStre
 
 int tr_launch_append(const TrAppendArgs& a, int dtype, hipStream_t s)
 {
-    // many tokens: the form with 16-byte accesses (57 -> 51 us for 32768 rows of 8 heads); a request's few query tokens:
-    // one thread per pair, whose single angle is the shortest path to the first store
-    const int head_units = a.head_dim * (dtype == TR_BF16 ? 2 : 4) / 16;
-    if ((int64_t)a.total_tokens * head_units >= 65536) {
-        const int64_t n = (int64_t)a.total_tokens * head_units;
-        auto kern = dtype == TR_BF16 ? (a.rope_half ? append_units_kernel<TR_BF16, true> : append_units_kernel<TR_BF16, false>)
-                                     : (a.rope_half ? append_units_kernel<TR_F32, true> : append_units_kernel<TR_F32, false>);
-        hipLaunchKernelGGL(kern, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
-        TR_HIP(hipGetLastError());
-        return TR_OK;
-    }
-    int64_t threads = (int64_t)a.total_tokens * (a.head_dim / 2);
-    if (threads <= 0) return TR_OK;
-    int blocks = (int)((threads + 255) / 256);
+    if (a.total_tokens <= 0) return TR_OK;
+    const int64_t blocks = ((int64_t)a.total_tokens + APPEND_WAVES - 1) / APPEND_WAVES;
     auto kern = dtype == TR_BF16 ? (a.rope_half ? append_kernel<TR_BF16, true> : append_kernel<TR_BF16, false>)
                                  : (a.rope_half ? append_kernel<TR_F32, true> : append_kernel<TR_F32, false>);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * APPEND_WAVES), 0, s, a);
     TR_HIP(hipGetLastError());
     return TR_OK;
 }

@@ -86,6 +86,7 @@ struct TrCopyDesc {
     int32_t delta;
     int32_t blk_start; // first block of the grid that works on this run
 };
+#define TR_APPEND_TOKENS_PER_BLOCK 4 // a wave per token
 #define TR_MAX_COPY_DESC 168 // what the 4 KB argument block holds
 // optional tail of an assemble launch: one request's query tokens appended by the blocks from first_block on
 struct TrAppendTail {
@@ -95,7 +96,7 @@ struct TrAppendTail {
     int32_t n_q; // 0: no tail
     int32_t dst_row0;
     int32_t first_block;
-    int32_t n_kv_heads;
+    int32_t pad_;
 };
 struct TrAssembleArgs {
     const void* k_src;
@@ -135,6 +136,7 @@ struct TrAppendArgs {
     int32_t pad_;
     double theta[64];
     TrAppendDesc desc[TR_MAX_APPEND_DESC];
+    int32_t tok0[TR_MAX_APPEND_DESC]; // first token of each run among the launch's tokens
 };
 
 // prefix attention: one request

@@ -14,6 +14,7 @@
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_any __attribute__((aligned(4))); // the caller's rows may start at any element
 
 struct F32Row {
     const float* q;   // raw query vector
@@ -42,8 +43,8 @@ __device__ __forceinline__ void attn_f32_row(const F32Row& r, const float* __res
     __shared__ float ml[GROUPS][2];
     const int tid = threadIdx.x, grp = tid / LANES, c4 = tid % LANES;
     const int64_t row = (int64_t)n_kv_heads * (D / 4); // 16-byte pieces per cache row
-    const f32x4* kp = (const f32x4*)k + (int64_t)r.kvh * (D / 4) + c4;
-    const f32x4* vp = (const f32x4*)v + (int64_t)r.kvh * (D / 4) + c4;
+    const f32x4_any* kp = (const f32x4_any*)k + (int64_t)r.kvh * (D / 4) + c4;
+    const f32x4_any* vp = (const f32x4_any*)v + (int64_t)r.kvh * (D / 4) + c4;
     f32x4 kx[KEYS], vx[KEYS];
     auto load = [&](int j0) { // keys past the last visible one read that one and get no weight
 #pragma unroll
@@ -77,13 +78,15 @@ __device__ __forceinline__ void attn_f32_row(const F32Row& r, const float* __res
             s[i] = j + GROUPS * i <= r.key_hi ? group_sum<LANES>(x) * scale : -INFINITY;
             top = fmaxf(top, s[i]);
         }
-        const float alpha = expf(m - top); // key j is visible, so top is finite
+        // a batch whose scores are all -inf (a product that overflowed) gives the group no weight, it must not make NaN of
+        // the other groups' keys
+        const float alpha = top == -INFINITY ? 1.0f : expf(m - top);
         l *= alpha;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] *= alpha;
 #pragma unroll
         for (int i = 0; i < KEYS; ++i) {
-            const bool visible = j + GROUPS * i <= r.key_hi;
+            const bool visible = j + GROUPS * i <= r.key_hi && s[i] != -INFINITY;
             const float p = visible ? expf(s[i] - top) : 0.0f;
             l += p;
 #pragma unroll
@@ -99,7 +102,7 @@ __device__ __forceinline__ void attn_f32_row(const F32Row& r, const float* __res
         ml[grp][1] = l;
     }
     __syncthreads();
-    if (tid < D) { // one channel per thread; group 0 always holds the first visible key
+    if (tid < D) { // one channel per thread; groups without a visible key have weight 0
         float M = -INFINITY, L = 0.0f, x = 0.0f;
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) M = fmaxf(M, ml[g][0]);

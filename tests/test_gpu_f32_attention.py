@@ -33,3 +33,30 @@ def test_f32_attention_edges(head_dim, n_doc, n_q, layout):
                         (n_doc + np.arange(n_q)).astype(np.int32), n_doc, [n_doc])
     rows = None if n_q < 100 else np.linspace(0, n_q - 1, 40).astype(int)
     H.check_request(B, sh, store, sd, req, rows=rows, k_mismatch_frac=1e-4)
+
+
+@pytest.mark.parametrize("head_dim,n_q", [(64, 2), (64, 1030), (128, 2)])
+def test_f32_attention_scores_that_overflow(head_dim, n_q):
+    """Keys whose scores are -inf have weight 0, also where they are all the keys of one group of lanes' batch (every
+    32nd, 16th, 8th or 4th key): with equal scores elsewhere the result is the mean over the other visible keys.  Error
+    bound: fp32 sums of at most 1091 values of size 1, under 1e-5 relative to them."""
+    import torch
+    from paper_2410_07590_amd import binding as B
+    n_doc = 61
+    kv_len = n_doc + n_q
+    gs = H.gpu_shape(B, synth.Shape(4, 2, head_dim, "f32", 1e4, 0))
+    k = torch.zeros(kv_len, 2, head_dim)
+    gone = torch.zeros(kv_len, dtype=torch.bool)
+    gone[5::32] = True
+    gone[3::16] = True
+    gone[2::8] = True
+    k[gone] = -3e38                                     # times a query of ones: the sum over the channels overflows
+    v = torch.randn(kv_len, 2, head_dim, generator=torch.Generator().manual_seed(3))
+    q = torch.ones(n_q, 4, head_dim)
+    out = torch.empty_like(q).cuda()
+    B.tr_prefill_attn(gs, q.cuda(), k.cuda(), v.cuda(), torch.zeros(n_q, dtype=torch.int32).cuda(), kv_len, out,
+                      B.workspace(B.tr_prefill_attn_workspace_size(gs, n_q, kv_len)))
+    w = (~gone).double()[:, None, None]
+    mean = (torch.cumsum(v.double() * w, 0) / torch.cumsum(w, 0))[n_doc:]
+    want = mean.repeat_interleave(2, 1)
+    assert (out.cpu().double() - want).abs().max() < 1e-5

@@ -637,6 +637,8 @@ __device__ __forceinline__ void prologue(const __bf16* __restrict__ k, const __b
 // short its dependent chain is: staging the rows through LDS for whole-line stores, with two lane permutes per four rows,
 // took 2.4 us of the 12.4 us of a workgroup that walks five key tiles; without it the request over 8 x 512 rows went
 // from 25.6 to 24.1 us, 64 x 512 offline tokens from 296 to 284 us.  64-byte pieces (one more swap) measured no better.
+// The caller's rows may start at any multiple of an element: unaligned 16-byte stores are one instruction all the same.
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
 template <int D, bool PARTIAL>
 __device__ __forceinline__ void store_rows(const Acc<D>& acc, float l_tot, bool valid, int64_t dst_row, void* dst, int lane)
 {
@@ -671,7 +673,7 @@ __device__ __forceinline__ void store_rows(const Acc<D>& acc, float l_tot, bool 
             if (valid) {
                 // ordinary stores, partials too: a streaming store would send the 32-byte pieces on before the L2 has
                 // put a line together (8 x 512 rows, 64 query tokens: 25.3 us against 24.1)
-                *(u32x4*)(row + (32 * db + 16 * p) * 2) = w;
+                *(u32x4_any*)(row + (32 * db + 16 * p) * 2) = w;
             }
         }
 }

@@ -130,6 +130,17 @@ __device__ __forceinline__ uint4 ld_stream(const uint4* p)
     return make_uint4(r[0], r[1], r[2], r[3]);
 }
 
+// The append's 16-byte accesses, for rows that start at any multiple of an element: the caller's tensors may be views.  The
+// vector memory path serves such an address with one instruction (the target's unaligned access mode, which lets the
+// compiler emit the same wide accesses as for aligned rows).
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+__device__ __forceinline__ uint4 ld_stream_any(const uint4* p)
+{
+    const u32x4 r = __builtin_nontemporal_load((const u32x4_any*)p);
+    return make_uint4(r[0], r[1], r[2], r[3]);
+}
+__device__ __forceinline__ void st_any(uint4* p, uint4 x) { *(u32x4_any*)p = u32x4{x.x, x.y, x.z, x.w}; }
+
 // ---- one row of the query append: K' rotated at its position id, V copied, for every KV head -----------------
 // A wave owns a token: lane m computes (cos, sin) of pair m once (the fp64 sincos is by far the longest thing here, so
 // it is done once per pair and token, and the first loads go out before it), parks it in LDS, and the lanes then walk
@@ -160,8 +171,8 @@ __device__ __forceinline__ void append_token(const void* k_new, const void* v_ne
 #pragma unroll
         for (int i = 0; i < APPEND_UNITS; ++i)
             if (u0 + 64 * i < row_units) {
-                kx[i] = ld_stream(ks + u0 + 64 * i);
-                if (v_new) vx[i] = ld_stream(vs + u0 + 64 * i);
+                kx[i] = ld_stream_any(ks + u0 + 64 * i);
+                if (v_new) vx[i] = ld_stream_any(vs + u0 + 64 * i);
             }
         if (u0 == lane) {
             if (lane < half_dim) {
@@ -185,8 +196,8 @@ __device__ __forceinline__ void append_token(const void* k_new, const void* v_ne
                 uint4 y;
                 if constexpr (HALF) y = UnitHalf<DTYPE>::rotate(kx[i], shfl_xor_u4(kx[i], hmask), low, c, s);
                 else y = Unit<DTYPE>::rotate(kx[i], c, s);
-                kd[u0 + 64 * i] = y;
-                if (v_new) vd[u0 + 64 * i] = vx[i]; // v_new == NULL: keys only
+                st_any(kd + u0 + 64 * i, y);
+                if (v_new) st_any(vd + u0 + 64 * i, vx[i]); // v_new == NULL: keys only
             }
     }
 }

@@ -49,3 +49,27 @@ def test_appended_rows(n_kv, head_dim, dtype, layout, n_req, longest):
     H.assert_same_bits(H.bits(cv.cpu())[dst], H.bits(v), "appended values")
     rest = np.setdiff1d(np.arange(rows + 2), dst)
     assert torch.isnan(ck.cpu().float()[rest]).all() and torch.isnan(cv.cpu().float()[rest]).all()
+
+
+@pytest.mark.parametrize("dtype,layout,n_q", [("bf16", 0, 1), ("bf16", 1, 6), ("f32", 0, 3), ("f32", 1, 2)])
+def test_rows_that_start_at_any_element(dtype, layout, n_q):
+    """Views whose first element is not 16-byte aligned: the appended rows have the bits that aligned copies give."""
+    from paper_2410_07590_amd import binding as B
+    sh = synth.Shape(3, 3, 64, dtype, 1e4, layout)
+    gs = H.gpu_shape(B, sh)
+    g = torch.Generator().manual_seed(9)
+
+    def off(t, by):     # a copy that starts `by` elements into its allocation
+        room = torch.zeros(t.numel() + 16, dtype=t.dtype, device="cuda")
+        room[by:by + t.numel()] = t.reshape(-1).cuda()
+        return room[by:by + t.numel()].view(t.shape)
+
+    k, v = (torch.randn(n_q, 3, 64, generator=g).to(sh.torch_dtype) for _ in range(2))
+    pos = torch.arange(7, 7 + n_q, dtype=torch.int32).cuda()
+    got = {}
+    for by in (0, 1, 3):
+        ck, cv = off(torch.zeros_like(k), by), off(torch.zeros_like(v), by)
+        B.tr_kv_append(gs, off(k, by), off(v, by), pos, ck, cv, 0)
+        got[by] = (ck.cpu().clone(), cv.cpu().clone())
+    for by in (1, 3):
+        assert torch.equal(got[by][0], got[0][0]) and torch.equal(got[by][1], got[0][1]) and torch.equal(got[by][1], v)

@@ -490,7 +490,7 @@ constexpr int MIN_SPLIT_KEYS = 256;
 #ifndef TR_MAX_SPLIT
 #define TR_MAX_SPLIT 64
 #endif
-constexpr int MAX_SPLIT = TR_MAX_SPLIT;  // the combine kernel holds two splits per lane of a half-wave
+constexpr int MAX_SPLIT = TR_MAX_SPLIT;  // the wide form of the combine kernel holds the statistics of 64
 
 // Packed rows per workgroup: 256 (8 waves, deep LDS ring) when one KV head has enough rows to fill such tiles,
 // else 128 (4 waves).  The wg_rows override of tr_set_tuning wins.

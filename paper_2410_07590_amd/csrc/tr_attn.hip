@@ -31,6 +31,7 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
@@ -1107,96 +1108,106 @@ __global__ __launch_bounds__(64 * SHORT_NW, 1) void short_attn_kernel(const TrPr
 
 // Merge the split-KV partial results: out = sum_s w_s l_s P_s / sum_s w_s l_s with w_s = 2^(m_s - max_s m_s) and
 // P_s = O_s / l_s the normalised partial of split s.
-// 32 lanes per output row (4 channels each); lane i of the row also owns split i's statistics.
-// WIDE: some request of the launch has more than 32 key splits, so a lane of the row's half-wave holds two of them
-// (splits i and i + 32); the narrow form keeps one and is what every launch with at most 32 splits runs.
-template <int D, bool WIDE>
-__global__ __launch_bounds__(256) void combine_kernel(const TrPrefixArgs a, int total_rows)
+// A lane owns eight channels of a row (one 16-byte piece of each partial, 16 or 8 lanes per row) and the statistics of every
+// LPR-th split.  A merge is a chain of latencies, so the first round of partials is requested together with the statistics
+// and before the reductions over the row, which run on the vector unit's cross-lane path.  (Half a wave per row, the
+// reductions as LDS permutes with the partials behind them, and a 64-bit division took 15.4 us for 39.8 k
+// rows of a serving batch, now 11.1; 6.4 for 8.2 k rows, now 5.6; 4.2 for 1.8 k, now 4.0.)
+// WIDE: some request of the launch has more than 32 key splits; the narrow form keeps statistics of 32.
+template <bool MAX, int LANES> __device__ __forceinline__ float row_reduce(float x)
 {
-    static_assert(D == 128 || D == 64, "");
-    constexpr int LPR = 32;                     // lanes per row
-    constexpr int CPLN = D / LPR;               // channels per lane: 4 or 2
-    const int lane_r = threadIdx.x & 31;
-    const int64_t R = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
-    const int tq = a.seq[0].q_row0 + (int)(R / a.n_q_heads);
-    const int hq = (int)(R % a.n_q_heads);
-    int sq = 0;
-    if (a.n_seq > 1) { // the wave's two rows may belong to two requests
+    static_assert(LANES == 8 || LANES == 16, "");
+    auto step = [&](int y) { return MAX ? fmaxf(x, __builtin_bit_cast(float, y)) : x + __builtin_bit_cast(float, y); };
+    auto bits = [&]() { return __builtin_bit_cast(int, x); };
+    x = step(__builtin_amdgcn_update_dpp(bits(), bits(), 0xB1, 0xf, 0xf, false));  // quad_perm [1,0,3,2]
+    x = step(__builtin_amdgcn_update_dpp(bits(), bits(), 0x4E, 0xf, 0xf, false));  // quad_perm [2,3,0,1]
+    x = step(__builtin_amdgcn_update_dpp(bits(), bits(), 0x141, 0xf, 0xf, false)); // row_half_mirror
+    if (LANES == 16) x = step(__builtin_amdgcn_update_dpp(bits(), bits(), 0x140, 0xf, 0xf, false)); // row_mirror
+    return x;
+}
+constexpr int COMBINE_THREADS = 128; // two waves: the few thousand rows of one request then reach every compute unit
+template <int D> constexpr int combine_rows() { return COMBINE_THREADS / (D / 8); } // output rows per workgroup
+
+template <int D, bool WIDE>
+__global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const TrPrefixArgs a, int total_rows)
+{
+    constexpr int LPR = D / 8;                   // lanes per row
+    constexpr int NK = (WIDE ? 64 : 32) / LPR;   // statistics per lane
+    constexpr int PER_ROUND = 8;                 // partials in flight per lane
+    const int lane = threadIdx.x & 63, lane_r = lane % LPR;
+    const uint32_t R = blockIdx.x * combine_rows<D>() + threadIdx.x / LPR;
+    const int tq = a.seq[0].q_row0 + (int)(R / (uint32_t)a.n_q_heads);
+    const int hq = (int)(R % (uint32_t)a.n_q_heads);
+    // the wave's rows ascend, so they belong to the requests from s0 to s1, nearly always one
+    int s0 = 0, s1 = 0;
+    if (a.n_seq > 1) {
         auto first = [&](int i) { return a.seq[i].q_row0; };
-        const int s0 = last_not_above(a.n_seq, __builtin_amdgcn_readlane(tq, 0), first);
-        const int s1 = last_not_above(a.n_seq, __builtin_amdgcn_readlane(tq, 32), first);
-        sq = (threadIdx.x & 32) ? s1 : s0;
+        s0 = last_not_above(a.n_seq, __builtin_amdgcn_readlane(tq, 0), first);
+        s1 = last_not_above(a.n_seq, __builtin_amdgcn_readlane(tq, 63), first);
     }
-    if (R >= total_rows) return;
-    const TrSeqDesc sd = a.seq[sq];
-    if (sd.n_split == 1) return;
+    if (R >= (uint32_t)total_rows) return;
+    int n_split = a.seq[s0].n_split, ws_row0 = a.seq[s0].ws_row0, n_q = a.seq[s0].n_q, q_row0 = a.seq[s0].q_row0;
+    if (s0 != s1) {
+        int sq = s0;
+        while (sq < s1 && a.seq[sq + 1].q_row0 <= tq) ++sq;
+        n_split = a.seq[sq].n_split;
+        ws_row0 = a.seq[sq].ws_row0;
+        n_q = a.seq[sq].n_q;
+        q_row0 = a.seq[sq].q_row0;
+    }
+    if (n_split == 1) return;
     const int g = a.group;
     const int kvh = hq / g;
-    const int64_t rows_s = (int64_t)sd.n_q * g;
-    const int64_t prow0 = (int64_t)sd.ws_row0 + kvh * rows_s + (tq - sd.q_row0) * g + hq % g;
+    const int64_t rows_s = (int64_t)n_q * g;
+    const int64_t prow0 = (int64_t)ws_row0 + kvh * rows_s + (tq - q_row0) * g + hq % g;
     const int64_t pstride = (int64_t)a.n_kv_heads * rows_s; // partial rows between consecutive splits
-    // statistics: lane i of the row's half-wave loads split i (and split i + 32 in the wide form)
-    constexpr int NK = WIDE ? 2 : 1;
-    float m_i[2] = {-INFINITY, -INFINITY}, l_i[2] = {0.0f, 0.0f};
+    float2 ml[NK];
 #pragma unroll
-    for (int k = 0; k < NK; ++k)
-        if (lane_r + 32 * k < sd.n_split) {
-            const float2 ml = *(const float2*)(a.ws_ml + (prow0 + (lane_r + 32 * k) * pstride) * 2);
-            m_i[k] = ml.x;
-            l_i[k] = ml.y;
-        }
-    float M = fmaxf(m_i[0], m_i[1]);
-#pragma unroll
-    for (int o = 16; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
-    float w_i[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) w_i[k] = (k >= NK || m_i[k] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m_i[k] - M) * l_i[k];
-    float L = w_i[0] + w_i[1];
-#pragma unroll
-    for (int o = 16; o >= 1; o >>= 1) L += __shfl_xor(L, o);
-    float acc[CPLN];
-#pragma unroll
-    for (int e = 0; e < CPLN; ++e) acc[e] = 0.0f;
-    const _Float16* base = a.ws_o + prow0 * D + CPLN * lane_r;
-    const int row_lane0 = threadIdx.x & 32; // first lane of this row's half-wave
-    // eight splits per round so that eight loads are in flight (the loop count is a run-time value)
-    constexpr int PER_ROUND = 8;
-    for (int sp0 = 0; sp0 < sd.n_split; sp0 += PER_ROUND) {
-        f32x4 x[PER_ROUND];
-        float w[PER_ROUND];
-        const float w_src = (!WIDE || sp0 < 32) ? w_i[0] : w_i[1]; // a round never straddles 32
+    for (int k = 0; k < NK; ++k) {
+        ml[k] = make_float2(-INFINITY, 0.0f);
+        if (lane_r + LPR * k < n_split) ml[k] = *(const float2*)(a.ws_ml + (prow0 + (lane_r + LPR * k) * pstride) * 2);
+    }
+    const _Float16* base = a.ws_o + prow0 * D + 8 * lane_r;
+    f16x8 x[PER_ROUND];
+    auto load = [&](int sp0) { // splits past the last one give zeros
 #pragma unroll
         for (int u = 0; u < PER_ROUND; ++u) {
-            const int sp = sp0 + u;
-            const bool ok = sp < sd.n_split;
-            const _Float16* p = base + (int64_t)(ok ? sp : 0) * pstride * D;
-            if (CPLN == 4) {
-                const f16x4 t = *(const f16x4*)p;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[u][e] = (float)t[e];
-            } else {
-                const f16x2 t = *(const f16x2*)p;
-                x[u][0] = (float)t[0]; x[u][1] = (float)t[1]; x[u][2] = 0.0f; x[u][3] = 0.0f;
-            }
-            const float ws = __shfl(w_src, row_lane0 + (sp & 31));
-            w[u] = ok ? ws : 0.0f;
+            x[u] = f16x8{};
+            if (sp0 + u < n_split) x[u] = *(const f16x8*)(base + (sp0 + u) * pstride * D);
         }
+    };
+    load(0);
+    float M = ml[0].x;
 #pragma unroll
-        for (int u = 0; u < PER_ROUND; ++u)
+    for (int k = 1; k < NK; ++k) M = fmaxf(M, ml[k].x);
+    M = row_reduce<true, LPR>(M);
+    float w[NK], L = 0.0f;
 #pragma unroll
-            for (int e = 0; e < CPLN; ++e) acc[e] += w[u] * x[u][e];
+    for (int k = 0; k < NK; ++k) {
+        w[k] = ml[k].x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ml[k].x - M) * ml[k].y;
+        L += w[k];
+    }
+    L = row_reduce<false, LPR>(L);
+    float acc[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+    const int row_lane0 = lane - lane_r; // first lane of this row
+#pragma unroll
+    for (int sp0 = 0; sp0 < NK * LPR; sp0 += PER_ROUND) { // a round is inside one k: LPR is a multiple of it
+        if (sp0 >= n_split) break;
+        if (sp0 > 0) load(sp0);
+#pragma unroll
+        for (int u = 0; u < PER_ROUND; ++u) {
+            const float ws = __shfl(w[sp0 / LPR], row_lane0 + (sp0 + u) % LPR); // zero past the last split
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] += ws * (float)x[u][e];
+        }
     }
     const float inv = 1.0f / L;
-    __bf16* op = (__bf16*)a.out + ((int64_t)tq * a.n_q_heads + hq) * D + CPLN * lane_r;
-    if (CPLN == 4) {
-        bf16x4 y;
+    bf16x8 y;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = (__bf16)(acc[e] * inv);
-        *(bf16x4*)op = y;
-    } else {
-        op[0] = (__bf16)(acc[0] * inv);
-        op[1] = (__bf16)(acc[1] * inv);
-    }
+    for (int e = 0; e < 8; ++e) y[e] = (__bf16)(acc[e] * inv);
+    *(u32x4_any*)((__bf16*)a.out + ((int64_t)tq * a.n_q_heads + hq) * D + 8 * lane_r) = __builtin_bit_cast(u32x4, y);
 }
 
 // ---- step 2 (offline): block-diagonal causal attention over packed chunks --------------------------------------
@@ -1374,18 +1385,19 @@ int blockdiag_dispatch(const TrBlockDiagArgs& a, int head_dim, int wg_rows, hipS
 
 } // namespace
 
-// the merge kernel for a launch whose largest split count is max_split
-static int launch_combine(const TrPrefixArgs& a, int head_dim, int blocks, int total_rows, hipStream_t s)
+// the merge kernel for a launch of total_rows output rows
+template <int D> static void launch_combine_d(const TrPrefixArgs& a, bool wide, int total_rows, hipStream_t s)
+{
+    const dim3 blocks((unsigned)((total_rows + combine_rows<D>() - 1) / combine_rows<D>()));
+    if (wide) hipLaunchKernelGGL((combine_kernel<D, true>), blocks, dim3(COMBINE_THREADS), 0, s, a, total_rows);
+    else hipLaunchKernelGGL((combine_kernel<D, false>), blocks, dim3(COMBINE_THREADS), 0, s, a, total_rows);
+}
+static int launch_combine(const TrPrefixArgs& a, int head_dim, int total_rows, hipStream_t s)
 {
     int max_split = 1;
     for (int i = 0; i < a.n_seq; ++i) max_split = a.seq[i].n_split > max_split ? a.seq[i].n_split : max_split;
-    if (max_split > 32) {
-        if (head_dim == 128) hipLaunchKernelGGL((combine_kernel<128, true>), dim3(blocks), dim3(256), 0, s, a, total_rows);
-        else hipLaunchKernelGGL((combine_kernel<64, true>), dim3(blocks), dim3(256), 0, s, a, total_rows);
-    } else {
-        if (head_dim == 128) hipLaunchKernelGGL((combine_kernel<128, false>), dim3(blocks), dim3(256), 0, s, a, total_rows);
-        else hipLaunchKernelGGL((combine_kernel<64, false>), dim3(blocks), dim3(256), 0, s, a, total_rows);
-    }
+    if (head_dim == 128) launch_combine_d<128>(a, max_split > 32, total_rows, s);
+    else launch_combine_d<64>(a, max_split > 32, total_rows, s);
     TR_HIP(hipGetLastError());
     return TR_OK;
 }
@@ -1398,9 +1410,7 @@ int tr_launch_prefix_attn(const TrPrefixArgs& a, int head_dim, int wg_rows, bool
     const int rc = a.rope_half ? prefix_dispatch<true>(a, head_dim, wg_rows, s) : prefix_dispatch<false>(a, head_dim, wg_rows, s);
     if (rc) return rc;
     if (any_split) {
-        const int rows_per_block = 256 / 32;
-        const int blocks = (total_rows + rows_per_block - 1) / rows_per_block;
-        if (int rc2 = launch_combine(a, head_dim, blocks, total_rows, s)) return rc2;
+        if (int rc2 = launch_combine(a, head_dim, total_rows, s)) return rc2;
     }
     return TR_OK;
 }
@@ -1414,8 +1424,7 @@ int tr_launch_gather_attn(const TrGatherArgs& a, const TrPrefixArgs& combine_arg
     if (rc) return rc;
     if (a.n_split > 1) {
         const int total_rows = a.n_q * a.n_q_heads;
-        const int blocks = (total_rows + 7) / 8;
-        if (int rc2 = launch_combine(combine_args, head_dim, blocks, total_rows, s)) return rc2;
+        if (int rc2 = launch_combine(combine_args, head_dim, total_rows, s)) return rc2;
     }
     return TR_OK;
 }
@@ -1427,8 +1436,7 @@ int tr_launch_blockdiag_attn(const TrBlockDiagArgs& a, const TrPrefixArgs* combi
     const int rc = a.rope_half ? blockdiag_dispatch<true>(a, head_dim, wg_rows, s) : blockdiag_dispatch<false>(a, head_dim, wg_rows, s);
     if (rc) return rc;
     if (combine && combine_rows > 0) {
-        const int blocks = (combine_rows + 7) / 8;
-        if (int rc2 = launch_combine(*combine, head_dim, blocks, combine_rows, s)) return rc2;
+        if (int rc2 = launch_combine(*combine, head_dim, combine_rows, s)) return rc2;
     }
     return TR_OK;
 }

@@ -160,6 +160,7 @@ struct Work {
 };
 
 // The library call runs without the interpreter lock (a full queue can make a launch wait), then its status is looked at.
+// `call` holds nothing but the C call on values read before: whatever it threw would reach entry() without the lock.
 template <class F> PyObject* run(F&& call)
 {
     int rc;
@@ -389,6 +390,7 @@ PyObject* linear(Args a) // x, [w], [y], workspace, stream
     if (x.dim() != 2) fail(PyExc_ValueError, "x has two dimensions");
     if (!PyList_Check(a[1]) || !PyList_Check(a[2])) fail(PyExc_TypeError, "lists of tensors are expected");
     const int64_t M = x.size(0), K = x.size(1);
+    const void* xp = x.data_ptr(); // may throw, as every tensor access may: none of them inside run()
     const Py_ssize_t n = PyList_GET_SIZE(a[1]), ny = PyList_GET_SIZE(a[2]);
     std::vector<const void*> w((size_t)n);
     std::vector<void*> y((size_t)ny);
@@ -407,7 +409,7 @@ PyObject* linear(Args a) // x, [w], [y], workspace, stream
     if (ny < n) fail(PyExc_AssertionError, "as many outputs as weights are expected");
     const Work ws(a[3]);
     void* s = stream(a[4]);
-    return run([&] { return api.tr_linear(x.data_ptr(), (int32_t)M, (int32_t)K, (int32_t)n, w.data(), y.data(), f.data(), ws.p, ws.bytes, s); });
+    return run([&] { return api.tr_linear(xp, (int32_t)M, (int32_t)K, (int32_t)n, w.data(), y.data(), f.data(), ws.p, ws.bytes, s); });
 }
 
 // addresses: dict name -> address of the library's entry point; error: the exception class for a failed call

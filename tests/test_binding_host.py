@@ -1,4 +1,8 @@
 """The extension module behind the binding: what it accepts, converts and refuses (CPU: nothing is enqueued)."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -33,3 +37,23 @@ def test_library_errors_and_wrong_arguments(store):
         B.tr_kv_append(store.shape, "k", None, None, None, None, 0, stream=0)
     with pytest.raises(AttributeError):
         B.tr_plan(None, [0], B.TR_POS_REORDERED)
+
+
+def test_a_tensor_without_an_address_is_an_error_like_any_other():
+    """A tensor that refuses its address (a traced one) makes the call raise.  In a process of its own: an exception that
+    left the library call without the interpreter lock would end the process."""
+    code = """
+import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
+from paper_2410_07590_amd import binding as B
+with FakeTensorMode():
+    x = torch.empty(2, 64, dtype=torch.bfloat16, device="cuda")
+torch._C._set_throw_on_mutable_data_ptr(x)
+try:
+    B.tr_linear(x, [], [], stream=0)
+except RuntimeError as e:
+    print("refused:", "data pointer" in str(e))
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=root, timeout=300)
+    assert res.returncode == 0 and "refused: True" in res.stdout, (res.returncode, res.stdout, res.stderr[-2000:])

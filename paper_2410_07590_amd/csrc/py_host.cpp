@@ -397,7 +397,7 @@ PyObject* linear(Args a) // x, [w], [y], workspace, stream
     std::vector<int32_t> f((size_t)n);
     for (Py_ssize_t j = 0; j < n; ++j) {
         const at::Tensor& t = device_tensor(PyList_GET_ITEM(a[1], j));
-        if (t.dim() != 2 || t.size(1) != K) fail(PyExc_AssertionError, "w[j] has K columns");
+        if (t.dim() < 2 || t.size(1) != K) fail(PyExc_AssertionError, "w[j] has K columns");
         w[(size_t)j] = t.data_ptr();
         f[(size_t)j] = (int32_t)t.size(0);
     }

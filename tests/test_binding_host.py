@@ -57,3 +57,19 @@ except RuntimeError as e:
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=root, timeout=300)
     assert res.returncode == 0 and "refused: True" in res.stdout, (res.returncode, res.stdout, res.stderr[-2000:])
+
+
+def test_linear_takes_weights_with_trailing_dimensions():
+    """A weight of shape [N, K, 1] (a convolution over one position) passes the shape check as it does with two dimensions:
+    the call gets as far as the library, which refuses the missing memory of a tensor that has none."""
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    with FakeTensorMode():
+        x, y = (torch.empty(2, 64, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        good = [torch.empty(*s, dtype=torch.bfloat16, device="cuda") for s in ((64, 64), (64, 64, 1))]
+        bad = [torch.empty(*s, dtype=torch.bfloat16, device="cuda") for s in ((64, 32), (64, 32, 2), (64,))]
+    for w in good:
+        with pytest.raises(B.TurboRagError, match="NULL pointer"):
+            B.tr_linear(x, w, y, stream=0)
+    for w in bad:
+        with pytest.raises(AssertionError):
+            B.tr_linear(x, w, y, stream=0)

@@ -184,7 +184,11 @@ namespace {
 
 struct CopyRun { int64_t src_row, dst_row, n_rows, delta; };
 
-// tail (optional): query tokens appended by extra blocks of the last launch
+int launch_append(const tr_shape* shape, const void* k_new, const void* v_new, const int32_t* q_pos,
+                  const std::vector<TrAppendDesc>& descs, void* cache_k, void* cache_v, hipStream_t stream);
+
+// tail (optional): query tokens appended by extra blocks of the last launch, or by launches of their own where one launch
+// cannot hold so many
 int launch_runs(const tr_store* store, const std::vector<CopyRun>& runs, void* out_k, void* out_v, hipStream_t stream,
                 const TrAppendTail* tail = nullptr)
 {
@@ -230,15 +234,19 @@ int launch_runs(const tr_store* store, const std::vector<CopyRun>& runs, void* o
         }
         a.n_desc = n;
         if (n == 0) continue;
-        if (tail && i == runs.size()) { // last launch carries the append
+        const int64_t tail_blocks = tail ? ((int64_t)tail->n_q + TR_APPEND_TOKENS_PER_BLOCK - 1) / TR_APPEND_TOKENS_PER_BLOCK : 0;
+        if (tail && i == runs.size() && blocks + tail_blocks <= TR_MAX_BLOCKS_256) { // last launch carries the append
             a.app = *tail;
             a.app.first_block = blocks;
-            blocks += (int)(((int64_t)tail->n_q + TR_APPEND_TOKENS_PER_BLOCK - 1) / TR_APPEND_TOKENS_PER_BLOCK);
+            blocks += (int)tail_blocks;
+            tail = nullptr;
         }
         int rc = tr_launch_assemble(a, sh->dtype, blocks, stream);
         if (rc) return rc;
     }
-    return TR_OK;
+    if (!tail) return TR_OK;
+    const TrAppendDesc d = {0, tail->n_q, tail->dst_row0, 0};
+    return launch_append(sh, tail->k_new, tail->v_new, tail->q_pos, {d}, out_k, out_v, stream);
 }
 
 } // namespace
@@ -338,10 +346,19 @@ int launch_append(const tr_shape* shape, const void* k_new, const void* v_new, c
     a.rope_half = tr_rope_half(shape);
     tr_fill_theta(shape, a.theta);
     size_t i = 0;
+    int done = 0; // tokens of descs[i] that earlier launches carry
     while (i < descs.size()) {
         int n = 0, tokens = 0;
-        while (i < descs.size() && n < TR_MAX_APPEND_DESC) {
-            if (descs[i].n_q > 0) { a.tok0[n] = tokens; a.desc[n++] = descs[i]; tokens += descs[i].n_q; }
+        while (i < descs.size() && n < TR_MAX_APPEND_DESC && tokens < TR_MAX_APPEND_TOKENS) {
+            TrAppendDesc d = descs[i];
+            d.q_row0 += done;
+            d.dst_row0 += done;
+            d.pos0 += done;
+            d.n_q = std::min(d.n_q - done, TR_MAX_APPEND_TOKENS - tokens);
+            if (d.n_q > 0) { a.tok0[n] = tokens; a.desc[n++] = d; tokens += d.n_q; }
+            done += d.n_q;
+            if (done < descs[i].n_q) break; // the launch is full
+            done = 0;
             ++i;
         }
         a.n_desc = n;

@@ -87,6 +87,10 @@ struct TrCopyDesc {
     int32_t blk_start; // first block of the grid that works on this run
 };
 #define TR_APPEND_TOKENS_PER_BLOCK 4 // a wave per token
+// A launch has fewer than 2^32 threads.  More tokens than this (2^31 threads) are appended by several launches, and blocks of
+// 256 threads beyond that count are never put into one.
+#define TR_MAX_APPEND_TOKENS (1 << 25)
+#define TR_MAX_BLOCKS_256 ((1 << 24) - 1)
 #define TR_MAX_COPY_DESC 168 // what the 4 KB argument block holds
 // optional tail of an assemble launch: one request's query tokens appended by the blocks from first_block on
 struct TrAppendTail {

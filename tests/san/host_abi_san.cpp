@@ -28,6 +28,8 @@ struct Expect {
     size_t ws_bytes = 0;
     int head_dim = 0;
     long launches = 0;
+    int64_t next_src = -1, next_dst = 0; // >= 0: appended rows follow one another from here, over all launches
+    int64_t next_pos = -1;               // >= 0: so do the position ids of the descriptors
 } g_ex;
 
 long g_checks = 0;
@@ -84,6 +86,9 @@ int tr_launch_assemble(const TrAssembleArgs& a, int, int n_blocks, hipStream_t)
         REQUIRE(a.app.first_block == blk, "assemble: appended tokens start at block %d, expected %d", a.app.first_block, blk);
         REQUIRE(a.app.dst_row0 >= 0 && (int64_t)a.app.dst_row0 + a.app.n_q <= g_ex.dst_rows, "assemble: appended tokens leave the cache");
         REQUIRE(n_blocks > blk, "assemble: no block for the appended tokens");
+        REQUIRE((int64_t)(n_blocks - blk) * TR_APPEND_TOKENS_PER_BLOCK >= a.app.n_q, "assemble: %d blocks for %d appended tokens", n_blocks - blk, a.app.n_q);
+        REQUIRE((int64_t)n_blocks * 256 < (int64_t)1 << 32, "assemble: %d blocks in one launch", n_blocks);
+        g_ex.next_dst += g_ex.next_src >= 0 ? a.app.n_q : 0;
     } else {
         REQUIRE(n_blocks == blk, "assemble: %d blocks launched, descriptors cover %d", n_blocks, blk);
     }
@@ -99,8 +104,17 @@ int tr_launch_append(const TrAppendArgs& a, int, hipStream_t)
         const TrAppendDesc& d = a.desc[i];
         REQUIRE(d.n_q >= 0 && d.q_row0 >= 0 && (int64_t)d.q_row0 + d.n_q <= g_ex.src_rows, "append: request %d reads tokens %d..+%d of %" PRId64, i, d.q_row0, d.n_q, g_ex.src_rows);
         REQUIRE(d.dst_row0 >= 0 && (int64_t)d.dst_row0 + d.n_q <= g_ex.dst_rows, "append: request %d writes rows %d..+%d of %" PRId64, i, d.dst_row0, d.n_q, g_ex.dst_rows);
+        REQUIRE(a.tok0[i] == tokens, "append: request %d starts at token %d of the launch, expected %" PRId64, i, a.tok0[i], tokens);
+        if (g_ex.next_src >= 0) {
+            REQUIRE(d.q_row0 == g_ex.next_src && d.dst_row0 == g_ex.next_dst, "append: rows %d -> %d, expected %" PRId64 " -> %" PRId64, d.q_row0, d.dst_row0, g_ex.next_src, g_ex.next_dst);
+            REQUIRE(g_ex.next_pos < 0 || d.pos0 == g_ex.next_pos, "append: position %d, expected %" PRId64, d.pos0, g_ex.next_pos);
+            g_ex.next_src += d.n_q;
+            g_ex.next_dst += d.n_q;
+            g_ex.next_pos += g_ex.next_pos >= 0 ? d.n_q : 0;
+        }
         tokens += d.n_q;
     }
+    REQUIRE(tokens <= TR_MAX_APPEND_TOKENS && tokens * 64 < (int64_t)1 << 32, "append: %" PRId64 " tokens in one launch", tokens);
     REQUIRE(tokens == a.total_tokens, "append: %" PRId64 " tokens in the descriptors, %d announced", tokens, a.total_tokens);
     return 0;
 }
@@ -491,12 +505,58 @@ void argument_errors()
     REQUIRE(tr_prefill_attn_static_scratch_bytes() > 0, "static scratch size");
 }
 
+// More tokens than one launch holds: every row is covered once, in order, by launches of a legal size.
+void appends_of_many_tokens()
+{
+    char buf[256];
+    const int32_t* pos = (const int32_t*)buf;
+    const int64_t MAX = TR_MAX_APPEND_TOKENS;
+    for (int64_t n : {MAX - 1, MAX, MAX + 1, 2 * MAX, 5 * MAX + 7, ((int64_t)1 << 31) - 1 - 1000}) {
+        tr_shape sh;
+        std::memset(&sh, 0, sizeof sh);
+        sh.n_q_heads = sh.n_kv_heads = 1; sh.head_dim = 64; sh.dtype = TR_BF16; sh.rope_base = 1e4;
+        auto expect = [&](int64_t src, int64_t dst, int64_t pos0) {
+            g_ex.next_src = src; g_ex.next_dst = dst; g_ex.next_pos = pos0;
+        };
+        g_ex.src_rows = n; g_ex.dst_rows = n + 1000;
+        expect(0, 1000, -1);
+        OK(tr_kv_append(&sh, buf, buf, pos, (int32_t)n, buf, buf, 1000, n + 1000, nullptr));
+        REQUIRE(g_ex.next_dst == n + 1000, "%" PRId64 " of %" PRId64 " tokens appended", g_ex.next_dst - 1000, n);
+        // two requests: the second one begins in the middle of a launch
+        const int32_t cu[] = {0, 100, (int32_t)n};
+        const int64_t start[] = {0, 100, n};
+        expect(0, 0, -1);
+        OK(tr_kv_append_batched(&sh, buf, buf, pos, cu, start, 2, buf, buf, n, nullptr));
+        REQUIRE(g_ex.next_dst == n, "%" PRId64 " of %" PRId64 " tokens appended", g_ex.next_dst, n);
+        // a store of un-rotated keys, both position schemes
+        const int64_t rows[] = {0, 100, n};
+        tr_store* st = nullptr;
+        OK(tr_store_create(&sh, buf, buf, rows, 2, &st));
+        const int32_t ids[] = {0, 1}, last[] = {1};
+        const int64_t off1[] = {0, n - 100};
+        expect(0, 0, 0);
+        OK(tr_kv_assemble_raw(st, ids, rows, 2, TR_POS_REORDERED, buf, buf, n, nullptr));
+        REQUIRE(g_ex.next_dst == n && g_ex.next_pos == n, "%" PRId64 " of %" PRId64 " rows assembled", g_ex.next_dst, n);
+        expect(100, 0, 0);
+        OK(tr_kv_assemble_raw(st, last, off1, 1, TR_POS_COMPOSITE, buf, buf, n, nullptr));
+        REQUIRE(g_ex.next_dst == n - 100, "%" PRId64 " of %" PRId64 " rows assembled", g_ex.next_dst, n - 100);
+        // documents, and the tokens behind them in the same launch or in their own
+        const int64_t off2[] = {0, 100};
+        expect(0, 100, -1);
+        OK(tr_kv_assemble_append(st, ids, off2, 1, TR_POS_REORDERED, buf, buf, pos, (int32_t)n, buf, buf, n + 1000, nullptr));
+        REQUIRE(g_ex.next_dst == n + 100, "%" PRId64 " of %" PRId64 " tokens appended", g_ex.next_dst - 100, n);
+        OK(tr_store_destroy(st));
+    }
+    g_ex.next_src = g_ex.next_pos = -1;
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
 {
     const int rounds = argc > 1 ? std::atoi(argv[1]) : 300;
     argument_errors();
+    appends_of_many_tokens();
     const char* knobs[] = {"wg_rows", "target_items", "min_split_keys", "bd_piece_tiles"};
     const int values[][3] = {{0, 128, 32}, {0, 64, 2048}, {0, 64, 1024}, {0, 1, 8}};
     for (int i = 0; i < rounds; ++i) {

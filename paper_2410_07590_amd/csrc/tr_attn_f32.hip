@@ -117,11 +117,12 @@ __device__ __forceinline__ void attn_f32_row(const F32Row& r, const float* __res
 }
 
 template <int D, int NW>
-__global__ __launch_bounds__(64 * NW) void prefix_attn_f32_kernel(const TrPrefixArgs a)
+__global__ __launch_bounds__(64 * NW) void prefix_attn_f32_kernel(const TrPrefixArgs a, uint32_t row0)
 {
-    // block = (packed token of this launch, query head)
-    const int tq = a.seq[0].q_row0 + blockIdx.x / a.n_q_heads;
-    const int hq = blockIdx.x % a.n_q_heads;
+    // row = (packed token of the call, query head); this launch covers rows from row0 on
+    const uint32_t row = row0 + blockIdx.x;
+    const int tq = a.seq[0].q_row0 + (int)(row / (uint32_t)a.n_q_heads);
+    const int hq = (int)(row % (uint32_t)a.n_q_heads);
     int lo = 0, hi = a.n_seq - 1;
     while (lo < hi) {
         int mid = (lo + hi + 1) >> 1;
@@ -140,10 +141,11 @@ __global__ __launch_bounds__(64 * NW) void prefix_attn_f32_kernel(const TrPrefix
 }
 
 template <int D, int NW>
-__global__ __launch_bounds__(64 * NW) void blockdiag_attn_f32_kernel(const TrBlockDiagArgs a)
+__global__ __launch_bounds__(64 * NW) void blockdiag_attn_f32_kernel(const TrBlockDiagArgs a, uint32_t row0)
 {
-    const int t = blockIdx.x / a.n_q_heads;
-    const int hq = blockIdx.x % a.n_q_heads;
+    const uint32_t row = row0 + blockIdx.x;
+    const int t = (int)(row / (uint32_t)a.n_q_heads);
+    const int hq = (int)(row % (uint32_t)a.n_q_heads);
     F32Row r;
     r.q = (const float*)a.q + ((int64_t)t * a.n_q_heads + hq) * D;
     r.out = (float*)a.out + ((int64_t)t * a.n_q_heads + hq) * D;
@@ -158,27 +160,33 @@ __global__ __launch_bounds__(64 * NW) void blockdiag_attn_f32_kernel(const TrBlo
 // over all its keys), two for the many rows of a packed sequence, whose key ranges are short.
 constexpr int FEW_ROWS = 2048;
 
+// kern over `rows` rows with `threads` threads each, in launches of at most 2^31 threads (one has fewer than 2^32)
+template <class Args> int launch_rows(void (*kern)(Args, uint32_t), const Args& a, int64_t rows, int threads, hipStream_t s)
+{
+    const int64_t most = ((int64_t)1 << 31) / threads;
+    for (int64_t row0 = 0; row0 < rows; row0 += most) {
+        const int64_t n = rows - row0 < most ? rows - row0 : most;
+        hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(threads), 0, s, a, (uint32_t)row0);
+        TR_HIP(hipGetLastError());
+    }
+    return TR_OK;
+}
+
 } // namespace
 
 int tr_launch_prefix_attn_f32(const TrPrefixArgs& a, int head_dim, int total_rows, hipStream_t s)
 {
-    if (total_rows <= 0) return TR_OK;
     const bool few = total_rows <= FEW_ROWS;
     auto kern = head_dim == 128 ? (few ? prefix_attn_f32_kernel<128, 8> : prefix_attn_f32_kernel<128, 2>)
                                 : (few ? prefix_attn_f32_kernel<64, 8> : prefix_attn_f32_kernel<64, 2>);
-    hipLaunchKernelGGL(kern, dim3(total_rows), dim3(few ? 512 : 128), 0, s, a);
-    TR_HIP(hipGetLastError());
-    return TR_OK;
+    return launch_rows(kern, a, total_rows, few ? 512 : 128, s);
 }
 
 int tr_launch_blockdiag_attn_f32(const TrBlockDiagArgs& a, int head_dim, hipStream_t s)
 {
-    if (a.total_tokens <= 0) return TR_OK;
-    const int blocks = a.total_tokens * a.n_q_heads;
-    const bool few = blocks <= FEW_ROWS;
+    const int64_t rows = (int64_t)a.total_tokens * a.n_q_heads;
+    const bool few = rows <= FEW_ROWS;
     auto kern = head_dim == 128 ? (few ? blockdiag_attn_f32_kernel<128, 8> : blockdiag_attn_f32_kernel<128, 2>)
                                 : (few ? blockdiag_attn_f32_kernel<64, 8> : blockdiag_attn_f32_kernel<64, 2>);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(few ? 512 : 128), 0, s, a);
-    TR_HIP(hipGetLastError());
-    return TR_OK;
+    return launch_rows(kern, a, rows, few ? 512 : 128, s);
 }

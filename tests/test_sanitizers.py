@@ -1,6 +1,6 @@
 """AddressSanitizer + UndefinedBehaviorSanitizer builds of the CPU oracle and of the host side of the C-ABI.
 
-Both run on the CPU: the oracle is plain C; the C-ABI's host code (validation, gather plans, launch planning,
+All run on the CPU: the oracle is plain C; the C-ABI's host code (validation, gather plans, launch planning,
 workspace layout) is built from csrc/tr_api.hip with stand-ins for the kernel launchers, which also check the
 argument blocks a kernel would receive (tests/san/).  No kernel is launched, with or without a GPU in the machine.
 """
@@ -41,3 +41,13 @@ def test_host_side_of_the_c_abi_under_address_and_undefined_behaviour_sanitizers
           "-o", exe, os.path.join(SAN, "host_abi_san.cpp"), os.path.join(ROOT, "paper_2410_07590_amd", "csrc", "tr_api.hip")])
     out = _run([exe, "300"])
     assert "host abi sanitizer run ok: 300 request mixes" in out
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not found")
+def test_launches_of_very_many_rows_are_legal(tmp_path):
+    """The built library against a stand-in of the runtime's launch call, in a program of its own."""
+    from paper_2410_07590_amd import binding as B
+    B.lib()
+    exe = str(tmp_path / "launch_sizes")
+    _run(["g++", "-O1", "-std=c++17", "-Wall", "-rdynamic", "-o", exe, os.path.join(SAN, "launch_sizes.cpp"), "-ldl"])
+    assert "launch sizes ok" in _run([exe, B.lib_path()])

@@ -330,6 +330,74 @@ __global__ __launch_bounds__(64 * APPEND_WAVES) void append_kernel(const TrAppen
                               a.theta, (int64_t)d.q_row0 + i, (int64_t)d.dst_row0 + i, cs + 64 * wave, lane);
 }
 
+// The same rows for launches of many short ones (a store of un-rotated keys, or the key rotation of the one-pass call, with
+// few KV heads per device): the lanes of a head's units own a token, so a wave holds 64 / head_units tokens side by side, and
+// a token's lanes walk its heads.  With a wave to a token a row of fewer than 64 units leaves lanes idle through the whole
+// load, rotate and store, and there are enough tokens here to fill the chip without that.  Each lane computes the angles of
+// its own pairs (in the half-split layout half of them, its partner lane the other half).  Same arithmetic, so the same bits.
+// 32768 rows, us, a wave to a token against this: bf16, one head of 64 21.6 -> 7.8 (131072 rows 86 -> 26), two heads of 128
+// 27.1 -> 19.2, fp32, one head of 64 12.6 -> 7.6.  (Angles per lane without the partner's half: 9.2, 19.9 and 9.1.)
+template <int DTYPE, bool HALF>
+__global__ __launch_bounds__(64 * APPEND_WAVES) void append_packed_kernel(const TrAppendArgs a)
+{
+    constexpr int P = Unit<DTYPE>::PAIRS, N_CS = HALF ? 2 * P : P;
+    static_assert(UnitHalf<DTYPE>::ELEMS == 2 * P, "partner lanes share the angles of their unit evenly");
+    const int head_units = a.head_dim * (DTYPE == TR_BF16 ? 2 : 4) / 16; // a power of two, at most 32
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int per_wave = 64 / head_units, unit = lane % head_units;
+    const int tok0 = ((int)blockIdx.x * APPEND_WAVES + wave) * per_wave, tok = tok0 + lane / head_units;
+    int r = a.n_desc == 1 ? 0 : last_not_above(a.tok0, a.n_desc, tok0, lane);
+    if (tok >= a.total_tokens) return; // whole tokens leave together, so a partner lane stays
+    while (r + 1 < a.n_desc && a.tok0[r + 1] <= tok) ++r;
+    const TrAppendDesc d = a.desc[r];
+    const int i = tok - a.tok0[r];
+    const int pos = a.q_pos ? a.q_pos[d.q_row0 + i] : d.pos0 + i;
+    const int64_t row_units = (int64_t)a.n_kv_heads * head_units;
+    const uint4* ks = (const uint4*)a.k_new + ((int64_t)d.q_row0 + i) * row_units + unit;
+    const uint4* vs = (const uint4*)a.v_new + ((int64_t)d.q_row0 + i) * row_units + unit;
+    uint4* kd = (uint4*)a.cache_k + ((int64_t)d.dst_row0 + i) * row_units + unit;
+    uint4* vd = (uint4*)a.cache_v + ((int64_t)d.dst_row0 + i) * row_units + unit;
+    const int hmask = head_units >> 1;
+    const bool low = unit < hmask;
+    const int m0 = HALF ? (low ? unit : unit - hmask) * N_CS : unit * N_CS;
+    double c[N_CS], s[N_CS];
+    for (int h0 = 0; h0 < a.n_kv_heads; h0 += APPEND_UNITS) {
+        uint4 kx[APPEND_UNITS], vx[APPEND_UNITS];
+#pragma unroll
+        for (int j = 0; j < APPEND_UNITS; ++j)
+            if (h0 + j < a.n_kv_heads) {
+                kx[j] = ld_stream_any(ks + (h0 + j) * head_units);
+                if (a.v_new) vx[j] = ld_stream_any(vs + (h0 + j) * head_units);
+            }
+        if (h0 == 0) { // the loads are on their way while the angles are computed
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                double sn, cn;
+                sincos((double)pos * a.theta[m0 + (HALF && !low ? P : 0) + p], &sn, &cn);
+                if constexpr (HALF) {
+                    const double co = __shfl_xor(cn, hmask), so = __shfl_xor(sn, hmask);
+                    c[p] = low ? cn : co;
+                    s[p] = low ? sn : so;
+                    c[P + p] = low ? co : cn;
+                    s[P + p] = low ? so : sn;
+                } else {
+                    c[p] = cn;
+                    s[p] = sn;
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < APPEND_UNITS; ++j)
+            if (h0 + j < a.n_kv_heads) {
+                uint4 y;
+                if constexpr (HALF) y = UnitHalf<DTYPE>::rotate(kx[j], shfl_xor_u4(kx[j], hmask), low, c, s);
+                else y = Unit<DTYPE>::rotate(kx[j], c, s);
+                st_any(kd + (h0 + j) * head_units, y);
+                if (a.v_new) st_any(vd + (h0 + j) * head_units, vx[j]); // v_new == NULL: keys only
+            }
+    }
+}
+
 // ---- offline key rotation (Sec. 3.4 step 2): K' = R(t - cu[c]) k -------------------------------------------
 // table[pos][m] = (cos, sin)(pos * theta_m) in fp64, positions 0 .. n_pos-1
 struct ThetaArg { double v[64]; };
@@ -411,12 +479,30 @@ int tr_launch_assemble(const TrAssembleArgs& a, int dtype, int n_blocks, hipStre
     return TR_OK;
 }
 
+// Several tokens per wave where rows are short enough for that to pay and there are enough of them to fill the chip all the
+// same.  Both sides in us, a wave to a token / several, interleaved layout: rows of 8 units of 16 bytes (one bf16 head of 64)
+// 5.3 / 4.6 at 4096 tokens; of 32 units 5.5 / 5.6 at 4096, 7.9 / 6.8 at 8192; of 64 units (four bf16 heads of 128; eight of
+// 64) 17.5 / 17.2 and 17.8 / 18.1 at 16384, 31.3 / 29.8 and 31.2 / 26.3 at 32768; of 128 units 174 / 193 at 131072.  fp32 has
+// half the angles and rotations per unit to share: 32 units of head size 64 (four tokens to a wave) 9.2 / 7.4 at 16384, of
+// head size 128 (two tokens) 8.6 / 9.9, 48 units 11.0 / 12.5.
+static bool append_packed(int tokens, int row_units, int head_units, int dtype)
+{
+    if (head_units > 16 || row_units > (dtype == TR_BF16 ? 64 : 32)) return false;
+    return tokens >= (row_units <= 16 ? 4096 : row_units < 64 ? 8192 : 32768);
+}
+
 int tr_launch_append(const TrAppendArgs& a, int dtype, hipStream_t s)
 {
     if (a.total_tokens <= 0) return TR_OK;
-    const int64_t blocks = ((int64_t)a.total_tokens + APPEND_WAVES - 1) / APPEND_WAVES;
+    const int head_units = a.head_dim * (dtype == TR_BF16 ? 2 : 4) / 16;
+    const bool packed = append_packed(a.total_tokens, a.n_kv_heads * head_units, head_units, dtype);
+    const int per_block = APPEND_WAVES * (packed ? 64 / head_units : 1);
+    const int64_t blocks = ((int64_t)a.total_tokens + per_block - 1) / per_block;
     auto kern = dtype == TR_BF16 ? (a.rope_half ? append_kernel<TR_BF16, true> : append_kernel<TR_BF16, false>)
                                  : (a.rope_half ? append_kernel<TR_F32, true> : append_kernel<TR_F32, false>);
+    if (packed)
+        kern = dtype == TR_BF16 ? (a.rope_half ? append_packed_kernel<TR_BF16, true> : append_packed_kernel<TR_BF16, false>)
+                                : (a.rope_half ? append_packed_kernel<TR_F32, true> : append_packed_kernel<TR_F32, false>);
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * APPEND_WAVES), 0, s, a);
     TR_HIP(hipGetLastError());
     return TR_OK;

@@ -1,7 +1,7 @@
 // The launches of calls with very many rows, on the CPU: this program defines the runtime's launch entry points itself, so the
 // built library's launches end here and only their sizes are looked at.  A launch has fewer than 2^32 threads.
 // Argument: path of libturborag_hip.so.  Exit status 0 and "launch sizes ok" on stdout mean every launch was legal and the
-// workgroups of each call add up.
+// workgroups of each call add up, also where a rule chooses between two divisions of the work.
 #include <dlfcn.h>
 #include <initializer_list>
 #include <stdint.h>
@@ -68,6 +68,33 @@ static void check(const char* what, int64_t n, int rc, uint64_t want_blocks)
     blocks = largest = 0;
 }
 
+// Many tokens with rows shorter than a wave share waves, few ones and long rows have a wave each (four waves to a workgroup).
+static void appends_of_short_rows()
+{
+    static char buf[4096] __attribute__((aligned(256)));
+    const struct {
+        int dtype, heads, head_dim, tokens, per_wave;
+    } cases[] = {
+        {TR_BF16, 1, 64, 64, 1},      {TR_BF16, 1, 64, 4095, 1},    {TR_BF16, 1, 64, 4096, 8},     {TR_BF16, 1, 128, 32769, 4},
+        {TR_BF16, 4, 64, 8191, 1},    {TR_BF16, 4, 64, 8192, 8},    {TR_BF16, 4, 128, 32767, 1},   {TR_BF16, 4, 128, 131071, 4},
+        {TR_BF16, 8, 64, 32768, 8},   {TR_BF16, 9, 64, 1 << 20, 1}, {TR_BF16, 8, 128, 1 << 20, 1}, {TR_F32, 1, 64, 131073, 4},
+        {TR_F32, 2, 64, 8192, 4},     {TR_F32, 3, 64, 1 << 20, 1},  {TR_F32, 1, 128, 1 << 20, 1},
+    };
+    for (const auto& c : cases) {
+        tr_shape s;
+        memset(&s, 0, sizeof s);
+        s.n_q_heads = s.n_kv_heads = c.heads;
+        s.head_dim = c.head_dim;
+        s.rope_base = 1e4;
+        s.dtype = c.dtype;
+        for (int half : {0, 1}) {
+            s.rope_layout = half ? TR_ROPE_HALF : TR_ROPE_INTERLEAVED;
+            check("append", c.tokens, CALL(tr_kv_append)(&s, buf, buf, (const int32_t*)buf, c.tokens, buf, buf, 0, c.tokens, nullptr),
+                  (uint64_t)((c.tokens + 4 * c.per_wave - 1) / (4 * c.per_wave)));
+        }
+    }
+}
+
 int main(int, char** argv)
 {
     lib = dlopen(argv[1], RTLD_NOW);
@@ -86,10 +113,13 @@ int main(int, char** argv)
         for (int64_t n : {((int64_t)1 << 25) - 1, (int64_t)1 << 25, ((int64_t)1 << 26) - 1, ((int64_t)1 << 28) + 3}) {
             s.head_dim = d;
             check("fp32 prefill", n, CALL(tr_prefill_attn)(&s, buf, buf, buf, idx, (int32_t)n, n, buf, nullptr, 0, nullptr), (uint64_t)n);
-            // one pass over packed segments: a wave per token turns the keys (four to a workgroup), then the attention
+            // one pass over packed segments: the keys are turned, four waves to a workgroup and at a head size of 64 four
+            // tokens to a wave, then the attention
+            const int64_t tokens = d == 64 ? 16 : 4;
             check("fp32 sequence", n, CALL(tr_sequence_prefill_attn)(&s, buf, buf, buf, idx, idx, nullptr, n, buf, buf, nullptr, 0, nullptr),
-                  (uint64_t)n + (uint64_t)(n + 3) / 4);
+                  (uint64_t)n + (uint64_t)((n + tokens - 1) / tokens));
         }
+    appends_of_short_rows();
     puts("launch sizes ok");
     return 0;
 }

@@ -51,6 +51,47 @@ def test_appended_rows(n_kv, head_dim, dtype, layout, n_req, longest):
     assert torch.isnan(ck.cpu().float()[rest]).all() and torch.isnan(cv.cpu().float()[rest]).all()
 
 
+@pytest.mark.parametrize("n_kv,head_dim,dtype,layout,n_req,total,by", [
+    (1, 64, "bf16", 0, 1, 4096, 0),      # the fewest tokens that share waves: eight to a wave
+    (1, 64, "bf16", 1, 70, 4099, 1),     # runs that begin inside a wave, a last wave that is not full, rows at odd elements
+    (3, 64, "bf16", 0, 90, 8192, 3),
+    (2, 128, "bf16", 1, 3, 8195, 0),     # four to a wave
+    (5, 64, "bf16", 1, 128, 8197, 0),    # a second round of heads with one head
+    (4, 128, "bf16", 1, 2, 32770, 0),    # rows that fill a wave
+    (1, 64, "f32", 1, 1, 4097, 1),
+    (2, 64, "f32", 0, 40, 8195, 0),
+])
+def test_many_short_rows(n_kv, head_dim, dtype, layout, n_req, total, by):
+    """Launches in which tokens share a wave give the bits that launches of few tokens give, a wave to a token."""
+    from paper_2410_07590_amd import binding as B
+    sh = synth.Shape(n_kv, n_kv, head_dim, dtype, 5e5, layout)
+    gs = H.gpu_shape(B, sh)
+    rng = np.random.Generator(np.random.PCG64([78, n_kv, head_dim, total]))
+    cut = np.sort(rng.choice(total - 1, n_req - 1, replace=False) + 1)
+    cu = np.concatenate([[0], cut, [total]]).astype(np.int32)     # every request has a token
+    start = cu.astype(np.int64) + np.arange(n_req + 1)            # and a row in front of them
+    rows, pos = int(start[-1]), torch.from_numpy(rng.integers(0, 40000, total).astype(np.int32)).cuda()
+
+    def view(n, value=None):     # `by` elements into its allocation
+        room = torch.full((n * n_kv * head_dim + 8,), float("nan"), dtype=sh.torch_dtype, device="cuda")
+        t = room[by:by + n * n_kv * head_dim].view(n, n_kv, head_dim)
+        return t if value is None else t.copy_(value)
+
+    k, v = (view(total, synth.normal_tensor(rng, (total, n_kv, head_dim), sh.torch_dtype)) for _ in range(2))
+    ck, cv = view(rows), view(rows)
+    B.tr_kv_append_batched(gs, k, v, pos, cu, start, ck, cv)
+    want_k, want_v = torch.empty_like(k), torch.empty_like(v)
+    for t0 in range(0, total, 1000):
+        t1 = min(t0 + 1000, total)
+        B.tr_kv_append(gs, k[t0:t1], v[t0:t1], pos[t0:t1], want_k[t0:t1], want_v[t0:t1], 0)
+    dst = torch.from_numpy(np.concatenate([np.arange(start[r] + 1, start[r + 1]) for r in range(n_req)])).cuda()
+    bits = torch.int16 if dtype == "bf16" else torch.int32
+    assert torch.equal(ck[dst].view(bits), want_k.view(bits)) and torch.equal(cv[dst].view(bits), want_v.view(bits))
+    assert torch.equal(cv[dst], v)
+    rest = torch.from_numpy(start[:-1]).cuda()
+    assert torch.isnan(ck[rest].float()).all() and torch.isnan(cv[rest].float()).all()
+
+
 @pytest.mark.parametrize("dtype,layout,n_q", [("bf16", 0, 1), ("bf16", 1, 6), ("f32", 0, 3), ("f32", 1, 2)])
 def test_rows_that_start_at_any_element(dtype, layout, n_q):
     """Views whose first element is not 16-byte aligned: the appended rows have the bits that aligned copies give."""

@@ -102,7 +102,7 @@ __device__ __forceinline__ void attn_f32_row(const F32Row& r, const float* __res
         ml[grp][1] = l;
     }
     __syncthreads();
-    if (tid < D) { // one channel per thread; groups without a visible key have weight 0
+    for (int t = tid; t < D; t += 64 * NW) { // one channel per thread; groups without a visible key have weight 0
         float M = -INFINITY, L = 0.0f, x = 0.0f;
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) M = fmaxf(M, ml[g][0]);
@@ -110,9 +110,9 @@ __device__ __forceinline__ void attn_f32_row(const F32Row& r, const float* __res
         for (int g = 0; g < GROUPS; ++g) {
             const float w = expf(ml[g][0] - M);
             L = fmaf(w, ml[g][1], L);
-            x = fmaf(w, ((const float*)os[g])[tid], x);
+            x = fmaf(w, ((const float*)os[g])[t], x);
         }
-        r.out[tid] = x / L;
+        r.out[t] = x / L;
     }
 }
 
@@ -156,9 +156,22 @@ __global__ __launch_bounds__(64 * NW) void blockdiag_attn_f32_kernel(const TrBlo
     attn_f32_row<D, NW>(r, (const float*)a.k, (const float*)a.v, a.n_kv_heads, a.theta, a.scale, a.rope_half);
 }
 
-// Waves per row: eight while the rows leave the chip's 256 compute units room for them (a request's few query tokens
-// over all its keys), two for the many rows of a packed sequence, whose key ranges are short.
-constexpr int FEW_ROWS = 2048;
+// Waves per row.  A row is a chain of latencies, which more waves shorten; but every wave requests a whole batch of keys
+// (`batch` of them) whether the row sees that many or not, and once the rows alone fill the chip a wave without keys of its
+// own only delays another row.  So the more rows there are, the more keys a wave has to have.  keys: what a row sees on
+// average.  us for 1 / 2 / 4 / 8 waves, head size 64 (in brackets: one wave per row with a key per lane, the form before):
+//   64 rows     24 keys   4.8  4.8  4.9  6.0 (5.4)    136 keys  12.2  8.0  7.0  6.4 (10.4)   2040 keys  123  65   35   22  (98)
+//   512 rows    24 keys   5.1  5.0  5.5  8.1 (5.6)    136 keys  12.4  8.7  7.9  9.2 (11.0)   2040 keys  129  71   40   42  (121)
+//   2048 rows   16 keys   6.2  8.8  15   27  (6.9)    112 keys  13.6  15   17   26  (15.6)   2016 keys  145  144  120  155 (203)
+//   16384 rows  32 keys   30   41   82   188 (31)     256 keys  132   139  176  282 (170)    1024 keys  477  466  496  684 (614)
+int waves_per_row(int64_t rows, int64_t keys, int head_dim)
+{
+    const int batch = KEYS * 256 / head_dim;
+    const int least = rows <= 512 ? batch / 4 : rows <= 2048 ? batch : 2 * batch;
+    int waves = rows <= 256 ? 8 : rows <= 2048 ? 4 : 2;
+    while (waves > 1 && (int64_t)waves * least > keys) waves /= 2;
+    return waves;
+}
 
 // kern over `rows` rows with `threads` threads each, in launches of at most 2^31 threads (one has fewer than 2^32)
 template <class Args> int launch_rows(void (*kern)(Args, uint32_t), const Args& a, int64_t rows, int threads, hipStream_t s)
@@ -176,17 +189,23 @@ template <class Args> int launch_rows(void (*kern)(Args, uint32_t), const Args& 
 
 int tr_launch_prefix_attn_f32(const TrPrefixArgs& a, int head_dim, int total_rows, hipStream_t s)
 {
-    const bool few = total_rows <= FEW_ROWS;
-    auto kern = head_dim == 128 ? (few ? prefix_attn_f32_kernel<128, 8> : prefix_attn_f32_kernel<128, 2>)
-                                : (few ? prefix_attn_f32_kernel<64, 8> : prefix_attn_f32_kernel<64, 2>);
-    return launch_rows(kern, a, total_rows, few ? 512 : 128, s);
+    int64_t toks = 0, keys = 0;
+    for (int i = 0; i < a.n_seq; ++i) {
+        const int64_t n = a.seq[i].n_q;
+        toks += n;
+        keys += n * (a.seq[i].kv_len - n) + n * (n + 1) / 2;
+    }
+    const int waves = waves_per_row(total_rows, toks > 0 ? keys / toks : 0, head_dim);
+#define KERN(D) (waves == 8 ? prefix_attn_f32_kernel<D, 8> : waves == 4 ? prefix_attn_f32_kernel<D, 4> : waves == 2 ? prefix_attn_f32_kernel<D, 2> : prefix_attn_f32_kernel<D, 1>)
+    return launch_rows(head_dim == 128 ? KERN(128) : KERN(64), a, total_rows, 64 * waves, s);
+#undef KERN
 }
 
-int tr_launch_blockdiag_attn_f32(const TrBlockDiagArgs& a, int head_dim, hipStream_t s)
+int tr_launch_blockdiag_attn_f32(const TrBlockDiagArgs& a, int64_t mean_keys, int head_dim, hipStream_t s)
 {
     const int64_t rows = (int64_t)a.total_tokens * a.n_q_heads;
-    const bool few = rows <= FEW_ROWS;
-    auto kern = head_dim == 128 ? (few ? blockdiag_attn_f32_kernel<128, 8> : blockdiag_attn_f32_kernel<128, 2>)
-                                : (few ? blockdiag_attn_f32_kernel<64, 8> : blockdiag_attn_f32_kernel<64, 2>);
-    return launch_rows(kern, a, rows, few ? 512 : 128, s);
+    const int waves = waves_per_row(rows, mean_keys, head_dim);
+#define KERN(D) (waves == 8 ? blockdiag_attn_f32_kernel<D, 8> : waves == 4 ? blockdiag_attn_f32_kernel<D, 4> : waves == 2 ? blockdiag_attn_f32_kernel<D, 2> : blockdiag_attn_f32_kernel<D, 1>)
+    return launch_rows(head_dim == 128 ? KERN(128) : KERN(64), a, rows, 64 * waves, s);
+#undef KERN
 }

@@ -218,7 +218,7 @@ int tr_launch_gather_attn(const TrGatherArgs& a, const TrPrefixArgs&, int, hipSt
     return 0;
 }
 
-int tr_launch_blockdiag_attn_f32(const TrBlockDiagArgs& a, int, hipStream_t)
+int tr_launch_blockdiag_attn_f32(const TrBlockDiagArgs& a, int64_t, int, hipStream_t)
 {
     ++g_ex.launches;
     REQUIRE(a.total_tokens >= 0, "fp32 block-diagonal attention: %d tokens", a.total_tokens);

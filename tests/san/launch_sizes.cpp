@@ -15,6 +15,7 @@ struct Dim3 {
     uint32_t x, y, z;
 };
 static uint64_t blocks, largest;
+static uint32_t block_threads; // of the last launch
 
 static Dim3 next_grid, next_block;
 extern "C" unsigned __hipPushCallConfiguration(Dim3 grid, Dim3 block, size_t, void*)
@@ -35,6 +36,7 @@ extern "C" int hipLaunchKernel(const void*, Dim3 grid, Dim3 block, void**, size_
 {
     const uint64_t n = (uint64_t)grid.x * grid.y * grid.z, threads = n * block.x * block.y * block.z;
     blocks += n;
+    block_threads = block.x;
     if (threads > largest) largest = threads;
     return 0;
 }
@@ -47,16 +49,16 @@ extern "C" int hipGetDevice(int* d)
 extern "C" int hipFuncSetAttribute(const void*, int, int) { return 0; }
 
 static void* lib;
-template <class F> F* entry(F*, const char* name)
+static void* entry(const char* name)
 {
     void* p = dlsym(lib, name);
     if (!p) {
         fprintf(stderr, "%s\n", dlerror());
         exit(1);
     }
-    return (F*)p;
+    return p;
 }
-#define CALL(name) entry(&name, #name)
+#define CALL(name) ((decltype(&name))entry(#name))
 
 static void check(const char* what, int64_t n, int rc, uint64_t want_blocks)
 {
@@ -95,6 +97,52 @@ static void appends_of_short_rows()
     }
 }
 
+// fp32 attention: waves per row by the number of rows and by the keys a row sees.
+static void fp32_waves()
+{
+    static char buf[4096] __attribute__((aligned(256)));
+    const int32_t* idx = (const int32_t*)buf;
+    const struct {
+        int heads, head_dim, n_q, kv_len, waves;
+    } prefill[] = {
+        {4, 64, 1, 15, 1},    {4, 64, 1, 31, 2},    {4, 64, 16, 144, 8},   {4, 64, 64, 8192, 8},  {32, 64, 16, 64, 4},  {8, 64, 65, 8192, 4},
+        {32, 64, 64, 64, 1},  {32, 64, 64, 144, 2}, {32, 64, 64, 4096, 4}, {32, 64, 65, 160, 2},  {32, 64, 65, 150, 1}, {4, 128, 1, 17, 4},
+        {4, 128, 1, 32, 8},   {32, 128, 64, 64, 2}, {32, 128, 64, 512, 4}, {32, 128, 65, 144, 2}, {32, 128, 65, 90, 1}, {32, 128, 512, 4096, 2},
+    };
+    for (const auto& c : prefill) {
+        tr_shape s;
+        memset(&s, 0, sizeof s);
+        s.n_q_heads = s.n_kv_heads = c.heads;
+        s.head_dim = c.head_dim;
+        s.rope_base = 1e4;
+        s.dtype = TR_F32;
+        check("fp32 rows", c.n_q, CALL(tr_prefill_attn)(&s, buf, buf, buf, idx, c.n_q, c.kv_len, buf, nullptr, 0, nullptr), (uint64_t)c.n_q * c.heads);
+        if (block_threads != 64u * c.waves) {
+            fprintf(stderr, "fp32 prefill of %d x %d rows of %d over %d keys: %u threads a row, expected %d waves\n", c.n_q, c.heads, c.head_dim, c.kv_len, block_threads, c.waves);
+            exit(1);
+        }
+    }
+    const struct {
+        int head_dim, chunk, n_chunks, waves;
+    } offline[] = {{64, 32, 16, 1}, {64, 512, 1, 4}, {64, 64, 64, 1}, {64, 512, 8, 2}, {128, 64, 64, 1}, {128, 128, 32, 2}, {128, 100, 1, 4}};
+    for (const auto& c : offline) {
+        tr_shape s;
+        memset(&s, 0, sizeof s);
+        s.n_q_heads = 4;
+        s.n_kv_heads = 2;
+        s.head_dim = c.head_dim;
+        s.rope_base = 1e4;
+        s.dtype = TR_F32;
+        const int64_t total = (int64_t)c.chunk * c.n_chunks;
+        const int rc = CALL(tr_chunk_prefill_attn)(&s, buf, buf, buf, idx, c.n_chunks, total, c.chunk, buf, buf, buf, (size_t)1 << 30, nullptr);
+        if (rc != TR_OK || block_threads != 64u * c.waves) {
+            fprintf(stderr, "fp32 chunks, %d x %d of %d: status %d, %u threads a row, expected %d waves\n", c.n_chunks, c.chunk, c.head_dim, rc, block_threads, c.waves);
+            exit(1);
+        }
+        blocks = largest = 0;
+    }
+}
+
 int main(int, char** argv)
 {
     lib = dlopen(argv[1], RTLD_NOW);
@@ -120,6 +168,7 @@ int main(int, char** argv)
                   (uint64_t)n + (uint64_t)((n + tokens - 1) / tokens));
         }
     appends_of_short_rows();
+    fp32_waves();
     puts("launch sizes ok");
     return 0;
 }

@@ -1,5 +1,5 @@
-"""fp32 attention at the edges of its key batches (32 groups of 8 keys at head_dim 64, 16 at 128, a quarter of that when there
-are many rows) and on both sides of the rule that chooses the waves per row, against the oracle."""
+"""fp32 attention at the edges of its key batches (8 keys for each group of lanes, four groups to a wave at head_dim 64, two at
+128) with every number of waves per row that the rule chooses, against the oracle and fp64."""
 import numpy as np
 import pytest
 
@@ -15,6 +15,8 @@ pytestmark = pytest.mark.gpu
     (64, 600, 3, 0),      # a remainder in the third batch
     (128, 125, 5, 0),     # 126 .. 130 keys, the batch being 128
     (128, 300, 2, 1),
+    (64, 380, 130, 1),    # 520 rows: four waves per row, 381 .. 510 keys in batches of 128
+    (128, 125, 130, 0),   # 126 .. 255 keys in batches of 64
     (64, 61, 1030, 0),    # 4 x 1030 rows: two waves per row, 62 .. 1091 keys in batches of 64
     (128, 30, 513, 1),    # one row block above the rule's line (4 x 513 rows), batches of 32 keys
 ])
@@ -33,6 +35,44 @@ def test_f32_attention_edges(head_dim, n_doc, n_q, layout):
                         (n_doc + np.arange(n_q)).astype(np.int32), n_doc, [n_doc])
     rows = None if n_q < 100 else np.linspace(0, n_q - 1, 40).astype(int)
     H.check_request(B, sh, store, sd, req, rows=rows, k_mismatch_frac=1e-4)
+
+
+@pytest.mark.parametrize("head_dim,n_req,n_q,lo,hi", [
+    (64, 40, 16, 1, 50),     # 2560 rows of 2 .. 65 keys: one wave per row, batches of 32
+    (128, 40, 16, 1, 50),    # batches of 16
+    (64, 9, 16, 1, 70),      # 576 rows: one wave or two
+    (128, 3, 5, 1, 20),      # 60 rows of few keys
+])
+def test_f32_rows_of_few_keys(head_dim, n_req, n_q, lo, hi):
+    """Many requests over short caches, some keys with a score of -inf: every fourth (all the keys of one group of lanes) and a
+    few more.  Positions are 0, so the result is a plain softmax, taken in fp64.  Error bound: fp32 sums of at most 70 values
+    of size up to 5, 5 * 70 * 2^-24 < 3e-5."""
+    import torch
+    from paper_2410_07590_amd import binding as B
+    gs = H.gpu_shape(B, synth.Shape(4, 2, head_dim, "f32", 1e4, 0))
+    rng = np.random.Generator(np.random.PCG64([32, head_dim, n_req]))
+    start = np.concatenate([[0], np.cumsum(rng.integers(lo, hi, n_req) + n_q)]).astype(np.int64)
+    cu = (np.arange(n_req + 1) * n_q).astype(np.int32)
+    g = torch.Generator().manual_seed(head_dim + n_req)
+    q = torch.randn(n_req * n_q, 4, head_dim, generator=g).abs()     # times a key of -3e38 in every channel: -inf
+    k, v = (torch.randn(int(start[-1]), 2, head_dim, generator=g) for _ in range(2))
+    gone = torch.zeros(int(start[-1]), dtype=torch.bool)
+    for r in range(n_req):
+        gone[int(start[r]) + 1:int(start[r + 1]):4] = True
+        gone[int(start[r]) + 6:int(start[r + 1]):16] = True
+    k[gone] = -3e38
+    out = torch.full_like(q, float("nan")).cuda()
+    B.tr_prefill_attn_batched(gs, q.cuda(), k.cuda(), v.cuda(), torch.zeros(n_req * n_q, dtype=torch.int32).cuda(), cu, start, out,
+                              B.workspace(B.tr_prefill_attn_batched_workspace_size(gs, cu, start)))
+    out = out.cpu().double()
+    for r in range(n_req):
+        keys = slice(int(start[r]), int(start[r + 1]))
+        n = keys.stop - keys.start
+        s = torch.einsum("thd,khd->thk", q[cu[r]:cu[r + 1]].double(), k[keys].repeat_interleave(2, 1).double()) / head_dim ** 0.5
+        hidden = torch.arange(n)[None, :] > torch.arange(n - n_q, n)[:, None]
+        s = s.masked_fill((hidden | gone[keys][None])[:, None], float("-inf"))
+        want = torch.einsum("thk,khd->thd", torch.softmax(s, -1), v[keys].repeat_interleave(2, 1).double())
+        assert (out[cu[r]:cu[r + 1]] - want).abs().max() < 3e-5, r
 
 
 @pytest.mark.parametrize("head_dim,n_q", [(64, 2), (64, 1030), (128, 2)])

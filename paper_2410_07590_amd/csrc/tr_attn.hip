@@ -1113,29 +1113,37 @@ __global__ __launch_bounds__(64 * SHORT_NW, 1) void short_attn_kernel(const TrPr
 // and before the reductions over the row, which run on the vector unit's cross-lane path.  (Half a wave per row, the
 // reductions as LDS permutes with the partials behind them, and a 64-bit division took 15.4 us for 39.8 k
 // rows of a serving batch, now 11.1; 6.4 for 8.2 k rows, now 5.6; 4.2 for 1.8 k, now 4.0.)
-// WIDE: some request of the launch has more than 32 key splits; the narrow form keeps statistics of 32.
+// SPLITS: statistics a row's lanes hold; 32 unless some request of the launch has more key splits.
+// GROUPS: sets of D/8 lanes that share a row, each merging every GROUPS-th split.  A lane spends sixteen vector instructions
+// on a partial, so one group walks 64 splits in some 2 us of issue alone (49 splits of 32 rows: 7.3 us, with half a wave of
+// four-channel lanes 7.8, with a whole wave of four groups 4.9).
 template <bool MAX, int LANES> __device__ __forceinline__ float row_reduce(float x)
 {
-    static_assert(LANES == 8 || LANES == 16, "");
+    static_assert(LANES == 8 || LANES == 16 || LANES == 64, "");
     auto step = [&](int y) { return MAX ? fmaxf(x, __builtin_bit_cast(float, y)) : x + __builtin_bit_cast(float, y); };
     auto bits = [&]() { return __builtin_bit_cast(int, x); };
     x = step(__builtin_amdgcn_update_dpp(bits(), bits(), 0xB1, 0xf, 0xf, false));  // quad_perm [1,0,3,2]
     x = step(__builtin_amdgcn_update_dpp(bits(), bits(), 0x4E, 0xf, 0xf, false));  // quad_perm [2,3,0,1]
     x = step(__builtin_amdgcn_update_dpp(bits(), bits(), 0x141, 0xf, 0xf, false)); // row_half_mirror
-    if (LANES == 16) x = step(__builtin_amdgcn_update_dpp(bits(), bits(), 0x140, 0xf, 0xf, false)); // row_mirror
+    if (LANES >= 16) x = step(__builtin_amdgcn_update_dpp(bits(), bits(), 0x140, 0xf, 0xf, false)); // row_mirror
+    if (LANES == 64) {
+        x = step(__shfl_xor(bits(), 16));
+        x = step(__shfl_xor(bits(), 32));
+    }
     return x;
 }
 constexpr int COMBINE_THREADS = 128; // two waves: the few thousand rows of one request then reach every compute unit
-template <int D> constexpr int combine_rows() { return COMBINE_THREADS / (D / 8); } // output rows per workgroup
+template <int D, int GROUPS> constexpr int combine_rows() { return COMBINE_THREADS / (D / 8 * GROUPS); } // output rows per workgroup
 
-template <int D, bool WIDE>
+template <int D, int SPLITS, int GROUPS>
 __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const TrPrefixArgs a, int total_rows)
 {
-    constexpr int LPR = D / 8;                   // lanes per row
-    constexpr int NK = (WIDE ? 64 : 32) / LPR;   // statistics per lane
-    constexpr int PER_ROUND = 8;                 // partials in flight per lane
-    const int lane = threadIdx.x & 63, lane_r = lane % LPR;
-    const uint32_t R = blockIdx.x * combine_rows<D>() + threadIdx.x / LPR;
+    constexpr int LPG = D / 8, LPR = LPG * GROUPS; // lanes per group and per row
+    constexpr int NK = SPLITS / LPR;               // statistics per lane
+    constexpr int PER_ROUND = 8;                   // partials in flight per lane
+    static_assert(LPR <= 64 && NK >= 1 && SPLITS / GROUPS % PER_ROUND == 0, "");
+    const int lane = threadIdx.x & 63, lane_r = lane % LPR, grp = lane_r / LPG, piece = lane % LPG;
+    const uint32_t R = blockIdx.x * combine_rows<D, GROUPS>() + threadIdx.x / LPR;
     const int tq = a.seq[0].q_row0 + (int)(R / (uint32_t)a.n_q_heads);
     const int hq = (int)(R % (uint32_t)a.n_q_heads);
     // the wave's rows ascend, so they belong to the requests from s0 to s1, nearly always one
@@ -1167,13 +1175,14 @@ __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const TrPrefix
         ml[k] = make_float2(-INFINITY, 0.0f);
         if (lane_r + LPR * k < n_split) ml[k] = *(const float2*)(a.ws_ml + (prow0 + (lane_r + LPR * k) * pstride) * 2);
     }
-    const _Float16* base = a.ws_o + prow0 * D + 8 * lane_r;
+    const _Float16* base = a.ws_o + prow0 * D + 8 * piece;
     f16x8 x[PER_ROUND];
-    auto load = [&](int sp0) { // splits past the last one give zeros
+    auto load = [&](int j0) { // the group's j-th split is GROUPS j + grp; splits past the last one give zeros
 #pragma unroll
         for (int u = 0; u < PER_ROUND; ++u) {
+            const int sp = GROUPS * (j0 + u) + grp;
             x[u] = f16x8{};
-            if (sp0 + u < n_split) x[u] = *(const f16x8*)(base + (sp0 + u) * pstride * D);
+            if (sp < n_split) x[u] = *(const f16x8*)(base + sp * pstride * D);
         }
     };
     load(0);
@@ -1193,21 +1202,29 @@ __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const TrPrefix
     for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
     const int row_lane0 = lane - lane_r; // first lane of this row
 #pragma unroll
-    for (int sp0 = 0; sp0 < NK * LPR; sp0 += PER_ROUND) { // a round is inside one k: LPR is a multiple of it
-        if (sp0 >= n_split) break;
-        if (sp0 > 0) load(sp0);
+    for (int j0 = 0; j0 < SPLITS / GROUPS; j0 += PER_ROUND) {
+        if (GROUPS * j0 >= n_split) break;
+        if (j0 > 0) load(j0);
 #pragma unroll
         for (int u = 0; u < PER_ROUND; ++u) {
-            const float ws = __shfl(w[sp0 / LPR], row_lane0 + (sp0 + u) % LPR); // zero past the last split
+            const int sp = GROUPS * (j0 + u); // + grp, which stays below LPR: the same statistics register for all groups
+            const float ws = __shfl(w[sp / LPR], row_lane0 + sp % LPR + grp); // zero past the last split
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[e] += ws * (float)x[u][e];
         }
+    }
+    if (GROUPS > 1) {
+#pragma unroll
+        for (int o = LPG; o < LPR; o <<= 1)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], o);
+        if (grp != 0) return;
     }
     const float inv = 1.0f / L;
     bf16x8 y;
 #pragma unroll
     for (int e = 0; e < 8; ++e) y[e] = (__bf16)(acc[e] * inv);
-    *(u32x4_any*)((__bf16*)a.out + ((int64_t)tq * a.n_q_heads + hq) * D + 8 * lane_r) = __builtin_bit_cast(u32x4, y);
+    *(u32x4_any*)((__bf16*)a.out + ((int64_t)tq * a.n_q_heads + hq) * D + 8 * piece) = __builtin_bit_cast(u32x4, y);
 }
 
 // ---- step 2 (offline): block-diagonal causal attention over packed chunks --------------------------------------
@@ -1386,24 +1403,34 @@ int blockdiag_dispatch(const TrBlockDiagArgs& a, int head_dim, int wg_rows, hipS
 } // namespace
 
 // the merge kernel for a launch of total_rows output rows
-template <int D> static void launch_combine_d(const TrPrefixArgs& a, bool wide, int total_rows, hipStream_t s)
+template <int D, int SPLITS, int GROUPS> static void launch_combine_d(const TrPrefixArgs& a, int total_rows, hipStream_t s)
 {
-    const dim3 blocks((unsigned)((total_rows + combine_rows<D>() - 1) / combine_rows<D>()));
-    if (wide) hipLaunchKernelGGL((combine_kernel<D, true>), blocks, dim3(COMBINE_THREADS), 0, s, a, total_rows);
-    else hipLaunchKernelGGL((combine_kernel<D, false>), blocks, dim3(COMBINE_THREADS), 0, s, a, total_rows);
+    constexpr int per_block = combine_rows<D, GROUPS>();
+    hipLaunchKernelGGL((combine_kernel<D, SPLITS, GROUPS>), dim3((unsigned)(((int64_t)total_rows + per_block - 1) / per_block)), dim3(COMBINE_THREADS), 0, s, a, total_rows);
 }
+// A wave for each row where a launch merges many splits of few rows, which lanes of one group would walk one after the other
+// while most of the chip is idle; D/8 lanes per row elsewhere.  us, lanes / wave, head size 128: 9 splits 3.6 / 4.2 at 32
+// rows, 4.4 / 4.5 at 1024; 17 splits 4.6 / 3.8 at 32, 5.0 / 4.4 at 1024, 5.9 / 6.4 at 3584; 49 splits 7.3 / 4.9 at 32,
+// 7.8 / 6.8 at 2048, 10.6 / 11.2 at 3584; head size 64: 49 splits 7.9 / 4.2 at 32, 7.8 / 6.4 at 2048.
+constexpr int COMBINE_WAVE_ROWS = 2048, COMBINE_WAVE_SPLITS = 17;
 static int launch_combine(const TrPrefixArgs& a, int head_dim, int total_rows, hipStream_t s)
 {
     int max_split = 1;
     for (int i = 0; i < a.n_seq; ++i) max_split = a.seq[i].n_split > max_split ? a.seq[i].n_split : max_split;
-    if (head_dim == 128) launch_combine_d<128>(a, max_split > 32, total_rows, s);
-    else launch_combine_d<64>(a, max_split > 32, total_rows, s);
+    if (max_split >= COMBINE_WAVE_SPLITS && total_rows <= COMBINE_WAVE_ROWS) {
+        if (head_dim == 128) launch_combine_d<128, 64, 4>(a, total_rows, s);
+        else launch_combine_d<64, 64, 8>(a, total_rows, s);
+    } else if (max_split > 32) {
+        if (head_dim == 128) launch_combine_d<128, 64, 1>(a, total_rows, s);
+        else launch_combine_d<64, 64, 1>(a, total_rows, s);
+    } else {
+        if (head_dim == 128) launch_combine_d<128, 32, 1>(a, total_rows, s);
+        else launch_combine_d<64, 32, 1>(a, total_rows, s);
+    }
     TR_HIP(hipGetLastError());
     return TR_OK;
 }
 
-// wg_rows: 128 (4 waves, 2-stage ring, two workgroups per CU), 256 (8 waves, 4-stage ring, one per CU) or 32 (the
-// short-query kernel: 4 waves share 32 rows and split the keys)
 int tr_launch_prefix_attn(const TrPrefixArgs& a, int head_dim, int wg_rows, bool any_split, int total_rows, hipStream_t s)
 {
     if (a.n_items <= 0) return TR_OK;

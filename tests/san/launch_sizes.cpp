@@ -15,7 +15,7 @@ struct Dim3 {
     uint32_t x, y, z;
 };
 static uint64_t blocks, largest;
-static uint32_t block_threads; // of the last launch
+static uint32_t block_threads, n_blocks; // of the last launch
 
 static Dim3 next_grid, next_block;
 extern "C" unsigned __hipPushCallConfiguration(Dim3 grid, Dim3 block, size_t, void*)
@@ -37,6 +37,7 @@ extern "C" int hipLaunchKernel(const void*, Dim3 grid, Dim3 block, void**, size_
     const uint64_t n = (uint64_t)grid.x * grid.y * grid.z, threads = n * block.x * block.y * block.z;
     blocks += n;
     block_threads = block.x;
+    n_blocks = grid.x;
     if (threads > largest) largest = threads;
     return 0;
 }
@@ -143,6 +144,36 @@ static void fp32_waves()
     }
 }
 
+// Merge of split keys: a wave per row for many splits of few rows, D/8 lanes per row otherwise (two waves to a workgroup).
+static void merges()
+{
+    static char buf[4096] __attribute__((aligned(256)));
+    const int32_t* idx = (const int32_t*)buf;
+    const struct {
+        int heads, head_dim, n_q, kv_len, splits, rows_per_block;
+    } cases[] = {
+        {2, 128, 16, 256 * 64, 64, 2}, {2, 128, 16, 256 * 17, 17, 2},   {2, 128, 16, 256 * 16, 16, 8},  {2, 64, 16, 256 * 64, 64, 2},
+        {2, 64, 16, 256 * 16, 16, 16}, {2, 128, 1024, 256 * 20, 20, 2}, {2, 128, 1025, 256 * 20, 20, 8}, {2, 64, 1025, 256 * 20, 20, 16},
+    };
+    for (const auto& c : cases) {
+        tr_shape s;
+        memset(&s, 0, sizeof s);
+        s.n_q_heads = c.heads;
+        s.n_kv_heads = 1;
+        s.head_dim = c.head_dim;
+        s.rope_base = 1e4;
+        s.dtype = TR_BF16;
+        const size_t ws = CALL(tr_prefill_attn_workspace_size)(&s, c.n_q, c.kv_len), row = 2 * (size_t)c.head_dim + 8;
+        const uint32_t rows = (uint32_t)(c.n_q * c.heads), want = (rows + c.rows_per_block - 1) / c.rows_per_block;
+        const int rc = CALL(tr_prefill_attn)(&s, buf, buf, buf, idx, c.n_q, c.kv_len, buf, buf, ws, nullptr);
+        if (rc != TR_OK || ws / row / rows != (size_t)c.splits || n_blocks != want) {
+            fprintf(stderr, "merge of %zu splits (expected %d) of %u rows of %d: status %d, %u workgroups, expected %u\n", ws / row / rows, c.splits, rows, c.head_dim, rc, n_blocks, want);
+            exit(1);
+        }
+    }
+    blocks = largest = 0;
+}
+
 int main(int, char** argv)
 {
     lib = dlopen(argv[1], RTLD_NOW);
@@ -169,6 +200,7 @@ int main(int, char** argv)
         }
     appends_of_short_rows();
     fp32_waves();
+    merges();
     puts("launch sizes ok");
     return 0;
 }

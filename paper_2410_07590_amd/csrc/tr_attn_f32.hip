@@ -102,7 +102,10 @@ __device__ __forceinline__ void attn_f32_row(const F32Row& r, const float* __res
         ml[grp][1] = l;
     }
     __syncthreads();
-    for (int t = tid; t < D; t += 64 * NW) { // one channel per thread; groups without a visible key have weight 0
+#pragma unroll
+    for (int i = 0; i < (D + 64 * NW - 1) / (64 * NW); ++i) { // a channel at a time; groups without a visible key have weight 0
+        const int t = tid + 64 * NW * i;
+        if (t >= D) break;
         float M = -INFINITY, L = 0.0f, x = 0.0f;
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) M = fmaxf(M, ml[g][0]);

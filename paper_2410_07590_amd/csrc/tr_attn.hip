@@ -640,6 +640,7 @@ __device__ __forceinline__ void prologue(const __bf16* __restrict__ k, const __b
 // from 25.6 to 24.1 us, 64 x 512 offline tokens from 296 to 284 us.  64-byte pieces (one more swap) measured no better.
 // The caller's rows may start at any multiple of an element: unaligned 16-byte stores are one instruction all the same.
 typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef bf16x4 bf16x4_any __attribute__((aligned(2)));
 template <int D, bool PARTIAL>
 __device__ __forceinline__ void store_rows(const Acc<D>& acc, float l_tot, bool valid, int64_t dst_row, void* dst, int lane)
 {
@@ -1089,7 +1090,7 @@ __global__ __launch_bounds__(64 * SHORT_NW, 1) void short_attn_kernel(const TrPr
             bf16x4 y;
 #pragma unroll
             for (int e = 0; e < 4; ++e) y[e] = (__bf16)(o[4 * e4 + e] * inv);
-            *(bf16x4*)(op + 4 * e4) = y;
+            *(bf16x4_any*)(op + 4 * e4) = y;
         }
     } else {
         const int rows_s = sd.n_q * g;

@@ -1,6 +1,7 @@
 """Appended cache rows at the edges of the kernel's walk: rows shorter and longer than what a wave has in flight (256 units of
 16 bytes), tokens that do not fill a workgroup, and numbers of requests around one and two rounds of the run search (64) and
-around what one launch carries (128).  Whole numbers are compared: the oracle rotates in fp64 and rounds once."""
+around what one launch carries (128); and launches of so many short rows that tokens share a wave.  Whole numbers are
+compared: the oracle rotates in fp64 and rounds once."""
 import numpy as np
 import pytest
 import torch
@@ -12,24 +13,30 @@ from tests import helpers as H
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_kv,head_dim,dtype,layout,n_req,longest", [
-    (1, 64, "bf16", 0, 1, 1),       # 8 units: most of the wave idle
-    (4, 128, "bf16", 1, 1, 7),      # 64 units, tokens not a multiple of a workgroup's four
-    (8, 128, "bf16", 0, 64, 1),     # one round of the search, full
-    (3, 64, "bf16", 1, 65, 3),      # a second round with one entry; requests of no tokens among them
-    (8, 128, "bf16", 1, 128, 2),
-    (2, 128, "bf16", 0, 131, 2),    # two launches
-    (17, 128, "bf16", 1, 3, 9),     # 272 units: a second batch with a remainder
-    (40, 128, "f32", 0, 2, 5),      # 1280 units: five whole batches
-    (9, 128, "f32", 1, 66, 2),      # 288 units
-    (5, 64, "f32", 0, 5, 4),
+@pytest.mark.parametrize("n_kv,head_dim,dtype,layout,n_req,longest,empty", [
+    (1, 64, "bf16", 0, 1, 1, 0),       # 8 units: most of the wave idle
+    (4, 128, "bf16", 1, 1, 7, 0),      # 64 units, tokens not a multiple of a workgroup's four
+    (8, 128, "bf16", 0, 64, 1, 0),     # one round of the search, full
+    (3, 64, "bf16", 1, 65, 3, 0),      # a second round with one entry
+    (3, 64, "bf16", 1, 65, 3, 30),     # and requests of no tokens among them
+    (8, 128, "bf16", 1, 128, 2, 0),    # all that a launch carries
+    (2, 128, "bf16", 0, 129, 2, 0),    # two launches, one request in the second
+    (2, 128, "bf16", 0, 131, 2, 40),
+    (8, 64, "f32", 1, 259, 1, 0),      # three launches
+    (17, 128, "bf16", 1, 3, 9, 0),     # 272 units: a second batch with a remainder
+    (40, 128, "f32", 0, 2, 5, 0),      # 1280 units: five whole batches
+    (9, 128, "f32", 1, 66, 2, 3),      # 288 units
+    (5, 64, "f32", 0, 5, 4, 1),
 ])
-def test_appended_rows(n_kv, head_dim, dtype, layout, n_req, longest):
+def test_appended_rows(n_kv, head_dim, dtype, layout, n_req, longest, empty):
+    """n_req requests with tokens, which is what the launch counts, and `empty` ones without at random places among them."""
     from paper_2410_07590_amd import binding as B
     sh = synth.Shape(n_kv, n_kv, head_dim, dtype, 5e5, layout)
     rng = np.random.Generator(np.random.PCG64([77, n_kv, head_dim, n_req]))
-    n_q = rng.integers(0, longest + 1, n_req)
-    n_q[-1] = longest
+    n_q = np.concatenate([rng.integers(1, longest + 1, n_req - 1), [longest], np.zeros(empty, np.int64)])
+    n_q = rng.permutation(n_q)
+    assert (n_q > 0).sum() == n_req
+    n_req += empty
     free = rng.integers(0, 3, n_req)                    # rows in front of the query tokens
     start = np.concatenate([[0], np.cumsum(n_q + free)]).astype(np.int64)
     cu = np.concatenate([[0], np.cumsum(n_q)]).astype(np.int32)

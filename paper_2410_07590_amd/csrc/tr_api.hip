@@ -234,7 +234,7 @@ int launch_runs(const tr_store* store, const std::vector<CopyRun>& runs, void* o
         }
         a.n_desc = n;
         if (n == 0) continue;
-        const int64_t tail_blocks = tail ? ((int64_t)tail->n_q + TR_APPEND_TOKENS_PER_BLOCK - 1) / TR_APPEND_TOKENS_PER_BLOCK : 0;
+        const int64_t tail_blocks = tail ? tr_append_blocks(tail->n_q, row_units, sh->head_dim / 2) : 0;
         if (tail && i == runs.size() && blocks + tail_blocks <= TR_MAX_BLOCKS_256) { // last launch carries the append
             a.app = *tail;
             a.app.first_block = blocks;
@@ -346,15 +346,17 @@ int launch_append(const tr_shape* shape, const void* k_new, const void* v_new, c
     a.rope_half = tr_rope_half(shape);
     tr_fill_theta(shape, a.theta);
     size_t i = 0;
+    const int groups = tr_append_groups(shape->n_kv_heads * (shape->head_dim * tr_elem_bytes(shape) / 16), shape->head_dim / 2);
+    const int max_tokens = std::max(TR_MAX_APPEND_TOKENS / std::max(groups, 1), 1);
     int done = 0; // tokens of descs[i] that earlier launches carry
     while (i < descs.size()) {
         int n = 0, tokens = 0;
-        while (i < descs.size() && n < TR_MAX_APPEND_DESC && tokens < TR_MAX_APPEND_TOKENS) {
+        while (i < descs.size() && n < TR_MAX_APPEND_DESC && tokens < max_tokens) {
             TrAppendDesc d = descs[i];
             d.q_row0 += done;
             d.dst_row0 += done;
             d.pos0 += done;
-            d.n_q = std::min(d.n_q - done, TR_MAX_APPEND_TOKENS - tokens);
+            d.n_q = std::min(d.n_q - done, max_tokens - tokens);
             if (d.n_q > 0) { a.tok0[n] = tokens; a.desc[n++] = d; tokens += d.n_q; }
             done += d.n_q;
             if (done < descs[i].n_q) break; // the launch is full
@@ -481,7 +483,7 @@ extern "C" int tr_kv_assemble_raw(const tr_store* store, const int32_t* chunk_id
     const int rc = request_runs("tr_kv_assemble_raw", store, chunk_ids, offsets, n_chunks, pos_mode, out_k, out_v, out_capacity_rows, &runs);
     if (rc) return rc;
     // every row is a token whose key is turned once, at its position id (the run's first id plus the row's index):
-    // the arithmetic of the query append, one wave per row
+    // the arithmetic of the query append
     std::vector<TrAppendDesc> d;
     d.reserve(runs.size());
     for (const CopyRun& r : runs) {

@@ -142,20 +142,23 @@ __device__ __forceinline__ uint4 ld_stream_any(const uint4* p)
 __device__ __forceinline__ void st_any(uint4* p, uint4 x) { *(u32x4_any*)p = u32x4{x.x, x.y, x.z, x.w}; }
 
 // ---- one row of the query append: K' rotated at its position id, V copied, for every KV head -----------------
-// A wave owns a token: lane m computes (cos, sin) of pair m once (the fp64 sincos is by far the longest thing here, so
-// it is done once per pair and token, and the first loads go out before it), parks it in LDS, and the lanes then walk
-// the row in 16-byte units.  64 is a multiple of the units per head, so a lane keeps its unit position, hence its pairs.
-// Nothing is shared between waves, so there is no barrier: the only dependent chain is load, angle, rotate, store.
-// (A thread per pair that walked all heads in 2- or 4-byte pieces took 7.6 us for 21 tokens of 8 heads and 10.8 us for 64
-// requests of one token, 5.3 and 4.7 us as it is here; a thread per unit with an angle for each of its pairs took
-// 15.1 us for 6200 rows of 4 heads, half-split layout, now 12.5 us.)
-constexpr int APPEND_WAVES = TR_APPEND_TOKENS_PER_BLOCK;
-constexpr int APPEND_UNITS = 4;  // 16-byte units of K (and of V) a lane has in flight
+// A group of half_dim lanes (a wave at 128 channels, half of one at 64) owns two 16-byte units per lane of a token's row; a
+// longer row has several groups.  Lane m computes (cos, sin) of pair m once (the fp64 sincos is by far the longest thing
+// here, so it is done once per pair and group, and the loads go out before it), parks it in LDS, and the lanes rotate their
+// units.  half_dim is a multiple of the units per head, so a lane keeps its unit position, hence its pairs.  Nothing is
+// shared between groups, so there is no barrier: the only dependent chain is load, angle, rotate, store, and its length
+// does not grow with the row: the angles a long row computes again cost less than a second trip.
+// Measured, every call on fresh rows (us, one group per row with four units per lane and as many trips as the row needs /
+// this): bf16, 8 heads of 128, 30000 rows 53.8 (a thread per unit position) / 47.0; replayed on the same rows: 40 heads of
+// 128, 64 rows 10.1 / 4.6, 1024 rows 13.7 / 9.4; fp32, 40 heads of 128, 1024 rows 25.4 / 14.6; bf16, one head of 64, 256
+// rows (a whole wave per token) 4.25 / 3.9.
+constexpr int APPEND_WAVES = TR_APPEND_WAVES_PER_BLOCK;
+constexpr int APPEND_UNITS = TR_APPEND_UNITS; // 16-byte units of K (and of V) a lane has in flight
 
 template <int DTYPE, bool HALF>
 __device__ __forceinline__ void append_token(const void* k_new, const void* v_new, int pos, void* cache_k, void* cache_v, int row_units,
-                                             int head_units, int half_dim, const double* theta, int64_t src_row, int64_t dst_row,
-                                             double2* cs /* LDS, 64 entries of this wave's own */, int lane)
+                                             int head_units, int half_dim, const double* theta, int64_t src_row, int64_t dst_row, int part,
+                                             double2* cs /* LDS, this group's half_dim entries */, int lane /* in the group */)
 {
     const uint4* ks = (const uint4*)k_new + src_row * row_units;
     const uint4* vs = (const uint4*)v_new + src_row * row_units;
@@ -165,41 +168,36 @@ __device__ __forceinline__ void append_token(const void* k_new, const void* v_ne
     const int hu = lane % head_units, hmask = head_units >> 1;
     const bool low = hu < hmask;
     const int m0 = (HALF && !low ? hu - hmask : hu) * N_CS;
-    double c[N_CS], s[N_CS];
-    for (int u0 = lane; u0 - lane < row_units; u0 += 64 * APPEND_UNITS) { // wave-uniform trip count
-        uint4 kx[APPEND_UNITS], vx[APPEND_UNITS];
+    const int u0 = part * APPEND_UNITS * half_dim + lane;
+    uint4 kx[APPEND_UNITS], vx[APPEND_UNITS];
 #pragma unroll
-        for (int i = 0; i < APPEND_UNITS; ++i)
-            if (u0 + 64 * i < row_units) {
-                kx[i] = ld_stream_any(ks + u0 + 64 * i);
-                if (v_new) vx[i] = ld_stream_any(vs + u0 + 64 * i);
-            }
-        if (u0 == lane) {
-            if (lane < half_dim) {
-                double sn, cn;
-                sincos((double)pos * theta[lane], &sn, &cn);
-                cs[lane] = make_double2(cn, sn);
-            }
-            // LDS serves a wave's accesses in order; only the compiler has to keep them so
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int p = 0; p < N_CS; ++p) {
-                const double2 e = cs[m0 + p];
-                c[p] = e.x;
-                s[p] = e.y;
-            }
+    for (int i = 0; i < APPEND_UNITS; ++i)
+        if (u0 + half_dim * i < row_units) {
+            kx[i] = ld_stream_any(ks + u0 + half_dim * i);
+            if (v_new) vx[i] = ld_stream_any(vs + u0 + half_dim * i);
         }
+    double sn, cn;
+    sincos((double)pos * theta[lane], &sn, &cn);
+    cs[lane] = make_double2(cn, sn);
+    // LDS serves a wave's accesses in order; only the compiler has to keep them so
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    double c[N_CS], s[N_CS];
 #pragma unroll
-        for (int i = 0; i < APPEND_UNITS; ++i)
-            if (u0 + 64 * i < row_units) { // rows are whole heads, so a lane and its partner's lane are here together
-                uint4 y;
-                if constexpr (HALF) y = UnitHalf<DTYPE>::rotate(kx[i], shfl_xor_u4(kx[i], hmask), low, c, s);
-                else y = Unit<DTYPE>::rotate(kx[i], c, s);
-                st_any(kd + u0 + 64 * i, y);
-                if (v_new) st_any(vd + u0 + 64 * i, vx[i]); // v_new == NULL: keys only
-            }
+    for (int p = 0; p < N_CS; ++p) {
+        const double2 e = cs[m0 + p];
+        c[p] = e.x;
+        s[p] = e.y;
     }
+#pragma unroll
+    for (int i = 0; i < APPEND_UNITS; ++i)
+        if (u0 + half_dim * i < row_units) { // rows are whole heads, so a lane and its partner's lane are here together
+            uint4 y;
+            if constexpr (HALF) y = UnitHalf<DTYPE>::rotate(kx[i], shfl_xor_u4(kx[i], hmask), low, c, s);
+            else y = Unit<DTYPE>::rotate(kx[i], c, s);
+            st_any(kd + u0 + half_dim * i, y);
+            if (v_new) st_any(vd + u0 + half_dim * i, vx[i]); // v_new == NULL: keys only
+        }
 }
 
 // ---- KV-cache formation: Sec. 3.4 step 5 with the reordered-position rotation of Sec. 3.2 -------------------
@@ -216,12 +214,13 @@ __global__ __launch_bounds__(256) void assemble_kernel(const TrAssembleArgs a)
     __shared__ double2 cs[64 * APPEND_WAVES]; // a copy block uses the first 64
     const int b = blockIdx.x;
     if (a.app.n_q > 0 && b >= a.app.first_block) {
-        // tail blocks: the request's own query tokens, one wave each
-        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-        const int tok = (b - a.app.first_block) * APPEND_WAVES + wave;
+        // tail blocks: the request's own query tokens
+        const uint32_t grp = ((uint32_t)(b - a.app.first_block) * 256 + threadIdx.x) >> tr_append_shift(a.half_dim);
+        const uint32_t parts = (uint32_t)tr_append_groups(a.row_units, a.half_dim);
+        const int tok = (int)(parts == 1 ? grp : grp / parts), lane = threadIdx.x & (a.half_dim - 1);
         if (tok < a.app.n_q)
-            append_token<DTYPE, HALF>(a.app.k_new, a.app.v_new, a.app.q_pos[tok], a.k_dst, a.v_dst, a.row_units, a.head_units,
-                                      a.half_dim, a.theta, tok, (int64_t)a.app.dst_row0 + tok, cs + 64 * wave, threadIdx.x & 63);
+            append_token<DTYPE, HALF>(a.app.k_new, a.app.v_new, a.app.q_pos[tok], a.k_dst, a.v_dst, a.row_units, a.head_units, a.half_dim,
+                                      a.theta, tok, (int64_t)a.app.dst_row0 + tok, (int)(grp - tok * parts), cs + (threadIdx.x - lane), lane);
         return;
     }
     int lo = 0, hi = a.n_desc - 1;
@@ -315,28 +314,36 @@ template <int DTYPE, bool HALF>
 __global__ __launch_bounds__(64 * APPEND_WAVES) void append_kernel(const TrAppendArgs a)
 {
     __shared__ double2 cs[64 * APPEND_WAVES];
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int64_t tok64 = (int64_t)blockIdx.x * APPEND_WAVES + wave;
-    if (tok64 >= a.total_tokens) return;
-    const int tok = (int)tok64;
-    // the run that owns packed token `tok` of this launch
-    const int r = a.n_desc == 1 ? 0 : last_not_above(a.tok0, a.n_desc, tok, lane);
+    const int half_dim = a.head_dim >> 1, shift = tr_append_shift(half_dim);
+    const int head_units = a.head_dim * (DTYPE == TR_BF16 ? 2 : 4) / 16; // a power of two, at most 32
+    const int row_units = a.n_kv_heads * head_units;
+    const uint32_t parts = (uint32_t)tr_append_groups(row_units, half_dim);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    // the wave's first group, whose token is wave-uniform, finds its run; a second group is in the same one or behind it
+    const uint32_t grp0 = (blockIdx.x * APPEND_WAVES + wave) << (6 - shift), grp = grp0 + ((threadIdx.x & 63) >> shift);
+    const int tok0 = (int)(parts == 1 ? grp0 : grp0 / parts);
+    if (tok0 >= a.total_tokens) return;
+    int r = a.n_desc == 1 ? 0 : last_not_above(a.tok0, a.n_desc, tok0, threadIdx.x & 63), tok = tok0;
+    if (shift == 5) {
+        tok = (int)(parts == 1 ? grp : grp / parts);
+        if (tok >= a.total_tokens) return;
+        if (r + 1 < a.n_desc && a.tok0[r + 1] <= tok) ++r; // tok is tok0 or the token behind it, and every run has one
+    }
     const TrAppendDesc d = a.desc[r];
     const int i = tok - a.tok0[r];
     // position id: the caller's, or (raw-store assembly) the run's first position plus the row's index in the run
     const int pos = a.q_pos ? a.q_pos[d.q_row0 + i] : d.pos0 + i;
-    const int head_units = a.head_dim * (DTYPE == TR_BF16 ? 2 : 4) / 16; // a power of two, at most 32
-    append_token<DTYPE, HALF>(a.k_new, a.v_new, pos, a.cache_k, a.cache_v, a.n_kv_heads * head_units, head_units, a.head_dim >> 1,
-                              a.theta, (int64_t)d.q_row0 + i, (int64_t)d.dst_row0 + i, cs + 64 * wave, lane);
+    const int lane = threadIdx.x & (half_dim - 1);
+    append_token<DTYPE, HALF>(a.k_new, a.v_new, pos, a.cache_k, a.cache_v, row_units, head_units, half_dim, a.theta,
+                              (int64_t)d.q_row0 + i, (int64_t)d.dst_row0 + i, (int)(grp - tok * parts), cs + (threadIdx.x - lane), lane);
 }
 
 // The same rows for launches of many short ones (a store of un-rotated keys, or the key rotation of the one-pass call, with
-// few KV heads per device): the lanes of a head's units own a token, so a wave holds 64 / head_units tokens side by side, and
-// a token's lanes walk its heads.  With a wave to a token a row of fewer than 64 units leaves lanes idle through the whole
-// load, rotate and store, and there are enough tokens here to fill the chip without that.  Each lane computes the angles of
+// one or two KV heads per device): the lanes of a head's units own a token, so a wave holds 64 / head_units tokens side by
+// side, and a token's lanes walk its heads.  A group of half_dim lanes leaves at least half of them idle there through the
+// whole load, rotate and store, and there are enough tokens to fill the chip without that.  Each lane computes the angles of
 // its own pairs (in the half-split layout half of them, its partner lane the other half).  Same arithmetic, so the same bits.
-// 32768 rows, us, a wave to a token against this: bf16, one head of 64 21.6 -> 7.8 (131072 rows 86 -> 26), two heads of 128
-// 27.1 -> 19.2, fp32, one head of 64 12.6 -> 7.6.  (Angles per lane without the partner's half: 9.2, 19.9 and 9.1.)
+constexpr int PACKED_HEADS = 2;
 template <int DTYPE, bool HALF>
 __global__ __launch_bounds__(64 * APPEND_WAVES) void append_packed_kernel(const TrAppendArgs a)
 {
@@ -361,41 +368,38 @@ __global__ __launch_bounds__(64 * APPEND_WAVES) void append_packed_kernel(const 
     const bool low = unit < hmask;
     const int m0 = HALF ? (low ? unit : unit - hmask) * N_CS : unit * N_CS;
     double c[N_CS], s[N_CS];
-    for (int h0 = 0; h0 < a.n_kv_heads; h0 += APPEND_UNITS) {
-        uint4 kx[APPEND_UNITS], vx[APPEND_UNITS];
+    uint4 kx[PACKED_HEADS], vx[PACKED_HEADS];
 #pragma unroll
-        for (int j = 0; j < APPEND_UNITS; ++j)
-            if (h0 + j < a.n_kv_heads) {
-                kx[j] = ld_stream_any(ks + (h0 + j) * head_units);
-                if (a.v_new) vx[j] = ld_stream_any(vs + (h0 + j) * head_units);
-            }
-        if (h0 == 0) { // the loads are on their way while the angles are computed
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                double sn, cn;
-                sincos((double)pos * a.theta[m0 + (HALF && !low ? P : 0) + p], &sn, &cn);
-                if constexpr (HALF) {
-                    const double co = __shfl_xor(cn, hmask), so = __shfl_xor(sn, hmask);
-                    c[p] = low ? cn : co;
-                    s[p] = low ? sn : so;
-                    c[P + p] = low ? co : cn;
-                    s[P + p] = low ? so : sn;
-                } else {
-                    c[p] = cn;
-                    s[p] = sn;
-                }
-            }
+    for (int j = 0; j < PACKED_HEADS; ++j)
+        if (j < a.n_kv_heads) {
+            kx[j] = ld_stream_any(ks + j * head_units);
+            if (a.v_new) vx[j] = ld_stream_any(vs + j * head_units);
         }
+    // the loads are on their way while the angles are computed
 #pragma unroll
-        for (int j = 0; j < APPEND_UNITS; ++j)
-            if (h0 + j < a.n_kv_heads) {
-                uint4 y;
-                if constexpr (HALF) y = UnitHalf<DTYPE>::rotate(kx[j], shfl_xor_u4(kx[j], hmask), low, c, s);
-                else y = Unit<DTYPE>::rotate(kx[j], c, s);
-                st_any(kd + (h0 + j) * head_units, y);
-                if (a.v_new) st_any(vd + (h0 + j) * head_units, vx[j]); // v_new == NULL: keys only
-            }
+    for (int p = 0; p < P; ++p) {
+        double sn, cn;
+        sincos((double)pos * a.theta[m0 + (HALF && !low ? P : 0) + p], &sn, &cn);
+        if constexpr (HALF) {
+            const double co = __shfl_xor(cn, hmask), so = __shfl_xor(sn, hmask);
+            c[p] = low ? cn : co;
+            s[p] = low ? sn : so;
+            c[P + p] = low ? co : cn;
+            s[P + p] = low ? so : sn;
+        } else {
+            c[p] = cn;
+            s[p] = sn;
+        }
     }
+#pragma unroll
+    for (int j = 0; j < PACKED_HEADS; ++j)
+        if (j < a.n_kv_heads) {
+            uint4 y;
+            if constexpr (HALF) y = UnitHalf<DTYPE>::rotate(kx[j], shfl_xor_u4(kx[j], hmask), low, c, s);
+            else y = Unit<DTYPE>::rotate(kx[j], c, s);
+            st_any(kd + j * head_units, y);
+            if (a.v_new) st_any(vd + j * head_units, vx[j]); // v_new == NULL: keys only
+        }
 }
 
 // ---- offline key rotation (Sec. 3.4 step 2): K' = R(t - cu[c]) k -------------------------------------------
@@ -479,25 +483,27 @@ int tr_launch_assemble(const TrAssembleArgs& a, int dtype, int n_blocks, hipStre
     return TR_OK;
 }
 
-// Several tokens per wave where rows are short enough for that to pay and there are enough of them to fill the chip all the
-// same.  Both sides in us, a wave to a token / several, interleaved layout: rows of 8 units of 16 bytes (one bf16 head of 64)
-// 5.3 / 4.6 at 4096 tokens; of 32 units 5.5 / 5.6 at 4096, 7.9 / 6.8 at 8192; of 64 units (four bf16 heads of 128; eight of
-// 64) 17.5 / 17.2 and 17.8 / 18.1 at 16384, 31.3 / 29.8 and 31.2 / 26.3 at 32768; of 128 units 174 / 193 at 131072.  fp32 has
-// half the angles and rotations per unit to share: 32 units of head size 64 (four tokens to a wave) 9.2 / 7.4 at 16384, of
-// head size 128 (two tokens) 8.6 / 9.9, 48 units 11.0 / 12.5.
-static bool append_packed(int tokens, int row_units, int head_units, int dtype)
+// Tokens share the lanes of a group where a row leaves at least half of them idle and there are enough tokens to fill the
+// chip all the same.  us, a group to a token / several, fresh rows, interleaved layout, bf16: one head of 64 (a quarter of
+// the lanes) 4.5 / 4.7 at 6000 tokens, 5.1 / 5.0 at 8192, 11.2 / 8.1 at 30000; one head of 128 4.5 / 4.7 at 3000, 5.2 / 4.9 at
+// 4096; two heads of 64 (half of them) 7.0 / 7.1 at 12000, 8.2 / 7.9 at 16384; two heads of 128 6.9 / 7.2 at 6000, 8.0 / 7.9 at
+// 8192, 62 / 48 at 100000; three heads of 64 14.8 / 14.6 at 30000, 36.6 / 36.9 at 100000; four heads of 128 26.4 / 29.9 at
+// 30000.  fp32 has half the angles per unit: one head of 64 (half of the lanes) 4.6 / 4.6 at 8192, 5.9 / 5.3 at 12000.
+static bool append_packed(int tokens, int n_kv_heads, int head_units, int half_dim, int dtype)
 {
-    if (head_units > 16 || row_units > (dtype == TR_BF16 ? 64 : 32)) return false;
-    return tokens >= (row_units <= 16 ? 4096 : row_units < 64 ? 8192 : 32768);
+    const int row_units = n_kv_heads * head_units;
+    if (n_kv_heads > PACKED_HEADS || head_units > 16 || row_units * 2 > half_dim) return false;
+    const int waves = row_units * 4 <= half_dim || dtype == TR_F32 ? 4096 : 8192; // of a group to a token
+    return tokens >= waves * (64 / half_dim);
 }
 
 int tr_launch_append(const TrAppendArgs& a, int dtype, hipStream_t s)
 {
     if (a.total_tokens <= 0) return TR_OK;
     const int head_units = a.head_dim * (dtype == TR_BF16 ? 2 : 4) / 16;
-    const bool packed = append_packed(a.total_tokens, a.n_kv_heads * head_units, head_units, dtype);
-    const int per_block = APPEND_WAVES * (packed ? 64 / head_units : 1);
-    const int64_t blocks = ((int64_t)a.total_tokens + per_block - 1) / per_block;
+    const int row_units = a.n_kv_heads * head_units;
+    const bool packed = append_packed(a.total_tokens, a.n_kv_heads, head_units, a.head_dim / 2, dtype);
+    const int64_t blocks = packed ? ((int64_t)a.total_tokens * head_units + 64 * APPEND_WAVES - 1) / (64 * APPEND_WAVES) : tr_append_blocks(a.total_tokens, row_units, a.head_dim / 2);
     auto kern = dtype == TR_BF16 ? (a.rope_half ? append_kernel<TR_BF16, true> : append_kernel<TR_BF16, false>)
                                  : (a.rope_half ? append_kernel<TR_F32, true> : append_kernel<TR_F32, false>);
     if (packed)

@@ -86,10 +86,25 @@ struct TrCopyDesc {
     int32_t delta;
     int32_t blk_start; // first block of the grid that works on this run
 };
-#define TR_APPEND_TOKENS_PER_BLOCK 4 // a wave per token
-// A launch has fewer than 2^32 threads.  More tokens than this (2^31 threads) are appended by several launches, and blocks of
-// 256 threads beyond that count are never put into one.
-#define TR_MAX_APPEND_TOKENS (1 << 25)
+// Query append: a token's row is walked by groups of half_dim = head_dim / 2 lanes (a lane per pair of a head), each of which
+// owns TR_APPEND_UNITS 16-byte units per lane; four waves to a workgroup.
+#define TR_APPEND_UNITS 2
+#define TR_APPEND_WAVES_PER_BLOCK 4
+__host__ __device__ static inline int tr_append_shift(int half_dim) { return half_dim == 64 ? 6 : 5; }
+__host__ __device__ static inline int tr_append_groups(int row_units, int half_dim)
+{
+    const int shift = tr_append_shift(half_dim) + 1;
+    static_assert(TR_APPEND_UNITS == 2, "");
+    return (row_units + (1 << shift) - 1) >> shift;
+}
+static inline int64_t tr_append_blocks(int64_t tokens, int row_units, int half_dim)
+{
+    const int per_block = 64 / half_dim * TR_APPEND_WAVES_PER_BLOCK;
+    return (tokens * tr_append_groups(row_units, half_dim) + per_block - 1) / per_block;
+}
+// A launch has fewer than 2^32 threads.  More groups than this (at most 2^31 threads) are appended by several launches, and
+// blocks of 256 threads beyond that count are never put into one.
+#define TR_MAX_APPEND_TOKENS (1 << 25) // of one group each
 #define TR_MAX_BLOCKS_256 ((1 << 24) - 1)
 #define TR_MAX_COPY_DESC 168 // what the 4 KB argument block holds
 // optional tail of an assemble launch: one request's query tokens appended by the blocks from first_block on

@@ -86,7 +86,7 @@ int tr_launch_assemble(const TrAssembleArgs& a, int, int n_blocks, hipStream_t)
         REQUIRE(a.app.first_block == blk, "assemble: appended tokens start at block %d, expected %d", a.app.first_block, blk);
         REQUIRE(a.app.dst_row0 >= 0 && (int64_t)a.app.dst_row0 + a.app.n_q <= g_ex.dst_rows, "assemble: appended tokens leave the cache");
         REQUIRE(n_blocks > blk, "assemble: no block for the appended tokens");
-        REQUIRE((int64_t)(n_blocks - blk) * TR_APPEND_TOKENS_PER_BLOCK >= a.app.n_q, "assemble: %d blocks for %d appended tokens", n_blocks - blk, a.app.n_q);
+        REQUIRE(n_blocks - blk == tr_append_blocks(a.app.n_q, a.row_units, a.half_dim), "assemble: %d blocks for %d appended tokens", n_blocks - blk, a.app.n_q);
         REQUIRE((int64_t)n_blocks * 256 < (int64_t)1 << 32, "assemble: %d blocks in one launch", n_blocks);
         g_ex.next_dst += g_ex.next_src >= 0 ? a.app.n_q : 0;
     } else {
@@ -95,7 +95,7 @@ int tr_launch_assemble(const TrAssembleArgs& a, int, int n_blocks, hipStream_t)
     return 0;
 }
 
-int tr_launch_append(const TrAppendArgs& a, int, hipStream_t)
+int tr_launch_append(const TrAppendArgs& a, int dtype, hipStream_t)
 {
     ++g_ex.launches;
     REQUIRE(a.n_desc >= 0 && a.n_desc <= TR_MAX_APPEND_DESC, "append: %d descriptors", a.n_desc);
@@ -114,7 +114,9 @@ int tr_launch_append(const TrAppendArgs& a, int, hipStream_t)
         }
         tokens += d.n_q;
     }
-    REQUIRE(tokens <= TR_MAX_APPEND_TOKENS && tokens * 64 < (int64_t)1 << 32, "append: %" PRId64 " tokens in one launch", tokens);
+    const int units = a.head_dim * (dtype == TR_BF16 ? 2 : 4) / 16;
+    REQUIRE(tokens <= TR_MAX_APPEND_TOKENS && tr_append_blocks(tokens, a.n_kv_heads * units, a.head_dim / 2) * 64 * TR_APPEND_WAVES_PER_BLOCK < (int64_t)1 << 32,
+            "append: %" PRId64 " tokens in one launch", tokens);
     REQUIRE(tokens == a.total_tokens, "append: %" PRId64 " tokens in the descriptors, %d announced", tokens, a.total_tokens);
     return 0;
 }
@@ -511,10 +513,11 @@ void appends_of_many_tokens()
     char buf[256];
     const int32_t* pos = (const int32_t*)buf;
     const int64_t MAX = TR_MAX_APPEND_TOKENS;
+    for (int heads : {1, 40}) // one group of lanes per token, and twenty
     for (int64_t n : {MAX - 1, MAX, MAX + 1, 2 * MAX, 5 * MAX + 7, ((int64_t)1 << 31) - 1 - 1000}) {
         tr_shape sh;
         std::memset(&sh, 0, sizeof sh);
-        sh.n_q_heads = sh.n_kv_heads = 1; sh.head_dim = 64; sh.dtype = TR_BF16; sh.rope_base = 1e4;
+        sh.n_q_heads = sh.n_kv_heads = heads; sh.head_dim = heads == 1 ? 64 : 128; sh.dtype = heads == 1 ? TR_BF16 : TR_F32; sh.rope_base = 1e4;
         auto expect = [&](int64_t src, int64_t dst, int64_t pos0) {
             g_ex.next_src = src; g_ex.next_dst = dst; g_ex.next_pos = pos0;
         };

@@ -71,17 +71,20 @@ static void check(const char* what, int64_t n, int rc, uint64_t want_blocks)
     blocks = largest = 0;
 }
 
-// Many tokens with rows shorter than a wave share waves, few ones and long rows have a wave each (four waves to a workgroup).
-static void appends_of_short_rows()
+// A group of head_dim / 2 lanes owns up to twice as many units of a token's row, a workgroup has 256 lanes; many tokens whose
+// rows leave half of a group idle share lanes instead.
+static void appends()
 {
     static char buf[4096] __attribute__((aligned(256)));
     const struct {
-        int dtype, heads, head_dim, tokens, per_wave;
+        int dtype, heads, head_dim, tokens, lanes; // lanes per token
     } cases[] = {
-        {TR_BF16, 1, 64, 64, 1},      {TR_BF16, 1, 64, 4095, 1},    {TR_BF16, 1, 64, 4096, 8},     {TR_BF16, 1, 128, 32769, 4},
-        {TR_BF16, 4, 64, 8191, 1},    {TR_BF16, 4, 64, 8192, 8},    {TR_BF16, 4, 128, 32767, 1},   {TR_BF16, 4, 128, 131071, 4},
-        {TR_BF16, 8, 64, 32768, 8},   {TR_BF16, 9, 64, 1 << 20, 1}, {TR_BF16, 8, 128, 1 << 20, 1}, {TR_F32, 1, 64, 131073, 4},
-        {TR_F32, 2, 64, 8192, 4},     {TR_F32, 3, 64, 1 << 20, 1},  {TR_F32, 1, 128, 1 << 20, 1},
+        {TR_BF16, 1, 64, 64, 32},      {TR_BF16, 1, 64, 8191, 32},    {TR_BF16, 1, 64, 8192, 8},      {TR_BF16, 2, 64, 16383, 32},
+        {TR_BF16, 2, 64, 16384, 8},    {TR_BF16, 3, 64, 1 << 20, 32}, {TR_BF16, 8, 64, 100, 32},      {TR_BF16, 9, 64, 1001, 64},
+        {TR_BF16, 17, 64, 1001, 96},   {TR_BF16, 1, 128, 4095, 64},   {TR_BF16, 1, 128, 4097, 16},    {TR_BF16, 2, 128, 8191, 64},
+        {TR_BF16, 2, 128, 8192, 16},   {TR_BF16, 3, 128, 1 << 20, 64}, {TR_BF16, 8, 128, 1 << 20, 64}, {TR_BF16, 9, 128, 77, 128},
+        {TR_F32, 1, 64, 8191, 32},     {TR_F32, 1, 64, 8193, 16},     {TR_F32, 2, 64, 1 << 20, 32},   {TR_F32, 5, 64, 3, 64},
+        {TR_F32, 1, 128, 1 << 20, 64}, {TR_F32, 40, 128, 1000, 640},
     };
     for (const auto& c : cases) {
         tr_shape s;
@@ -93,7 +96,7 @@ static void appends_of_short_rows()
         for (int half : {0, 1}) {
             s.rope_layout = half ? TR_ROPE_HALF : TR_ROPE_INTERLEAVED;
             check("append", c.tokens, CALL(tr_kv_append)(&s, buf, buf, (const int32_t*)buf, c.tokens, buf, buf, 0, c.tokens, nullptr),
-                  (uint64_t)((c.tokens + 4 * c.per_wave - 1) / (4 * c.per_wave)));
+                  ((uint64_t)c.tokens * c.lanes + 255) / 256);
         }
     }
 }
@@ -192,13 +195,13 @@ int main(int, char** argv)
         for (int64_t n : {((int64_t)1 << 25) - 1, (int64_t)1 << 25, ((int64_t)1 << 26) - 1, ((int64_t)1 << 28) + 3}) {
             s.head_dim = d;
             check("fp32 prefill", n, CALL(tr_prefill_attn)(&s, buf, buf, buf, idx, (int32_t)n, n, buf, nullptr, 0, nullptr), (uint64_t)n);
-            // one pass over packed segments: the keys are turned, four waves to a workgroup and at a head size of 64 four
-            // tokens to a wave, then the attention
+            // one pass over packed segments: the keys are turned, at a head size of 64 by 16 lanes per token and at one of 128
+            // by 64, then the attention
             const int64_t tokens = d == 64 ? 16 : 4;
             check("fp32 sequence", n, CALL(tr_sequence_prefill_attn)(&s, buf, buf, buf, idx, idx, nullptr, n, buf, buf, nullptr, 0, nullptr),
                   (uint64_t)n + (uint64_t)((n + tokens - 1) / tokens));
         }
-    appends_of_short_rows();
+    appends();
     fp32_waves();
     merges();
     puts("launch sizes ok");

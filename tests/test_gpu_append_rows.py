@@ -1,6 +1,7 @@
-"""Appended cache rows at the edges of the kernel's walk: rows shorter and longer than what a wave has in flight (256 units of
-16 bytes), tokens that do not fill a workgroup, and numbers of requests around one and two rounds of the run search (64) and
-around what one launch carries (128); and launches of so many short rows that tokens share a wave.  Whole numbers are
+"""Appended cache rows at the edges of the kernel's walk: rows shorter and longer than what a group of lanes owns (128 units of
+16 bytes at 128 channels, 64 at 64, where a wave has two groups), tokens that do not fill a workgroup, and numbers of requests
+around one and two rounds of the run search (64) and around what one launch carries (128); and launches of so many short rows
+that tokens share a group.  Whole numbers are
 compared: the oracle rotates in fp64 and rounds once."""
 import numpy as np
 import pytest
@@ -15,6 +16,11 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n_kv,head_dim,dtype,layout,n_req,longest,empty", [
     (1, 64, "bf16", 0, 1, 1, 0),       # 8 units: most of the wave idle
+    (1, 64, "bf16", 1, 9, 1, 0),       # two tokens to a wave, of two requests
+    (8, 64, "bf16", 0, 70, 2, 5),      # 64 units: a full group
+    (9, 64, "bf16", 1, 5, 3, 0),       # 72 units: two groups, a wave to a token
+    (17, 64, "bf16", 1, 67, 2, 0),     # 136 units: three groups, so that tokens share waves and cross them
+    (13, 64, "f32", 0, 66, 2, 7),      # 208 units: four groups
     (4, 128, "bf16", 1, 1, 7, 0),      # 64 units, tokens not a multiple of a workgroup's four
     (8, 128, "bf16", 0, 64, 1, 0),     # one round of the search, full
     (3, 64, "bf16", 1, 65, 3, 0),      # a second round with one entry
@@ -23,8 +29,8 @@ pytestmark = pytest.mark.gpu
     (2, 128, "bf16", 0, 129, 2, 0),    # two launches, one request in the second
     (2, 128, "bf16", 0, 131, 2, 40),
     (8, 64, "f32", 1, 259, 1, 0),      # three launches
-    (17, 128, "bf16", 1, 3, 9, 0),     # 272 units: a second batch with a remainder
-    (40, 128, "f32", 0, 2, 5, 0),      # 1280 units: five whole batches
+    (17, 128, "bf16", 1, 3, 9, 0),     # 272 units: a third group with a remainder
+    (40, 128, "f32", 0, 2, 5, 0),      # 1280 units: ten whole groups
     (9, 128, "f32", 1, 66, 2, 3),      # 288 units
     (5, 64, "f32", 0, 5, 4, 1),
 ])
@@ -59,17 +65,18 @@ def test_appended_rows(n_kv, head_dim, dtype, layout, n_req, longest, empty):
 
 
 @pytest.mark.parametrize("n_kv,head_dim,dtype,layout,n_req,total,by", [
-    (1, 64, "bf16", 0, 1, 4096, 0),      # the fewest tokens that share waves: eight to a wave
-    (1, 64, "bf16", 1, 70, 4099, 1),     # runs that begin inside a wave, a last wave that is not full, rows at odd elements
-    (3, 64, "bf16", 0, 90, 8192, 3),
-    (2, 128, "bf16", 1, 3, 8195, 0),     # four to a wave
-    (5, 64, "bf16", 1, 128, 8197, 0),    # a second round of heads with one head
-    (4, 128, "bf16", 1, 2, 32770, 0),    # rows that fill a wave
-    (1, 64, "f32", 1, 1, 4097, 1),
-    (2, 64, "f32", 0, 40, 8195, 0),
+    (1, 64, "bf16", 0, 1, 8192, 0),      # the fewest tokens that share a group: eight to a wave
+    (1, 64, "bf16", 1, 70, 8195, 1),     # runs that begin inside a wave, a last wave that is not full, rows at odd elements
+    (2, 64, "bf16", 0, 90, 16384, 3),    # two heads per lane
+    (2, 64, "bf16", 1, 128, 16389, 0),
+    (1, 128, "bf16", 0, 2, 4099, 0),     # four to a wave
+    (2, 128, "bf16", 1, 3, 8195, 0),
+    (1, 64, "f32", 1, 1, 8193, 1),
+    (1, 64, "f32", 0, 40, 8192, 0),
+    (3, 64, "bf16", 0, 90, 20001, 3),    # more than half of the lanes busy: a group to a token, many of them
 ])
 def test_many_short_rows(n_kv, head_dim, dtype, layout, n_req, total, by):
-    """Launches in which tokens share a wave give the bits that launches of few tokens give, a wave to a token."""
+    """Launches in which tokens share a group give the bits that launches of few tokens give, a group to a token."""
     from paper_2410_07590_amd import binding as B
     sh = synth.Shape(n_kv, n_kv, head_dim, dtype, 5e5, layout)
     gs = H.gpu_shape(B, sh)
@@ -121,3 +128,27 @@ def test_rows_that_start_at_any_element(dtype, layout, n_q):
         got[by] = (ck.cpu().clone(), cv.cpu().clone())
     for by in (1, 3):
         assert torch.equal(got[by][0], got[0][0]) and torch.equal(got[by][1], got[0][1]) and torch.equal(got[by][1], v)
+
+
+@pytest.mark.parametrize("n_kv,head_dim,dtype,layout", [(1, 64, "bf16", 0), (17, 64, "bf16", 1), (3, 64, "f32", 1), (9, 128, "bf16", 0), (40, 128, "f32", 1)])
+@pytest.mark.parametrize("n_q", [1, 6, 27])
+def test_rows_appended_by_the_launch_that_assembles(n_kv, head_dim, dtype, layout, n_q):
+    """Bytes of the two calls, for rows of one to ten groups of lanes, and nothing behind the last token."""
+    from paper_2410_07590_amd import binding as B
+    sh = synth.Shape(n_kv, n_kv, head_dim, dtype, 5e5, layout)
+    gs = H.gpu_shape(B, sh)
+    rng = np.random.Generator(np.random.PCG64([79, n_kv, head_dim, n_q]))
+    rows = np.array([0, 5, 40], np.int64)
+    ks, vs = (synth.normal_tensor(rng, (40, n_kv, head_dim), sh.torch_dtype).cuda() for _ in range(2))
+    store = B.Store(gs, ks, vs, rows)
+    ids = np.array([1, 0], np.int32)
+    offsets, _ = B.tr_plan(store, ids, B.TR_POS_REORDERED, want_pos_ids=False)
+    k, v = (synth.normal_tensor(rng, (n_q, n_kv, head_dim), sh.torch_dtype).cuda() for _ in range(2))
+    pos = torch.arange(40, 40 + n_q, dtype=torch.int32, device="cuda")
+    got, want = (torch.full((2, 40 + n_q + 3, n_kv, head_dim), float("nan"), dtype=sh.torch_dtype, device="cuda") for _ in range(2))
+    B.tr_kv_assemble_append(store, ids, offsets, B.TR_POS_REORDERED, k, v, pos, got[0], got[1])
+    B.tr_kv_assemble(store, ids, offsets, B.TR_POS_REORDERED, want[0], want[1])
+    B.tr_kv_append(gs, k, v, pos, want[0], want[1], 40)
+    bits = torch.int16 if dtype == "bf16" else torch.int32
+    assert torch.equal(got.view(bits), want.view(bits))
+    assert not torch.isnan(got[:, :40 + n_q].float()).any()

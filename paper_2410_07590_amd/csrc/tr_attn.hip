@@ -1409,16 +1409,18 @@ template <int D, int SPLITS, int GROUPS> static void launch_combine_d(const TrPr
     constexpr int per_block = combine_rows<D, GROUPS>();
     hipLaunchKernelGGL((combine_kernel<D, SPLITS, GROUPS>), dim3((unsigned)(((int64_t)total_rows + per_block - 1) / per_block)), dim3(COMBINE_THREADS), 0, s, a, total_rows);
 }
-// A wave for each row where a launch merges many splits of few rows, which lanes of one group would walk one after the other
-// while most of the chip is idle; D/8 lanes per row elsewhere.  us, lanes / wave, head size 128: 9 splits 3.6 / 4.2 at 32
-// rows, 4.4 / 4.5 at 1024; 17 splits 4.6 / 3.8 at 32, 5.0 / 4.4 at 1024, 5.9 / 6.4 at 3584; 49 splits 7.3 / 4.9 at 32,
-// 7.8 / 6.8 at 2048, 10.6 / 11.2 at 3584; head size 64: 49 splits 7.9 / 4.2 at 32, 7.8 / 6.4 at 2048.
-constexpr int COMBINE_WAVE_ROWS = 2048, COMBINE_WAVE_SPLITS = 17;
+// A wave for each row where lanes of one group would walk the splits in more than one round of eight, one after the other,
+// while most of the chip is idle; D/8 lanes per row elsewhere.  A wave for each row against lanes, difference of the whole
+// attention call in us on a fresh cache and workspace (mean over heads and layouts of rows): 6 .. 8 splits +0.04 .. +0.28 at
+// any count of rows, 10 splits -0.28 .. -0.63 up to 1024 rows, 16 splits -0.36 .. -0.69, 20 splits -0.8 .. -1.1.  Of more
+// rows the lanes fill the chip: merge alone, lanes / wave, 12 splits of 2048 rows 4.7 / 4.8, 16 splits of 2048 rows of 64
+// 4.1 / 4.9, 17 splits 5.0 / 5.0, 24 splits 5.4 / 5.1; 24 splits of 3584 rows 6.0 / 6.0, 49 splits 10.6 / 11.2.
+static bool combine_by_waves(int splits, int rows) { return splits > 8 && rows <= (splits > 16 ? 2048 : 1024); }
 static int launch_combine(const TrPrefixArgs& a, int head_dim, int total_rows, hipStream_t s)
 {
     int max_split = 1;
     for (int i = 0; i < a.n_seq; ++i) max_split = a.seq[i].n_split > max_split ? a.seq[i].n_split : max_split;
-    if (max_split >= COMBINE_WAVE_SPLITS && total_rows <= COMBINE_WAVE_ROWS) {
+    if (combine_by_waves(max_split, total_rows)) {
         if (head_dim == 128) launch_combine_d<128, 64, 4>(a, total_rows, s);
         else launch_combine_d<64, 64, 8>(a, total_rows, s);
     } else if (max_split > 32) {
@@ -1432,6 +1434,8 @@ static int launch_combine(const TrPrefixArgs& a, int head_dim, int total_rows, h
     return TR_OK;
 }
 
+// wg_rows: 128 (4 waves, 2-stage ring, two workgroups per CU), 256 (8 waves, 4-stage ring, one per CU) or 32 (the
+// short-query kernel: 4 waves share 32 rows and split the keys)
 int tr_launch_prefix_attn(const TrPrefixArgs& a, int head_dim, int wg_rows, bool any_split, int total_rows, hipStream_t s)
 {
     if (a.n_items <= 0) return TR_OK;

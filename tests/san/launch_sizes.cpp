@@ -147,7 +147,8 @@ static void fp32_waves()
     }
 }
 
-// Merge of split keys: a wave per row for many splits of few rows, D/8 lanes per row otherwise (two waves to a workgroup).
+// Merge of split keys: a wave per row for more than eight splits of few rows, D/8 lanes per row otherwise (two waves to a
+// workgroup).
 static void merges()
 {
     static char buf[4096] __attribute__((aligned(256)));
@@ -155,8 +156,10 @@ static void merges()
     const struct {
         int heads, head_dim, n_q, kv_len, splits, rows_per_block;
     } cases[] = {
-        {2, 128, 16, 256 * 64, 64, 2}, {2, 128, 16, 256 * 17, 17, 2},   {2, 128, 16, 256 * 16, 16, 8},  {2, 64, 16, 256 * 64, 64, 2},
-        {2, 64, 16, 256 * 16, 16, 16}, {2, 128, 1024, 256 * 20, 20, 2}, {2, 128, 1025, 256 * 20, 20, 8}, {2, 64, 1025, 256 * 20, 20, 16},
+        {2, 128, 16, 256 * 64, 64, 2},    {2, 128, 16, 256 * 9, 9, 2},      {2, 128, 16, 256 * 8, 8, 8},      {2, 64, 16, 256 * 64, 64, 2},
+        {2, 64, 16, 256 * 9, 9, 2},       {2, 64, 16, 256 * 8, 8, 16},      {2, 128, 512, 256 * 16, 16, 2},   {2, 128, 513, 256 * 16, 16, 8},
+        {2, 64, 513, 256 * 16, 16, 16},   {2, 128, 513, 256 * 17, 17, 2},   {2, 128, 1024, 256 * 20, 20, 2},  {2, 128, 1025, 256 * 20, 20, 8},
+        {2, 64, 1025, 256 * 20, 20, 16},
     };
     for (const auto& c : cases) {
         tr_shape s;

@@ -1248,7 +1248,7 @@ extern "C" int tr_sequence_prefill_attn(const tr_shape* shape, const void* q, co
     a.scale = (float)(1.0 / sqrt((double)shape->head_dim));
     a.scale_log2e = (float)(1.4426950408889634074 / sqrt((double)shape->head_dim));
     // how far the segments reach is on the device (fp32 has no use for the host's copy): as in one sequence
-    if (shape->dtype == TR_F32) return tr_launch_blockdiag_attn_f32(a, total_tokens / 2, shape->head_dim, s);
+    if (shape->dtype == TR_F32) return tr_launch_blockdiag_attn_f32(a, total_tokens, shape->head_dim, s);
     return tr_launch_blockdiag_attn(a, comb_rows > 0 ? &comb : nullptr, comb_rows, shape->head_dim, wg_rows, s);
     });
 }
@@ -1407,7 +1407,7 @@ extern "C" int tr_chunk_prefill_attn(const tr_shape* shape, const void* q, const
     a.scale = (float)(1.0 / sqrt((double)shape->head_dim));
     a.scale_log2e = (float)(1.4426950408889634074 / sqrt((double)shape->head_dim));
     if (plan_blockdiag(shape, nullptr, total_tokens, a.tok_per_tile, &a, nullptr, nullptr) < 0) return TR_ERR_UNSUPPORTED;
-    if (shape->dtype == TR_F32) return tr_launch_blockdiag_attn_f32(a, max_chunk_len / 2, shape->head_dim, s);
+    if (shape->dtype == TR_F32) return tr_launch_blockdiag_attn_f32(a, max_chunk_len, shape->head_dim, s);
     return tr_launch_blockdiag_attn(a, nullptr, 0, shape->head_dim, wg_rows, s);
     });
 }

@@ -11,6 +11,8 @@
 // request 19.1 -> 9.6 us).
 #include "tr_internal.h"
 
+#include <algorithm>
+
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -23,7 +25,10 @@ struct F32Row {
     int pos;
 };
 
-constexpr int KEYS = 8; // keys in flight per group of lanes
+// Keys in flight per group of lanes.  Four take 85 vector registers, so five waves share a SIMD; with eight (134, three waves)
+// 16384 rows of 1024 keys took 410 us against 353 (head size 128: 897, 732), packed chunks of 24 tokens, 153600 rows, 179
+// against 123, and 64 rows of 128 keys 6.3 against 6.0.
+constexpr int KEYS = 4;
 
 // Sum over the D/4 lanes of a key (a power of two, neighbouring lanes).
 template <int LANES> __device__ __forceinline__ float group_sum(float x)
@@ -159,21 +164,40 @@ __global__ __launch_bounds__(64 * NW) void blockdiag_attn_f32_kernel(const TrBlo
     attn_f32_row<D, NW>(r, (const float*)a.k, (const float*)a.v, a.n_kv_heads, a.theta, a.scale, a.rope_half);
 }
 
-// Waves per row.  A row is a chain of latencies, which more waves shorten; but every wave requests a whole batch of keys
-// (`batch` of them) whether the row sees that many or not, and once the rows alone fill the chip a wave without keys of its
-// own only delays another row.  So the more rows there are, the more keys a wave has to have.  keys: what a row sees on
-// average.  us for 1 / 2 / 4 / 8 waves, head size 64 (in brackets: one wave per row with a key per lane, the form before):
-//   64 rows     24 keys   4.8  4.8  4.9  6.0 (5.4)    136 keys  12.2  8.0  7.0  6.4 (10.4)   2040 keys  123  65   35   22  (98)
-//   512 rows    24 keys   5.1  5.0  5.5  8.1 (5.6)    136 keys  12.4  8.7  7.9  9.2 (11.0)   2040 keys  129  71   40   42  (121)
-//   2048 rows   16 keys   6.2  8.8  15   27  (6.9)    112 keys  13.6  15   17   26  (15.6)   2016 keys  145  144  120  155 (203)
-//   16384 rows  32 keys   30   41   82   188 (31)     256 keys  132   139  176  282 (170)    1024 keys  477  466  496  684 (614)
-int waves_per_row(int64_t rows, int64_t keys, int head_dim)
+// Waves per row.  A row is a chain of latencies, one for each batch of keys (16 at head size 64, 8 at 128), which more waves
+// shorten; but a compute unit runs about sixteen of these waves at a time, so with many rows the workgroups take turns.  The
+// launch is priced in units of a batch's latency, which grows by 8 % with every resident wave, a turn costing one more, and
+// the cheapest division is taken.  Where the rows see very different numbers of keys (a causal triangle) the last turn fills
+// up as short rows end, and the longest row's batches come on top.  mean, longest: keys a row sees.  Over 352 launches (64 to
+// 262144 rows of 8 to 2048 keys, squares, triangles, packed chunks, both head sizes) the choice is within 0.6 % of the best of
+// the four on average and 11 % at worst.  us for 1 / 2 / 4 / 8 waves:
+//                head size 64                                         head size 128
+//   64 rows      24 keys    5.0  4.3  4.6  5.2                        16 keys    6.2  5.0  4.4  4.6
+//                128 keys   11.4 7.8  6.4  6.0                        64 keys    12.6 8.1  6.3  5.5
+//   768 rows     32 keys    5.9  5.4  5.3  9.1                        24 keys    7.7  6.1  5.4  8.1
+//                512 keys   36.3 21.9 15.6 18.8                       256 keys   39.9 23.2 16.0 16.9
+//   2048 rows    48 keys    7.7  6.9  8.6  16.9                       96 keys    20.0 14.9 15.9 22.1
+//                2048 keys  140  99.4 102  113                        2048 keys  307  199  202  219
+//   16384 rows   128 keys   54.9 59.1 75.5 127                        128 keys   108  108  123  165
+//                1024 keys  353  362  374  430                        1024 keys  732  922  798  891
+int waves_per_row(int64_t rows, int64_t mean, int64_t longest, int head_dim)
 {
-    const int batch = KEYS * 256 / head_dim;
-    const int least = rows <= 512 ? batch / 4 : rows <= 2048 ? batch : 2 * batch;
-    int waves = rows <= 256 ? 8 : rows <= 2048 ? 4 : 2;
-    while (waves > 1 && (int64_t)waves * least > keys) waves /= 2;
-    return waves;
+    const int64_t per_cu = (rows + TrChip::CUS - 1) / TrChip::CUS;
+    const bool uneven = 5 * mean < 4 * longest;
+    int best = 1;
+    double least = 0.0;
+    for (int w = 1; w <= 8; w *= 2) {
+        const int64_t resident = 16 / w, full = per_cu / resident, rest = per_cu % resident;
+        auto batches = [&](int64_t keys) { return std::max(1.0, (double)keys / (w * (KEYS * 256 / head_dim)) + 0.25); };
+        auto turn = [&](int64_t n) { return 1.0 + batches(mean) * (1.0 + 0.08 * (double)(n * w)); };
+        double cost = (double)full * turn(resident) + 0.7 * (batches(longest) - batches(mean));
+        if (rest) cost += uneven && full ? turn(resident) * (double)rest / (double)resident : turn(rest);
+        if (w == 1 || cost < least) {
+            least = cost;
+            best = w;
+        }
+    }
+    return best;
 }
 
 // kern over `rows` rows with `threads` threads each, in launches of at most 2^31 threads (one has fewer than 2^32)
@@ -192,22 +216,23 @@ template <class Args> int launch_rows(void (*kern)(Args, uint32_t), const Args& 
 
 int tr_launch_prefix_attn_f32(const TrPrefixArgs& a, int head_dim, int total_rows, hipStream_t s)
 {
-    int64_t toks = 0, keys = 0;
+    int64_t toks = 0, keys = 0, longest = 0;
     for (int i = 0; i < a.n_seq; ++i) {
         const int64_t n = a.seq[i].n_q;
         toks += n;
         keys += n * (a.seq[i].kv_len - n) + n * (n + 1) / 2;
+        if (n > 0) longest = std::max<int64_t>(longest, a.seq[i].kv_len);
     }
-    const int waves = waves_per_row(total_rows, toks > 0 ? keys / toks : 0, head_dim);
+    const int waves = waves_per_row(total_rows, toks > 0 ? keys / toks : 0, longest, head_dim);
 #define KERN(D) (waves == 8 ? prefix_attn_f32_kernel<D, 8> : waves == 4 ? prefix_attn_f32_kernel<D, 4> : waves == 2 ? prefix_attn_f32_kernel<D, 2> : prefix_attn_f32_kernel<D, 1>)
     return launch_rows(head_dim == 128 ? KERN(128) : KERN(64), a, total_rows, 64 * waves, s);
 #undef KERN
 }
 
-int tr_launch_blockdiag_attn_f32(const TrBlockDiagArgs& a, int64_t mean_keys, int head_dim, hipStream_t s)
+int tr_launch_blockdiag_attn_f32(const TrBlockDiagArgs& a, int64_t longest, int head_dim, hipStream_t s)
 {
     const int64_t rows = (int64_t)a.total_tokens * a.n_q_heads;
-    const int waves = waves_per_row(rows, mean_keys, head_dim);
+    const int waves = waves_per_row(rows, longest / 2, longest, head_dim);
 #define KERN(D) (waves == 8 ? blockdiag_attn_f32_kernel<D, 8> : waves == 4 ? blockdiag_attn_f32_kernel<D, 4> : waves == 2 ? blockdiag_attn_f32_kernel<D, 2> : blockdiag_attn_f32_kernel<D, 1>)
     return launch_rows(head_dim == 128 ? KERN(128) : KERN(64), a, rows, 64 * waves, s);
 #undef KERN

@@ -290,8 +290,8 @@ static inline int tr_rope_half(const tr_shape* s) { return s->rope_layout == TR_
 int tr_launch_blockdiag_attn(const TrBlockDiagArgs& a, const TrPrefixArgs* combine, int combine_rows, int head_dim, int wg_rows,
                              hipStream_t s);
 int tr_launch_gather_attn(const TrGatherArgs& a, const TrPrefixArgs& combine_args, int head_dim, hipStream_t s);
-// mean_keys: keys a row sees on average, as far as the host knows it; it decides how a row is shared out, not the result
-int tr_launch_blockdiag_attn_f32(const TrBlockDiagArgs& a, int64_t mean_keys, int head_dim, hipStream_t s);
+// longest: most keys that a row sees, as far as the host knows it; it decides how a row is shared out, not the result
+int tr_launch_blockdiag_attn_f32(const TrBlockDiagArgs& a, int64_t longest, int head_dim, hipStream_t s);
 // y_j = x w_j^T for at most 128 rows of x and up to TR_LINEAR_MAX_OUT weights that share x; N = sum of the feature
 // counts; partial: fp32 [tr_linear_splits(M, N, K), M, N] when that count exceeds 1
 #define TR_LINEAR_MAX_OUT 4

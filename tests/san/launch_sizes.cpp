@@ -101,7 +101,7 @@ static void appends()
     }
 }
 
-// fp32 attention: waves per row by the number of rows and by the keys a row sees.
+// fp32 attention: waves per row by the number of rows, the keys a row sees and how many turns the rows take on the chip.
 static void fp32_waves()
 {
     static char buf[4096] __attribute__((aligned(256)));
@@ -109,9 +109,10 @@ static void fp32_waves()
     const struct {
         int heads, head_dim, n_q, kv_len, waves;
     } prefill[] = {
-        {4, 64, 1, 15, 1},    {4, 64, 1, 31, 2},    {4, 64, 16, 144, 8},   {4, 64, 64, 8192, 8},  {32, 64, 16, 64, 4},  {8, 64, 65, 8192, 4},
-        {32, 64, 64, 64, 1},  {32, 64, 64, 144, 2}, {32, 64, 64, 4096, 4}, {32, 64, 65, 160, 2},  {32, 64, 65, 150, 1}, {4, 128, 1, 17, 4},
-        {4, 128, 1, 32, 8},   {32, 128, 64, 64, 2}, {32, 128, 64, 512, 4}, {32, 128, 65, 144, 2}, {32, 128, 65, 90, 1}, {32, 128, 512, 4096, 2},
+        {4, 64, 1, 12, 1},     {4, 64, 1, 20, 2},      {4, 64, 1, 40, 4},      {4, 64, 1, 130, 8},     {4, 64, 16, 144, 8},   {4, 128, 1, 6, 1},
+        {4, 128, 1, 10, 2},    {4, 128, 1, 20, 4},     {4, 128, 1, 70, 8},     {8, 128, 16, 17, 4},    {8, 128, 200, 201, 4}, {32, 64, 16, 24, 2},
+        {32, 64, 16, 36, 4},   {32, 64, 16, 100, 8},   {32, 64, 28, 100, 4},   {32, 64, 32, 2000, 4},  {32, 64, 56, 100, 2},  {32, 64, 64, 800, 2},
+        {32, 128, 64, 400, 2}, {32, 64, 96, 600, 4},   {32, 64, 112, 600, 1},  {32, 64, 250, 500, 1},  {32, 128, 128, 300, 2}, {32, 64, 1024, 1100, 1},
     };
     for (const auto& c : prefill) {
         tr_shape s;
@@ -128,7 +129,7 @@ static void fp32_waves()
     }
     const struct {
         int head_dim, chunk, n_chunks, waves;
-    } offline[] = {{64, 32, 16, 1}, {64, 512, 1, 4}, {64, 64, 64, 1}, {64, 512, 8, 2}, {128, 64, 64, 1}, {128, 128, 32, 2}, {128, 100, 1, 4}};
+    } offline[] = {{64, 32, 16, 2}, {64, 512, 1, 4}, {64, 64, 64, 1}, {64, 512, 8, 1}, {64, 24, 200, 1}, {128, 32, 8, 4}, {128, 100, 1, 8}};
     for (const auto& c : offline) {
         tr_shape s;
         memset(&s, 0, sizeof s);

@@ -1,4 +1,4 @@
-"""fp32 attention at the edges of its key batches (8 keys for each group of lanes, four groups to a wave at head_dim 64, two at
+"""fp32 attention at the edges of its key batches (4 keys for each group of lanes, four groups to a wave at head_dim 64, two at
 128) with every number of waves per row that the rule chooses, against the oracle and fp64."""
 import numpy as np
 import pytest
@@ -11,14 +11,20 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("head_dim,n_doc,n_q,layout", [
     (64, 1, 1, 0),        # two keys: all groups but two are empty
-    (64, 253, 4, 1),      # rows that see 254 .. 257 keys, the batch being 256
-    (64, 600, 3, 0),      # a remainder in the third batch
-    (128, 125, 5, 0),     # 126 .. 130 keys, the batch being 128
+    (64, 125, 4, 1),      # eight waves, rows that see 126 .. 129 keys, the batch being 128
+    (64, 253, 4, 1),      # 254 .. 257 keys: two batches
+    (64, 600, 3, 0),      # a remainder in the fifth batch
+    (128, 61, 5, 0),      # 62 .. 66 keys, the batch being 64
+    (128, 125, 5, 0),
     (128, 300, 2, 1),
-    (64, 380, 130, 1),    # 520 rows: four waves per row, 381 .. 510 keys in batches of 128
-    (128, 125, 130, 0),   # 126 .. 255 keys in batches of 64
-    (64, 61, 1030, 0),    # 4 x 1030 rows: two waves per row, 62 .. 1091 keys in batches of 64
-    (128, 30, 513, 1),    # one row block above the rule's line (4 x 513 rows), batches of 32 keys
+    (64, 380, 130, 1),    # 520 rows: four waves per row, 381 .. 510 keys in batches of 64
+    (128, 125, 130, 0),   # 126 .. 255 keys
+    (64, 61, 1030, 0),    # 4 x 1030 rows of 62 .. 1091 keys: four waves
+    (64, 1000, 300, 0),   # 1200 rows of about as many keys
+    (128, 1000, 300, 1),
+    (128, 30, 513, 1),    # 2052 rows: four waves, batches of 32
+    (128, 5, 3, 0),       # two waves
+    (128, 5, 1, 0),       # one
 ])
 def test_f32_attention_edges(head_dim, n_doc, n_q, layout):
     from paper_2410_07590_amd import binding as B
@@ -38,9 +44,11 @@ def test_f32_attention_edges(head_dim, n_doc, n_q, layout):
 
 
 @pytest.mark.parametrize("head_dim,n_req,n_q,lo,hi", [
-    (64, 40, 16, 1, 50),     # 2560 rows of 2 .. 65 keys: one wave per row, batches of 32
+    (64, 40, 16, 1, 50),     # 2560 rows of 2 .. 65 keys: two waves per row, batches of 32
     (128, 40, 16, 1, 50),    # batches of 16
-    (64, 9, 16, 1, 70),      # 576 rows: one wave or two
+    (64, 9, 16, 1, 70),      # 576 rows: four waves, some of them without keys
+    (64, 400, 16, 1, 30),    # 25600 rows: one wave
+    (128, 400, 16, 1, 10),
     (128, 3, 5, 1, 20),      # 60 rows of few keys
 ])
 def test_f32_rows_of_few_keys(head_dim, n_req, n_q, lo, hi):

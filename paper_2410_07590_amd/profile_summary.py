@@ -11,9 +11,12 @@
                              SQ_WAIT_INST_LDS SQ_WAVE_CYCLES SQ_ACTIVE_INST_VALU --output-format csv -d <dir>/<case>.sq -o out
                              -- python3 bench.py --case <case> --iters 5
 
-(each from /tmp with TMPDIR=/tmp, one run per counter set).  `copy.fetch` / `copy.write` calibrate the byte counters
-on a 256 MiB device copy.  Written: kernel_trace_by_workload.md, hbm_traffic_pmc.md, mfma_utilisation_pmc.md and
-traffic.json (HBM bytes per call keyed the way bench.py keys its roofline rows, with the commit and the digest of
+    <case>.passes  rocprofv3 --kernel-trace --output-format csv -d <dir>/<case>.passes -o out
+                             -- python3 -m paper_2410_07590_amd.profile_summary --run <case>, for the cases of perf/cases.py
+
+(each from /tmp with TMPDIR=/tmp and, for the last, PYTHONPATH=<repository>; one run per counter set).  `copy.fetch` / `copy.write` calibrate the byte counters
+on a 256 MiB device copy.  Written: kernel_trace_by_workload.md, hbm_traffic_pmc.md, mfma_utilisation_pmc.md,
+kernel_trace_cases.md and traffic.json (HBM bytes per call keyed the way bench.py keys its roofline rows, with the commit and the digest of
 the kernel sources they were measured on; bench.py reports them only while that digest still matches).
 
 Only launches of this library's kernels are kept; the first launch of every kernel in a run is dropped as warm-up.
@@ -28,8 +31,8 @@ import re
 import subprocess
 import sys
 
-OUR_KERNELS = ("assemble_kernel", "append_kernel", "prefix_attn_kernel", "combine_kernel", "short_attn_kernel",
-               "blockdiag_attn_kernel", "gather_attn_kernel", "rope_table_kernel", "rope_rows_kernel", "linear_kernel",
+OUR_KERNELS = ("assemble_kernel", "append_kernel", "append_packed_kernel", "prefix_attn", "combine_kernel", "short_attn_kernel",
+               "blockdiag_attn", "gather_attn_kernel", "rope_table_kernel", "rope_rows_kernel", "linear_kernel",
                "linear_combine_kernel", "mfma_loop_probe_kernel", "fill_kernel")
 COPY_KIB = 262144.0   # bench.py --case copy moves 256 MiB each way
 
@@ -134,6 +137,38 @@ def per_call(launches, iters):
     return launches // iters
 
 
+PASSES = 12   # of a case of perf/cases.py
+
+
+def run_passes(name):
+    """The program of the <case>.passes runs: the case's preparation, then its passes."""
+    import torch
+    from perf import cases
+    case, = [c for c in cases.listed() if c["name"] == name]
+    state = cases.prepare(case, 1)
+    for _ in range(PASSES):
+        cases.run(state)
+        torch.cuda.synchronize()
+    print("case %s: %d passes" % (name, PASSES))
+
+
+def passes_table(folder):
+    """[(kernel, workgroups, median us)] of one pass, in launch order; equal launches that alternate are given once, counted."""
+    rows = []
+    for r in sorted(read_csv(folder, "*kernel_trace.csv"), key=lambda r: int(r["Start_Timestamp"])):
+        name = short_name(r["Kernel_Name"])
+        if ours(name):
+            rows.append((name, int(r["Grid_Size_X"]) // max(1, int(r["Workgroup_Size_X"])), (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3))
+    n, rest = divmod(len(rows), PASSES)
+    if n == 0 or rest:
+        raise ValueError("%s: %d launches do not make %d passes" % (folder, len(rows), PASSES))
+    seen = collections.OrderedDict()
+    for i in range(n):
+        t = sorted(rows[p * n + i][2] for p in range(PASSES))
+        seen.setdefault(rows[i][:2], []).append((t[(PASSES - 1) // 2] + t[PASSES // 2]) / 2)
+    return [(name, grid, len(v), sum(v) / len(v)) for (name, grid), v in seen.items()]
+
+
 def git_commit():
     try:
         here = os.path.dirname(os.path.abspath(__file__))
@@ -157,9 +192,14 @@ def source_digest():
 
 def main():
     ap = argparse.ArgumentParser()
-    ap.add_argument("root")
+    ap.add_argument("root", nargs="?")
+    ap.add_argument("--run", metavar="CASE", help="run the passes of a case of perf/cases.py and nothing else")
     ap.add_argument("--out", default=os.path.join(os.path.dirname(os.path.abspath(__file__)), "..", "profiles"))
     args = ap.parse_args()
+    if args.run:
+        return run_passes(args.run)
+    if not args.root:
+        ap.error("a folder of runs is expected")
     runs = collections.defaultdict(dict)
     for d in sorted(os.listdir(args.root)):
         if "." in d and os.path.isdir(os.path.join(args.root, d)):
@@ -195,6 +235,21 @@ def main():
                 name, d["n"], mult[name] or "set-up", d["avg"], d["min"], d["max"], d["grid"], d["wg"], d["vgpr"], d["agpr"], d["lds"], d["scratch"]))
         lines.append("\ncall us (sum of avg x launches per call): %.2f" % total)
     write(args.out, "kernel_trace_by_workload.md", lines)
+
+    # ---------------------------------------------------------------- passes of the measured cases
+    lines = ["# Kernel times per pass of the cases in `perf/cases.py`\n", stamp,
+             "Each case is one run of `rocprofv3 --kernel-trace --output-format csv -d <dir>/<case>.passes -o out -- python3 -m "
+             "paper_2410_07590_amd.profile_summary --run <case>` (from /tmp, TMPDIR=/tmp, PYTHONPATH=<repository>), summarised by "
+             "`python -m paper_2410_07590_amd.profile_summary <dir>`: medians of %d passes, in launch order.  Every pass is waited "
+             "for and repeats on the same buffers.  Durations under the tracer include its cost per kernel (about 1 us on the "
+             "short ones), and the clock of long kernels is lower than in an undisturbed run.\n" % PASSES,
+             "| Case | Kernel | Workgroups | us |", "|---|---|---|---|"]
+    order = [c for c in runs if "passes" in runs[c]]
+    for case in order:
+        for name, grid, count, us in passes_table(runs[case]["passes"]):
+            lines.append("| %s | `%s`%s | %d | %.2f |" % (case, name, " x %d" % count if count > 1 else "", grid, us))
+    if order:
+        write(args.out, "kernel_trace_cases.md", lines)
 
     # ---------------------------------------------------------------- HBM traffic
     factor = {"FETCH_SIZE": None, "WRITE_SIZE": None}

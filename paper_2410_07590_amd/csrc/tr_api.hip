@@ -504,12 +504,17 @@ namespace {
 struct ReqGeom { int32_t q_row0, n_q; int64_t kv_row0, kv_len; };
 
 constexpr int KEY_TILE = 64;
-constexpr int TARGET_ITEMS = TrChip::CUS;   // workgroups to aim for when splitting keys: one per CU (more splits cost more partial traffic than they gain)
+// Workgroups to aim for when splitting keys, one per CU, and the fewest keys of a split.  One request on a fresh cache and
+// workspace, time against this rule (mean over two shapes of 128 channels and one of 64, contexts of 500 to 16384 rows): two
+// workgroups per CU 1.00 .. 1.01 for 1 to 64 query tokens, 1.11 for 128; splits of at least 512 keys 1.12 .. 1.23; of at least
+// 128 keys 0.92 for 1 to 16 query tokens and 0.94 .. 0.95 for 37 to 128, for up to 4000 rows of context, 1.00 above 8000,
+// with up to twice the workspace.
+constexpr int TARGET_ITEMS = TrChip::CUS;
 constexpr int MIN_SPLIT_KEYS = 256;
 #ifndef TR_MAX_SPLIT
 #define TR_MAX_SPLIT 64
 #endif
-constexpr int MAX_SPLIT = TR_MAX_SPLIT;  // the wide form of the combine kernel holds the statistics of 64
+constexpr int MAX_SPLIT = TR_MAX_SPLIT;  // the merge holds the statistics of at most 64
 
 // Packed rows per workgroup: 256 (8 waves, deep LDS ring) when one KV head has enough rows to fill such tiles,
 // else 128 (4 waves).  The wg_rows override of tr_set_tuning wins.

@@ -115,18 +115,6 @@ template <bool MAX> __device__ __forceinline__ int wave_reduce_i(int v)
 __device__ __forceinline__ int wave_max_i(int v) { return wave_reduce_i<true>(v); }
 __device__ __forceinline__ int wave_min_i(int v) { return wave_reduce_i<false>(v); }
 
-// Index of the last of n ascending entries that is <= x, for a wave-uniform x >= first(0): every lane looks at its own
-// entry and a ballot counts.  One trip to the argument block, where a search takes one for every step, some hundred
-// nanoseconds each, before a workgroup knows what to load (64 decode requests: six).  Every lane must be active.
-template <class First> __device__ __forceinline__ int last_not_above(int n, int x, First first)
-{
-    if (n == 1) return 0;
-    const int lane = threadIdx.x & 63;
-    int count = 0;
-    for (int i0 = 0; i0 < n; i0 += 64) count += __popcll(__ballot(i0 + lane < n && first(min(i0 + lane, n - 1)) <= x));
-    return count - 1;
-}
-
 // ---- rotated queries (Eq. 3 at the token's position id) -------------------------------------------------------
 // Lane (c = lane & 31, h = lane >> 5) ends up holding Q'[row c][16 ks + 8 h .. +7] for ks < D/16, scaled by
 // log2(e)/sqrt(d) before its single rounding to bf16.  Angles are reduced in fp64 to [-1/2, 1/2] revolutions and
@@ -633,11 +621,14 @@ __device__ __forceinline__ void prologue(const __bf16* __restrict__ k, const __b
 // A partial is normalised by its own denominator, so it is a convex combination of V rows and fp16 (11 bits,
 // 8 times finer than the bf16 result) holds it; the merge weighs it with l again.
 // Lanes c and c + 32 hold alternate groups of four channels of row c.  Two swaps of the vector unit give each of them
-// eight neighbouring channels, so a lane stores 16 bytes and a row receives 32 contiguous bytes per instruction; the L2
-// puts the pieces of a line together.  An epilogue is pure latency at the end of a workgroup, so what counts is how
-// short its dependent chain is: staging the rows through LDS for whole-line stores, with two lane permutes per four rows,
-// took 2.4 us of the 12.4 us of a workgroup that walks five key tiles; without it the request over 8 x 512 rows went
-// from 25.6 to 24.1 us, 64 x 512 offline tokens from 296 to 284 us.  64-byte pieces (one more swap) measured no better.
+// eight neighbouring channels, so a lane stores 16 bytes and a row receives 32 contiguous bytes per instruction.  An
+// epilogue is pure latency at the end of a workgroup, so what counts is how short its dependent chain is: staging the rows
+// through LDS for whole-line stores, with two lane permutes per four rows, took 2.4 us of the 12.4 us of a workgroup that
+// walks five key tiles; without it the request over 8 x 512 rows went from 25.6 to 24.1 us, 64 x 512 offline tokens from
+// 296 to 284 us.  Partials too are ordinary stores: 64-byte pieces (a third swap) that bypass the L2 are faster where a call
+// is repeated on one workspace that the caches still hold (8 MB of partials 22.6 -> 20.7 us, and whole lines through LDS 21.7),
+// but in every call on a workspace that other work has displaced, slower than the above by 4 to 9 % from 4 MB on
+// (16 heads, 100 tokens over 5000 keys 21.8 -> 23.8 us; through LDS 23.0); 64-byte pieces through the L2 make no difference.
 // The caller's rows may start at any multiple of an element: unaligned 16-byte stores are one instruction all the same.
 typedef u32x4 u32x4_any __attribute__((aligned(2)));
 typedef bf16x4 bf16x4_any __attribute__((aligned(2)));
@@ -672,11 +663,7 @@ __device__ __forceinline__ void store_rows(const Acc<D>& acc, float l_tot, bool 
                 w[i] = r[0];
                 w[2 + i] = r[1];
             }
-            if (valid) {
-                // ordinary stores, partials too: a streaming store would send the 32-byte pieces on before the L2 has
-                // put a line together (8 x 512 rows, 64 query tokens: 25.3 us against 24.1)
-                *(u32x4_any*)(row + (32 * db + 16 * p) * 2) = w;
-            }
+            if (valid) *(u32x4_any*)(row + (32 * db + 16 * p) * 2) = w;
         }
 }
 

@@ -299,17 +299,6 @@ __global__ __launch_bounds__(256) void assemble_kernel(const TrAssembleArgs a)
 }
 
 // ---- query append: cache rows of the query tokens (K' rotated at q_pos, V copied) -------------------------
-// Index of the last entry of first[0 .. n) that is <= x, for a wave-uniform x: every lane looks at its own entries and a
-// ballot counts, one trip to the argument block where a search takes one per step (each some hundred nanoseconds, which is
-// what a launch of a few tokens consists of).  first[] ascends and first[0] <= x.
-__device__ __forceinline__ int last_not_above(const int32_t* first, int n, int x, int lane)
-{
-    int count = 0;
-    for (int i0 = 0; i0 < n; i0 += 64) // at most two rounds: TR_MAX_APPEND_DESC entries
-        count += __popcll(__ballot(i0 + lane < n && first[min(i0 + lane, n - 1)] <= x));
-    return count - 1;
-}
-
 template <int DTYPE, bool HALF>
 __global__ __launch_bounds__(64 * APPEND_WAVES) void append_kernel(const TrAppendArgs a)
 {
@@ -323,7 +312,7 @@ __global__ __launch_bounds__(64 * APPEND_WAVES) void append_kernel(const TrAppen
     const uint32_t grp0 = (blockIdx.x * APPEND_WAVES + wave) << (6 - shift), grp = grp0 + ((threadIdx.x & 63) >> shift);
     const int tok0 = (int)(parts == 1 ? grp0 : grp0 / parts);
     if (tok0 >= a.total_tokens) return;
-    int r = a.n_desc == 1 ? 0 : last_not_above(a.tok0, a.n_desc, tok0, threadIdx.x & 63), tok = tok0;
+    int r = last_not_above(a.n_desc, tok0, [&](int i) { return a.tok0[i]; }), tok = tok0;
     if (shift == 5) {
         tok = (int)(parts == 1 ? grp : grp / parts);
         if (tok >= a.total_tokens) return;
@@ -353,7 +342,7 @@ __global__ __launch_bounds__(64 * APPEND_WAVES) void append_packed_kernel(const 
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int per_wave = 64 / head_units, unit = lane % head_units;
     const int tok0 = ((int)blockIdx.x * APPEND_WAVES + wave) * per_wave, tok = tok0 + lane / head_units;
-    int r = a.n_desc == 1 ? 0 : last_not_above(a.tok0, a.n_desc, tok0, lane);
+    int r = last_not_above(a.n_desc, tok0, [&](int i) { return a.tok0[i]; });
     if (tok >= a.total_tokens) return; // whole tokens leave together, so a partner lane stays
     while (r + 1 < a.n_desc && a.tok0[r + 1] <= tok) ++r;
     const TrAppendDesc d = a.desc[r];

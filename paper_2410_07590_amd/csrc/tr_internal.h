@@ -86,6 +86,18 @@ struct TrCopyDesc {
     int32_t delta;
     int32_t blk_start; // first block of the grid that works on this run
 };
+// Index of the last of n ascending entries that is <= x, for a wave-uniform x >= first(0): every lane looks at its own
+// entry and a ballot counts.  One trip to the argument block, where a search takes one for every step, some hundred
+// nanoseconds each, before a workgroup knows what to load (64 decode requests: six).  Every lane must be active.
+template <class First> __device__ __forceinline__ int last_not_above(int n, int x, First first)
+{
+    if (n == 1) return 0;
+    const int lane = threadIdx.x & 63;
+    int count = 0;
+    for (int i0 = 0; i0 < n; i0 += 64) count += __popcll(__ballot(i0 + lane < n && first(min(i0 + lane, n - 1)) <= x));
+    return count - 1;
+}
+
 // Query append: a token's row is walked by groups of half_dim = head_dim / 2 lanes (a lane per pair of a head), each of which
 // owns TR_APPEND_UNITS 16-byte units per lane; four waves to a workgroup.
 #define TR_APPEND_UNITS 2

@@ -14,10 +14,11 @@
     <case>.passes  rocprofv3 --kernel-trace --output-format csv -d <dir>/<case>.passes -o out
                              -- python3 -m paper_2410_07590_amd.profile_summary --run <case>, for the cases of perf/cases.py
 
-(each from /tmp with TMPDIR=/tmp and, for the last, PYTHONPATH=<repository>; one run per counter set).  `copy.fetch` / `copy.write` calibrate the byte counters
-on a 256 MiB device copy.  Written: kernel_trace_by_workload.md, hbm_traffic_pmc.md, mfma_utilisation_pmc.md,
-kernel_trace_cases.md and traffic.json (HBM bytes per call keyed the way bench.py keys its roofline rows, with the commit and the digest of
-the kernel sources they were measured on; bench.py reports them only while that digest still matches).
+(each from /tmp with TMPDIR=/tmp and, for the last, PYTHONPATH=<repository>; one run per counter set).  `copy.fetch` /
+`copy.write` calibrate the byte counters on a 256 MiB device copy.  Written: kernel_trace_by_workload.md, hbm_traffic_pmc.md,
+mfma_utilisation_pmc.md, kernel_trace_cases.md and traffic.json (HBM bytes per call keyed the way bench.py keys its roofline
+rows, with the commit and the digest of the kernel sources they were measured on; bench.py reports them only while that
+digest still matches).
 
 Only launches of this library's kernels are kept; the first launch of every kernel in a run is dropped as warm-up.
 """
@@ -158,7 +159,10 @@ def passes_table(folder):
     for r in sorted(read_csv(folder, "*kernel_trace.csv"), key=lambda r: int(r["Start_Timestamp"])):
         name = short_name(r["Kernel_Name"])
         if ours(name):
-            rows.append((name, int(r["Grid_Size_X"]) // max(1, int(r["Workgroup_Size_X"])), (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3))
+            groups = 1
+            for axis in "XYZ":
+                groups *= int(r["Grid_Size_" + axis]) // max(1, int(r["Workgroup_Size_" + axis]))
+            rows.append((name, groups, (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3))
     n, rest = divmod(len(rows), PASSES)
     if n == 0 or rest:
         raise ValueError("%s: %d launches do not make %d passes" % (folder, len(rows), PASSES))

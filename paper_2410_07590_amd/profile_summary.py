@@ -138,7 +138,9 @@ def per_call(launches, iters):
     return launches // iters
 
 
-PASSES = 12   # of a case of perf/cases.py
+# Passes of a case of perf/cases.py.  After an idle while the chip runs long passes up to 35 % slower until clock and power
+# have settled (offline-64x512 300, then 380, then 275 us; some forty passes), so the first ones are not looked at.
+SETTLE, PASSES = 100, 12
 
 
 def run_passes(name):
@@ -147,10 +149,10 @@ def run_passes(name):
     from perf import cases
     case, = [c for c in cases.listed() if c["name"] == name]
     state = cases.prepare(case, 1)
-    for _ in range(PASSES):
+    for _ in range(SETTLE + PASSES):
         cases.run(state)
         torch.cuda.synchronize()
-    print("case %s: %d passes" % (name, PASSES))
+    print("case %s: %d passes" % (name, SETTLE + PASSES))
 
 
 def passes_table(folder):
@@ -163,9 +165,10 @@ def passes_table(folder):
             for axis in "XYZ":
                 groups *= int(r["Grid_Size_" + axis]) // max(1, int(r["Workgroup_Size_" + axis]))
             rows.append((name, groups, (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3))
-    n, rest = divmod(len(rows), PASSES)
+    n, rest = divmod(len(rows), SETTLE + PASSES)
     if n == 0 or rest:
-        raise ValueError("%s: %d launches do not make %d passes" % (folder, len(rows), PASSES))
+        raise ValueError("%s: %d launches do not make %d passes" % (folder, len(rows), SETTLE + PASSES))
+    rows = rows[SETTLE * n:]
     seen = collections.OrderedDict()
     for i in range(n):
         t = sorted(rows[p * n + i][2] for p in range(PASSES))
@@ -219,7 +222,9 @@ def main():
              "python3 bench.py --case <case> --iters 12` (from /tmp, TMPDIR=/tmp), summarised by "
              "`python -m paper_2410_07590_amd.profile_summary <dir>`; the first launch of each kernel is dropped.  "
              "us = End_Timestamp - Start_Timestamp of the dispatch; `call us` = sum over the kernels of one library call; a kernel "
-             "marked set-up was launched by the preparation of the case only (it fills the cache the timed kernel reads).\n"]
+             "marked set-up was launched by the preparation of the case only (it fills the cache the timed kernel reads).  The "
+             "few launches of a run come right after an idle while, so the long kernels show the chip before its clock has "
+             "settled, up to a third slower than in a steady run.\n"]
     traces = {}
     for case in sorted(runs):
         if "trace" not in runs[case]:
@@ -244,9 +249,9 @@ def main():
     lines = ["# Kernel times per pass of the cases in `perf/cases.py`\n", stamp,
              "Each case is one run of `rocprofv3 --kernel-trace --output-format csv -d <dir>/<case>.passes -o out -- python3 -m "
              "paper_2410_07590_amd.profile_summary --run <case>` (from /tmp, TMPDIR=/tmp, PYTHONPATH=<repository>), summarised by "
-             "`python -m paper_2410_07590_amd.profile_summary <dir>`: medians of %d passes, in launch order.  Every pass is waited "
-             "for and repeats on the same buffers.  Durations under the tracer include its cost per kernel (about 1 us on the "
-             "short ones), and the clock of long kernels is lower than in an undisturbed run.\n" % PASSES,
+             "`python -m paper_2410_07590_amd.profile_summary <dir>`: medians of %d passes after %d others, in launch "
+             "order.  Every pass is waited for and repeats on the same buffers.  Durations under the tracer include its cost per "
+             "kernel (about 1 us on the short ones).\n" % (PASSES, SETTLE),
              "| Case | Kernel | Workgroups | us |", "|---|---|---|---|"]
     order = [c for c in runs if "passes" in runs[c]]
     for case in order:

@@ -328,7 +328,7 @@ def test_decode_split_keys(B):
 
 def test_more_than_32_key_splits(B):
     """One request with a long context and few query rows: fewer workgroups than CUs unless the keys are cut into more
-    than 32 pieces, which the merge kernel then handles two per lane.  16 query tokens (one row tile of the 128-row
+    than 32 pieces, of which the merge then keeps 64 statistics per row.  16 query tokens (one row tile of the 128-row
     kernel, streaming tile loads) and one query token (the short-query kernel) over 26 chunks of 450..550 rows."""
     for n_q in (16, 1):
         cfg = synth.scaled(synth.CONFIGS[2], store_chunks=30, chunk_len_lo=450, chunk_len_hi=550, n_requests=1,

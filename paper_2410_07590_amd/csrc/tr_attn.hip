@@ -48,7 +48,7 @@ template <int D> struct Geo {
     static constexpr int RPI = 64 / CPR;         // rows moved by one wave-wide 1 KB load
     static constexpr int NI = KT / RPI;          // such loads per K (or V) tile
     static constexpr int TILE_BYTES = KT * D * 2;
-    static constexpr int STAGE_BYTES = 2 * TILE_BYTES; // K tile then V tile
+    static constexpr int STAGE_BYTES = 2 * TILE_BYTES; // one K tile and one V tile
     static constexpr int GPR = CPR / 4;          // 64-byte groups per row
     // K: chunk c of row r sits at chunk c ^ kswz(r): 16 consecutive rows of one logical chunk cover all banks
     __device__ static __forceinline__ int kswz(int r) { return (r / (16 / CPR)) & (CPR - 1); }
@@ -240,18 +240,41 @@ __device__ __forceinline__ void rotate_queries(const u32x4 (&raw)[D / 16], LDS_A
 // Per-wave state of the tile loop.
 template <int D> struct Acc {
     f32x16 o[D / 32]; // O^T: element e of block db is channel 32 db + 8 (e >> 2) + 4 h + (e & 3) of query column c
-    float mref;       // reference maximum, log2 domain (score * log2(e)/sqrt(d))
+    // The negated reference maximum (log2 domain, score * log2(e)/sqrt(d)) of the lane's query column, in every element: the
+    // addend of a tile's first score products.  Kept as a register block of its own, a tile starts its scores with no moves
+    // (32 of some 130 vector instructions of a 64-key tile when they were written from a scalar each time).  With the test
+    // for a new reference reduced to one comparison and the masks to constants, 89 are left, and one set of LDS offsets for
+    // the whole ring frees the registers that the block takes (eight waves: 245 -> 206).  us before / after: one pass over
+    // 32 x 1024 + 256 tokens 562 / 549, 256 query tokens over 32 x 1024 rows 177.8 / 175.7, 64 over 8 x 512 23.35 / 22.61.
+    f32x16 nref;
     float l;          // this half-wave's share of the softmax denominator
+
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[db][e] = 0.0f;
+        l = 0.0f;
+        move_ref(0.0f);
+    }
+    __device__ __forceinline__ float mref() const { return -nref[0]; }
+    __device__ __forceinline__ void move_ref(float neg)
+    {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) nref[e] = neg;
+        asm volatile("" : "+v"(nref)); // a block of registers from here on, not a value to be spread again at each use
+    }
 };
 
-// Issue this wave's share of the direct global->LDS loads of tile [kt, kt+KROWS) into one stage (K rows, then V rows).
+// Issue this wave's share of the direct global->LDS loads of tile [kt, kt+KROWS): K rows to kdst, V rows to vdst.
 // AUX is the cache policy of the loads: 0 where other workgroups read the same tile soon (the row tiles of a long
 // query), DMA_STREAM (non-temporal) where every key is read exactly once (decode: 114 -> 100 us for 64 x 4096 rows;
 // the same hint on the long-query kernels, whose row tiles share keys through L2, cost 5-8 %).
 constexpr int DMA_STREAM = 2;
 template <int D, int NW, int KROWS = KT, int AUX = 0>
 __device__ __forceinline__ void issue_tile(const __bf16* __restrict__ k, const __bf16* __restrict__ v, int64_t row_elems,
-                                           int head_off, int kt, int key_clamp, LDS_AS char* stage, int wave, int lane)
+                                           int head_off, int kt, int key_clamp, LDS_AS char* kdst, LDS_AS char* vdst, int wave, int lane)
 {
     using G = Geo<D>;
     constexpr int NI = KROWS / G::RPI;
@@ -266,9 +289,8 @@ __device__ __forceinline__ void issue_tile(const __bf16* __restrict__ k, const _
         const int ck = pc ^ G::kswz(row);
         const int cv = 4 * ((pc >> 2) ^ G::vswz(row)) + (pc & 3);
         const int64_t base = (int64_t)key * row_elems + head_off;
-        __builtin_amdgcn_global_load_lds((const GLB_AS void*)(k + base + ck * 8), (LDS_AS void*)(stage + i * 1024), 16, 0, AUX);
-        __builtin_amdgcn_global_load_lds((const GLB_AS void*)(v + base + cv * 8),
-                                         (LDS_AS void*)(stage + KROWS * D * 2 + i * 1024), 16, 0, AUX);
+        __builtin_amdgcn_global_load_lds((const GLB_AS void*)(k + base + ck * 8), (LDS_AS void*)(kdst + i * 1024), 16, 0, AUX);
+        __builtin_amdgcn_global_load_lds((const GLB_AS void*)(v + base + cv * 8), (LDS_AS void*)(vdst + i * 1024), 16, 0, AUX);
     }
 }
 
@@ -282,16 +304,12 @@ struct NoHook {
 // there, so that their issue falls into the shadow of the matrix instructions instead of in front of them.
 template <int D, int KB, class Between = NoHook>
 __device__ __forceinline__ void scores_softmax(LDS_AS const char* krows, const bf16x8 (&qf)[D / 16], const RowCtx& rc, int kt,
-                                               bool need_mask, const int (&koff)[D / 16], int h, Acc<D>& acc, bf16x8 (&bpk)[KB][2],
+                                               bool need_mask, bool need_lo, const int (&koff)[D / 16], int h, Acc<D>& acc, bf16x8 (&bpk)[KB][2],
                                                Between between = Between())
 {
-    // scores relative to the row reference, in the log2 domain (the queries carry log2(e)/sqrt(d)): the
-    // accumulators start at -mref, so P = exp2(S) needs no further arithmetic
+    // scores relative to the row reference, in the log2 domain (the queries carry log2(e)/sqrt(d)): the first products add
+    // the negated reference, so P = exp2(S) needs no further arithmetic
     f32x16 s[KB];
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) s[kb][e] = -acc.mref;
     // operand reads run K_PREFETCH k-steps ahead of the products that use them (the compiler, left alone, reads one
     // step ahead and waits out the full LDS latency before every pair of products)
     constexpr int PD = K_PREFETCH, STEPS = D / 16;
@@ -303,7 +321,7 @@ __device__ __forceinline__ void scores_softmax(LDS_AS const char* krows, const b
 #pragma unroll
     for (int ks = 0; ks < STEPS; ++ks) {
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks % PD][kb], qf[ks], s[kb], 0, 0, 0);
+        for (int kb = 0; kb < KB; ++kb) s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks % PD][kb], qf[ks], ks == 0 ? acc.nref : s[kb], 0, 0, 0);
         if (ks + PD < STEPS) {
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) a[ks % PD][kb] = *(LDS_AS const bf16x8*)(krows + koff[ks + PD] + kb * 32 * D * 2);
@@ -311,43 +329,58 @@ __device__ __forceinline__ void scores_softmax(LDS_AS const char* krows, const b
         between(ks);
         __builtin_amdgcn_sched_barrier(0);
     }
-    // accumulator element e of block kb is key kt + 32 kb + 8 (e >> 2) + 4 h + (e & 3), query column c
+    // accumulator element e of block kb is key kt + 32 kb + 8 (e >> 2) + 4 h + (e & 3), query column c; the lane's share of
+    // that sum goes into the bound, so that an element is tested against a constant
     if (need_mask) { // workgroup-uniform: only tiles that straddle a mask edge
+        const int hi = rc.key_hi - kt - 4 * h;
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int key = kt + 32 * kb + 8 * (e >> 2) + 4 * h + (e & 3);
-                if (key < rc.key_lo || key > rc.key_hi) s[kb][e] = -INFINITY;
-            }
+            for (int e = 0; e < 16; ++e)
+                if (32 * kb + 8 * (e >> 2) + (e & 3) > hi) s[kb][e] = -INFINITY;
+        if (need_lo) {
+            const int lo = rc.key_lo - kt - 4 * h;
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (32 * kb + 8 * (e >> 2) + (e & 3) < lo) s[kb][e] = -INFINITY;
+        }
     }
-    float part[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY}; // four short chains instead of one long one
+    float part[4]; // four short chains instead of one long one
+#pragma unroll
+    for (int i = 0; i < 4; ++i) part[i] = s[0][i];
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) part[e & 3] = fmaxf(part[e & 3], s[kb][e]);
+        for (int e = kb == 0 ? 4 : 0; e < 16; ++e) part[e & 3] = fmaxf(part[e & 3], s[kb][e]);
     float mx = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
-    mx = column_max(mx); // both half-waves hold keys of the same query column
-    // lazy reference update (exact: any reference gives the same softmax).  `first`: nothing accumulated yet and the
-    // tile sits far below the reference - move the reference down so that exp2 does not underflow.  Lanes c and c + 32
-    // hold the two key halves of ONE query column and share its reference, so the decision is taken on the column's
-    // denominator: a row whose first visible keys all fell into one half must not move the other half's reference alone.
-    const float l_col = column_sum(acc.l);
-    const bool first = (l_col == 0.0f) && (mx < REREF_BELOW) && (mx > -INFINITY);
-    const bool grow = (mx > RESCALE_SLACK) || first;
-    if (__any(grow)) { // rare
-        const float delta = grow ? mx : 0.0f;
-        const float alpha = first ? 1.0f : __builtin_amdgcn_exp2f(-delta); // first: accumulators are still zero
-        acc.mref += delta;
-        acc.l *= alpha;
+    // Lazy reference update (exact: any reference gives the same softmax).  A lane whose scores stay below the slack and
+    // that has accumulated something cannot ask for one, so the tiles after the first nearly always go on with this one
+    // comparison; what the column decides is worked out only where some lane might.
+    if (__any(mx > RESCALE_SLACK || acc.l == 0.0f)) {
+        mx = column_max(mx); // both half-waves hold keys of the same query column
+        // `first`: nothing accumulated yet and the tile sits far below the reference - move the reference down so that exp2
+        // does not underflow.  Lanes c and c + 32 hold the two key halves of ONE query column and share its reference, so
+        // the decision is taken on the column's denominator: a row whose first visible keys all fell into one half must not
+        // move the other half's reference alone.
+        const float l_col = column_sum(acc.l);
+        const bool first = (l_col == 0.0f) && (mx < REREF_BELOW) && (mx > -INFINITY);
+        const bool grow = (mx > RESCALE_SLACK) || first;
+        if (__any(grow)) { // rare
+            const float delta = grow ? mx : 0.0f;
+            const float alpha = first ? 1.0f : __builtin_amdgcn_exp2f(-delta); // first: accumulators are still zero
+            acc.move_ref(acc.nref[0] - delta);
+            acc.l *= alpha;
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db)
+            for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc.o[db][e] *= alpha;
+                for (int e = 0; e < 16; ++e) acc.o[db][e] *= alpha;
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
+            for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) s[kb][e] -= delta;
+                for (int e = 0; e < 16; ++e) s[kb][e] -= delta;
+        }
     }
     // P = exp2(S), packed to bf16 B-operands; the denominator sums the rounded weights the product uses
     {
@@ -413,80 +446,21 @@ __device__ __forceinline__ Walk make_walk(int kt_begin, int kt_end, int key_clam
     return w;
 }
 
-// Tiles 0 .. NS-2 in flight.  Stage NS-1 stays free until the tile loop's first iteration has passed its barrier.
-template <int D, int NW, int NS, int AUX = 0>
-__device__ __forceinline__ void issue_prologue(const __bf16* __restrict__ k, const __bf16* __restrict__ v, const Walk& w,
-                                               LDS_AS char* smem, int wave, int lane)
-{
-#pragma unroll
-    for (int p = 0; p < NS - 1; ++p)
-        if (p < w.n_tiles)
-            issue_tile<D, NW, KT, AUX>(k, v, w.row_elems, w.head_off, w.kt_begin + p * KT, w.key_clamp, smem + p * Geo<D>::STAGE_BYTES, wave, lane);
-}
+// The ring: NS K tiles, then NS V tiles.  K and V lie apart so that every stage of either is within reach of the 16-bit
+// offset field of an LDS instruction (64 KB) and one set of lane offsets serves all stages.
+template <int D> constexpr int ring_k(int stage) { return stage * Geo<D>::TILE_BYTES; }
+template <int D, int NS> constexpr int ring_v(int stage) { return (NS + stage) * Geo<D>::TILE_BYTES; }
 
 // This wave's loads of one whole tile whose 64 rows all exist (no clamping): the lane's byte offsets inside the tile
-// were computed once (dk, dv), the tile's first row is a uniform base, so a load costs no vector arithmetic.
-// load pair ii of this wave: 1 KB of the K tile and 1 KB of the V tile
-template <int D, int NW, int AUX>
-__device__ __forceinline__ void issue_pair_at(const char* __restrict__ ktile, const char* __restrict__ vtile, uint32_t dk, uint32_t dv,
-                                              uint32_t lds_wave, int stage_off, int ii)
-{
-    const uint32_t dst = lds_wave + (uint32_t)(stage_off + NW * ii * 1024);
-    __builtin_amdgcn_global_load_lds((const GLB_AS void*)(ktile + dk), (LDS_AS void*)(uintptr_t)dst, 16, 0, AUX);
-    __builtin_amdgcn_global_load_lds((const GLB_AS void*)(vtile + dv), (LDS_AS void*)(uintptr_t)(dst + Geo<D>::TILE_BYTES), 16, 0, AUX);
-}
+// are computed once, the tile's first row is a uniform base, so a load costs no vector arithmetic.
+template <int D, int NW> struct TileLoads {
+    uint32_t dk[Geo<D>::NI / NW], dv[Geo<D>::NI / NW]; // byte offsets of this lane's 16 bytes from the tile's first row
+    uint32_t lds_wave; // LDS address of this wave's first 1 KB slot in K stage 0 (uniform)
 
-template <int D, int NW, int AUX>
-__device__ __forceinline__ void issue_tile_at(const char* __restrict__ ktile, const char* __restrict__ vtile,
-                                              const uint32_t (&dk)[Geo<D>::NI / NW], const uint32_t (&dv)[Geo<D>::NI / NW],
-                                              uint32_t lds_wave /* LDS address of this wave's first 1 KB slot in stage 0 (uniform) */,
-                                              int stage_off /* constant */)
-{
-    using G = Geo<D>;
-#pragma unroll
-    for (int ii = 0; ii < G::NI / NW; ++ii) issue_pair_at<D, NW, AUX>(ktile, vtile, dk[ii], dv[ii], lds_wave, stage_off, ii);
-}
-
-// The tile loop shared by both kernels (issue_prologue has run).  Tile [kt, kt+64) needs per-element masking iff
-// kt+63 > mask_hi_min or kt < mask_lo_max.  The loop is unrolled over the ring so that the stage of every LDS
-// access is a constant of the instruction: the operand reads then need no address arithmetic at all (the lane's
-// offsets inside a stage are loop constants, the stage goes into the instruction's offset field, whose 16 bits
-// reach two 32 KB stages: a four-stage ring keeps a second set of offsets for stages 2 and 3).
-template <int D, int NW, int NS, int AUX = 0>
-__device__ __forceinline__ void attn_tiles(const __bf16* __restrict__ k, const __bf16* __restrict__ v, const Walk& w,
-                                           const RowCtx& rc, const bf16x8 (&qf)[D / 16], int mask_hi_min, int mask_lo_max,
-                                           LDS_AS char* smem, Acc<D>& acc)
-{
-    using G = Geo<D>;
-    constexpr int IPW = 2 * G::NI / NW; // loads each wave issues per tile
-    static_assert(G::NI % NW == 0, "tile loads must divide evenly over the waves");
-    static_assert(NS == 2 || NS == 4, "the ring has two or four stages");
-    constexpr int BANKS = NS / 2;        // sets of lane offsets: one per 64 KB of ring
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c = lane & 31, h = lane >> 5;
-    const int i16 = lane & 15, colhalf = (lane >> 4) & 1;
-
-    const int wave_hi_max = wave_max_i(rc.valid ? rc.key_hi : INT32_MIN);
-    const int wave_lo_min = wave_min_i(rc.valid ? rc.key_lo : INT32_MAX);
-
-    // LDS addresses of this lane's operands in stage 2b (bank b serves stages 2b and 2b + 1): whole addresses, the
-    // ring's base included, so that what an access adds is a constant that fits its offset field
-    const int lds0 = (int)(uintptr_t)smem;
-    const uint32_t lds_wave = (uint32_t)__builtin_amdgcn_readfirstlane(lds0 + wave * 1024);
-    int koff[BANKS][D / 16];
-    int voff[BANKS][D / 32];
-#pragma unroll
-    for (int b = 0; b < BANKS; ++b) {
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) koff[b][ks] = lds0 + b * 2 * G::STAGE_BYTES + c * D * 2 + (((2 * ks + h) ^ G::kswz(c)) * 16);
-        const int r = 4 * h + (i16 >> 2); // row inside an 8-row k-slot block; rows 8 apart share the swizzle
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-            voff[b][db] = lds0 + b * 2 * G::STAGE_BYTES + r * D * 2 + (4 * (db ^ G::vswz(r)) + 2 * colhalf + ((i16 & 3) >> 1)) * 16 + (i16 & 1) * 8;
-    }
-    // byte offsets of this wave's tile loads from the tile's first row
-    uint32_t dk[G::NI / NW], dv[G::NI / NW];
+    __device__ __forceinline__ TileLoads(const Walk& w, LDS_AS char* smem, int wave, int lane)
     {
+        using G = Geo<D>;
+        lds_wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uintptr_t)smem + wave * 1024);
         const int r_in = lane / G::CPR, pc = lane % G::CPR;
         const uint32_t row_bytes = (uint32_t)w.row_elems * 2u;
 #pragma unroll
@@ -498,6 +472,73 @@ __device__ __forceinline__ void attn_tiles(const __bf16* __restrict__ k, const _
             dv[ii] = (uint32_t)row * row_bytes + (uint32_t)(w.head_off + cv * 8) * 2u;
         }
     }
+    // load pair ii of this wave: 1 KB of the K tile and 1 KB of the V tile; stage: a constant
+    template <int NS, int AUX>
+    __device__ __forceinline__ void pair(const char* __restrict__ ktile, const char* __restrict__ vtile, int stage, int ii) const
+    {
+        const uint32_t dst = lds_wave + (uint32_t)(NW * ii * 1024);
+        __builtin_amdgcn_global_load_lds((const GLB_AS void*)(ktile + dk[ii]), (LDS_AS void*)(uintptr_t)(dst + ring_k<D>(stage)), 16, 0, AUX);
+        __builtin_amdgcn_global_load_lds((const GLB_AS void*)(vtile + dv[ii]), (LDS_AS void*)(uintptr_t)(dst + ring_v<D, NS>(stage)), 16, 0, AUX);
+    }
+    template <int NS, int AUX>
+    __device__ __forceinline__ void tile(const char* __restrict__ ktile, const char* __restrict__ vtile, int stage) const
+    {
+#pragma unroll
+        for (int ii = 0; ii < Geo<D>::NI / NW; ++ii) pair<NS, AUX>(ktile, vtile, stage, ii);
+    }
+};
+
+// The loads of the tile whose first key is kt; a tile that lacks rows takes the clamping path.
+template <int D, int NW, int NS, int AUX>
+__device__ __forceinline__ void issue_any(const __bf16* __restrict__ k, const __bf16* __restrict__ v, const Walk& w,
+                                          const TileLoads<D, NW>& tl, int kt, int stage, LDS_AS char* smem, int wave, int lane)
+{
+    const int64_t off = (int64_t)kt * w.row_elems;
+    if (kt + KT - 1 <= w.key_clamp) tl.template tile<NS, AUX>((const char*)(k + off), (const char*)(v + off), stage);
+    else issue_tile<D, NW, KT, AUX>(k, v, w.row_elems, w.head_off, kt, w.key_clamp, smem + ring_k<D>(stage), smem + ring_v<D, NS>(stage), wave, lane);
+}
+
+// Tiles 0 .. NS-2 in flight.  Stage NS-1 stays free until the tile loop's first iteration has passed its barrier.
+template <int D, int NW, int NS, int AUX = 0>
+__device__ __forceinline__ void issue_prologue(const __bf16* __restrict__ k, const __bf16* __restrict__ v, const Walk& w,
+                                               const TileLoads<D, NW>& tl, LDS_AS char* smem, int wave, int lane)
+{
+#pragma unroll
+    for (int p = 0; p < NS - 1; ++p)
+        if (p < w.n_tiles) issue_any<D, NW, NS, AUX>(k, v, w, tl, w.kt_begin + p * KT, p, smem, wave, lane);
+}
+
+// The tile loop shared by both kernels (issue_prologue has run).  Tile [kt, kt+64) needs per-element masking iff
+// kt+63 > mask_hi_min or kt < mask_lo_max.  The loop is unrolled over the ring so that the stage of every LDS
+// access is a constant of the instruction: the operand reads then need no address arithmetic at all (the lane's
+// offsets inside a stage are loop constants, the stage goes into the instruction's offset field).
+template <int D, int NW, int NS, int AUX = 0>
+__device__ __forceinline__ void attn_tiles(const __bf16* __restrict__ k, const __bf16* __restrict__ v, const Walk& w,
+                                           const TileLoads<D, NW>& tl, const RowCtx& rc, const bf16x8 (&qf)[D / 16], int mask_hi_min,
+                                           int mask_lo_max, LDS_AS char* smem, Acc<D>& acc)
+{
+    using G = Geo<D>;
+    constexpr int IPW = 2 * G::NI / NW; // loads each wave issues per tile
+    static_assert(G::NI % NW == 0, "tile loads must divide evenly over the waves");
+    static_assert(NS == 2 || NS == 4, "the ring has two or four stages");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = lane & 31, h = lane >> 5;
+    const int i16 = lane & 15, colhalf = (lane >> 4) & 1;
+
+    const int wave_hi_max = wave_max_i(rc.valid ? rc.key_hi : INT32_MIN);
+    const int wave_lo_min = wave_min_i(rc.valid ? rc.key_lo : INT32_MAX);
+
+    // LDS addresses of this lane's operands in stage 0: whole addresses, the ring's base included, so that what an access
+    // adds is a constant that fits its offset field
+    const int lds0 = (int)(uintptr_t)smem;
+    int koff[D / 16];
+    int voff[D / 32];
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) koff[ks] = lds0 + c * D * 2 + (((2 * ks + h) ^ G::kswz(c)) * 16);
+    const int r = 4 * h + (i16 >> 2); // row inside an 8-row k-slot block; rows 8 apart share the swizzle
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+        voff[db] = lds0 + ring_v<D, NS>(0) + r * D * 2 + (4 * (db ^ G::vswz(r)) + 2 * colhalf + ((i16 & 3) >> 1)) * 16 + (i16 & 1) * 8;
     const int64_t row_bytes64 = w.row_elems * 2;
 
     const int n_tiles = w.n_tiles;
@@ -519,15 +560,14 @@ __device__ __forceinline__ void attn_tiles(const __bf16* __restrict__ k, const _
             for (int s = 0; s < NS; ++s) {
                 wait_vm<(NS - 2) * IPW>();
                 __builtin_amdgcn_s_barrier();
-                const int dst_off = ((s + NS - 1) % NS) * G::STAGE_BYTES;
                 const int ktn = w.kt_begin + (t0 + s + NS - 1) * KT;
                 const char* ktile = (const char*)k + (int64_t)ktn * row_bytes64;
                 const char* vtile = (const char*)v + (int64_t)ktn * row_bytes64;
-                LDS_AS const char* stage = (LDS_AS const char*)(uintptr_t)((s % 2) * G::STAGE_BYTES);
-                issue_tile_at<D, NW, AUX>(ktile, vtile, dk, dv, lds_wave, dst_off);
+                LDS_AS const char* stage = (LDS_AS const char*)(uintptr_t)(s * G::TILE_BYTES);
+                tl.template tile<NS, AUX>(ktile, vtile, (s + NS - 1) % NS);
                 if (wave_has_rows) {
-                    scores_softmax<D, 2>(stage, qf, rc, 0, false, koff[s / 2], h, acc, bpk);
-                    weighted_values<D, 2>(stage + G::TILE_BYTES, bpk, voff[s / 2], acc);
+                    scores_softmax<D, 2>(stage, qf, rc, 0, false, false, koff, h, acc, bpk);
+                    weighted_values<D, 2>(stage, bpk, voff, acc);
                 }
             }
         }
@@ -546,7 +586,7 @@ __device__ __forceinline__ void attn_tiles(const __bf16* __restrict__ k, const _
             __builtin_amdgcn_s_barrier(); // every wave's share of tile t is in LDS; everyone is done with tile t-1
             const bool active = (kt <= wave_hi_max) && (kt + KT - 1 >= wave_lo_min); // wave-uniform
             const int ktn = kt + (NS - 1) * KT;
-            const int dst_off = ((s + NS - 1) % NS) * G::STAGE_BYTES; // a constant once the loop is unrolled
+            const int dst = (s + NS - 1) % NS; // a constant once the loop is unrolled
             const bool more = t + NS - 1 < n_tiles;
             const bool whole = ktn + KT - 1 <= w.key_clamp;
             const char* ktile = (const char*)k + (int64_t)ktn * row_bytes64;
@@ -556,18 +596,16 @@ __device__ __forceinline__ void attn_tiles(const __bf16* __restrict__ k, const _
             // (measured: the four-wave kernels, whose waves issue twice as many loads per tile, gain 2-5 %; the
             // eight-wave kernel loses the 2 % the unrolled ring gave it, so it keeps its loads in front)
             const bool defer = (NW == 4) && more && whole && active;
-            if (more && !defer) {
-                if (whole) issue_tile_at<D, NW, AUX>(ktile, vtile, dk, dv, lds_wave, dst_off);
-                else issue_tile<D, NW, KT, AUX>(k, v, w.row_elems, w.head_off, ktn, w.key_clamp, smem + dst_off, wave, lane);
-            }
+            if (more && !defer) issue_any<D, NW, NS, AUX>(k, v, w, tl, ktn, dst, smem, wave, lane);
             if (active) {
-                // stages 2b and 2b + 1 are addressed from bank b's offsets; the rest is a constant of the instruction
-                LDS_AS const char* stage = (LDS_AS const char*)(uintptr_t)((s % 2) * G::STAGE_BYTES);
-                const bool need_mask = (kt + KT - 1 > mask_hi_min) || (kt < mask_lo_max);
-                scores_softmax<D, 2>(stage, qf, rc, kt, need_mask, koff[s / 2], h, acc, bpk, [&](int ks) {
-                    if (ks < G::NI / NW && defer) issue_pair_at<D, NW, AUX>(ktile, vtile, dk[ks], dv[ks], lds_wave, dst_off, ks);
+                // the stage is a constant of each access, of the K and of the V reads alike (their offsets include the base)
+                LDS_AS const char* stage = (LDS_AS const char*)(uintptr_t)(s * G::TILE_BYTES);
+                const bool need_lo = kt < mask_lo_max;
+                const bool need_mask = (kt + KT - 1 > mask_hi_min) || need_lo;
+                scores_softmax<D, 2>(stage, qf, rc, kt, need_mask, need_lo, koff, h, acc, bpk, [&](int ks) {
+                    if (ks < G::NI / NW && defer) tl.template pair<NS, AUX>(ktile, vtile, dst, ks);
                 });
-                weighted_values<D, 2>(stage + G::TILE_BYTES, bpk, voff[s / 2], acc);
+                weighted_values<D, 2>(stage, bpk, voff, acc);
             }
         }
     }
@@ -602,16 +640,19 @@ __device__ __forceinline__ void issue_q_loads(const __bf16* __restrict__ q, cons
 // of small GQA groups.  The rotation table sits in stage NS-1, which no tile load targets
 // before the first barrier of the tile loop.
 template <int D, int NW, int NS, bool HALF, int AUX = 0, class PosFn>
-__device__ __forceinline__ void prologue(const __bf16* __restrict__ k, const __bf16* __restrict__ v, const Walk& w, QLoads<D>& ql,
+__device__ __forceinline__ void prologue(const __bf16* __restrict__ k, const __bf16* __restrict__ v, const Walk& w,
+                                         const TileLoads<D, NW>& tl, QLoads<D>& ql,
                                          int pos_lane, int slot, int n_slots, PosFn pos_of_slot, float sl2e, LDS_AS char* smem,
                                          bf16x8 (&qf)[D / 16])
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5;
     asm volatile("" : "+v"(ql.th));
     __builtin_amdgcn_sched_barrier(0);
-    issue_prologue<D, NW, NS, AUX>(k, v, w, smem, wave, lane);
+    issue_prologue<D, NW, NS, AUX>(k, v, w, tl, smem, wave, lane);
     __builtin_amdgcn_sched_barrier(0);
-    LDS_AS char* tab = smem + (NS - 1) * Geo<D>::STAGE_BYTES + wave * (ROT_SLOTS * 4 * D);
+    constexpr int TAB = ROT_SLOTS * 4 * D, PER_TILE = Geo<D>::TILE_BYTES / TAB; // tables that fit a K or V tile
+    static_assert(NW <= 2 * PER_TILE, "the waves' tables fit one stage");
+    LDS_AS char* tab = smem + (wave < PER_TILE ? ring_k<D>(NS - 1) + wave * TAB : ring_v<D, NS>(NS - 1) + (wave - PER_TILE) * TAB);
     rotate_queries<D, HALF>(ql.raw, tab, ql.th, lane, h, slot, n_slots, sl2e,
                             [&](int s) { return s < ROT_SLOTS ? pos_lane : pos_of_slot(s); }, qf);
 }
@@ -710,18 +751,14 @@ __global__ __launch_bounds__(64 * NW, 2) void prefix_attn_kernel(const TrPrefixA
     const int se = min(sb + sd.split_len, sd.kv_row0 + sd.kv_len);
     const Walk w = make_walk(sb, min(se, sd.kv_row0 + n_doc + last_tok + 1), sd.kv_row0 + sd.kv_len - 1, a.n_kv_heads, kvh, D);
 
+    const TileLoads<D, NW> tl(w, smem, wave, lane);
     bf16x8 qf[D / 16];
-    prologue<D, NW, NS, HALF, AUX>((const __bf16*)a.k, (const __bf16*)a.v, w, ql, pos_lane, slot, n_slots, pos_of_slot, a.scale_log2e, smem, qf);
+    prologue<D, NW, NS, HALF, AUX>((const __bf16*)a.k, (const __bf16*)a.v, w, tl, ql, pos_lane, slot, n_slots, pos_of_slot, a.scale_log2e, smem, qf);
 
     Acc<D> acc;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc.o[db][e] = 0.0f;
-    acc.mref = 0.0f;
-    acc.l = 0.0f;
+    acc.clear();
 
-    attn_tiles<D, NW, NS, AUX>((const __bf16*)a.k, (const __bf16*)a.v, w, rc, qf, sd.kv_row0 + n_doc + first_tok, sd.kv_row0, smem, acc);
+    attn_tiles<D, NW, NS, AUX>((const __bf16*)a.k, (const __bf16*)a.v, w, tl, rc, qf, sd.kv_row0 + n_doc + first_tok, sd.kv_row0, smem, acc);
 
     const float l_tot = acc.l + __shfl_xor(acc.l, 32);
     if (sd.n_split == 1) {
@@ -731,7 +768,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefix_attn_kernel(const TrPrefixA
         const int64_t prow = (int64_t)sd.ws_row0 + (int64_t)(split * a.n_kv_heads + kvh) * rows_s + tok_local * g + rl % g;
         store_rows<D, true>(acc, l_tot, rc.valid, prow, a.ws_o, lane);
         // a split in which the row saw no key reports m = -inf so that the merge ignores it
-        if (rc.valid && h == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(l_tot > 0.0f ? acc.mref : -INFINITY, l_tot);
+        if (rc.valid && h == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(l_tot > 0.0f ? acc.mref() : -INFINITY, l_tot);
     }
 }
 
@@ -790,7 +827,7 @@ __global__ __launch_bounds__(64 * GATHER_NW, 2) void gather_attn_kernel(const Tr
         const int first = e.src_row + (gt - e.tile0) * KT;
         const bool from_cache = sg == tail;
         issue_tile<D, NW>((const __bf16*)(from_cache ? a.k_cache : a.k_store), (const __bf16*)(from_cache ? a.v_cache : a.v_store),
-                          row_elems, head_off, first, e.src_row + e.n_rows - 1, stage, wave, lane);
+                          row_elems, head_off, first, e.src_row + e.n_rows - 1, stage, stage + G::TILE_BYTES, wave, lane);
     };
 
     if (n_tiles > 0) issue(g0, s_issue, smem);
@@ -804,12 +841,7 @@ __global__ __launch_bounds__(64 * GATHER_NW, 2) void gather_attn_kernel(const Tr
     int cur_delta = INT32_MIN;
 
     Acc<D> acc;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc.o[db][e] = 0.0f;
-    acc.mref = 0.0f;
-    acc.l = 0.0f;
+    acc.clear();
 
     const int wave_hi_max = wave_max_i(rc.valid ? rc.key_hi : INT32_MIN);
     const int mask_hi_min = a.n_doc + first_tok;
@@ -895,7 +927,7 @@ __global__ __launch_bounds__(64 * GATHER_NW, 2) void gather_attn_kernel(const Tr
             RowCtx rct = rc;
             rct.key_hi = min(rc.key_hi, last_valid);
             const bool need_mask = (kt + KT - 1 > mask_hi_min) || (last_valid < kt + KT - 1);
-            scores_softmax<D, 2>(stage, qf, rct, kt, need_mask, koff, h, acc, bpk);
+            scores_softmax<D, 2>(stage, qf, rct, kt, need_mask, false, koff, h, acc, bpk);
             weighted_values<D, 2>(stage + G::TILE_BYTES, bpk, voff, acc);
         }
     }
@@ -907,7 +939,7 @@ __global__ __launch_bounds__(64 * GATHER_NW, 2) void gather_attn_kernel(const Tr
         const int rows_s = a.n_q * g;
         const int64_t prow = (int64_t)(split * a.n_kv_heads + kvh) * rows_s + tok_local * g + rl % g;
         store_rows<D, true>(acc, l_tot, rc.valid, prow, a.ws_o, lane);
-        if (rc.valid && h == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(l_tot > 0.0f ? acc.mref : -INFINITY, l_tot);
+        if (rc.valid && h == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(l_tot > 0.0f ? acc.mref() : -INFINITY, l_tot);
     }
 }
 
@@ -923,7 +955,7 @@ template <int D> constexpr int short_stage_bytes() { return 2 * SHORT_KT * D * 2
 template <int D> constexpr int short_merge_row_bytes() { return D * 4 + 16; }
 
 template <int D, bool HALF>
-__global__ __launch_bounds__(64 * SHORT_NW, 1) void short_attn_kernel(const TrPrefixArgs a)
+__global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPrefixArgs a)
 {
     using G = Geo<D>;
     constexpr int NW = SHORT_NW, NS = SHORT_NS;
@@ -973,7 +1005,7 @@ __global__ __launch_bounds__(64 * SHORT_NW, 1) void short_attn_kernel(const TrPr
     load_q_raw<D>((const __bf16*)a.q, rc, h, raw);
     asm volatile("" : "+v"(th));
     __builtin_amdgcn_sched_barrier(0);
-    if (n_tiles > 0) issue_tile<D, NW, SHORT_KT, DMA_STREAM>(kp, vp, row_elems, head_off, kt_begin, key_clamp, smem, wave, lane);
+    if (n_tiles > 0) issue_tile<D, NW, SHORT_KT, DMA_STREAM>(kp, vp, row_elems, head_off, kt_begin, key_clamp, smem, smem + SHORT_KT * D * 2, wave, lane);
     __builtin_amdgcn_sched_barrier(0);
     bf16x8 qf[D / 16];
     {
@@ -983,12 +1015,7 @@ __global__ __launch_bounds__(64 * SHORT_NW, 1) void short_attn_kernel(const TrPr
     }
 
     Acc<D> acc;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc.o[db][e] = 0.0f;
-    acc.mref = 0.0f;
-    acc.l = 0.0f;
+    acc.clear();
 
     const int wave_hi_max = wave_max_i(rc.valid ? rc.key_hi : INT32_MIN);
     const int mask_hi_min = sd.kv_row0 + n_doc + first_tok;
@@ -1009,12 +1036,13 @@ __global__ __launch_bounds__(64 * SHORT_NW, 1) void short_attn_kernel(const TrPr
         wait_vm<0>(); // two stages: tile t is the only load in flight here
         __builtin_amdgcn_s_barrier(); // tile t is in LDS; everyone is done with tile t-1
         if (t + 1 < n_tiles)
-            issue_tile<D, NW, SHORT_KT, DMA_STREAM>(kp, vp, row_elems, head_off, kt + SHORT_KT, key_clamp, smem + ((t + 1) % NS) * STAGE, wave, lane);
+            issue_tile<D, NW, SHORT_KT, DMA_STREAM>(kp, vp, row_elems, head_off, kt + SHORT_KT, key_clamp, smem + ((t + 1) % NS) * STAGE,
+                                                    smem + ((t + 1) % NS) * STAGE + SHORT_KT * D * 2, wave, lane);
         const int ktw = kt + 32 * wave; // this wave's 32 keys
         if (ktw <= wave_hi_max && ktw < kt_end) {
             LDS_AS const char* stage = smem + (t % NS) * STAGE;
             const bool need_mask = ktw + 31 > mask_hi_min;
-            scores_softmax<D, 1>(stage, qf, rc, ktw, need_mask, koff, h, acc, bpk);
+            scores_softmax<D, 1>(stage, qf, rc, ktw, need_mask, false, koff, h, acc, bpk);
             weighted_values<D, 1>(stage + SHORT_KT * D * 2, bpk, voff, acc);
         }
     }
@@ -1035,7 +1063,7 @@ __global__ __launch_bounds__(64 * SHORT_NW, 1) void short_attn_kernel(const TrPr
             *(LDS_AS f32x4*)(obuf + c * ROWB + (32 * db + 8 * q4 + 4 * h) * 4) = x;
         }
     if (h == 0) {
-        mlbuf[(wave * 32 + c) * 2] = l_tot > 0.0f ? acc.mref : -INFINITY;
+        mlbuf[(wave * 32 + c) * 2] = l_tot > 0.0f ? acc.mref() : -INFINITY;
         mlbuf[(wave * 32 + c) * 2 + 1] = l_tot;
     }
     __syncthreads();
@@ -1288,18 +1316,14 @@ __global__ __launch_bounds__(64 * NW, 2) void blockdiag_attn_kernel(const TrBloc
     }
     const Walk w = make_walk(kb, ke, T - 1, a.n_kv_heads, kvh, D);
 
+    const TileLoads<D, NW> tl(w, smem, wave, lane);
     bf16x8 qf[D / 16];
-    prologue<D, NW, NS, HALF>((const __bf16*)a.k, (const __bf16*)a.v, w, ql, pos_lane, slot, n_slots, pos_of_slot, a.scale_log2e, smem, qf);
+    prologue<D, NW, NS, HALF>((const __bf16*)a.k, (const __bf16*)a.v, w, tl, ql, pos_lane, slot, n_slots, pos_of_slot, a.scale_log2e, smem, qf);
 
     Acc<D> acc;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc.o[db][e] = 0.0f;
-    acc.mref = 0.0f;
-    acc.l = 0.0f;
+    acc.clear();
 
-    attn_tiles<D, NW, NS>((const __bf16*)a.k, (const __bf16*)a.v, w, rc, qf, t_first, lo_last, smem, acc);
+    attn_tiles<D, NW, NS>((const __bf16*)a.k, (const __bf16*)a.v, w, tl, rc, qf, t_first, lo_last, smem, acc);
 
     const float l_tot = acc.l + __shfl_xor(acc.l, 32);
     if (sg.n_split == 1) {
@@ -1308,7 +1332,7 @@ __global__ __launch_bounds__(64 * NW, 2) void blockdiag_attn_kernel(const TrBloc
         const int64_t rows_s = (int64_t)sg.n_tok * g;
         const int64_t prow = (int64_t)sg.ws_row0 + ((int64_t)split * a.n_kv_heads + kvh) * rows_s + (int64_t)(t - sg.tok0) * g + rl % g;
         store_rows<D, true>(acc, l_tot, rc.valid, prow, a.ws_o, lane);
-        if (rc.valid && lane < 32) *(float2*)(a.ws_ml + prow * 2) = make_float2(l_tot > 0.0f ? acc.mref : -INFINITY, l_tot);
+        if (rc.valid && lane < 32) *(float2*)(a.ws_ml + prow * 2) = make_float2(l_tot > 0.0f ? acc.mref() : -INFINITY, l_tot);
     }
 }
 

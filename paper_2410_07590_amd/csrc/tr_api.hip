@@ -731,6 +731,7 @@ int run_prefix(const tr_shape* sh, const void* q, const void* k, const void* v, 
     a.n_q_heads = sh->n_q_heads;
     a.n_kv_heads = sh->n_kv_heads;
     a.group = sh->n_q_heads / sh->n_kv_heads;
+    a.group_magic = tr_group_magic(a.group);
     a.scale = (float)(1.0 / sqrt((double)sh->head_dim));
     a.scale_log2e = (float)(1.4426950408889634074 / sqrt((double)sh->head_dim));
     a.rope_half = tr_rope_half(sh);
@@ -1005,6 +1006,7 @@ extern "C" int tr_prefill_attn_gather(const tr_store* store, const int32_t* chun
     a.n_q_heads = sh->n_q_heads;
     a.n_kv_heads = sh->n_kv_heads;
     a.group = sh->n_q_heads / sh->n_kv_heads;
+    a.group_magic = tr_group_magic(a.group);
     a.tok_per_tile = p.tok_per_tile;
     a.scale_log2e = (float)(1.4426950408889634074 / sqrt((double)sh->head_dim));
     a.rope_half = tr_rope_half(sh);
@@ -1248,6 +1250,7 @@ extern "C" int tr_sequence_prefill_attn(const tr_shape* shape, const void* q, co
     a.n_q_heads = shape->n_q_heads;
     a.n_kv_heads = shape->n_kv_heads;
     a.group = shape->n_q_heads / shape->n_kv_heads;
+    a.group_magic = tr_group_magic(a.group);
     a.rope_half = tr_rope_half(shape);
     a.n_tiles = (int32_t)((total_tokens + a.tok_per_tile - 1) / a.tok_per_tile);
     a.scale = (float)(1.0 / sqrt((double)shape->head_dim));
@@ -1402,6 +1405,7 @@ extern "C" int tr_chunk_prefill_attn(const tr_shape* shape, const void* q, const
     a.n_q_heads = shape->n_q_heads;
     a.n_kv_heads = shape->n_kv_heads;
     a.group = shape->n_q_heads / shape->n_kv_heads;
+    a.group_magic = tr_group_magic(a.group);
     a.rope_half = tr_rope_half(shape);
     // chunks are short (a row tile walks a few key tiles only), so two independent 4-wave workgroups per CU, which
     // overlap one's prologue and epilogue with the other's tile loop, beat one 8-wave workgroup

@@ -70,6 +70,10 @@ struct RowCtx {
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
+// x / g for the rows of a workgroup (x < 256, g <= 256): exact, as x * (tr_group_magic(g) * g - 2^16) < 2^16.  A division by a
+// number that is not known when the code is compiled takes some twenty instructions, and a wave's rows ask for five.
+__device__ __forceinline__ int by_group(int x, int magic) { return (int)(((uint32_t)x * (uint32_t)magic) >> 16); }
+
 __device__ __forceinline__ int xcd_remap(int bid, int n)
 {
     // Blocks are dealt round-robin to the 8 XCDs; give each XCD one contiguous range of items so that
@@ -125,6 +129,15 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int ROT_SLOTS = 8; // token slots per rotation pass; covers a wave's 32 packed rows when the GQA group is >= 4
 
+// theta_rev[m] of a kernel whose one argument is an Args block, by a load that is issued where it stands.  A plain load of an
+// argument is free to move, and did: to its first use, behind the tile loads, with which it was then waited for.
+template <class Args> __device__ __forceinline__ double load_theta(int m)
+{
+    uintptr_t args = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    return ((const GLB_AS double*)(args + offsetof(Args, theta_rev)))[m];
+}
+
 // Issue the loads of this lane's raw fragments; rows that do not exist read row 0 and are zeroed later.
 template <int D>
 __device__ __forceinline__ void load_q_raw(const __bf16* __restrict__ q, const RowCtx& rc, int h, u32x4 (&raw)[D / 16])
@@ -156,7 +169,9 @@ __device__ __forceinline__ void build_rot_table(LDS_AS char* tab, double th /* t
 #pragma unroll
     for (int pass = 0; pass < ROT_SLOTS / LPS; ++pass) {
         const int j = pass * LPS + lane / PAIRS;
-        double rev = (double)__shfl(pos_lane, j) * th;
+        int pos = __builtin_amdgcn_readlane(pos_lane, pass * LPS);
+        if (LPS == 2) pos = lane < PAIRS ? pos : __builtin_amdgcn_readlane(pos_lane, pass * LPS + 1);
+        double rev = (double)pos * th;
         rev -= rint(rev);
         const float x = (float)rev;
         f32x2 cs;
@@ -219,13 +234,32 @@ __device__ __forceinline__ void rotate_q_shared_half(const u32x4 (&raw)[D / 16],
 // belongs to (0 .. n_slots-1, n_slots wave-uniform); pos_of_slot(s): position id of the wave's token slot s (any
 // value for slots past the wave's last token).  Tokens go through the table ROT_SLOTS at a time: one pass when the
 // GQA group is >= 4, up to four for smaller groups.
-template <int D, bool HALF, class PosFn>
-__device__ __forceinline__ void rotate_queries(const u32x4 (&raw)[D / 16], LDS_AS char* tab, double th, int lane, int h, int slot,
-                                               int n_slots, float sl2e, PosFn pos_of_slot, bf16x8 (&qf)[D / 16])
+// LATER: vector-memory loads that this wave has issued behind the raw rows.  With a tile load in flight the compiler would
+// wait for everything before it touches a loaded register, so the waits by count are written out: theta and the position ids
+// (in front of the rows) first, the rows once the table is built.
+// (us before / after, with the table's position ids from scalar lanes instead of an LDS permute each and the divisions by the
+// group as products: one token for each of 64 requests of 4096 rows 95.5 / 94.1, for 5 ragged ones 18.5 / 17.8; 64 x 512
+// offline tokens 283 / 276, one pass over 32 x 1024 + 256 tokens 536 / 528.)
+template <int D, bool HALF, int LATER, class PosFn>
+__device__ __forceinline__ void rotate_queries(u32x4 (&raw)[D / 16], LDS_AS char* tab, double th, int pos_lane, int lane, int h,
+                                               int slot, int n_slots, float sl2e, PosFn pos_of_slot, bf16x8 (&qf)[D / 16])
 {
     n_slots = __builtin_amdgcn_readfirstlane(n_slots);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vm<LATER + D / 16>();
+    asm volatile("s_nop 0"); // the wait takes effect with the next instruction: that must not be one that needs it
+    asm volatile("" : "+v"(th), "+v"(pos_lane));
+    __builtin_amdgcn_sched_barrier(0);
     for (int p0 = 0; p0 < n_slots; p0 += ROT_SLOTS) {
-        build_rot_table<D>(tab, th, lane, pos_of_slot(p0 + (lane & (ROT_SLOTS - 1))), sl2e);
+        build_rot_table<D>(tab, th, lane, p0 == 0 ? pos_lane : pos_of_slot(p0 + (lane & (ROT_SLOTS - 1))), sl2e);
+        if (p0 == 0) {
+            __builtin_amdgcn_sched_barrier(0);
+            wait_vm<LATER>();
+            asm volatile("s_nop 0");
+#pragma unroll
+            for (int ks = 0; ks < D / 16; ++ks) asm volatile("" : "+v"(raw[ks]));
+            __builtin_amdgcn_sched_barrier(0);
+        }
         const bool mine = (slot >= p0) && (slot < p0 + ROT_SLOTS);
         bf16x8 f[D / 16];
         if (HALF) rotate_q_shared_half<D>(raw, tab, mine ? slot - p0 : 0, h, f);
@@ -453,6 +487,7 @@ template <int D, int NS> constexpr int ring_v(int stage) { return (NS + stage) *
 
 // This wave's loads of one whole tile whose 64 rows all exist (no clamping): the lane's byte offsets inside the tile
 // are computed once, the tile's first row is a uniform base, so a load costs no vector arithmetic.
+template <int D, int NW> constexpr int tile_loads() { return 2 * Geo<D>::NI / NW; } // load instructions of a wave for a tile
 template <int D, int NW> struct TileLoads {
     uint32_t dk[Geo<D>::NI / NW], dv[Geo<D>::NI / NW]; // byte offsets of this lane's 16 bytes from the tile's first row
     uint32_t lds_wave; // LDS address of this wave's first 1 KB slot in K stage 0 (uniform)
@@ -498,14 +533,33 @@ __device__ __forceinline__ void issue_any(const __bf16* __restrict__ k, const __
     else issue_tile<D, NW, KT, AUX>(k, v, w.row_elems, w.head_off, kt, w.key_clamp, smem + ring_k<D>(stage), smem + ring_v<D, NS>(stage), wave, lane);
 }
 
-// Tiles 0 .. NS-2 in flight.  Stage NS-1 stays free until the tile loop's first iteration has passed its barrier.
+// Tiles 0 .. NS-2 in flight.  Stage NS-1 stays free until the tile loop's first iteration has passed its barrier.  Tiles that
+// the walk does not have are requested all the same (rows past the last one read that row, and nothing looks at them), so
+// that the number of loads in flight is a constant and what was requested before them can be waited for by count.
 template <int D, int NW, int NS, int AUX = 0>
 __device__ __forceinline__ void issue_prologue(const __bf16* __restrict__ k, const __bf16* __restrict__ v, const Walk& w,
                                                const TileLoads<D, NW>& tl, LDS_AS char* smem, int wave, int lane)
 {
+    using G = Geo<D>;
+    static_assert(2 * G::NI / NW == tile_loads<D, NW>(), "");
 #pragma unroll
-    for (int p = 0; p < NS - 1; ++p)
-        if (p < w.n_tiles) issue_any<D, NW, NS, AUX>(k, v, w, tl, w.kt_begin + p * KT, p, smem, wave, lane);
+    for (int p = 0; p < NS - 1; ++p) {
+        // a branch around the offsets, not around the loads
+        const int kt = min(w.kt_begin + p * KT, w.key_clamp), last = w.key_clamp - kt; // last: row of the tile, if below KT
+        TileLoads<D, NW> t = tl;
+        if (last < KT - 1) {
+            const uint32_t row_bytes = (uint32_t)w.row_elems * 2u;
+#pragma unroll
+            for (int ii = 0; ii < G::NI / NW; ++ii) {
+                const int row = (wave + NW * ii) * G::RPI + lane / G::CPR;
+                const uint32_t back = (uint32_t)max(row - last, 0) * row_bytes;
+                t.dk[ii] -= back;
+                t.dv[ii] -= back;
+            }
+        }
+        const int64_t off = (int64_t)kt * w.row_elems;
+        t.template tile<NS, AUX>((const char*)(k + off), (const char*)(v + off), p);
+    }
 }
 
 // The tile loop shared by both kernels (issue_prologue has run).  Tile [kt, kt+64) needs per-element masking iff
@@ -620,25 +674,22 @@ template <int D> struct QLoads {
     u32x4 raw[D / 16];  // this lane's raw query fragments
 };
 
-// PINNED: theta is kept in front of the query rows and the batch is closed with a scheduling fence.  That pays where
-// the query rows come from HBM (the offline and one-pass kernels: every row is new); where they sit in L2 (a request's
-// few query tokens, read by every key split) the compiler's own order measured 2 % faster.
-template <int D, bool PINNED>
-__device__ __forceinline__ void issue_q_loads(const __bf16* __restrict__ q, const double* theta_rev, const RowCtx& rc, QLoads<D>& ql)
+// The order is fixed: the waits in front of the rotation count on it.
+template <int D, class Args>
+__device__ __forceinline__ void issue_q_loads(const __bf16* __restrict__ q, const RowCtx& rc, QLoads<D>& ql)
 {
     const int lane = threadIdx.x & 63, h = lane >> 5;
-    ql.th = theta_rev[lane % (D / 2)];
-    if (PINNED) __builtin_amdgcn_sched_barrier(0);
+    ql.th = load_theta<Args>(lane % (D / 2));
+    __builtin_amdgcn_sched_barrier(0);
     load_q_raw<D>(q, rc, h, ql.raw);
-    if (PINNED) __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_sched_barrier(0);
 }
 
-// The first K/V tiles, then the rotation: the tile loads fly while the angles are computed.  theta is waited for
-// before the tile loads go out (with it pos_lane, the position id of token slot (lane & 7) of this wave, which the
-// caller loaded in front of it): a vector-memory result that is first touched after the tile loads would wait for
-// the tiles as well.  The query rows are touched after the angle table is built; pos_of_slot serves the later passes
-// of small GQA groups.  The rotation table sits in stage NS-1, which no tile load targets
-// before the first barrier of the tile loop.
+// The first K/V tiles, then the rotation: the tile loads fly while the angles are computed.  Their addresses need no loaded
+// value, so they go out behind the query rows without a wait.  theta and pos_lane (the position id of token slot (lane & 7) of
+// this wave, which the caller loaded first) are touched next, the query rows after the angle table is built; pos_of_slot
+// serves the later passes of small GQA groups.  The rotation table sits in stage NS-1, which no tile load targets before the
+// first barrier of the tile loop.
 template <int D, int NW, int NS, bool HALF, int AUX = 0, class PosFn>
 __device__ __forceinline__ void prologue(const __bf16* __restrict__ k, const __bf16* __restrict__ v, const Walk& w,
                                          const TileLoads<D, NW>& tl, QLoads<D>& ql,
@@ -646,15 +697,12 @@ __device__ __forceinline__ void prologue(const __bf16* __restrict__ k, const __b
                                          bf16x8 (&qf)[D / 16])
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5;
-    asm volatile("" : "+v"(ql.th));
-    __builtin_amdgcn_sched_barrier(0);
     issue_prologue<D, NW, NS, AUX>(k, v, w, tl, smem, wave, lane);
     __builtin_amdgcn_sched_barrier(0);
     constexpr int TAB = ROT_SLOTS * 4 * D, PER_TILE = Geo<D>::TILE_BYTES / TAB; // tables that fit a K or V tile
     static_assert(NW <= 2 * PER_TILE, "the waves' tables fit one stage");
     LDS_AS char* tab = smem + (wave < PER_TILE ? ring_k<D>(NS - 1) + wave * TAB : ring_v<D, NS>(NS - 1) + (wave - PER_TILE) * TAB);
-    rotate_queries<D, HALF>(ql.raw, tab, ql.th, lane, h, slot, n_slots, sl2e,
-                            [&](int s) { return s < ROT_SLOTS ? pos_lane : pos_of_slot(s); }, qf);
+    rotate_queries<D, HALF, (NS - 1) * tile_loads<D, NW>()>(ql.raw, tab, ql.th, pos_lane, lane, h, slot, n_slots, sl2e, pos_of_slot, qf);
 }
 
 // Write the wave's 32 x D accumulator as rows, straight from registers.
@@ -730,20 +778,22 @@ __global__ __launch_bounds__(64 * NW, 2) void prefix_attn_kernel(const TrPrefixA
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 31, h = lane >> 5;
     const int rl = 32 * wave + c;
-    const int tok_local = tile * tpt + rl / g;
+    const int tok_in = by_group(rl, a.group_magic), head_in = rl - tok_in * g; // token and head inside the tile
+    const int tok_local = tile * tpt + tok_in;
     RowCtx rc;
     rc.valid = (rl < tpt * g) && (tok_local < sd.n_q);
-    rc.orow = (sd.q_row0 + tok_local) * a.n_q_heads + kvh * g + rl % g;
+    rc.orow = (sd.q_row0 + tok_local) * a.n_q_heads + kvh * g + head_in;
     rc.key_lo = sd.kv_row0;
     rc.key_hi = sd.kv_row0 + n_doc + tok_local;
     // position ids per token slot of the wave
-    const int wave_tok0 = tile * tpt + (32 * wave) / g;
-    const int slot = min(rl / g - (32 * wave) / g, 31);
-    const int n_slots = (32 * wave + 31) / g - (32 * wave) / g + 1;
+    const int wave_in = by_group(32 * wave, a.group_magic); // first token of the wave
+    const int wave_tok0 = tile * tpt + wave_in;
+    const int slot = min(tok_in - wave_in, 31);
+    const int n_slots = by_group(32 * wave + 31, a.group_magic) - wave_in + 1;
     auto pos_of_slot = [&](int s) { return a.q_pos[sd.q_row0 + min(wave_tok0 + s, sd.n_q - 1)]; };
     const int pos_lane = pos_of_slot(lane & (ROT_SLOTS - 1));
     QLoads<D> ql;
-    issue_q_loads<D, false>((const __bf16*)a.q, a.theta_rev, rc, ql);
+    issue_q_loads<D, TrPrefixArgs>((const __bf16*)a.q, rc, ql);
 
     const int first_tok = tile * tpt;
     const int last_tok = min(first_tok + tpt, sd.n_q) - 1;
@@ -765,7 +815,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefix_attn_kernel(const TrPrefixA
         store_rows<D, false>(acc, l_tot, rc.valid, (int64_t)rc.orow, a.out, lane);
     } else {
         const int rows_s = sd.n_q * g;
-        const int64_t prow = (int64_t)sd.ws_row0 + (int64_t)(split * a.n_kv_heads + kvh) * rows_s + tok_local * g + rl % g;
+        const int64_t prow = (int64_t)sd.ws_row0 + (int64_t)(split * a.n_kv_heads + kvh) * rows_s + tok_local * g + head_in;
         store_rows<D, true>(acc, l_tot, rc.valid, prow, a.ws_o, lane);
         // a split in which the row saw no key reports m = -inf so that the merge ignores it
         if (rc.valid && h == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(l_tot > 0.0f ? acc.mref() : -INFINITY, l_tot);
@@ -799,15 +849,17 @@ __global__ __launch_bounds__(64 * GATHER_NW, 2) void gather_attn_kernel(const Tr
     const int c = lane & 31, h = lane >> 5;
     const int i16 = lane & 15, colhalf = (lane >> 4) & 1;
     const int rl = 32 * wave + c;
-    const int tok_local = tile * tpt + rl / g;
+    const int tok_in = by_group(rl, a.group_magic), head_in = rl - tok_in * g; // token and head inside the tile
+    const int tok_local = tile * tpt + tok_in;
     RowCtx rc;
     rc.valid = (rl < tpt * g) && (tok_local < a.n_q);
-    rc.orow = tok_local * a.n_q_heads + kvh * g + rl % g;
+    rc.orow = tok_local * a.n_q_heads + kvh * g + head_in;
     rc.key_lo = 0;
     rc.key_hi = a.n_doc + tok_local;
-    const int wave_tok0 = tile * tpt + (32 * wave) / g;
-    const int slot = min(rl / g - (32 * wave) / g, 31);
-    const int n_slots = (32 * wave + 31) / g - (32 * wave) / g + 1;
+    const int wave_in = by_group(32 * wave, a.group_magic); // first token of the wave
+    const int wave_tok0 = tile * tpt + wave_in;
+    const int slot = min(tok_in - wave_in, 31);
+    const int n_slots = by_group(32 * wave + 31, a.group_magic) - wave_in + 1;
     const int first_tok = tile * tpt;
     const int last_tok = min(first_tok + tpt, a.n_q) - 1;
 
@@ -937,7 +989,7 @@ __global__ __launch_bounds__(64 * GATHER_NW, 2) void gather_attn_kernel(const Tr
         store_rows<D, false>(acc, l_tot, rc.valid, (int64_t)rc.orow, a.out, lane);
     } else {
         const int rows_s = a.n_q * g;
-        const int64_t prow = (int64_t)(split * a.n_kv_heads + kvh) * rows_s + tok_local * g + rl % g;
+        const int64_t prow = (int64_t)(split * a.n_kv_heads + kvh) * rows_s + tok_local * g + head_in;
         store_rows<D, true>(acc, l_tot, rc.valid, prow, a.ws_o, lane);
         if (rc.valid && h == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(l_tot > 0.0f ? acc.mref() : -INFINITY, l_tot);
     }
@@ -975,14 +1027,15 @@ __global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPr
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 31, h = lane >> 5;
     const int i16 = lane & 15, colhalf = (lane >> 4) & 1;
-    const int tok_local = tile * tpt + c / g;
+    const int tok_in = by_group(c, a.group_magic), head_in = c - tok_in * g; // token and head inside the tile
+    const int tok_local = tile * tpt + tok_in;
     RowCtx rc;
     rc.valid = (c < tpt * g) && (tok_local < sd.n_q);
-    rc.orow = (sd.q_row0 + tok_local) * a.n_q_heads + kvh * g + c % g;
+    rc.orow = (sd.q_row0 + tok_local) * a.n_q_heads + kvh * g + head_in;
     rc.key_lo = sd.kv_row0;
     rc.key_hi = sd.kv_row0 + n_doc + tok_local;
-    const int slot = min(c / g, 31);
-    const int n_slots = 31 / g + 1;
+    const int slot = min(tok_in, 31);
+    const int n_slots = by_group(31, a.group_magic) + 1;
     auto pos_of_slot = [&](int s) { return a.q_pos[sd.q_row0 + min(tile * tpt + s, sd.n_q - 1)]; };
     const int pos_lane = pos_of_slot(lane & (ROT_SLOTS - 1));
 
@@ -1000,18 +1053,17 @@ __global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPr
     const __bf16* vp = (const __bf16*)a.v;
 
     // prologue: ordinary loads, then tile 0, then the rotation (every wave rotates the same rows)
-    double th = a.theta_rev[lane % (D / 2)];
+    double th = load_theta<TrPrefixArgs>(lane % (D / 2));
+    __builtin_amdgcn_sched_barrier(0);
     u32x4 raw[D / 16];
     load_q_raw<D>((const __bf16*)a.q, rc, h, raw);
-    asm volatile("" : "+v"(th));
     __builtin_amdgcn_sched_barrier(0);
-    if (n_tiles > 0) issue_tile<D, NW, SHORT_KT, DMA_STREAM>(kp, vp, row_elems, head_off, kt_begin, key_clamp, smem, smem + SHORT_KT * D * 2, wave, lane);
+    issue_tile<D, NW, SHORT_KT, DMA_STREAM>(kp, vp, row_elems, head_off, kt_begin, key_clamp, smem, smem + SHORT_KT * D * 2, wave, lane);
     __builtin_amdgcn_sched_barrier(0);
     bf16x8 qf[D / 16];
     {
         LDS_AS char* tab = smem + STAGE + wave * (ROT_SLOTS * 4 * D); // stage 1 is free until the first barrier
-        rotate_queries<D, HALF>(raw, tab, th, lane, h, slot, n_slots, a.scale_log2e,
-                                [&](int s) { return s < ROT_SLOTS ? pos_lane : pos_of_slot(s); }, qf);
+        rotate_queries<D, HALF, 2 * SHORT_KT / G::RPI / NW>(raw, tab, th, pos_lane, lane, h, slot, n_slots, a.scale_log2e, pos_of_slot, qf);
     }
 
     Acc<D> acc;
@@ -1094,12 +1146,13 @@ __global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPr
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[4 * e4 + e] += ww[w] * x[e];
         }
-    const int r_tok = tile * tpt + r / g;
+    const int r_in = by_group(r, a.group_magic), r_head = r - r_in * g;
+    const int r_tok = tile * tpt + r_in;
     const bool r_valid = (r < tpt * g) && (r_tok < sd.n_q);
     if (!r_valid) return;
     const float inv = L > 0.0f ? 1.0f / L : 0.0f;
     if (sd.n_split == 1) {
-        __bf16* op = (__bf16*)a.out + ((int64_t)(sd.q_row0 + r_tok) * a.n_q_heads + kvh * g + r % g) * D + CPT * j;
+        __bf16* op = (__bf16*)a.out + ((int64_t)(sd.q_row0 + r_tok) * a.n_q_heads + kvh * g + r_head) * D + CPT * j;
 #pragma unroll
         for (int e4 = 0; e4 < CPT / 4; ++e4) {
             bf16x4 y;
@@ -1109,7 +1162,7 @@ __global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPr
         }
     } else {
         const int rows_s = sd.n_q * g;
-        const int64_t prow = (int64_t)sd.ws_row0 + (int64_t)(split * a.n_kv_heads + kvh) * rows_s + r_tok * g + r % g;
+        const int64_t prow = (int64_t)sd.ws_row0 + (int64_t)(split * a.n_kv_heads + kvh) * rows_s + r_tok * g + r_head;
         _Float16* op = a.ws_o + prow * D + CPT * j;
 #pragma unroll
         for (int e4 = 0; e4 < CPT / 4; ++e4) {
@@ -1267,14 +1320,16 @@ __global__ __launch_bounds__(64 * NW, 2) void blockdiag_attn_kernel(const TrBloc
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 31;
     const int rl = 32 * wave + c;
-    const int t = tile * tpt + rl / g;
+    const int tok_in = by_group(rl, a.group_magic), head_in = rl - tok_in * g; // token and head inside the tile
+    const int t = tile * tpt + tok_in;
     RowCtx rc;
     rc.valid = (rl < tpt * g) && (t < T);
-    rc.orow = t * a.n_q_heads + kvh * g + rl % g;
+    rc.orow = t * a.n_q_heads + kvh * g + head_in;
     rc.key_hi = t;
-    const int wave_t0 = tile * tpt + (32 * wave) / g;
-    const int slot = min(rl / g - (32 * wave) / g, 31);
-    const int n_slots = (32 * wave + 31) / g - (32 * wave) / g + 1;
+    const int wave_in = by_group(32 * wave, a.group_magic); // first token of the wave
+    const int wave_t0 = tile * tpt + wave_in;
+    const int slot = min(tok_in - wave_in, 31);
+    const int n_slots = by_group(32 * wave + 31, a.group_magic) - wave_in + 1;
     const int t_first = tile * tpt;
     const int t_last = min(t_first + tpt, T) - 1;
     // One batch of loads, nothing waited for in between: this row's chunk start, the position id (or chunk start) of
@@ -1286,7 +1341,7 @@ __global__ __launch_bounds__(64 * NW, 2) void blockdiag_attn_kernel(const TrBloc
     const int start_tile_raw = a.tok_start[min(t_first + lane, t_last)];
     __builtin_amdgcn_sched_barrier(0);
     QLoads<D> ql;
-    issue_q_loads<D, true>((const __bf16*)a.q, a.theta_rev, rc, ql);
+    issue_q_loads<D, TrBlockDiagArgs>((const __bf16*)a.q, rc, ql);
 
     rc.key_lo = rc.valid ? min(max(start_row_raw, 0), t) : 0;
     // position id of each token slot of this wave: given, or chunk-local
@@ -1330,7 +1385,7 @@ __global__ __launch_bounds__(64 * NW, 2) void blockdiag_attn_kernel(const TrBloc
         store_rows<D, false>(acc, l_tot, rc.valid, (int64_t)rc.orow, a.out, lane);
     } else { // the layout the merge kernel reads: [split][KV head][token of the segment x group]
         const int64_t rows_s = (int64_t)sg.n_tok * g;
-        const int64_t prow = (int64_t)sg.ws_row0 + ((int64_t)split * a.n_kv_heads + kvh) * rows_s + (int64_t)(t - sg.tok0) * g + rl % g;
+        const int64_t prow = (int64_t)sg.ws_row0 + ((int64_t)split * a.n_kv_heads + kvh) * rows_s + (int64_t)(t - sg.tok0) * g + head_in;
         store_rows<D, true>(acc, l_tot, rc.valid, prow, a.ws_o, lane);
         if (rc.valid && lane < 32) *(float2*)(a.ws_ml + prow * 2) = make_float2(l_tot > 0.0f ? acc.mref() : -INFINITY, l_tot);
     }

@@ -75,6 +75,10 @@ struct TrChip {
 // theta_m = base^(-2m/d) in double (text after Eq. 3)
 void tr_fill_theta(const tr_shape* s, double* theta /*[64]*/);
 
+// Divisor of the attention kernels' packed rows by the heads of a GQA group (x * magic >> 16 = x / group for x < 256; a larger
+// group does not fit a row tile).
+static inline int32_t tr_group_magic(int32_t group) { return (65536 + group - 1) / group; }
+
 // ---- kernel argument blocks (passed by value; each stays below 4 KB of kernarg) ------------------------------
 
 // One contiguous run of rows to move: src rows [src_row, src_row+n_rows) -> dst rows [dst_row, ...),
@@ -201,7 +205,7 @@ struct TrPrefixArgs {
     float scale_log2e; // log2(e) / sqrt(head_dim)
     float scale;       // 1 / sqrt(head_dim)
     int32_t rope_half;
-    int32_t pad_;
+    int32_t group_magic; // tr_group_magic(group)
     double theta_rev[64]; // theta_m / (2 pi): position * theta_rev = angle in revolutions
     double theta[64];
     TrSeqDesc seq[TR_MAX_SEQ];
@@ -242,6 +246,8 @@ struct TrGatherArgs {
     int32_t tok_per_tile;
     float scale_log2e;
     int32_t rope_half;
+    int32_t group_magic;
+    int32_t pad_;
     double theta_rev[64];
     TrGatherSeg seg[TR_MAX_GATHER_SEG];
 };
@@ -277,7 +283,7 @@ struct TrBlockDiagArgs {
     int32_t rope_half;
     int32_t n_seg;
     int32_t items_per_head;
-    int32_t pad_;
+    int32_t group_magic;
     _Float16* ws_o; // partial outputs and statistics of split tiles, laid out as in TrPrefixArgs
     float* ws_ml;
     double theta_rev[64];

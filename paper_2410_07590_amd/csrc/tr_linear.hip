@@ -14,10 +14,13 @@
 //   * Up to three chunks per workgroup are in flight in a ring of LDS slots while the current one is multiplied.
 // Slices of k that live in different workgroups write fp32 partial sums that a second small kernel adds in a fixed
 // order: no atomics, same inputs, same bits.
+// An attention projection is over before such a stream is long enough to pay for that second launch, so weights up to a size
+// go through linear_direct_kernel, whose workgroups keep all of k (see there and direct_plan).
 #include "tr_internal.h"
 
 #include <stdlib.h>
 #include <string.h>
+#include <algorithm>
 
 namespace {
 
@@ -38,6 +41,7 @@ struct TrLinearArgs {
     int32_t M, N, K;
     int32_t n_split;
     int32_t m_split;                    // 1, or 2: rows [0, 64) and [64, M) of x go to two workgroups of the same XCD
+    int32_t row_tiles;                  // of 16 XB rows (linear_direct_kernel)
 };
 
 constexpr int LIN_CK = 128;           // values of k per chunk: 256 bytes of every row
@@ -226,6 +230,140 @@ __global__ __launch_bounds__(256) void linear_combine_kernel(const TrLinearArgs 
     *(bf16x4*)(a.y[j] + (int64_t)m * (32 * (a.tile0[j + 1] - a.tile0[j])) + (n - 32 * a.tile0[j])) = o;
 }
 
+// All of k in one workgroup, so that no partial sums are left over: a tile of 16 XB rows of x and 16 WB features.  What bounds it
+// is how fast a CU takes bytes in, 62 GB/s through the direct loads wherever they come from, HBM or L2 (measured with nothing
+// else in the kernel): a workgroup asks for (XB + WB) * 16 rows of K values, and the best tile is the one that keeps the
+// largest share per CU small.  The row tiles of one feature tile run on the same XCD, whose L2 serves the weights to all but
+// the first of them.
+// k is walked in chunks of 128 values through a ring of LDS slots; of a chunk each of the four waves multiplies 32 values (one
+// k-step of v_mfma_f32_16x16x32_bf16: w rows = A, x rows = B), and the four sums meet in LDS at the end, added in wave order.
+// Ten layers' projections of 64 rows (3584 -> 3584 + 512 + 512, 3584 -> 3584) take 264 us instead of 307.
+constexpr int DIRECT_MAX_SLOTS = 8, DIRECT_LDS = 128 * 1024;
+template <int XB, int WB> constexpr int direct_slot_bytes() { return 16 * (XB + WB) * LIN_ROW; }
+template <int XB, int WB> constexpr int direct_slots()
+{
+    return DIRECT_LDS / direct_slot_bytes<XB, WB>() < DIRECT_MAX_SLOTS ? DIRECT_LDS / direct_slot_bytes<XB, WB>() : DIRECT_MAX_SLOTS;
+}
+
+template <int XB, int WB>
+__global__ __launch_bounds__(256) void linear_direct_kernel(const TrLinearArgs a)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
+    LDS_AS char* lds = (LDS_AS char*)lds_raw;
+    constexpr int SLOT = direct_slot_bytes<XB, WB>(), NSLOT = direct_slots<XB, WB>();
+    constexpr int IPC = XB + WB; // load instructions of a wave for a chunk, four rows x 256 bytes each
+    static_assert(NSLOT >= 3 && (NSLOT - 2) * IPC < 63 && 4 * XB * WB * 1024 <= NSLOT * SLOT, "");
+    const int place = blockIdx.x >> 3;
+    const int item = place / a.row_tiles * 8 + (blockIdx.x & 7); // feature tile
+    const int m0 = place % a.row_tiles * (16 * XB);
+    const int blocks = a.N / 16;                                 // of features
+    if (item * WB >= blocks) return;                             // padding of the grid (whole workgroup)
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto output_of = [&](int block) { // the output a block of features belongs to
+        int j = 0;
+#pragma unroll
+        for (int i = 1; i < TR_LINEAR_MAX_OUT; ++i) j += i < a.n_out && block >= 2 * a.tile0[i];
+        return j;
+    };
+
+    // Load i of this wave fills rows 4 g .. 4 g + 3 of a slot (x rows, then w rows), 16-byte pieces XOR-swizzled by the row on
+    // the source side.  Rows of x past the last one and features past the last one read the last one's and are not stored.
+    const int lrow = lane / LIN_PPR, ppiece = lane % LIN_PPR, last_piece = a.K / 8 - 1;
+    const __bf16* src[IPC];
+    int piece0[IPC];
+#pragma unroll
+    for (int i = 0; i < IPC; ++i) {
+        const int g = wave * IPC + i, row = 4 * g + lrow;
+        piece0[i] = ppiece ^ (row & (LIN_PPR - 1));
+        if (g < 4 * XB) {
+            src[i] = a.x + (int64_t)min(m0 + row, a.M - 1) * a.K;
+        } else {
+            const int block = min(item * WB + (g - 4 * XB) / 4, blocks - 1), j = output_of(block);
+            src[i] = a.w[j] + (int64_t)(16 * (block - 2 * a.tile0[j]) + (row & 15)) * a.K;
+        }
+    }
+    auto issue = [&](int c, int slot) {
+        LDS_AS char* dst = lds + slot * SLOT + wave * (IPC * 1024);
+#pragma unroll
+        for (int i = 0; i < IPC; ++i) {
+            const int piece = min(c * LIN_PPR + piece0[i], last_piece); // pieces past the end of a row are not used
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[i] + 8 * piece), (LDS_AS void*)(dst + i * 1024), 16, 0, 0);
+        }
+    };
+
+    f32x4 acc[WB][XB];
+#pragma unroll
+    for (int wb = 0; wb < WB; ++wb)
+#pragma unroll
+        for (int xb = 0; xb < XB; ++xb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[wb][xb][e] = 0.0f;
+
+    // rows that lie a multiple of 8 KB apart would all be asked for on the same few memory channels at the same time: there
+    // every feature tile starts its walk somewhere else (4096 x 4096, 37 rows of x 15.1 -> 11.4 us; 8192 x 8192, 32 rows
+    // 35.6 -> 26.5; elsewhere it costs up to a tenth)
+    const int n_chunks = (a.K + LIN_CK - 1) / LIN_CK, first = a.K % 4096 == 0 ? (int)((uint32_t)item * 5u % (uint32_t)n_chunks) : 0;
+    auto chunk = [&](int c) { return c + first < n_chunks ? c + first : c + first - n_chunks; };
+#pragma unroll
+    for (int p = 0; p < NSLOT - 1; ++p)
+        if (p < n_chunks) issue(chunk(p), p);
+    const int r = lane & 15, piece = 4 * wave + (lane >> 4); // this lane's operand row of a block and its piece of a chunk
+    const int off = lin_piece_off(r, piece);
+    int slot = 0;
+    for (int c = 0; c < n_chunks; ++c) {
+        // chunk c has landed once at most the loads of the chunks requested after it are outstanding
+        if (c + NSLOT - 1 <= n_chunks) lin_wait_vm<(NSLOT - 2) * IPC>();
+        else lin_wait_vm<0>();
+        __builtin_amdgcn_s_barrier(); // every wave's part of it; everyone is done with chunk c - 1, whose slot is free
+        if (c + NSLOT - 1 < n_chunks) issue(chunk(c + NSLOT - 1), slot == 0 ? NSLOT - 1 : slot - 1);
+        LDS_AS const char* base = lds + slot * SLOT + off;
+        bf16x8 xb_[XB], wb_[WB];
+#pragma unroll
+        for (int b = 0; b < XB; ++b) xb_[b] = *(LDS_AS const bf16x8*)(base + b * (16 * LIN_ROW));
+#pragma unroll
+        for (int b = 0; b < WB; ++b) wb_[b] = *(LDS_AS const bf16x8*)(base + (XB + b) * (16 * LIN_ROW));
+        if (chunk(c) * LIN_PPR + piece > last_piece) { // past the end of a row, in its short last chunk
+#pragma unroll
+            for (int b = 0; b < XB; ++b) xb_[b] = bf16x8{};
+#pragma unroll
+            for (int b = 0; b < WB; ++b) wb_[b] = bf16x8{};
+        }
+#pragma unroll
+        for (int w = 0; w < WB; ++w)
+#pragma unroll
+            for (int b = 0; b < XB; ++b) acc[w][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb_[w], xb_[b], acc[w][b], 0, 0, 0);
+        slot = slot + 1 == NSLOT ? 0 : slot + 1;
+    }
+
+    // element e of lane l's acc[w][b]: row m0 + 16 b + (l & 15) of x, feature 4 (l >> 4) + e of block w
+    __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0): this wave's operand reads are done
+    __builtin_amdgcn_s_barrier();       // ... and everyone else's: the ring becomes the exchange
+#pragma unroll
+    for (int w = 0; w < WB; ++w)
+#pragma unroll
+        for (int b = 0; b < XB; ++b) *(LDS_AS f32x4*)(lds + ((wave * WB + w) * XB + b) * 1024 + lane * 16) = acc[w][b];
+    __syncthreads();
+#pragma unroll
+    for (int t0 = 0; t0 < WB * XB; t0 += 4) {
+        const int t = t0 + wave;
+        if (t >= WB * XB) break;
+        f32x4 s = *(LDS_AS const f32x4*)(lds + t * 1024 + lane * 16);
+#pragma unroll
+        for (int v = 1; v < 4; ++v) {
+            const f32x4 q = *(LDS_AS const f32x4*)(lds + (v * WB * XB + t) * 1024 + lane * 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] += q[e];
+        }
+        const int block = item * WB + t / XB, m = m0 + 16 * (t % XB) + r;
+        if (block >= blocks || m >= a.M) continue;
+        const int j = output_of(block);
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (__bf16)s[e];
+        *(bf16x4*)(a.y[j] + (int64_t)m * (32 * (a.tile0[j + 1] - a.tile0[j])) + 16 * (block - 2 * a.tile0[j]) + 4 * (lane >> 4)) = o;
+    }
+}
+
 } // namespace
 
 // k-slices across workgroups.  Small weights: one workgroup per CU, about 200 of them measured best (more slices
@@ -251,6 +389,56 @@ int tr_linear_splits(int32_t M, int32_t N, int32_t K)
     if (const int forced = tr_knob(TR_KNOB_LIN_SPLIT, 0); forced >= 1 && forced <= chunks && forced <= LIN_MAX_SPLIT) n_split = forced;
     if (n_split < 1) n_split = 1;
     return n_split;
+}
+
+// The tile of linear_direct_kernel, in blocks of 16 rows of x and 16 features; xb = 0: slices of k and a merge.
+// Of the tiles that fit one workgroup per CU, the one that asks for the fewest bytes per CU (of equal ones the squarest: fewer
+// workgroups read the same weights or the same x).  Its time and that of the slices are estimated from fits to 19 shapes at 11
+// row counts each (1 .. 128), weights not in the caches, on which they are right to 6 % (rms):
+//   direct   launch + the larger of 0.1 + 0.058 (xb + wb) us a chunk of k and the weights at the HBM rate
+//   slices   two launches + weights, partial sums, and rows of x (which the slices read once per 128 features)
+// and the direct kernel is taken where it is the faster one by 7 %.  us, slices / direct: 3584 x 3584 14.2 / 11.5 at 64 rows,
+// 10.0 / 9.3 at one, 16.4 / 14.8 at 128; 4608 x 3584 15.6 / 14.1 at 64; 6144 x 4096 18.3 / 16.0 at 64; 512 x 3584 6.6 / 8.4 at
+// one and 9.6 / 8.6 at 128; 512 x 512 7.6 / 3.3; 8192 x 8192 37.6 / 32.6 at 64; 3584 x 18944 36.2 / 47 at 64; 2048 x 8192
+// 15.2 / 21 at 64: with few features or a long k the slices have more CUs at work, or longer streams.
+struct DirectPlan { int xb, wb; };
+static DirectPlan direct_plan(int32_t M, int32_t N, int32_t K, int n_split)
+{
+    if (tr_knob(TR_KNOB_LIN_SPLIT, 0) || tr_knob(TR_KNOB_LIN_MSPLIT, 0)) return {0, 0}; // a forced split is a split
+    const int blocks = N / 16;
+    DirectPlan best = {0, 0};
+    for (int xb = 1; xb <= 4; ++xb)
+        for (int wb = 1; wb <= 4; ++wb) {
+            if ((int64_t)((M + 16 * xb - 1) / (16 * xb)) * ((blocks + wb - 1) / wb) > TrChip::CUS) continue;
+            const int d = xb + wb - best.xb - best.wb;
+            if (best.xb == 0 || d < 0 || (d == 0 && abs(xb - wb) < abs(best.xb - best.wb))) best = {xb, wb};
+        }
+    if (best.xb == 0) return best;
+    const double mb = 2e-6 * N * (double)K, chunks = (K + LIN_CK - 1) / LIN_CK;
+    const double direct = 2.8 + std::max(chunks * (0.1 + 0.058 * (best.xb + best.wb)), mb / 5.3 + 1.5);
+    const double slices = 6.3 + 0.146 * mb + (n_split > 1 ? 0.71e-6 * n_split * M * (double)N : 0.0) + (0.69 + 0.0314 * mb) * M / 32;
+    return direct <= 0.93 * slices ? best : DirectPlan{0, 0};
+}
+
+template <int XB, int WB> static int launch_direct(const TrLinearArgs& a, hipStream_t s)
+{
+    auto kern = linear_direct_kernel<XB, WB>;
+    constexpr int lds = direct_slots<XB, WB>() * direct_slot_bytes<XB, WB>();
+    static std::atomic<uint64_t> configured{0};
+    if (int rc = tr_raise_lds_limit((const void*)kern, lds, &configured)) return rc;
+    const int tiles = (a.N / 16 + WB - 1) / WB;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * a.row_tiles * ((tiles + 7) / 8))), dim3(256), lds, s, a);
+    TR_HIP(hipGetLastError());
+    return TR_OK;
+}
+template <int XB> static int launch_direct_x(const TrLinearArgs& a, int wb, hipStream_t s)
+{
+    switch (wb) {
+    case 1: return launch_direct<XB, 1>(a, s);
+    case 2: return launch_direct<XB, 2>(a, s);
+    case 3: return launch_direct<XB, 3>(a, s);
+    default: return launch_direct<XB, 4>(a, s);
+    }
 }
 
 template <int MT, bool DEEP>
@@ -286,6 +474,17 @@ int tr_launch_linear(const void* x, int32_t n_out, const void* const* w, void* c
     a.M = M;
     a.N = N;
     a.K = K;
+    const DirectPlan d = direct_plan(M, N, K, tr_linear_splits(M, N, K));
+    if (d.xb > 0) {
+        a.n_split = a.m_split = 1;
+        a.row_tiles = (M + 16 * d.xb - 1) / (16 * d.xb);
+        switch (d.xb) {
+        case 1: return launch_direct_x<1>(a, d.wb, s);
+        case 2: return launch_direct_x<2>(a, d.wb, s);
+        case 3: return launch_direct_x<3>(a, d.wb, s);
+        default: return launch_direct_x<4>(a, d.wb, s);
+        }
+    }
     a.n_split = tr_linear_splits(M, N, K);
     a.m_split = lin_m_split(M, N, K);
     int rc;

@@ -1,0 +1,83 @@
+"""Projections whose workgroups keep all of k: every tile of 16 .. 64 rows of x by 16 .. 64 features, at row counts around the
+tiles' edges, feature counts that leave the last tile short or put two outputs into one tile, k of less than a chunk, with a short
+last chunk, shorter and longer than the ring, and a multiple of 4096 (where tiles start their walk in different places)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2410_07590_amd import synth
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2410_07590_amd import binding
+    binding.lib()
+    return binding
+
+ROWS = [1, 15, 16, 17, 33, 48, 49, 64, 65, 96, 97, 128]
+FEATURES = [(32,), (96, 32, 64), (4064,), (2048, 1056)]
+DEPTHS = [16, 80, 128, 144, 1040, 4096]
+
+
+def run(B, x, weights, guard=2):
+    M = x.shape[0]
+    ys = [torch.full((M + guard, w.shape[0]), float("nan"), dtype=torch.bfloat16, device="cuda") for w in weights]
+    feats = [w.shape[0] for w in weights]
+    scratch = B.workspace(B.tr_linear_workspace_size(M, feats, x.shape[1]))
+    B.tr_linear(x.cuda(), [w.cuda() for w in weights], [y[:M] for y in ys], scratch)
+    torch.cuda.synchronize()
+    assert all(torch.isnan(y[M:]).all() for y in ys), "rows behind the last one were written"
+    return [H.to_f64(y[:M]) for y in ys]
+
+
+@pytest.mark.parametrize("K", DEPTHS)
+@pytest.mark.parametrize("feats", FEATURES, ids=lambda f: "x".join(map(str, f)))
+def test_against_fp64(B, feats, K):
+    """|err| <= 2^-8 |y| (the rounding of the result) + 1e-3: fp32 sums of up to 4096 products of unit variance over sqrt(K)."""
+    rng = np.random.Generator(np.random.PCG64([612, sum(feats), K]))
+    weights = [(synth.normal_tensor(rng, (n, K), torch.float32) * K ** -0.5).to(torch.bfloat16) for n in feats]
+    xs = synth.normal_tensor(rng, (max(ROWS), K), torch.bfloat16)
+    want = [oracle.linear(H.bits(xs), H.bits(w)) for w in weights]
+    worst = 0.0
+    for M in ROWS:
+        for got, w in zip(run(B, xs[:M], weights), want):
+            assert np.isfinite(got).all(), M
+            err = np.abs(got - w[:M])
+            assert (err <= 2.0 ** -8 * np.abs(w[:M]) + 1e-3).all(), "%d rows: max abs err %.3e" % (M, err.max())
+            worst = max(worst, float(err.max()))
+    print("features %s K %d: max abs err %.3e" % (feats, K, worst))
+
+
+def test_infinity_stays_in_its_row(B):
+    """The pieces of a short last chunk that lie past the end of a row take no part, whatever the row ends in."""
+    K, n = 144, 64
+    rng = np.random.Generator(np.random.PCG64([613]))
+    x = synth.normal_tensor(rng, (20, K), torch.bfloat16)
+    x[3, K - 1] = float("inf")
+    w = (synth.normal_tensor(rng, (n, K), torch.float32) * K ** -0.5).to(torch.bfloat16)
+    got, = run(B, x, [w])
+    assert np.array_equal(got[3], np.sign(H.to_f64(w)[:, K - 1]) * np.inf)
+    assert np.isfinite(np.delete(got, 3, axis=0)).all()
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 3584, 3584), (5, 2048, 2048), (128, 4608, 4096)])
+def test_no_less_precise_than_the_slices(B, M, N, K):
+    """Distance from the fp64 product, all of k in a workgroup against forced slices: the same rounding of the result dominates
+    both, so they may differ by what a few values on the edge of a rounding make."""
+    rng = np.random.Generator(np.random.PCG64([614, M]))
+    x = synth.normal_tensor(rng, (M, K), torch.bfloat16)
+    w = (synth.normal_tensor(rng, (N, K), torch.float32) * K ** -0.5).to(torch.bfloat16)
+    want = oracle.linear(H.bits(x), H.bits(w))
+    direct, = run(B, x, [w])
+    B.tr_set_tuning("lin_split", 4)
+    try:
+        slices, = run(B, x, [w])
+    finally:
+        B.tr_set_tuning("lin_split", 0)
+    e = [float(np.linalg.norm(y - want)) for y in (direct, slices)]
+    print("%d x %d x %d: |error| direct / slices %.6f" % (M, N, K, e[0] / e[1]))
+    assert e[0] <= 1.001 * e[1]

@@ -1392,7 +1392,12 @@ extern "C" int tr_chunk_prefill_attn(const tr_shape* shape, const void* q, const
     memset(&a, 0, sizeof a);
     tr_fill_theta(shape, a.theta);
     for (int m = 0; m < 64; ++m) a.theta_rev[m] = a.theta[m] / 6.283185307179586476925;
-    rc = tr_launch_rope_table(table, max_chunk_len, shape->head_dim / 2, a.theta, s);
+    // A table of angles costs a launch and a wait, angles in the rotation kernel a sincos for each token and pair.  Whole call, us,
+    // table / none: 32 / 8 heads of 128 at 64 tokens 16.9 / 13.9, 2048 23.5 / 21.0, 8192 in chunks of 512 75.7 / 74.4, 12288
+    // 64.2 / 63.8, 16384 88.8 / 90.2, 32768 166.8 / 171.4; 14 / 2 heads of 64 at 16384 27.4 / 26.2, 32768 44.0 / 44.2; one KV head
+    // of 128 at 12288 23.8 / 23.4, 32768 44.1 / 46.1.  The line is drawn in angles, at 12288 tokens of 64 pairs.
+    if (total_tokens * (shape->head_dim / 2) <= 12288 * 64) table = nullptr;
+    else rc = tr_launch_rope_table(table, max_chunk_len, shape->head_dim / 2, a.theta, s);
     if (rc) return rc;
     rc = tr_launch_rope_rows(k, k_rot_out, cu_chunk_lens, n_chunks, max_chunk_len, tok_start, table, max_chunk_len, total_tokens, shape, s);
     if (rc) return rc;

@@ -406,17 +406,21 @@ __global__ __launch_bounds__(256) void rope_table_kernel(double2* table, int n_p
 }
 
 // Grid (row blocks, chunks); a thread owns one 16-byte unit position inside a head for one token and walks the
-// KV heads, so the (cos, sin) it fetched from the table serve every head.  Row blocks stride over the chunk, so
+// KV heads, so the (cos, sin) of its pairs serve every head.  Row blocks stride over the chunk, so
 // every token of [cu[c], cu[c+1]) is covered whatever the chunk's length.  Also records, per token, the first
 // row of its chunk.
+// TABLE: the angles come from rope_table_kernel's table, which serves every chunk.  Otherwise each thread works out the
+// angles of one unit's pairs, the first heads' loads being on their way (in the half-split layout partner lanes have half each):
+// no launch in front and no table to wait for, but tokens x half_dim fp64 sincos in all, which a long call does not hide.
 constexpr int ROPE_ROWS_HEADS = 8; // KV heads in flight per thread
 
-template <int DTYPE, bool HALF>
+template <int DTYPE, bool HALF, bool TABLE>
 __global__ __launch_bounds__(256) void rope_rows_kernel(const uint4* k, uint4* k_rot, const int32_t* cu, int32_t* tok_start,
-                                                        const double2* table, int table_rows, int64_t total_tokens,
+                                                        const double2* table, int table_rows, const ThetaArg theta, int64_t total_tokens,
                                                         int n_kv_heads, int head_units, int half_dim)
 {
-    constexpr int P = Unit<DTYPE>::PAIRS, E = UnitHalf<DTYPE>::ELEMS;
+    constexpr int P = Unit<DTYPE>::PAIRS, N_CS = HALF ? UnitHalf<DTYPE>::ELEMS : P; // N_CS: pairs this thread's unit takes part in
+    static_assert(UnitHalf<DTYPE>::ELEMS == 2 * P, "partner lanes share the angles of a unit evenly");
     const int hmask = head_units >> 1;
     const int chunk = blockIdx.y;
     int start = cu[chunk], end = cu[chunk + 1];
@@ -425,29 +429,46 @@ __global__ __launch_bounds__(256) void rope_rows_kernel(const uint4* k, uint4* k
     const int tpb = 256 / head_units; // tokens per block
     const int unit = threadIdx.x % head_units;
     const int row_units = n_kv_heads * head_units;
+    const bool low = unit < hmask;
+    const int m0 = (HALF && !low ? unit - hmask : unit) * N_CS;
     for (int t = start + blockIdx.x * tpb + threadIdx.x / head_units; t < end; t += gridDim.x * tpb) {
         if (unit == 0) tok_start[t] = start;
         int pos = t - start;
         if (pos > table_rows - 1) pos = table_rows - 1; // caller promised max_chunk_len; never read past the table
         const uint4* src = k + (int64_t)t * row_units + unit;
         uint4* dst = k_rot + (int64_t)t * row_units + unit;
+        double c[N_CS], s[N_CS];
         for (int h0 = 0; h0 < n_kv_heads; h0 += ROPE_ROWS_HEADS) {
             uint4 x[ROPE_ROWS_HEADS];
 #pragma unroll
             for (int j = 0; j < ROPE_ROWS_HEADS; ++j)
                 if (h0 + j < n_kv_heads) x[j] = ld_stream(src + (h0 + j) * head_units);
-            constexpr int N_CS = HALF ? E : P; // pairs this thread's unit takes part in
-            double c[N_CS], s[N_CS];
-            const bool low = unit < hmask;
-            const int m0 = HALF ? (low ? unit : unit - hmask) * E : unit * P;
-#pragma unroll
-            for (int p = 0; p < N_CS; ++p) {
-                const double2 e = table[(int64_t)pos * half_dim + m0 + p];
-                c[p] = e.x;
-                s[p] = e.y;
-            }
             // a token's units sit in neighbouring lanes (head_units of them, a power of two), so the partner lane of the
             // half-split layout is in this iteration too
+            if constexpr (TABLE) {
+#pragma unroll
+                for (int p = 0; p < N_CS; ++p) {
+                    const double2 e = table[(int64_t)pos * half_dim + m0 + p];
+                    c[p] = e.x;
+                    s[p] = e.y;
+                }
+            } else if (h0 == 0) {
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    double sn, cn;
+                    sincos((double)pos * theta.v[m0 + (HALF && !low ? P : 0) + p], &sn, &cn);
+                    if constexpr (HALF) {
+                        const double co = __shfl_xor(cn, hmask), so = __shfl_xor(sn, hmask);
+                        c[p] = low ? cn : co;
+                        s[p] = low ? sn : so;
+                        c[P + p] = low ? co : cn;
+                        s[P + p] = low ? so : sn;
+                    } else {
+                        c[p] = cn;
+                        s[p] = sn;
+                    }
+                }
+            }
 #pragma unroll
             for (int j = 0; j < ROPE_ROWS_HEADS; ++j)
                 if (h0 + j < n_kv_heads) {
@@ -521,6 +542,8 @@ int tr_launch_rope_rows(const void* k, void* k_rot, const int32_t* cu, int n_chu
     const int eb = tr_elem_bytes(shape);
     const int head_units = shape->head_dim * eb / 16;
     if (total_tokens <= 0 || n_chunks <= 0) return TR_OK;
+    ThetaArg th = {};
+    tr_fill_theta(shape, th.v);
     const int tpb = 256 / head_units;
     int row_blocks = (max_chunk_len + tpb - 1) / tpb;
     if (row_blocks < 1) row_blocks = 1;
@@ -530,10 +553,13 @@ int tr_launch_rope_rows(const void* k, void* k_rot, const int32_t* cu, int n_chu
         const int nc = n_chunks - c0 < 65535 ? n_chunks - c0 : 65535;
         dim3 grid((unsigned)row_blocks, (unsigned)nc);
         const bool half = tr_rope_half(shape) != 0;
-        auto kern = shape->dtype == TR_BF16 ? (half ? rope_rows_kernel<TR_BF16, true> : rope_rows_kernel<TR_BF16, false>)
-                                            : (half ? rope_rows_kernel<TR_F32, true> : rope_rows_kernel<TR_F32, false>);
+        auto kern = shape->dtype == TR_BF16 ? (half ? rope_rows_kernel<TR_BF16, true, true> : rope_rows_kernel<TR_BF16, false, true>)
+                                            : (half ? rope_rows_kernel<TR_F32, true, true> : rope_rows_kernel<TR_F32, false, true>);
+        if (!table)
+            kern = shape->dtype == TR_BF16 ? (half ? rope_rows_kernel<TR_BF16, true, false> : rope_rows_kernel<TR_BF16, false, false>)
+                                           : (half ? rope_rows_kernel<TR_F32, true, false> : rope_rows_kernel<TR_F32, false, false>);
         hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, (const uint4*)k, (uint4*)k_rot, cu + c0, tok_start, (const double2*)table,
-                           table_rows, total_tokens, shape->n_kv_heads, head_units, shape->head_dim / 2);
+                           table_rows, th, total_tokens, shape->n_kv_heads, head_units, shape->head_dim / 2);
         TR_HIP(hipGetLastError());
     }
     return TR_OK;

@@ -301,6 +301,7 @@ int tr_launch_append(const TrAppendArgs& a, int dtype, hipStream_t s);
 int tr_launch_prefix_attn(const TrPrefixArgs& a, int head_dim, int wg_rows, bool any_split, int total_rows, hipStream_t s);
 int tr_launch_prefix_attn_f32(const TrPrefixArgs& a, int head_dim, int total_rows, hipStream_t s);
 int tr_launch_rope_table(double* table, int n_pos, int half_dim, const double* theta, hipStream_t s);
+// table == NULL: the kernel works out the angles itself; table_rows bounds the positions either way
 int tr_launch_rope_rows(const void* k, void* k_rot, const int32_t* cu, int n_chunks, int max_chunk_len, int32_t* tok_start,
                         const double* table, int table_rows, int64_t total_tokens, const tr_shape* shape, hipStream_t s);
 static inline int tr_rope_half(const tr_shape* s) { return s->rope_layout == TR_ROPE_HALF ? 1 : 0; }

@@ -34,7 +34,7 @@ import sys
 
 OUR_KERNELS = ("assemble_kernel", "append_kernel", "append_packed_kernel", "prefix_attn", "combine_kernel", "short_attn_kernel",
                "blockdiag_attn", "gather_attn_kernel", "rope_table_kernel", "rope_rows_kernel", "linear_kernel",
-               "linear_combine_kernel", "mfma_loop_probe_kernel", "fill_kernel")
+               "linear_direct_kernel", "linear_combine_kernel", "mfma_loop_probe_kernel", "fill_kernel")
 COPY_KIB = 262144.0   # bench.py --case copy moves 256 MiB each way
 
 # case -> [(kernel-name filter or None for "every kernel of the run", bench.py row key)]

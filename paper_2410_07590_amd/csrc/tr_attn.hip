@@ -1119,7 +1119,10 @@ __global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPr
     // merge the four key slices: every wave parks (m, l) and its unnormalised O in LDS
     constexpr int ROWB = short_merge_row_bytes<D>();
     const float l_tot = acc.l + __shfl_xor(acc.l, 32);
-    __builtin_amdgcn_s_barrier(); // all waves are done with the K/V stages
+    // All waves are done with the K/V stages, and nothing is on its way to them: a workgroup whose split lies behind its tokens'
+    // causal end walks no tile, and the first tile, requested all the same, must not land on the rows parked here.
+    wait_vm<0>();
+    __builtin_amdgcn_s_barrier();
     LDS_AS char* obuf = smem + wave * (32 * ROWB);
     LDS_AS float* mlbuf = (LDS_AS float*)(smem + NW * 32 * ROWB);
 #pragma unroll

@@ -237,7 +237,14 @@ __global__ __launch_bounds__(256) void linear_combine_kernel(const TrLinearArgs 
 // the first of them.
 // k is walked in chunks of 128 values through a ring of LDS slots; of a chunk each of the four waves multiplies 32 values (one
 // k-step of v_mfma_f32_16x16x32_bf16: w rows = A, x rows = B), and the four sums meet in LDS at the end, added in wave order.
-// Ten layers' projections of 64 rows (3584 -> 3584 + 512 + 512, 3584 -> 3584) take 264 us instead of 307.
+// Ten layers' projections of 64 rows (3584 -> 3584 + 512 + 512, 3584 -> 3584) take 270 us instead of 307.
+// The rounding error of a chain through the matrix unit's accumulator grows with the chain's length, that of several chains with the
+// root of their number, and a slice of linear_kernel may be as short as two chunks: 256 values in a row.  So after DIRECT_FOLD chunks, of each of which 32 values
+// are a wave's own (224 in a row), the accumulator is added to a second one and starts again.  Error of the sums alone (operands
+// whose exact results are zero), this kernel / the slices: 3584 x 3584 at 64 rows 5.2e-6 / 7.2e-6, 512 x 3584 at 128 rows 5.2e-6 /
+// 5.4e-6, 2048 x 2048 at 64 rows 3.7e-6 / 3.9e-6; in one chain 9.1e-6, 9.1e-6 and 5.2e-6.  The additions run while the operand
+// reads do and cost 1 % (ten layers of 64 rows 267 -> 270 us).
+constexpr int DIRECT_FOLD = 7;
 constexpr int DIRECT_MAX_SLOTS = 8, DIRECT_LDS = 128 * 1024;
 template <int XB, int WB> constexpr int direct_slot_bytes() { return 16 * (XB + WB) * LIN_ROW; }
 template <int XB, int WB> constexpr int direct_slots()
@@ -245,8 +252,10 @@ template <int XB, int WB> constexpr int direct_slots()
     return DIRECT_LDS / direct_slot_bytes<XB, WB>() < DIRECT_MAX_SLOTS ? DIRECT_LDS / direct_slot_bytes<XB, WB>() : DIRECT_MAX_SLOTS;
 }
 
+// Two workgroups per CU in the bounds, though LDS leaves room for one: with more registers the compiler keeps the accumulators in
+// the other half of the file and moves them there and back in every chunk (3584 x 3584 at 64 rows 12.1 -> 14.8 us).
 template <int XB, int WB>
-__global__ __launch_bounds__(256) void linear_direct_kernel(const TrLinearArgs a)
+__global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArgs a)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
     LDS_AS char* lds = (LDS_AS char*)lds_raw;
@@ -291,13 +300,22 @@ __global__ __launch_bounds__(256) void linear_direct_kernel(const TrLinearArgs a
         }
     };
 
-    f32x4 acc[WB][XB];
+    // acc: products of at most DIRECT_FOLD chunks, sum: of all before them
+    f32x4 acc[WB][XB], sum[WB][XB];
 #pragma unroll
     for (int wb = 0; wb < WB; ++wb)
 #pragma unroll
-        for (int xb = 0; xb < XB; ++xb)
+        for (int xb = 0; xb < XB; ++xb) acc[wb][xb] = sum[wb][xb] = f32x4{};
+    auto fold = [&]() {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[wb][xb][e] = 0.0f;
+        for (int wb = 0; wb < WB; ++wb)
+#pragma unroll
+            for (int xb = 0; xb < XB; ++xb) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[wb][xb][e] += acc[wb][xb][e];
+                acc[wb][xb] = f32x4{};
+            }
+    };
 
     // rows that lie a multiple of 8 KB apart would all be asked for on the same few memory channels at the same time: there
     // every feature tile starts its walk somewhere else (4096 x 4096, 37 rows of x 15.1 -> 11.4 us; 8192 x 8192, 32 rows
@@ -309,7 +327,7 @@ __global__ __launch_bounds__(256) void linear_direct_kernel(const TrLinearArgs a
         if (p < n_chunks) issue(chunk(p), p);
     const int r = lane & 15, piece = 4 * wave + (lane >> 4); // this lane's operand row of a block and its piece of a chunk
     const int off = lin_piece_off(r, piece);
-    int slot = 0;
+    int slot = 0, chain = 0; // chain: chunks in acc
     for (int c = 0; c < n_chunks; ++c) {
         // chunk c has landed once at most the loads of the chunks requested after it are outstanding
         if (c + NSLOT - 1 <= n_chunks) lin_wait_vm<(NSLOT - 2) * IPC>();
@@ -322,6 +340,12 @@ __global__ __launch_bounds__(256) void linear_direct_kernel(const TrLinearArgs a
         for (int b = 0; b < XB; ++b) xb_[b] = *(LDS_AS const bf16x8*)(base + b * (16 * LIN_ROW));
 #pragma unroll
         for (int b = 0; b < WB; ++b) wb_[b] = *(LDS_AS const bf16x8*)(base + (XB + b) * (16 * LIN_ROW));
+        if (chain == DIRECT_FOLD) { // in the shadow of the operand reads
+            asm volatile("");       // a branch, not selects in every iteration
+            fold();
+            chain = 0;
+        }
+        ++chain;
         if (chunk(c) * LIN_PPR + piece > last_piece) { // past the end of a row, in its short last chunk
 #pragma unroll
             for (int b = 0; b < XB; ++b) xb_[b] = bf16x8{};
@@ -334,14 +358,15 @@ __global__ __launch_bounds__(256) void linear_direct_kernel(const TrLinearArgs a
             for (int b = 0; b < XB; ++b) acc[w][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb_[w], xb_[b], acc[w][b], 0, 0, 0);
         slot = slot + 1 == NSLOT ? 0 : slot + 1;
     }
+    fold();
 
-    // element e of lane l's acc[w][b]: row m0 + 16 b + (l & 15) of x, feature 4 (l >> 4) + e of block w
+    // element e of lane l's sum[w][b]: row m0 + 16 b + (l & 15) of x, feature 4 (l >> 4) + e of block w
     __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0): this wave's operand reads are done
     __builtin_amdgcn_s_barrier();       // ... and everyone else's: the ring becomes the exchange
 #pragma unroll
     for (int w = 0; w < WB; ++w)
 #pragma unroll
-        for (int b = 0; b < XB; ++b) *(LDS_AS f32x4*)(lds + ((wave * WB + w) * XB + b) * 1024 + lane * 16) = acc[w][b];
+        for (int b = 0; b < XB; ++b) *(LDS_AS f32x4*)(lds + ((wave * WB + w) * XB + b) * 1024 + lane * 16) = sum[w][b];
     __syncthreads();
 #pragma unroll
     for (int t0 = 0; t0 < WB * XB; t0 += 4) {

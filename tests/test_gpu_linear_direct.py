@@ -64,20 +64,34 @@ def test_infinity_stays_in_its_row(B):
     assert np.isfinite(np.delete(got, 3, axis=0)).all()
 
 
-@pytest.mark.parametrize("M,N,K", [(64, 3584, 3584), (5, 2048, 2048), (128, 4608, 4096)])
+@pytest.mark.parametrize("M,N,K", [(64, 3584, 3584), (5, 2048, 2048), (128, 4608, 3584), (64, 4608, 3584), (128, 512, 3584),
+                                   (128, 4608, 4096), (16, 4096, 4096), (64, 8192, 8192), (16, 512, 512)])
 def test_no_less_precise_than_the_slices(B, M, N, K):
-    """Distance from the fp64 product, all of k in a workgroup against forced slices: the same rounding of the result dominates
-    both, so they may differ by what a few values on the edge of a rounding make."""
-    rng = np.random.Generator(np.random.PCG64([614, M]))
-    x = synth.normal_tensor(rng, (M, K), torch.bfloat16)
-    w = (synth.normal_tensor(rng, (N, K), torch.float32) * K ** -0.5).to(torch.bfloat16)
-    want = oracle.linear(H.bits(x), H.bits(w))
-    direct, = run(B, x, [w])
-    B.tr_set_tuning("lin_split", 4)
-    try:
-        slices, = run(B, x, [w])
-    finally:
-        B.tr_set_tuning("lin_split", 0)
-    e = [float(np.linalg.norm(y - want)) for y in (direct, slices)]
-    print("%d x %d x %d: |error| direct / slices %.6f" % (M, N, K, e[0] / e[1]))
-    assert e[0] <= 1.001 * e[1]
+    """The error of the fp32 sums alone, all of k in a workgroup against the slices that the call would take otherwise: every
+    product has its negative somewhere in the row, so the exact results are zero and what is left is rounding of the sums (a result
+    near one hides it behind its own rounding, 2^-9 against 1e-7).  Root mean square over at least 8192 results, known to 1 %;
+    a chain of k through the accumulators that is a third longer shows as 15 %."""
+    gen = torch.Generator().manual_seed(614 + M + N)
+    a, b = (torch.randn(n, K // 2, generator=gen).bfloat16() for n in (M, N))
+    places = torch.randperm(K, generator=gen)
+    x, w = torch.cat([a, a], 1)[:, places].contiguous().cuda(), torch.cat([b, -b], 1)[:, places].contiguous().cuda()
+    need = B.tr_linear_workspace_size(M, [N], K)
+    slices = need // (4 * M * N)
+    assert slices > 1
+
+    def rms(split):
+        y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.tr_set_tuning("lin_split", split)
+        try:
+            scratch = B.workspace(need)
+            scratch.fill_(0x5A)
+            B.tr_linear(x, [w], [y], scratch)
+            torch.cuda.synchronize()
+        finally:
+            B.tr_set_tuning("lin_split", 0)
+        assert bool((scratch == 0x5A).all()) == (split == 0)   # the slices leave partial sums there, a whole row of k none
+        return float(y.double().square().mean().sqrt())
+
+    e = rms(0), rms(slices)
+    print("%d x %d x %d: rms error of the sums %.3e, in %d slices %.3e, ratio %.2f" % (M, N, K, e[0], slices, e[1], e[0] / e[1]))
+    assert 0 < e[0] <= 1.02 * e[1]

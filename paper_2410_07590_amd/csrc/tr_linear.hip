@@ -332,7 +332,8 @@ __global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArg
         // chunk c has landed once at most the loads of the chunks requested after it are outstanding
         if (c + NSLOT - 1 <= n_chunks) lin_wait_vm<(NSLOT - 2) * IPC>();
         else lin_wait_vm<0>();
-        __builtin_amdgcn_s_barrier(); // every wave's part of it; everyone is done with chunk c - 1, whose slot is free
+        __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0): this wave's operand reads of chunk c - 1 are done
+        __builtin_amdgcn_s_barrier();       // ... and everyone else's, so its slot is free; every wave's part of chunk c has landed
         if (c + NSLOT - 1 < n_chunks) issue(chunk(c + NSLOT - 1), slot == 0 ? NSLOT - 1 : slot - 1);
         LDS_AS const char* base = lds + slot * SLOT + off;
         bf16x8 xb_[XB], wb_[WB];

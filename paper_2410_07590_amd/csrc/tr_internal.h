@@ -315,6 +315,9 @@ int tr_launch_blockdiag_attn_f32(const TrBlockDiagArgs& a, int64_t longest, int 
 // counts; partial: fp32 [tr_linear_splits(M, N, K), M, N] when that count exceeds 1
 #define TR_LINEAR_MAX_OUT 4
 int tr_linear_splits(int32_t M, int32_t N, int32_t K);
+// Which kernel a product takes under the overrides in force, for tests: 16 xb + wb where workgroups keep all of k for a tile of
+// 16 xb rows of x by 16 wb features, 0 where k is cut into slices.  Not part of the public interface.
+extern "C" int tr_linear_direct_tile(int32_t M, int32_t N, int32_t K);
 // sink: 256 * 512 floats.  *flops receives the multiply-add count x 2 of the launch.
 int tr_launch_mfma_loop_probe(int iters, int random_operands, float* sink, hipStream_t s, double* flops);
 int tr_launch_linear(const void* x, int32_t n_out, const void* const* w, void* const* y, const int32_t* n_features, void* partial,

@@ -417,35 +417,6 @@ int tr_linear_splits(int32_t M, int32_t N, int32_t K)
     return n_split;
 }
 
-// The tile of linear_direct_kernel, in blocks of 16 rows of x and 16 features; xb = 0: slices of k and a merge.
-// Of the tiles that fit one workgroup per CU, the one that asks for the fewest bytes per CU (of equal ones the squarest: fewer
-// workgroups read the same weights or the same x).  Its time and that of the slices are estimated from fits to 19 shapes at 11
-// row counts each (1 .. 128), weights not in the caches, on which they are right to 6 % (rms):
-//   direct   launch + the larger of 0.1 + 0.058 (xb + wb) us a chunk of k and the weights at the HBM rate
-//   slices   two launches + weights, partial sums, and rows of x (which the slices read once per 128 features)
-// and the direct kernel is taken where it is the faster one by 7 %.  us, slices / direct: 3584 x 3584 14.2 / 11.5 at 64 rows,
-// 10.0 / 9.3 at one, 16.4 / 14.8 at 128; 4608 x 3584 15.6 / 14.1 at 64; 6144 x 4096 18.3 / 16.0 at 64; 512 x 3584 6.6 / 8.4 at
-// one and 9.6 / 8.6 at 128; 512 x 512 7.6 / 3.3; 8192 x 8192 37.6 / 32.6 at 64; 3584 x 18944 36.2 / 47 at 64; 2048 x 8192
-// 15.2 / 21 at 64: with few features or a long k the slices have more CUs at work, or longer streams.
-struct DirectPlan { int xb, wb; };
-static DirectPlan direct_plan(int32_t M, int32_t N, int32_t K, int n_split)
-{
-    if (tr_knob(TR_KNOB_LIN_SPLIT, 0) || tr_knob(TR_KNOB_LIN_MSPLIT, 0)) return {0, 0}; // a forced split is a split
-    const int blocks = N / 16;
-    DirectPlan best = {0, 0};
-    for (int xb = 1; xb <= 4; ++xb)
-        for (int wb = 1; wb <= 4; ++wb) {
-            if ((int64_t)((M + 16 * xb - 1) / (16 * xb)) * ((blocks + wb - 1) / wb) > TrChip::CUS) continue;
-            const int d = xb + wb - best.xb - best.wb;
-            if (best.xb == 0 || d < 0 || (d == 0 && abs(xb - wb) < abs(best.xb - best.wb))) best = {xb, wb};
-        }
-    if (best.xb == 0) return best;
-    const double mb = 2e-6 * N * (double)K, chunks = (K + LIN_CK - 1) / LIN_CK;
-    const double direct = 2.8 + std::max(chunks * (0.1 + 0.058 * (best.xb + best.wb)), mb / 5.3 + 1.5);
-    const double slices = 6.3 + 0.146 * mb + (n_split > 1 ? 0.71e-6 * n_split * M * (double)N : 0.0) + (0.69 + 0.0314 * mb) * M / 32;
-    return direct <= 0.93 * slices ? best : DirectPlan{0, 0};
-}
-
 template <int XB, int WB> static int launch_direct(const TrLinearArgs& a, hipStream_t s)
 {
     auto kern = linear_direct_kernel<XB, WB>;
@@ -457,14 +428,49 @@ template <int XB, int WB> static int launch_direct(const TrLinearArgs& a, hipStr
     TR_HIP(hipGetLastError());
     return TR_OK;
 }
-template <int XB> static int launch_direct_x(const TrLinearArgs& a, int wb, hipStream_t s)
+// The tiles there are, in blocks of 16 rows of x and 16 features.  Tiles of two or more row blocks by one feature block and (4, 2) would
+// never be taken: where one fits, so does one with fewer bytes or a squarer one of as many.
+struct DirectTile {
+    int xb, wb;
+    int (*launch)(const TrLinearArgs& a, hipStream_t s);
+};
+static const DirectTile DIRECT_TILES[] = {
+    {1, 1, launch_direct<1, 1>}, {1, 2, launch_direct<1, 2>}, {1, 3, launch_direct<1, 3>}, {1, 4, launch_direct<1, 4>},
+    {2, 2, launch_direct<2, 2>}, {2, 3, launch_direct<2, 3>}, {2, 4, launch_direct<2, 4>}, {3, 2, launch_direct<3, 2>},
+    {3, 3, launch_direct<3, 3>}, {3, 4, launch_direct<3, 4>}, {4, 3, launch_direct<4, 3>}, {4, 4, launch_direct<4, 4>},
+};
+
+// The tile of linear_direct_kernel, or none: slices of k and a merge.
+// Of the tiles that fit one workgroup per CU, the one that asks for the fewest bytes per CU (of equal ones the squarest: fewer
+// workgroups read the same weights or the same x).  Its time and that of the slices are estimated from fits to 19 shapes at 11
+// row counts each (1 .. 128), weights not in the caches, on which they are right to 6 % (rms):
+//   direct   launch + the larger of 0.1 + 0.058 (xb + wb) us a chunk of k and the weights at the HBM rate
+//   slices   two launches + weights, partial sums, and rows of x (which the slices read once per 128 features)
+// and the direct kernel is taken where it is the faster one by 7 %.  us, slices / direct: 3584 x 3584 14.2 / 11.5 at 64 rows,
+// 10.0 / 9.3 at one, 16.4 / 14.8 at 128; 4608 x 3584 15.6 / 14.1 at 64; 6144 x 4096 18.3 / 16.0 at 64; 512 x 3584 6.6 / 8.4 at
+// one and 9.6 / 8.6 at 128; 512 x 512 7.6 / 3.3; 8192 x 8192 37.6 / 32.6 at 64; 3584 x 18944 36.2 / 47 at 64; 2048 x 8192
+// 15.2 / 21 at 64: with few features or a long k the slices have more CUs at work, or longer streams.
+static const DirectTile* direct_plan(int32_t M, int32_t N, int32_t K, int n_split)
 {
-    switch (wb) {
-    case 1: return launch_direct<XB, 1>(a, s);
-    case 2: return launch_direct<XB, 2>(a, s);
-    case 3: return launch_direct<XB, 3>(a, s);
-    default: return launch_direct<XB, 4>(a, s);
+    if (tr_knob(TR_KNOB_LIN_SPLIT, 0) || tr_knob(TR_KNOB_LIN_MSPLIT, 0)) return nullptr; // a forced split is a split
+    const int blocks = N / 16;
+    const DirectTile* best = nullptr;
+    for (const DirectTile& t : DIRECT_TILES) {
+        if ((int64_t)((M + 16 * t.xb - 1) / (16 * t.xb)) * ((blocks + t.wb - 1) / t.wb) > TrChip::CUS) continue;
+        const int d = best ? t.xb + t.wb - best->xb - best->wb : -1;
+        if (d < 0 || (d == 0 && abs(t.xb - t.wb) < abs(best->xb - best->wb))) best = &t;
     }
+    if (!best) return nullptr;
+    const double mb = 2e-6 * N * (double)K, chunks = (K + LIN_CK - 1) / LIN_CK;
+    const double direct = 2.8 + std::max(chunks * (0.1 + 0.058 * (best->xb + best->wb)), mb / 5.3 + 1.5);
+    const double slices = 6.3 + 0.146 * mb + (n_split > 1 ? 0.71e-6 * n_split * M * (double)N : 0.0) + (0.69 + 0.0314 * mb) * M / 32;
+    return direct <= 0.93 * slices ? best : nullptr;
+}
+
+extern "C" int tr_linear_direct_tile(int32_t M, int32_t N, int32_t K)
+{
+    const DirectTile* t = M > 0 ? direct_plan(M, N, K, tr_linear_splits(M, N, K)) : nullptr;
+    return t ? 16 * t->xb + t->wb : 0;
 }
 
 template <int MT, bool DEEP>
@@ -500,18 +506,13 @@ int tr_launch_linear(const void* x, int32_t n_out, const void* const* w, void* c
     a.M = M;
     a.N = N;
     a.K = K;
-    const DirectPlan d = direct_plan(M, N, K, tr_linear_splits(M, N, K));
-    if (d.xb > 0) {
+    const int n_split = tr_linear_splits(M, N, K);
+    if (const DirectTile* t = direct_plan(M, N, K, n_split)) {
         a.n_split = a.m_split = 1;
-        a.row_tiles = (M + 16 * d.xb - 1) / (16 * d.xb);
-        switch (d.xb) {
-        case 1: return launch_direct_x<1>(a, d.wb, s);
-        case 2: return launch_direct_x<2>(a, d.wb, s);
-        case 3: return launch_direct_x<3>(a, d.wb, s);
-        default: return launch_direct_x<4>(a, d.wb, s);
-        }
+        a.row_tiles = (M + 16 * t->xb - 1) / (16 * t->xb);
+        return t->launch(a, s);
     }
-    a.n_split = tr_linear_splits(M, N, K);
+    a.n_split = n_split;
     a.m_split = lin_m_split(M, N, K);
     int rc;
     const bool deep = !lin_large(N, K);

@@ -526,3 +526,19 @@ def test_launch_planners_on_random_request_mixes(L):
         if seg.size:
             ws = B.tr_sequence_prefill_attn_workspace_size(sh, seg, seg.size)
             assert 0 <= ws <= 64 * seg.size * hkv * g * (2 * d + 8) + 256
+
+
+def test_linear_tiles_that_products_take(L):
+    """Every tile that a product of 1 .. 128 rows can take is among those that the GPU test runs, and none of those is out of reach;
+    a forced number of slices, one included, takes slices."""
+    from tests.test_gpu_linear_direct import TILES
+    taken = {L.tr_linear_direct_tile(M, N, K) for M in range(1, 129) for N in range(32, 20000, 96) for K in (16, 144, 1040, 2064, 4096)}
+    assert taken == {0} | {16 * xb + wb for xb, wb in TILES}
+    for splits in (1, 2):
+        assert L.tr_set_tuning(b"lin_split", C.c_int32(splits)) == B.TR_OK
+        try:
+            assert L.tr_linear_direct_tile(64, 3584, 3584) == 0
+        finally:
+            assert L.tr_set_tuning(b"lin_split", C.c_int32(0)) == B.TR_OK
+    assert L.tr_linear_direct_tile(64, 3584, 3584) != 0
+    assert L.tr_linear_direct_tile(0, 3584, 3584) == 0

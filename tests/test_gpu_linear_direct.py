@@ -1,6 +1,6 @@
-"""Projections whose workgroups keep all of k: every tile of 16 .. 64 rows of x by 16 .. 64 features, at row counts around the
-tiles' edges, feature counts that leave the last tile short or put two outputs into one tile, k of less than a chunk, with a short
-last chunk, shorter and longer than the ring, and a multiple of 4096 (where tiles start their walk in different places)."""
+"""Projections whose workgroups keep all of k: the tiles of 16 .. 64 rows of x by 16 .. 64 features, at row counts around the tiles'
+edges, feature counts that leave the last tile short or put two outputs into one tile, k of less than a chunk, with a short last
+chunk, shorter and longer than the ring, and a multiple of 4096 (where tiles start their walk in different places)."""
 import numpy as np
 import pytest
 import torch
@@ -37,7 +37,8 @@ def run(B, x, weights, guard=2):
 @pytest.mark.parametrize("K", DEPTHS)
 @pytest.mark.parametrize("feats", FEATURES, ids=lambda f: "x".join(map(str, f)))
 def test_against_fp64(B, feats, K):
-    """|err| <= 2^-8 |y| (the rounding of the result) + 1e-3: fp32 sums of up to 4096 products of unit variance over sqrt(K)."""
+    """Row counts one after the other over the same weights, in whichever kernel the call takes (few features with a long k take
+    slices).  |err| <= 2^-8 |y| (the rounding of the result) + 1e-3: fp32 sums of up to 4096 products of unit variance over sqrt(K)."""
     rng = np.random.Generator(np.random.PCG64([612, sum(feats), K]))
     weights = [(synth.normal_tensor(rng, (n, K), torch.float32) * K ** -0.5).to(torch.bfloat16) for n in feats]
     xs = synth.normal_tensor(rng, (max(ROWS), K), torch.bfloat16)
@@ -50,6 +51,39 @@ def test_against_fp64(B, feats, K):
             assert (err <= 2.0 ** -8 * np.abs(w[:M]) + 1e-3).all(), "%d rows: max abs err %.3e" % (M, err.max())
             worst = max(worst, float(err.max()))
     print("features %s K %d: max abs err %.3e" % (feats, K, worst))
+
+
+# tile in blocks of 16 rows and 16 features -> products that take it at the depths of the test below
+TILES = {
+    (1, 1): [(1, (4064,)), (16, (2048, 1056)), (128, (32,)), (49, (96, 32, 64))],
+    (1, 2): [(1, (4128,)), (16, (5536, 64, 32)), (17, (4064,)), (32, (2048, 1056))],
+    (1, 3): [(15, (8288,)), (16, (10272,))],
+    (1, 4): [(15, (12352,)), (16, (12416, 32))],
+    (2, 2): [(17, (8192,)), (32, (4096, 1056, 1056)), (49, (4064,)), (64, (2048, 1056))],
+    (2, 3): [(17, (8256,)), (32, (10272,)), (33, (2048, 2080)), (96, (4064,))],
+    (2, 4): [(17, (12352,)), (32, (16384,)), (49, (4096, 1056, 1056)), (128, (4096,))],
+    (3, 2): [(33, (6176,)), (48, (8192,)), (65, (4096,)), (96, (4096,))],
+    (3, 3): [(33, (8288,)), (48, (10272,)), (65, (5536, 64, 32)), (97, (2048, 1056))],
+    (3, 4): [(33, (12416, 32)), (48, (16384,)), (81, (6176,)), (128, (2048, 2080))],
+    (4, 3): [(49, (8256,)), (64, (10272,)), (97, (5504,)), (128, (5536, 64, 32))],
+    (4, 4): [(49, (12352,)), (64, (16384,)), (97, (4096, 1056, 1056)), (128, (6176,))],
+}
+TILE_DEPTHS = [144, 2064]   # a short last chunk inside the ring, and behind more chunks than the ring and one accumulator take
+
+
+@pytest.mark.parametrize("tile", TILES, ids=lambda t: "%dx%d" % t)
+def test_every_tile_against_fp64(B, tile):
+    """The tile is the one that the library says it takes; the bound is that of the test above, for sums of up to 2064 products."""
+    for case, (M, feats) in enumerate(TILES[tile]):
+        for K in TILE_DEPTHS:
+            assert B.lib().tr_linear_direct_tile(M, sum(feats), K) == 16 * tile[0] + tile[1], (M, feats, K)
+            g = torch.Generator(device="cuda").manual_seed(615 + case + K)
+            draw = lambda *size: torch.randn(size, generator=g, device="cuda")
+            x, weights = draw(M, K).bfloat16(), [(draw(n, K) * K ** -0.5).bfloat16() for n in feats]
+            for got, w in zip(run(B, x, weights), weights):
+                want = H.to_f64(torch.matmul(x.double(), w.double().T))
+                err = np.abs(got - want)
+                assert (err <= 2.0 ** -8 * np.abs(want) + 1e-3).all(), (M, feats, K, float(err.max()))
 
 
 def test_infinity_stays_in_its_row(B):

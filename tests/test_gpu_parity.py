@@ -794,16 +794,37 @@ def _check_linear(B, M, feats, K, seed):
     return worst
 
 
+def _random_linear(seed):
+    rng = np.random.Generator(np.random.PCG64([778, seed]))
+    M = int(rng.choice([1, 7, 31, 32, 33, 64, 65, 95, 96, 97, 127, 128])) if seed < 6 else int(rng.integers(1, 129))
+    feats = tuple(int(32 * rng.integers(1, 33)) for _ in range(int(rng.integers(1, 5))))
+    K = int(16 * rng.integers(1, 257))
+    return M, feats, K
+
+
 @pytest.mark.parametrize("seed", range(12))
 def test_random_linear_shapes(B, seed):
     """Seeded random projection shapes: 1..128 rows (all four row-block counts and the two-workgroup split above 96
     rows), one to four outputs of 32..1024 features, k a multiple of 16 up to 4096 (whole chunks, short last chunks,
     a single k-step)."""
-    rng = np.random.Generator(np.random.PCG64([778, seed]))
-    M = int(rng.choice([1, 7, 31, 32, 33, 64, 65, 95, 96, 97, 127, 128])) if seed < 6 else int(rng.integers(1, 129))
-    feats = tuple(int(32 * rng.integers(1, 33)) for _ in range(int(rng.integers(1, 5))))
-    K = int(16 * rng.integers(1, 257))
+    M, feats, K = _random_linear(seed)
     print("random linear %d: M %d features %s K %d: max abs err %.3e" % (seed, M, feats, K, _check_linear(B, M, feats, K, 900 + seed)))
+
+
+# the sizes above but those that take slices by themselves, and a weight above 64 MB (one chunk in flight) of many features
+SLICED = [c for c in LINEAR_CASES if c[0] * sum(c[1]) * c[2] < 4e9] + [_random_linear(seed) for seed in range(12)] + [(9, (40960,), 1040)]
+
+
+@pytest.mark.parametrize("slices", [1, 3])
+@pytest.mark.parametrize("case", range(len(SLICED)))
+def test_linear_in_slices(B, tuning, case, slices):
+    """k cut into slices whether or not the call would do so by itself: one slice (results stored straight from the accumulators) and
+    three, row counts and short last chunks of both, and with more than 96 rows two workgroups for the rows."""
+    M, feats, K = SLICED[case]
+    slices = min(slices, (K + 127) // 128)
+    tuning("lin_split", slices)
+    assert B.lib().tr_linear_direct_tile(M, sum(feats), K) == 0
+    print("%d slices, M %d features %s K %d: max abs err %.3e" % (slices, M, feats, K, _check_linear(B, M, feats, K, 950 + case)))
 
 
 # ---- seeded random shapes: group sizes, head dims, layouts, ragged lengths, all four attention entry points -------------

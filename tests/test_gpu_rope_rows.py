@@ -10,7 +10,7 @@ from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
 
-LINE = 12288 * 64   # angles up to which a call has no table
+LINE = 12288 * 64   # angles up to which a call has no table; the test sees which side it is on by what the call writes
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
@@ -23,7 +23,7 @@ def test_both_sides_of_the_line(dtype, layout, kv_heads, head_dim):
     edge = LINE // (head_dim // 2)
     lens = [1, 700, 33, 64]
     lens += [128] * ((edge - sum(lens)) // 128)
-    lens.append(edge - sum(lens) or 1)
+    lens.append(edge - sum(lens))
     T = edge + 130
     rng = np.random.Generator(np.random.PCG64([93, kv_heads, head_dim, layout]))
     q, k, v = (synth.normal_tensor(rng, (T, kv_heads, head_dim), sh.torch_dtype) for _ in range(3))
@@ -33,13 +33,17 @@ def test_both_sides_of_the_line(dtype, layout, kv_heads, head_dim):
         n = int(cu[-1])
         out, k_rot = torch.empty_like(q[:n], device="cuda"), torch.empty_like(k[:n], device="cuda")
         ws = B.workspace(B.tr_chunk_prefill_attn_workspace_size(gs, n, 700))
+        ws.fill_(0x5A)
         B.tr_chunk_prefill_attn(gs, q[:n].cuda(), k[:n].cuda(), v[:n].cuda(), torch.from_numpy(cu).cuda(), cu.size - 1, 700, out, k_rot, ws)
         torch.cuda.synchronize()
-        return H.bits(k_rot.cpu()), H.bits(out.cpu())
+        table = ws[:700 * (head_dim // 2) * 16]      # the workspace starts with it: cosine and sine in fp64, position by pair
+        return H.bits(k_rot.cpu()), H.bits(out.cpu()), not bool((table == 0x5A).all())
 
-    assert sum(lens) == edge
-    k_own, out_own = run(lens)
-    k_table, out_table = run(lens + [130])
+    assert sum(lens) == edge and min(lens) > 0
+    k_own, out_own, has_table = run(lens)
+    assert not has_table
+    k_table, out_table, has_table = run(lens + [130])
+    assert has_table
     assert np.array_equal(k_own, k_table[:edge]) and np.array_equal(out_own, out_table[:edge])
     few = 1 + 700 + 33
     cu = np.array([0, 1, 701, few], np.int32)

@@ -1396,7 +1396,14 @@ extern "C" int tr_chunk_prefill_attn(const tr_shape* shape, const void* q, const
     // table / none: 32 / 8 heads of 128 at 64 tokens 16.9 / 13.9, 2048 23.5 / 21.0, 8192 in chunks of 512 75.7 / 74.4, 12288
     // 64.2 / 63.8, 16384 88.8 / 90.2, 32768 166.8 / 171.4; 14 / 2 heads of 64 at 16384 27.4 / 26.2, 32768 44.0 / 44.2; one KV head
     // of 128 at 12288 23.8 / 23.4, 32768 44.1 / 46.1.  The line is drawn in angles, at 12288 tokens of 64 pairs.
-    if (total_tokens * (shape->head_dim / 2) <= 12288 * 64) table = nullptr;
+    // Chunks of a few tokens leave the kernel's workgroups (rot_rows tokens each) part empty, on average half of one per chunk, and a
+    // table of few positions is read from the L1: 12000 tokens in chunks of 20, one KV head of 128 19.6 / 21.3, 32 / 8 heads
+    // 73.5 / 76.2, 24000 in chunks of 8, one KV head of 64 16.1 / 17.6; but 4096 tokens in chunks of 8, 14 / 2 heads of 64 12.9 /
+    // 12.7.  In the half-split layout a thread reads twice as many angles from the table as it works out, and none is as fast or faster
+    // there too (28 / 4 heads of 128, chunks of 20, 64.2 / 63.7).
+    const int64_t rot_rows = 4096 / (shape->head_dim * tr_elem_bytes(shape));
+    const int64_t rot_tokens = total_tokens + (tr_rope_half(shape) ? 0 : n_chunks * rot_rows / 2);
+    if (rot_tokens * (shape->head_dim / 2) <= 12288 * 64) table = nullptr;
     else rc = tr_launch_rope_table(table, max_chunk_len, shape->head_dim / 2, a.theta, s);
     if (rc) return rc;
     rc = tr_launch_rope_rows(k, k_rot_out, cu_chunk_lens, n_chunks, max_chunk_len, tok_start, table, max_chunk_len, total_tokens, shape, s);

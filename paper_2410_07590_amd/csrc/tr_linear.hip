@@ -251,8 +251,9 @@ template <int XB, int WB> constexpr int direct_slots()
 {
     return DIRECT_LDS / direct_slot_bytes<XB, WB>() < DIRECT_MAX_SLOTS ? DIRECT_LDS / direct_slot_bytes<XB, WB>() : DIRECT_MAX_SLOTS;
 }
+template <int XB, int WB> constexpr int direct_lds_bytes() { return direct_slots<XB, WB>() * direct_slot_bytes<XB, WB>(); }
 
-// Two workgroups per CU in the bounds, though LDS leaves room for one: with more registers the compiler keeps the accumulators in
+// Two workgroups per CU in the bounds, though LDS leaves room for one of most tiles: with more registers the compiler keeps the accumulators in
 // the other half of the file and moves them there and back in every chunk (3584 x 3584 at 64 rows 12.1 -> 14.8 us).
 template <int XB, int WB>
 __global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArgs a)
@@ -420,7 +421,7 @@ int tr_linear_splits(int32_t M, int32_t N, int32_t K)
 template <int XB, int WB> static int launch_direct(const TrLinearArgs& a, hipStream_t s)
 {
     auto kern = linear_direct_kernel<XB, WB>;
-    constexpr int lds = direct_slots<XB, WB>() * direct_slot_bytes<XB, WB>();
+    constexpr int lds = direct_lds_bytes<XB, WB>();
     static std::atomic<uint64_t> configured{0};
     if (int rc = tr_raise_lds_limit((const void*)kern, lds, &configured)) return rc;
     const int tiles = (a.N / 16 + WB - 1) / WB;
@@ -432,12 +433,13 @@ template <int XB, int WB> static int launch_direct(const TrLinearArgs& a, hipStr
 // never be taken: where one fits, so does one with fewer bytes or a squarer one of as many.
 struct DirectTile {
     int xb, wb;
+    int per_cu; // workgroups that the LDS of a CU holds
     int (*launch)(const TrLinearArgs& a, hipStream_t s);
 };
-static const DirectTile DIRECT_TILES[] = {
-    {1, 1, launch_direct<1, 1>}, {1, 2, launch_direct<1, 2>}, {1, 3, launch_direct<1, 3>}, {1, 4, launch_direct<1, 4>},
-    {2, 2, launch_direct<2, 2>}, {2, 3, launch_direct<2, 3>}, {2, 4, launch_direct<2, 4>}, {3, 2, launch_direct<3, 2>},
-    {3, 3, launch_direct<3, 3>}, {3, 4, launch_direct<3, 4>}, {4, 3, launch_direct<4, 3>}, {4, 4, launch_direct<4, 4>},
+template <int XB, int WB> constexpr DirectTile direct_tile() { return {XB, WB, 160 * 1024 / direct_lds_bytes<XB, WB>(), launch_direct<XB, WB>}; }
+static constexpr DirectTile DIRECT_TILES[] = {
+    direct_tile<1, 1>(), direct_tile<1, 2>(), direct_tile<1, 3>(), direct_tile<1, 4>(), direct_tile<2, 2>(), direct_tile<2, 3>(),
+    direct_tile<2, 4>(), direct_tile<3, 2>(), direct_tile<3, 3>(), direct_tile<3, 4>(), direct_tile<4, 3>(), direct_tile<4, 4>(),
 };
 
 // The tile of linear_direct_kernel, or none: slices of k and a merge.
@@ -456,7 +458,11 @@ static const DirectTile* direct_plan(int32_t M, int32_t N, int32_t K, int n_spli
     const int blocks = N / 16;
     const DirectTile* best = nullptr;
     for (const DirectTile& t : DIRECT_TILES) {
-        if ((int64_t)((M + 16 * t.xb - 1) / (16 * t.xb)) * ((blocks + t.wb - 1) / t.wb) > TrChip::CUS) continue;
+        const int row_tiles = (M + 16 * t.xb - 1) / (16 * t.xb), tiles = (blocks + t.wb - 1) / t.wb;
+        // A feature tile's row tiles all go to one XCD, so they have to fit there too: a workgroup that waits for a CU doubles the
+        // time (5408 x 8192 at 127 rows in tiles of 48 x 64, 33 workgroups for 32 CUs: 60.7 us, the slices 38.5).
+        if ((int64_t)row_tiles * tiles > TrChip::CUS) continue;
+        if (row_tiles * ((tiles + TrChip::XCDS - 1) / TrChip::XCDS) > t.per_cu * (TrChip::CUS / TrChip::XCDS)) continue;
         const int d = best ? t.xb + t.wb - best->xb - best->wb : -1;
         if (d < 0 || (d == 0 && abs(t.xb - t.wb) < abs(best->xb - best->wb))) best = &t;
     }

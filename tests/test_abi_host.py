@@ -542,3 +542,14 @@ def test_linear_tiles_that_products_take(L):
             assert L.tr_set_tuning(b"lin_split", C.c_int32(0)) == B.TR_OK
     assert L.tr_linear_direct_tile(64, 3584, 3584) != 0
     assert L.tr_linear_direct_tile(0, 3584, 3584) == 0
+
+
+def test_linear_workgroups_fit_each_xcd(L):
+    """Blocks are dealt to eight XCDs of 32 compute units, a feature tile's row tiles to the same one.  Tiles of 16 x 16 leave room for
+    two workgroups in a unit's LDS, the others for one: none has to wait for another to end."""
+    for M in range(1, 129):
+        for N in range(32, 20000, 32):
+            t = L.tr_linear_direct_tile(M, N, 272)
+            if t:
+                row_tiles, tiles = -(-M // (t // 16 * 16)), -(-N // (t % 16 * 16))
+                assert row_tiles * tiles <= 256 and row_tiles * -(-tiles // 8) <= (64 if t == 0x11 else 32), (M, N, t)

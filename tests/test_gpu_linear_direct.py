@@ -60,7 +60,7 @@ TILES = {
     (1, 3): [(15, (8288,)), (16, (10272,))],
     (1, 4): [(15, (12352,)), (16, (12416, 32))],
     (2, 2): [(17, (8192,)), (32, (4096, 1056, 1056)), (49, (4064,)), (64, (2048, 1056))],
-    (2, 3): [(17, (8256,)), (32, (10272,)), (33, (2048, 2080)), (96, (4064,))],
+    (2, 3): [(17, (8256,)), (32, (10272,)), (33, (2048, 2080)), (80, (2048, 1056))],
     (2, 4): [(17, (12352,)), (32, (16384,)), (49, (4096, 1056, 1056)), (128, (4096,))],
     (3, 2): [(33, (6176,)), (48, (8192,)), (65, (4096,)), (96, (4096,))],
     (3, 3): [(33, (8288,)), (48, (10272,)), (65, (5536, 64, 32)), (97, (2048, 1056))],

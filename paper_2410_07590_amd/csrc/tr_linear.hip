@@ -21,6 +21,7 @@
 #include <stdlib.h>
 #include <string.h>
 #include <algorithm>
+#include <cmath>
 
 namespace {
 
@@ -318,10 +319,11 @@ __global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArg
             }
     };
 
-    // rows that lie a multiple of 8 KB apart would all be asked for on the same few memory channels at the same time: there
-    // every feature tile starts its walk somewhere else (4096 x 4096, 37 rows of x 15.1 -> 11.4 us; 8192 x 8192, 32 rows
-    // 35.6 -> 26.5; elsewhere it costs up to a tenth)
-    const int n_chunks = (a.K + LIN_CK - 1) / LIN_CK, first = a.K % 4096 == 0 ? (int)((uint32_t)item * 5u % (uint32_t)n_chunks) : 0;
+    // rows that lie a multiple of 8 KB apart, or all but so, would all be asked for on the same few memory channels at the same time:
+    // there every feature tile starts its walk somewhere else (4096 x 4096, 37 rows of x 15.1 -> 11.4 us; 8192 x 8192, 32 rows 35.6 ->
+    // 26.5; 44 sizes within 64 bytes of 8 KB 1.09 times as fast, 63 of 16 KB 1.15; elsewhere it costs up to a tenth)
+    const bool staggered = (a.K + 32) % 4096 <= 64;
+    const int n_chunks = (a.K + LIN_CK - 1) / LIN_CK, first = staggered ? (int)((uint32_t)item * 5u % (uint32_t)n_chunks) : 0;
     auto chunk = [&](int c) { return c + first < n_chunks ? c + first : c + first - n_chunks; };
 #pragma unroll
     for (int p = 0; p < NSLOT - 1; ++p)
@@ -470,7 +472,16 @@ static const DirectTile* direct_plan(int32_t M, int32_t N, int32_t K, int n_spli
     const double mb = 2e-6 * N * (double)K, chunks = (K + LIN_CK - 1) / LIN_CK;
     const double direct = 2.8 + std::max(chunks * (0.1 + 0.058 * (best->xb + best->wb)), mb / 5.3 + 1.5);
     const double slices = 6.3 + 0.146 * mb + (n_split > 1 ? 0.71e-6 * n_split * M * (double)N : 0.0) + (0.69 + 0.0314 * mb) * M / 32;
-    return direct <= 0.93 * slices ? best : nullptr;
+    if (direct > 0.93 * slices) return nullptr;
+    if (K <= 4096 || K == 8192) return best;
+    // Rows further apart than 8 KB take the direct kernel up to 1.4 times that estimate (8864 features x 8160 at 44 rows 58 us, the
+    // slices 41; 6144 x 8224 at 59 rows 39 / 32), but for two whole 8 KB, where its tiles start their walks in different places (59
+    // sizes of 8192 values: 1.02 .. 1.29 times as fast as the slices).  There both are estimated from fits to 560 sizes of 4112 ..
+    // 20000 values as well, and the line is a tenth: none of the 86 that it sends to the direct kernel is slower by more than 2 %.
+    const double far_direct = 2.6 + chunks * (0.10 + 0.06 * (best->xb + best->wb)) + 0.054 * mb;
+    const double far_slices = 3.0 + 0.127 * mb + (n_split > 1 ? 2.3 + 2.0e-6 * n_split * M * (double)N : 0.0) + (0.75 + 0.0097 * mb) * M / 32 +
+                              0.55 * ceil(chunks / n_split);
+    return far_direct <= 0.9 * far_slices ? best : nullptr;
 }
 
 extern "C" int tr_linear_direct_tile(int32_t M, int32_t N, int32_t K)

@@ -553,3 +553,13 @@ def test_linear_workgroups_fit_each_xcd(L):
             if t:
                 row_tiles, tiles = -(-M // (t // 16 * 16)), -(-N // (t % 16 * 16))
                 assert row_tiles * tiles <= 256 and row_tiles * -(-tiles // 8) <= (64 if t == 0x11 else 32), (M, N, t)
+
+
+def test_linear_far_rows_take_slices(L):
+    """Sizes with rows of more than 8 KB at which all of k in a workgroup takes 1.1 to 1.6 times as long as slices, and two of 16 KB at
+    which it is the faster one."""
+    for M, N, K in [(44, 8864, 8160), (62, 8192, 8224), (122, 7040, 8160), (57, 8576, 7088), (96, 5568, 5104), (59, 6144, 8224), (63, 8192, 18896),
+                    (46, 8192, 16352), (112, 8192, 16384), (87, 8192, 14160)]:
+        assert L.tr_linear_direct_tile(M, N, K) == 0, (M, N, K)
+    for M, N, K in [(64, 8192, 8192), (32, 8192, 8192), (64, 3584, 3584), (64, 4608, 3584), (1, 3584, 3584), (128, 4608, 4096)]:
+        assert L.tr_linear_direct_tile(M, N, K) != 0, (M, N, K)

@@ -86,6 +86,20 @@ def test_every_tile_against_fp64(B, tile):
                 assert (err <= 2.0 ** -8 * np.abs(want) + 1e-3).all(), (M, feats, K, float(err.max()))
 
 
+@pytest.mark.parametrize("M,N,K", [(5, 3584, 4064), (33, 6144, 4064), (17, 6144, 4080), (128, 4096, 4112), (5, 4096, 4128),
+                                   (128, 5120, 4128), (32, 8192, 8192)])
+def test_rows_about_a_multiple_of_8_kb_apart(B, M, N, K):
+    """Tiles start their walks at different chunks, the short last one among them, and wrap round.  Bound as above."""
+    assert B.lib().tr_linear_direct_tile(M, N, K) != 0
+    g = torch.Generator(device="cuda").manual_seed(616 + K)
+    x = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    w = (torch.randn(N, K, generator=g, device="cuda") * K ** -0.5).bfloat16()
+    got, = run(B, x, [w])
+    want = H.to_f64(torch.matmul(x.double(), w.double().T))
+    err = np.abs(got - want)
+    assert (err <= 2.0 ** -8 * np.abs(want) + 1e-3).all(), float(err.max())
+
+
 def test_infinity_stays_in_its_row(B):
     """The pieces of a short last chunk that lie past the end of a row take no part, whatever the row ends in."""
     K, n = 144, 64

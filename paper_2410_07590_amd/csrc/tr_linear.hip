@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256) void linear_combine_kernel(const TrLinearArgs 
 // are a wave's own (224 in a row), the accumulator is added to a second one and starts again.  Error of the sums alone (operands
 // whose exact results are zero), this kernel / the slices: 3584 x 3584 at 64 rows 5.2e-6 / 7.2e-6, 512 x 3584 at 128 rows 5.2e-6 /
 // 5.4e-6, 2048 x 2048 at 64 rows 3.7e-6 / 3.9e-6; in one chain 9.1e-6, 9.1e-6 and 5.2e-6.  The additions run while the operand
-// reads do and cost 1 % (ten layers of 64 rows 267 -> 270 us).
+// reads do; up to seven chunks there are none.  Cost: ten layers of 64 rows 267 -> 269 us, 6144 x 3072 at 17 rows 11.5 -> 11.75.
 constexpr int DIRECT_FOLD = 7;
 constexpr int DIRECT_MAX_SLOTS = 8, DIRECT_LDS = 128 * 1024;
 template <int XB, int WB> constexpr int direct_slot_bytes() { return 16 * (XB + WB) * LIN_ROW; }
@@ -308,21 +308,11 @@ __global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArg
     for (int wb = 0; wb < WB; ++wb)
 #pragma unroll
         for (int xb = 0; xb < XB; ++xb) acc[wb][xb] = sum[wb][xb] = f32x4{};
-    auto fold = [&]() {
-#pragma unroll
-        for (int wb = 0; wb < WB; ++wb)
-#pragma unroll
-            for (int xb = 0; xb < XB; ++xb) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sum[wb][xb][e] += acc[wb][xb][e];
-                acc[wb][xb] = f32x4{};
-            }
-    };
 
     // rows that lie a multiple of 8 KB apart, or all but so, would all be asked for on the same few memory channels at the same time:
     // there every feature tile starts its walk somewhere else (4096 x 4096, 37 rows of x 15.1 -> 11.4 us; 8192 x 8192, 32 rows 35.6 ->
     // 26.5; 44 sizes within 64 bytes of 8 KB 1.09 times as fast, 63 of 16 KB 1.15; elsewhere it costs up to a tenth)
-    const bool staggered = (a.K + 32) % 4096 <= 64;
+    const bool staggered = a.K > 32 && (a.K + 32) % 4096 <= 64;
     const int n_chunks = (a.K + LIN_CK - 1) / LIN_CK, first = staggered ? (int)((uint32_t)item * 5u % (uint32_t)n_chunks) : 0;
     auto chunk = [&](int c) { return c + first < n_chunks ? c + first : c + first - n_chunks; };
 #pragma unroll
@@ -346,7 +336,14 @@ __global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArg
         for (int b = 0; b < WB; ++b) wb_[b] = *(LDS_AS const bf16x8*)(base + (XB + b) * (16 * LIN_ROW));
         if (chain == DIRECT_FOLD) { // in the shadow of the operand reads
             asm volatile("");       // a branch, not selects in every iteration
-            fold();
+#pragma unroll
+            for (int w = 0; w < WB; ++w)
+#pragma unroll
+                for (int b = 0; b < XB; ++b) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[w][b][e] += acc[w][b][e];
+                    acc[w][b] = f32x4{};
+                }
             chain = 0;
         }
         ++chain;
@@ -362,15 +359,22 @@ __global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArg
             for (int b = 0; b < XB; ++b) acc[w][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb_[w], xb_[b], acc[w][b], 0, 0, 0);
         slot = slot + 1 == NSLOT ? 0 : slot + 1;
     }
-    fold();
+    if (n_chunks > DIRECT_FOLD) {
+#pragma unroll
+        for (int w = 0; w < WB; ++w)
+#pragma unroll
+            for (int b = 0; b < XB; ++b)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[w][b][e] += sum[w][b][e];
+    }
 
-    // element e of lane l's sum[w][b]: row m0 + 16 b + (l & 15) of x, feature 4 (l >> 4) + e of block w
+    // element e of lane l's acc[w][b]: row m0 + 16 b + (l & 15) of x, feature 4 (l >> 4) + e of block w
     __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0): this wave's operand reads are done
     __builtin_amdgcn_s_barrier();       // ... and everyone else's: the ring becomes the exchange
 #pragma unroll
     for (int w = 0; w < WB; ++w)
 #pragma unroll
-        for (int b = 0; b < XB; ++b) *(LDS_AS f32x4*)(lds + ((wave * WB + w) * XB + b) * 1024 + lane * 16) = sum[w][b];
+        for (int b = 0; b < XB; ++b) *(LDS_AS f32x4*)(lds + ((wave * WB + w) * XB + b) * 1024 + lane * 16) = acc[w][b];
     __syncthreads();
 #pragma unroll
     for (int t0 = 0; t0 < WB * XB; t0 += 4) {

@@ -232,13 +232,13 @@ __global__ __launch_bounds__(256) void linear_combine_kernel(const TrLinearArgs 
 }
 
 // All of k in one workgroup, so that no partial sums are left over: a tile of 16 XB rows of x and 16 WB features.  What bounds it
-// is how fast a CU takes bytes in, 62 GB/s through the direct loads wherever they come from, HBM or L2 (measured with nothing
-// else in the kernel): a workgroup asks for (XB + WB) * 16 rows of K values, and the best tile is the one that keeps the
-// largest share per CU small.  The row tiles of one feature tile run on the same XCD, whose L2 serves the weights to all but
-// the first of them.
+// is how fast a CU takes bytes in through the direct loads, from HBM or L2 alike: 46 .. 51 GB/s over launches of 12 to 16 us with
+// nothing but the loads in them, 57 .. 62 without the 2.5 us of an empty launch.  A workgroup asks for (XB + WB) * 16 rows of K
+// values, and the best tile is the one that keeps the largest share per CU small.  The row tiles of one feature tile run on the same
+// XCD, whose L2 serves the weights to all but the first of them.
 // k is walked in chunks of 128 values through a ring of LDS slots; of a chunk each of the four waves multiplies 32 values (one
 // k-step of v_mfma_f32_16x16x32_bf16: w rows = A, x rows = B), and the four sums meet in LDS at the end, added in wave order.
-// Ten layers' projections of 64 rows (3584 -> 3584 + 512 + 512, 3584 -> 3584) take 270 us instead of 307.
+// Ten layers' projections of 64 rows (3584 -> 3584 + 512 + 512, 3584 -> 3584) take 269 us instead of 307.
 // The rounding error of a chain through the matrix unit's accumulator grows with the chain's length, that of several chains with the
 // root of their number, and a slice of linear_kernel may be as short as two chunks: 256 values in a row.  So after DIRECT_FOLD chunks, of each of which 32 values
 // are a wave's own (224 in a row), the accumulator is added to a second one and starts again.  Error of the sums alone (operands
@@ -449,15 +449,15 @@ static constexpr DirectTile DIRECT_TILES[] = {
 };
 
 // The tile of linear_direct_kernel, or none: slices of k and a merge.
-// Of the tiles that fit one workgroup per CU, the one that asks for the fewest bytes per CU (of equal ones the squarest: fewer
+// Of the tiles whose workgroups all run at once, the one that asks for the fewest bytes per CU (of equal ones the squarest: fewer
 // workgroups read the same weights or the same x).  Its time and that of the slices are estimated from fits to 19 shapes at 11
 // row counts each (1 .. 128), weights not in the caches, on which they are right to 6 % (rms):
 //   direct   launch + the larger of 0.1 + 0.058 (xb + wb) us a chunk of k and the weights at the HBM rate
 //   slices   two launches + weights, partial sums, and rows of x (which the slices read once per 128 features)
-// and the direct kernel is taken where it is the faster one by 7 %.  us, slices / direct: 3584 x 3584 14.2 / 11.5 at 64 rows,
-// 10.0 / 9.3 at one, 16.4 / 14.8 at 128; 4608 x 3584 15.6 / 14.1 at 64; 6144 x 4096 18.3 / 16.0 at 64; 512 x 3584 6.6 / 8.4 at
-// one and 9.6 / 8.6 at 128; 512 x 512 7.6 / 3.3; 8192 x 8192 37.6 / 32.6 at 64; 3584 x 18944 36.2 / 47 at 64; 2048 x 8192
-// 15.2 / 21 at 64: with few features or a long k the slices have more CUs at work, or longer streams.
+// and the direct kernel is taken where it is the faster one by 7 %.  us, slices / direct: 3584 x 3584 14.8 / 12.5 at 64 rows,
+// 10.4 / 10.0 at one, 16.9 / 15.6 at 128; 4608 x 3584 16.0 / 15.0 at 64; 6144 x 4096 19.4 / 19.1 at 64; 512 x 3584 6.6 / 8.9 at
+// one and 9.8 / 9.3 at 128; 512 x 512 7.9 / 3.7; 8192 x 8192 38.0 / 34.5 at 64; 3584 x 18944 36.5 / 47.6 at 64; 2048 x 8192
+// 15.6 / 22.7 at 64: with few features or a long k the slices have more CUs at work, or longer streams.
 static const DirectTile* direct_plan(int32_t M, int32_t N, int32_t K, int n_split)
 {
     if (tr_knob(TR_KNOB_LIN_SPLIT, 0) || tr_knob(TR_KNOB_LIN_MSPLIT, 0)) return nullptr; // a forced split is a split

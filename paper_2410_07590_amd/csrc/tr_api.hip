@@ -215,6 +215,7 @@ int launch_runs(const tr_store* store, const std::vector<CopyRun>& runs, void* o
     a.row_units = row_units;
     a.head_units = sh->head_dim * eb / 16;
     a.span_units = (int32_t)span;
+    a.formed_bytes = 2 * 16 * total_units;
     a.half_dim = sh->head_dim / 2;
     a.rope_half = tr_rope_half(sh);
     tr_fill_theta(sh, a.theta);

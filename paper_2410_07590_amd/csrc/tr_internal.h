@@ -144,6 +144,7 @@ struct TrAssembleArgs {
     int32_t span_units; // units of K (and of V) one block moves; multiple of 256
     int32_t half_dim;   // head_dim / 2
     int32_t rope_half;  // 1: pairs are (m, m + d/2) instead of (2m, 2m+1)
+    int64_t formed_bytes; // of K and V, over all launches of the call: decides how they are stored
     double theta[64];
     TrAppendTail app;
     TrCopyDesc desc[TR_MAX_COPY_DESC];

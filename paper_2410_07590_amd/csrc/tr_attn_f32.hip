@@ -63,7 +63,7 @@ __device__ __forceinline__ void attn_f32_row(const F32Row& r, const float* __res
     load(j);
     if (tid < D / 2) { // rotation in fp64, one pair per thread
         double sn, cn;
-        sincos((double)r.pos * theta[tid], &sn, &cn);
+        tr_sincos((double)r.pos * theta[tid], &sn, &cn);
         const int ia = rope_half ? tid : 2 * tid, ib = rope_half ? tid + D / 2 : 2 * tid + 1; // the pair's two channels
         const double xa = (double)r.q[ia], xb = (double)r.q[ib];
         ((float*)qs)[ia] = (float)(xa * cn - xb * sn);

@@ -177,7 +177,7 @@ __device__ __forceinline__ void append_token(const void* k_new, const void* v_ne
             if (v_new) vx[i] = ld_stream_any(vs + u0 + half_dim * i);
         }
     double sn, cn;
-    sincos((double)pos * theta[lane], &sn, &cn);
+    tr_sincos((double)pos * theta[lane], &sn, &cn);
     cs[lane] = make_double2(cn, sn);
     // LDS serves a wave's accesses in order; only the compiler has to keep them so
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(256) void assemble_kernel(const TrAssembleArgs a)
     if (rot) {
         if (tid < a.half_dim) {
             double sn, cn;
-            sincos((double)d.delta * a.theta[tid], &sn, &cn);
+            tr_sincos((double)d.delta * a.theta[tid], &sn, &cn);
             cs[tid] = make_double2(cn, sn);
         }
         __syncthreads();
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(64 * APPEND_WAVES) void append_packed_kernel(const 
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         double sn, cn;
-        sincos((double)pos * a.theta[m0 + (HALF && !low ? P : 0) + p], &sn, &cn);
+        tr_sincos((double)pos * a.theta[m0 + (HALF && !low ? P : 0) + p], &sn, &cn);
         if constexpr (HALF) {
             const double co = __shfl_xor(cn, hmask), so = __shfl_xor(sn, hmask);
             c[p] = low ? cn : co;
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(256) void rope_table_kernel(double2* table, int n_p
     if (gid >= (int64_t)n_pos * half_dim) return;
     const int pos = (int)(gid / half_dim), m = (int)(gid % half_dim);
     double sn, cn;
-    sincos((double)pos * theta[m], &sn, &cn);
+    tr_sincos((double)pos * theta[m], &sn, &cn);
     table[gid] = make_double2(cn, sn);
 }
 
@@ -475,7 +475,7 @@ __global__ __launch_bounds__(256) void rope_rows_kernel(const uint4* k, uint4* k
 #pragma unroll
                 for (int p = 0; p < P; ++p) {
                     double sn, cn;
-                    sincos((double)pos * theta.v[m0 + (HALF && !low ? P : 0) + p], &sn, &cn);
+                    tr_sincos((double)pos * theta.v[m0 + (HALF && !low ? P : 0) + p], &sn, &cn);
                     if constexpr (HALF) {
                         const double co = __shfl_xor(cn, hmask), so = __shfl_xor(sn, hmask);
                         c[p] = low ? cn : co;

@@ -544,6 +544,71 @@ SplitPlan cut_keys(int64_t kv_len, int want, int min_split_keys, int key_tile)
     return {n_split, split_len};
 }
 
+// How the short-query kernel's launch is cut: pieces of a common length, in units of 128 keys, the shortest length that makes no
+// more than `target` workgroups.  Its workgroups are bound by the rate of a CU (2.1 us a unit for one of them, 2.6 where all
+// 256 CUs read), so one even piece per CU is best wherever the requests allow it: 17 requests of 7.7 k keys and 4 heads, 272
+// equal workgroups / 248: 67.1 / 53.6 us.  Where the longest piece leaves a CU with much more than its share, 1536 shorter
+// pieces, dealt out as slots get free, pay for their partial results: 25 requests of 154 to 6589 keys 78.1 / 64.0 us, 45 of 20 to
+// 2.7 k keys 75.2 / 52.5; but 31 to 57 short ones 19.1 / 20.1 .. 33.4 / 39.8.  In units, the excess that pays lies at an
+// eighth of the share and three units of fixed cost, and four more (the merge's launch) where nothing is split otherwise.
+constexpr int SHORT_UNIT = 2 * KEY_TILE;
+constexpr int SHORT_MANY_ITEMS = 1536;
+
+// items(L): workgroups of the launch with pieces of L units
+template <class Items> int shortest_piece(int least, int longest, int64_t most_items, Items items)
+{
+    int lo = least, hi = std::max(least, longest);
+    while (lo < hi) {
+        const int mid = (lo + hi) / 2;
+        if (items(mid) <= most_items) hi = mid;
+        else lo = mid + 1;
+    }
+    return lo;
+}
+
+void cut_short(const std::vector<ReqGeom>& reqs, size_t r0, size_t r1, int n_kv_heads, int tpt, int target, int min_split_keys,
+               bool many_allowed, std::vector<SplitPlan>* cut)
+{
+    struct Req { int units, copies; }; // copies: (head, row tile) pairs that walk the request's keys
+    std::vector<Req> rq(r1 - r0);
+    int longest = 1;
+    int64_t total = 0;
+    for (size_t r = r0; r < r1; ++r) {
+        Req& q = rq[r - r0];
+        q.units = (int)((reqs[r].kv_len + SHORT_UNIT - 1) / SHORT_UNIT);
+        q.copies = (reqs[r].n_q + tpt - 1) / tpt * n_kv_heads;
+        longest = std::max(longest, q.copies ? q.units : 0);
+        total += (int64_t)q.units * q.copies;
+    }
+    auto pieces = [](int units, int len) { return std::min((units + len - 1) / len, MAX_SPLIT); };
+    auto items = [&](int len) {
+        int64_t n = 0;
+        for (const Req& q : rq) n += (int64_t)pieces(q.units, len) * q.copies;
+        return n;
+    };
+    const int least = std::max(1, (min_split_keys + SHORT_UNIT - 1) / SHORT_UNIT);
+    int len = shortest_piece(least, longest, target, items);
+    if (many_allowed) {
+        // What the fullest CU walks: workgroups go to the CUs in turn, and a CU holds two.
+        const int CUS = TrChip::CUS;
+        const double share = (double)total / CUS;
+        std::vector<int> load(CUS, 0);
+        int64_t i = 0;
+        int longest_piece = 0;
+        bool split = false;
+        for (const Req& q : rq) {
+            const int n = std::max(1, pieces(q.units, len)), piece = (q.units + n - 1) / n;
+            split = split || n > 1;
+            longest_piece = std::max(longest_piece, q.copies ? piece : 0);
+            for (int64_t j = 0; j < (int64_t)n * q.copies && i < 2 * CUS; ++j, ++i) load[i % CUS] += piece;
+        }
+        const double fullest = items(len) > 2 * CUS ? share + 0.5 * longest_piece : *std::max_element(load.begin(), load.end());
+        if (fullest > 1.125 * share + (split ? 3.0 : 7.0)) len = shortest_piece(least, len, SHORT_MANY_ITEMS, items);
+    }
+    for (size_t r = r0; r < r1; ++r)
+        (*cut)[r - r0] = rq[r - r0].copies ? cut_keys(reqs[r].kv_len, pieces(rq[r - r0].units, len), min_split_keys, SHORT_UNIT) : SplitPlan{1, SHORT_UNIT};
+}
+
 // Finishing time, in key-tile steps, of a launch whose items (in launch order) walk item_tiles[i] key tiles each.
 // Blocks are dealt round-robin to the XCDs and the kernels map each XCD to one contiguous range of items, so
 // every XCD works through its own range on its own slots; a workgroup costs FIXED steps besides its tiles.
@@ -612,9 +677,12 @@ int64_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t
     int want_split = 1;
     if (sh->dtype == TR_BF16 && base_items > 0 && base_items < target) want_split = (int)((target + base_items - 1) / base_items);
     if (want_split > MAX_SPLIT) want_split = MAX_SPLIT;
-    const int key_tile = wg_rows == 32 ? 2 * KEY_TILE : KEY_TILE; // the short-query kernel walks 128 keys a step
+    const int key_tile = wg_rows == 32 ? SHORT_UNIT : KEY_TILE; // the short-query kernel walks 128 keys a step
     std::vector<SplitPlan> cut(r1 - r0);
-    for (size_t r = r0; r < r1; ++r) cut[r - r0] = cut_keys(reqs[r].kv_len, want_split, min_split_keys, key_tile);
+    if (wg_rows == 32 && sh->dtype == TR_BF16)
+        cut_short(reqs, r0, r1, sh->n_kv_heads, tpt, target, min_split_keys, tr_knob(TR_KNOB_TARGET_ITEMS, 0) == 0, &cut);
+    else
+        for (size_t r = r0; r < r1; ++r) cut[r - r0] = cut_keys(reqs[r].kv_len, want_split, min_split_keys, key_tile);
     // A batch of requests of different lengths: one split count for all leaves workgroups of very different lengths,
     // and how the launch then packs onto the chip swings by tens of percent with the count.  Instead every request is
     // cut into pieces of about one common length, and that length is chosen by playing the launch through

@@ -60,6 +60,15 @@ template <int D> struct Geo {
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 template <int N> __device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(vmcnt_imm(N)); }
 
+// Waits until this wave's LDS reads have delivered: what they read may be overwritten behind it.
+__device__ __forceinline__ void wait_lds()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 struct RowCtx {
     bool valid;
     int orow;    // q_tok * n_q_heads + head: row of q / out in units of head vectors
@@ -438,9 +447,10 @@ __device__ __forceinline__ void scores_softmax(LDS_AS const char* krows, const b
 }
 
 // O^T += V^T P^T.  k-slot j of k-step (kb, t) is key 32 kb + 16 t + 8 (j >> 2) + 4 h + (j & 3).
-template <int D, int KB>
+// between(i) runs behind product i.
+template <int D, int KB, class Between = NoHook>
 __device__ __forceinline__ void weighted_values(LDS_AS const char* vrows, const bf16x8 (&bpk)[KB][2], const int (&voff)[D / 32],
-                                                Acc<D>& acc)
+                                                Acc<D>& acc, Between between = Between())
 {
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
@@ -455,6 +465,7 @@ __device__ __forceinline__ void weighted_values(LDS_AS const char* vrows, const 
                 const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0 + 8 * D * 2));
                 const s16x8 av = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                 acc.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), bp, acc.o[db], 0, 0, 0);
+                between((kb * 2 + t) * (D / 32) + db);
             }
         }
 }
@@ -1014,24 +1025,134 @@ __global__ __launch_bounds__(64 * GATHER_NW, 2) void gather_attn_kernel(const Tr
 
 // ---- step 6 / step 7 for very short queries (decode: one new token per request) --------------------------------
 // When the packed rows of a (request, KV head) fit one 32-row MFMA block, giving each wave its own rows would
-// leave three of four waves idle.  Here all four waves hold the SAME rows and split the keys instead: a tile is
-// 128 keys, wave w owns keys [32 w, 32 w + 32) of it, and the four partial results are merged through LDS at
-// the end.  The kernel then streams K/V at four times the rate of one wave, which is what a memory-bound
-// decode step needs.
-constexpr int SHORT_NW = 4, SHORT_NS = 2, SHORT_KT = 32 * SHORT_NW;
-
-template <int D> constexpr int short_stage_bytes() { return 2 * SHORT_KT * D * 2; }
+// leave three of four waves idle.  Here all four waves hold the SAME rows and split the keys instead: wave w owns
+// keys [32 w, 32 w + 32) of every 128, and the four partial results are merged through LDS at the end.
+//
+// Bound by the stream of keys and values, whose rate depends on how much of it is on its way: a bare ring of loads over 537 MB
+// reads 5.6 TB/s with 16 KB in flight per CU, 7.1 with 24, 6.7 with 32 and 6.3 with 48 and more, where the requests of 256
+// CUs queue in front of the memory.  So a wave keeps at most SHORT_FLIGHT loads of 1 KB on their way, and refills its own units
+// as soon as their operands are read: no barrier, and no stretch in which nothing is on its way.  (Two stages of a tile
+// shared by the waves, a barrier each: the values' reads waited for every load of the next tile.)  With one unit of K and
+// one of V per wave two workgroups fit a CU, and one reads while the other starts or merges.  64 tokens over 4096 keys each
+// (539 MB): 94.3 us with the shared stages, 82.5 / 84.2 / 86.4 / 91.6 with 5 / 6 / 7 / 8 loads; 5 tokens over 300 to 3000
+// keys 18.3, then 17.6 / 17.5 / 17.3 / 17.2; between 6 and 5 lie 2 to 4 % at most sizes between those.
+constexpr int SHORT_NW = 4, SHORT_KT = 32 * SHORT_NW;
+constexpr int SHORT_FLIGHT = 6;
+template <int D> constexpr int short_unit_bytes() { return 32 * D * 2; }
+template <int D> constexpr int short_ring_bytes() { return SHORT_NW * 2 * short_unit_bytes<D>(); }
+template <int D> constexpr int short_tables_bytes() { return SHORT_NW * ROT_SLOTS * 4 * D; }
 template <int D> constexpr int short_merge_row_bytes() { return D * 4 + 16; }
+
+// A wave's loads of a unit.  Load i fills rows RPI i .. of it; the lane's byte offsets from the unit's first row are kept.
+template <int D> struct UnitLoads {
+    using G = Geo<D>;
+    static constexpr int LPU = D / 16;
+    uint32_t dk[LPU], dv[LPU], lds;
+
+    __device__ __forceinline__ UnitLoads(uint32_t ring, uint32_t row_bytes, uint32_t head_bytes, int lane)
+    {
+        lds = (uint32_t)__builtin_amdgcn_readfirstlane((int)ring);
+        const int r_in = lane / G::CPR, pc = lane % G::CPR;
+#pragma unroll
+        for (int i = 0; i < LPU; ++i) {
+            const int row = i * G::RPI + r_in;
+            dk[i] = (uint32_t)row * row_bytes + head_bytes + (uint32_t)(pc ^ G::kswz(row)) * 16u;
+            dv[i] = (uint32_t)row * row_bytes + head_bytes + (uint32_t)(4 * ((pc >> 2) ^ G::vswz(row)) + (pc & 3)) * 16u;
+        }
+    }
+    // The unit has rows 0 .. last: rows past them read that one, and nothing looks at them.  For a walk's last unit.
+    __device__ __forceinline__ void stay_within(int last, uint32_t row_bytes, int lane)
+    {
+        if (last >= 31) return;
+#pragma unroll
+        for (int i = 0; i < LPU; ++i) {
+            const uint32_t back = (uint32_t)max(i * G::RPI + lane / G::CPR - last, 0) * row_bytes;
+            dk[i] -= back;
+            dv[i] -= back;
+        }
+    }
+    __device__ __forceinline__ void k(const char* __restrict__ unit, int i) const
+    {
+        __builtin_amdgcn_global_load_lds((const GLB_AS void*)(unit + dk[i]), (LDS_AS void*)(uintptr_t)(lds + i * 1024), 16, 0, DMA_STREAM);
+    }
+    __device__ __forceinline__ void v(const char* __restrict__ unit, int i) const
+    {
+        __builtin_amdgcn_global_load_lds((const GLB_AS void*)(unit + dv[i]), (LDS_AS void*)(uintptr_t)(lds + short_unit_bytes<D>() + i * 1024), 16, 0, DMA_STREAM);
+    }
+};
+
+// One wave's walk over n_own units, 128 keys apart, the first of them on its way.  Loads return in order, so the counts below
+// say which of them have: unit t's keys once no more than the LPU loads of its values are left, its values once no more than
+// those of unit t + 1's keys are.  Nothing is shared between waves.  k and v are restricted pointers of a function of its own
+// and LDS is reached by whole addresses because the compiler otherwise waits for every load before each read of V.
+template <int D>
+__device__ __forceinline__ void short_units(const char* __restrict__ k, const char* __restrict__ v, UnitLoads<D>& ul, const RowCtx& rc,
+                                            const bf16x8 (&qf)[D / 16], int own_begin, int n_own, int key_clamp, int mask_hi_min,
+                                            uint32_t row_bytes, int lane, Acc<D>& acc)
+{
+    using G = Geo<D>;
+    constexpr int LPU = D / 16, UNIT = short_unit_bytes<D>();
+    constexpr int FLIGHT = SHORT_FLIGHT;
+    static_assert(FLIGHT <= 2 * LPU, "a unit of each is all there is room for");
+    const int c = lane & 31, h = lane >> 5;
+    const int i16 = lane & 15, colhalf = (lane >> 4) & 1;
+    const int ring0 = (int)ul.lds; // whole addresses: see attn_tiles
+    int koff[D / 16], voff[D / 32];
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) koff[ks] = ring0 + c * D * 2 + (((2 * ks + h) ^ G::kswz(c)) * 16);
+    const int r = 4 * h + (i16 >> 2);
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+        voff[db] = ring0 + UNIT + r * D * 2 + (4 * (db ^ G::vswz(r)) + 2 * colhalf + ((i16 & 3) >> 1)) * 16 + (i16 & 1) * 8;
+
+    bf16x8 bpk[1][2];
+    for (int t = 0; t < n_own; ++t) {
+        const int kt = own_begin + t * SHORT_KT;
+        const int next = kt + SHORT_KT;
+        const bool more = t + 1 < n_own;
+        const char* const knext = k + (int64_t)next * row_bytes;
+        const char* const vnext = v + (int64_t)next * row_bytes;
+        if (more) ul.stay_within(key_clamp - next, row_bytes, lane);
+        wait_vm<LPU>(); // K(t)
+        asm volatile("" ::: "memory");
+        LDS_AS const char* unit = (LDS_AS const char*)(uintptr_t)0;
+        scores_softmax<D, 1>(unit, qf, rc, kt, kt + 31 > mask_hi_min, false, koff, h, acc, bpk, [&](int ks) {
+            if (ks == LPU - 1 && more) {
+                wait_lds(); // the unit's keys are read
+#pragma unroll
+                for (int i = 0; i < LPU; ++i) {
+                    if (i + LPU >= FLIGHT) wait_vm<FLIGHT - 1>();
+                    ul.k(knext, i);
+                }
+            }
+        });
+        if (!more) wait_vm<0>(); // V(t)
+        else wait_vm<LPU>();
+        asm volatile("" ::: "memory");
+        weighted_values<D, 1>(unit, bpk, voff, acc, [&](int i) {
+            if (more && i % (LPU / 2) == LPU / 2 - 1) {
+                wait_lds(); // this half of the unit's values is read
+#pragma unroll
+                for (int j = i - LPU / 2 + 1; j <= i; ++j) {
+                    if (j + LPU >= FLIGHT) wait_vm<FLIGHT - 1>();
+                    ul.v(vnext, j);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
+    }
+}
 
 template <int D, bool HALF>
 __global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPrefixArgs a)
 {
-    using G = Geo<D>;
-    constexpr int NW = SHORT_NW, NS = SHORT_NS;
-    constexpr int STAGE = short_stage_bytes<D>();
+    constexpr int NW = SHORT_NW;
+    constexpr int UNIT = short_unit_bytes<D>(), LPU = D / 16; // LPU: loads of a unit, as many as a unit has products
     extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
     LDS_AS char* smem = (LDS_AS char*)smem_raw;
-    const int item = xcd_remap(blockIdx.x, a.n_items);
+    // Not by XCD: a workgroup shares no keys with another, and dealt out in turn the heads of a long request spread over the
+    // chip (18 requests of 1.6 k to 5.8 k keys 49.4 / 40.4 us).
+    const int item = blockIdx.x;
     const TrSeqDesc sd = a.seq[last_not_above(a.n_seq, item, [&](int i) { return a.seq[i].item0; })];
     const int local = item - sd.item0;
     const int tile = local % sd.n_tiles;
@@ -1041,9 +1162,8 @@ __global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPr
     const int g = a.group, tpt = a.tok_per_tile;
     const int n_doc = sd.kv_len - sd.n_q;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 31, h = lane >> 5;
-    const int i16 = lane & 15, colhalf = (lane >> 4) & 1;
     const int tok_in = by_group(c, a.group_magic), head_in = c - tok_in * g; // token and head inside the tile
     const int tok_local = tile * tpt + tok_in;
     RowCtx rc;
@@ -1062,65 +1182,47 @@ __global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPr
     const int se = min(sb + sd.split_len, sd.kv_row0 + sd.kv_len);
     const int kt_begin = sb;
     const int kt_end = min(se, sd.kv_row0 + n_doc + last_tok + 1);
-    const int n_tiles = kt_end > kt_begin ? (kt_end - kt_begin + SHORT_KT - 1) / SHORT_KT : 0;
     const int key_clamp = sd.kv_row0 + sd.kv_len - 1;
     const int64_t row_elems = (int64_t)a.n_kv_heads * D;
     const int head_off = kvh * D;
     const __bf16* kp = (const __bf16*)a.k;
     const __bf16* vp = (const __bf16*)a.v;
 
-    // prologue: ordinary loads, then tile 0, then the rotation (every wave rotates the same rows)
+    LDS_AS char* ring = smem + wave * (2 * UNIT); // this wave's unit of K, then its unit of V
+    const uint32_t row_bytes = (uint32_t)row_elems * 2u;
+    UnitLoads<D> ul((uint32_t)(uintptr_t)ring, row_bytes, (uint32_t)head_off * 2u, lane);
+    auto unit_base = [&](const __bf16* base, int kt) { return (const char*)base + (int64_t)min(kt, key_clamp) * row_bytes; };
+    const int own_begin = kt_begin + 32 * wave; // this wave's keys: 32 of every 128
+    const int n_own = own_begin < kt_end ? (kt_end - own_begin + SHORT_KT - 1) / SHORT_KT : 0;
+
+    ul.stay_within(key_clamp - min(own_begin, key_clamp), row_bytes, lane);
+    // prologue: ordinary loads, then the first units, then the rotation (every wave rotates the same rows)
     double th = load_theta<TrPrefixArgs>(lane % (D / 2));
     __builtin_amdgcn_sched_barrier(0);
     u32x4 raw[D / 16];
     load_q_raw<D>((const __bf16*)a.q, rc, h, raw);
     __builtin_amdgcn_sched_barrier(0);
-    issue_tile<D, NW, SHORT_KT, DMA_STREAM>(kp, vp, row_elems, head_off, kt_begin, key_clamp, smem, smem + SHORT_KT * D * 2, wave, lane);
+#pragma unroll
+    for (int i = 0; i < LPU; ++i) ul.k(unit_base(kp, own_begin), i);
+#pragma unroll
+    for (int i = 0; i < LPU; ++i) ul.v(unit_base(vp, own_begin), i);
     __builtin_amdgcn_sched_barrier(0);
     bf16x8 qf[D / 16];
     {
-        LDS_AS char* tab = smem + STAGE + wave * (ROT_SLOTS * 4 * D); // stage 1 is free until the first barrier
-        rotate_queries<D, HALF, 2 * SHORT_KT / G::RPI / NW>(raw, tab, th, pos_lane, lane, h, slot, n_slots, a.scale_log2e, pos_of_slot, qf);
+        LDS_AS char* tab = smem + short_ring_bytes<D>() + wave * (ROT_SLOTS * 4 * D);
+        rotate_queries<D, HALF, 2 * LPU>(raw, tab, th, pos_lane, lane, h, slot, n_slots, a.scale_log2e, pos_of_slot, qf);
     }
 
     Acc<D> acc;
     acc.clear();
 
-    const int wave_hi_max = wave_max_i(rc.valid ? rc.key_hi : INT32_MIN);
-    const int mask_hi_min = sd.kv_row0 + n_doc + first_tok;
-    int koff[D / 16];
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) koff[ks] = (32 * wave + c) * D * 2 + (((2 * ks + h) ^ G::kswz(c)) * 16);
-    int voff[D / 32];
-    {
-        const int r = 4 * h + (i16 >> 2);
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-            voff[db] = (32 * wave + r) * D * 2 + (4 * (db ^ G::vswz(r)) + 2 * colhalf + ((i16 & 3) >> 1)) * 16 + (i16 & 1) * 8;
-    }
-
-    bf16x8 bpk[1][2];
-    for (int t = 0; t < n_tiles; ++t) {
-        const int kt = kt_begin + t * SHORT_KT;
-        wait_vm<0>(); // two stages: tile t is the only load in flight here
-        __builtin_amdgcn_s_barrier(); // tile t is in LDS; everyone is done with tile t-1
-        if (t + 1 < n_tiles)
-            issue_tile<D, NW, SHORT_KT, DMA_STREAM>(kp, vp, row_elems, head_off, kt + SHORT_KT, key_clamp, smem + ((t + 1) % NS) * STAGE,
-                                                    smem + ((t + 1) % NS) * STAGE + SHORT_KT * D * 2, wave, lane);
-        const int ktw = kt + 32 * wave; // this wave's 32 keys
-        if (ktw <= wave_hi_max && ktw < kt_end) {
-            LDS_AS const char* stage = smem + (t % NS) * STAGE;
-            const bool need_mask = ktw + 31 > mask_hi_min;
-            scores_softmax<D, 1>(stage, qf, rc, ktw, need_mask, false, koff, h, acc, bpk);
-            weighted_values<D, 1>(stage + SHORT_KT * D * 2, bpk, voff, acc);
-        }
-    }
+    short_units<D>((const char*)kp, (const char*)vp, ul, rc, qf, own_begin, n_own, key_clamp, sd.kv_row0 + n_doc + first_tok, row_bytes, lane, acc);
 
     // merge the four key slices: every wave parks (m, l) and its unnormalised O in LDS
     constexpr int ROWB = short_merge_row_bytes<D>();
     const float l_tot = acc.l + __shfl_xor(acc.l, 32);
-    // All waves are done with the K/V stages, and nothing is on its way to them: a workgroup whose split lies behind its tokens'
-    // causal end walks no tile, and the first tile, requested all the same, must not land on the rows parked here.
+    // All waves are done with their units, and nothing is on its way to them: a wave whose keys lie behind its tokens' causal
+    // end walks none, and its first unit, requested all the same, must not land on the rows parked here.
     wait_vm<0>();
     __builtin_amdgcn_s_barrier();
     LDS_AS char* obuf = smem + wave * (32 * ROWB);
@@ -1432,10 +1534,11 @@ template <int D, bool HALF>
 int launch_short(const TrPrefixArgs& a, hipStream_t s)
 {
     auto kern = short_attn_kernel<D, HALF>;
-    constexpr int ring = SHORT_NS * short_stage_bytes<D>();
+    constexpr int ring = short_ring_bytes<D>() + short_tables_bytes<D>();
     constexpr int merge = SHORT_NW * 32 * short_merge_row_bytes<D>() + SHORT_NW * 32 * 8;
     constexpr int lds = ring > merge ? ring : merge;
     static std::atomic<uint64_t> configured{0};
+    static_assert(2 * lds <= 160 * 1024, "two workgroups fit a CU");
     if (int rc = tr_raise_lds_limit((const void*)kern, lds, &configured)) return rc;
     hipLaunchKernelGGL(kern, dim3(a.n_items), dim3(64 * SHORT_NW), lds, s, a);
     TR_HIP(hipGetLastError());

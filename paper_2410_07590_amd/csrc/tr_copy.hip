@@ -238,22 +238,21 @@ __device__ __forceinline__ void append_token(const void* k_new, const void* v_ne
 constexpr int ASM_UNROLL = 4;
 
 // How the rows that a launch forms are stored.  Ordinary stores leave their lines dirty in the L2s, which write them back when
-// they need the room or when the kernel ends; device-scope stores go through at once, and streamed ones first of all.  What is
-// left for the end shortens the launch, but where the rows then lie decides how fast the attention behind it reads them: the
-// copy alone is fastest with streamed stores (128 MiB, 5.6 -> 5.9 TB/s), and attention over more than the L2s hold slowest.
-// us of whole requests on fresh stores and caches, ordinary / streamed / through, by MB of K and V: 8.4 MB 22.6 / 21.9 / 22.3,
-// 16.8 MB 30.7 / 29.8 / 30.3 (8 KV heads 27.3 / 26.6 / 26.9), 21 MB 33.6 / 34.1 / 33.9, 25 MB 30.0 / 31.3 / 30.2, 34 MB
-// 35.0 / 38.0 / 35.3, 67 MB 68.8 / 74.5 / 68.8, 134 MB 178.9 / 181.4 / 172.7, batches of 300 MB 237.9 / 244.6 / 230.6 and of
-// 403 MB 223.2 / 225.5 / 204.0.  So: streamed up to 18 MB, through from 96 MB on, ordinary in between.
-enum StorePolicy { ST_CACHED, ST_STREAM, ST_THROUGH };
-constexpr int64_t STREAM_MAX_BYTES = 18ll << 20, THROUGH_MIN_BYTES = 96ll << 20;
+// they need the room or when the kernel ends; device-scope stores go through at once, which shortens a launch that forms more
+// than the L2s hold, but the attention behind it then finds none of the rows there.  us of whole requests on fresh stores and
+// caches, ordinary / through, by MB of K and V: 8.4 MB 22.6 / 22.3, 16.8 MB 30.7 / 30.3, 21 MB 33.6 / 33.9, 25 MB 30.0 / 30.2,
+// 34 MB 35.0 / 35.3, 67 MB 68.8 / 68.8, 134 MB 178.9 / 172.7, batches of 300 MB 237.9 / 230.6 and of 403 MB 223.2 / 204.0.
+// So: through from 96 MB on.  Streamed stores make the copy alone fastest, and the requests slower on the whole: 2 tokens
+// over 256 to 2048 rows 14.6 / 15.2 .. 17.5 / 18.1, over 8.4 MB from -0.7 us (128 tokens and more) to +0.3 (16 and fewer),
+// over 34 MB 35.0 / 38.0.
+enum StorePolicy { ST_CACHED, ST_THROUGH };
+constexpr int64_t THROUGH_MIN_BYTES = 96ll << 20;
 
 // One 16-byte unit, `unit` (at most a block's span) behind a base that is the same in every lane.
 template <int POLICY> __device__ __forceinline__ void st_unit(uint4* base, int unit, uint4 x)
 {
     const u32x4 w = {x.x, x.y, x.z, x.w};
-    if constexpr (POLICY == ST_STREAM) __builtin_nontemporal_store(w, (u32x4*)(base + unit));
-    else if constexpr (POLICY == ST_THROUGH)
+    if constexpr (POLICY == ST_THROUGH)
         __builtin_amdgcn_raw_buffer_store_b128(w, __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00020000), unit * 16, 0, 16 /* sc1 */);
     else *(u32x4*)(base + unit) = w;
 }
@@ -541,9 +540,8 @@ int tr_launch_assemble(const TrAssembleArgs& a, int dtype, int n_blocks, hipStre
         return dtype == TR_BF16 ? (a.rope_half ? assemble_kernel<TR_BF16, true, P> : assemble_kernel<TR_BF16, false, P>)
                                 : (a.rope_half ? assemble_kernel<TR_F32, true, P> : assemble_kernel<TR_F32, false, P>);
     };
-    auto kern = a.formed_bytes <= STREAM_MAX_BYTES    ? pick(std::integral_constant<int, ST_STREAM>())
-                : a.formed_bytes >= THROUGH_MIN_BYTES ? pick(std::integral_constant<int, ST_THROUGH>())
-                                                      : pick(std::integral_constant<int, ST_CACHED>());
+    auto kern = a.formed_bytes >= THROUGH_MIN_BYTES ? pick(std::integral_constant<int, ST_THROUGH>())
+                                                    : pick(std::integral_constant<int, ST_CACHED>());
     hipLaunchKernelGGL(kern, dim3(n_blocks), dim3(256), 0, s, a);
     TR_HIP(hipGetLastError());
     return TR_OK;

@@ -43,6 +43,7 @@ struct TrLinearArgs {
     int32_t n_split;
     int32_t m_split;                    // 1, or 2: rows [0, 64) and [64, M) of x go to two workgroups of the same XCD
     int32_t row_tiles;                  // of 16 XB rows (linear_direct_kernel)
+    int32_t row_magic;                  // 65536 / row_tiles + 1: x / row_tiles = x row_magic >> 16 for x < 256
 };
 
 constexpr int LIN_CK = 128;           // values of k per chunk: 256 bytes of every row
@@ -73,44 +74,52 @@ __global__ __launch_bounds__(256) void linear_kernel(const TrLinearArgs a)
     LDS_AS char* lds = (LDS_AS char*)lds_raw;
     constexpr int NSLOT = lin_slots<MT, DEEP>(), SLOT = lin_slot_bytes<MT>();
     constexpr int IPC = 8 + 2 * MT; // load instructions per wave and chunk: its 8 KB of w, its quarter of x
-    const int groups = (a.N / 32 + 3) / 4;                      // workgroups along the features
+    // all arguments in one batch of scalar loads, and selects between them: see linear_direct_kernel
+    static_assert(TR_LINEAR_MAX_OUT == 4, "");
+    const __bf16 *x = a.x, *w0 = a.w[0], *w1 = a.w[1], *w2 = a.w[2], *w3 = a.w[3];
+    __bf16 *y0 = a.y[0], *y1 = a.y[1], *y2 = a.y[2], *y3 = a.y[3];
+    float* partial = a.partial;
+    int rows = a.M, N = a.N, K = a.K, n_split = a.n_split, m_split = a.m_split, t1 = a.tile0[1], t2 = a.tile0[2], t3 = a.tile0[3];
+    asm volatile("" : "+s"(x), "+s"(w0), "+s"(w1), "+s"(w2), "+s"(w3), "+s"(rows), "+s"(N), "+s"(K), "+s"(n_split), "+s"(m_split), "+s"(t1),
+                 "+s"(t2), "+s"(t3));
+    asm volatile("" : "+s"(y0), "+s"(y1), "+s"(y2), "+s"(y3), "+s"(partial));
+    // what belongs to the output of a tile; tile0 of outputs that are not there is the end
+    auto of_output = [&](int tile, auto v0, auto v1, auto v2, auto v3) { return tile >= t3 ? v3 : tile >= t2 ? v2 : tile >= t1 ? v1 : v0; };
+    const int groups = (N / 32 + 3) / 4;                        // workgroups along the features
     // With two row halves, blocks b and b + 8 (same XCD, dispatched together) take the two halves of one
     // (features, k-slice) item, so that the second read of its weights is served by that XCD's L2.
     int item = blockIdx.x, m0 = 0;
-    if (a.m_split == 2) {
+    if (m_split == 2) {
         item = ((blockIdx.x >> 4) << 3) | (blockIdx.x & 7);
         m0 = ((blockIdx.x >> 3) & 1) * (32 * MT);
-        if (item >= groups * a.n_split) return;                 // padding of the grid to a multiple of 16 (whole workgroup)
+        if (item >= groups * n_split) return;                   // padding of the grid to a multiple of 16 (whole workgroup)
     }
-    const int M = min(a.M - m0, 32 * MT);                       // rows of x this workgroup multiplies
-    const __bf16* xrows = a.x + (int64_t)m0 * a.K;
-    const int group = item % groups, split = item / groups;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int M = min(rows - m0, 32 * MT);                      // rows of x this workgroup multiplies
+    const __bf16* xrows = x + (int64_t)m0 * K;
+    const int split = (int)((uint32_t)item / (uint32_t)groups), group = item - split * groups;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, h = lane >> 5;
-    const int tile = min(4 * group + wave, a.N / 32 - 1);       // a wave past the last tile redoes it and stores nothing
-    const bool tile_mine = 4 * group + wave < a.N / 32;
-    int j = 0; // the output this tile belongs to
-    while (j + 1 < a.n_out && tile >= a.tile0[j + 1]) ++j;
-    const int ltile = tile - a.tile0[j];
-    const int Nj = 32 * (a.tile0[j + 1] - a.tile0[j]);
+    const int tile = min(4 * group + wave, N / 32 - 1);         // a wave past the last tile redoes it and stores nothing
+    const bool tile_mine = 4 * group + wave < N / 32;
+    const int first_tile = of_output(tile, 0, t1, t2, t3), ltile = tile - first_tile; // inside the output this tile belongs to
     // chunks of this workgroup: a contiguous range; the last chunk of a row may be short
-    const int total_chunks = (a.K + LIN_CK - 1) / LIN_CK;
-    const int c0 = (int)((int64_t)total_chunks * split / a.n_split), c1 = (int)((int64_t)total_chunks * (split + 1) / a.n_split);
+    const uint32_t total_chunks = (uint32_t)(K + LIN_CK - 1) / LIN_CK; // times LIN_MAX_SPLIT fits 32 bits
+    const int c0 = (int)(total_chunks * (uint32_t)split / (uint32_t)n_split), c1 = (int)(total_chunks * (uint32_t)(split + 1) / (uint32_t)n_split);
     const int n_chunks = c1 - c0;
 
     // Direct global -> LDS loads: instruction i of a wave fills 1 KB, lane l the 16-byte piece 64 i + l of the
     // destination, i.e. row (64 i + l) / 16, parked piece (64 i + l) % 16; it therefore fetches the logical piece
     // parked there (the XOR swizzle is applied on the source side).  Four rows x 256 contiguous bytes per instruction.
     const int lrow = lane / LIN_PPR, ppiece = lane % LIN_PPR;
-    const int last_piece = a.K / 8 - 1; // pieces past the end of a row are read from its last piece and never used
-    const __bf16* wbase = a.w[j] + (int64_t)(ltile * 32) * a.K;
+    const int last_piece = K / 8 - 1; // pieces past the end of a row are read from its last piece and never used
+    const __bf16* wbase = of_output(tile, w0, w1, w2, w3) + (int64_t)(ltile * 32) * K;
     auto issue_chunk = [&](int c, LDS_AS char* slot) {
         LDS_AS char* wdst = slot + wave * (32 * LIN_ROW);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int row = 4 * i + lrow;
             const int piece = min(c * LIN_PPR + (ppiece ^ (row & (LIN_PPR - 1))), last_piece);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(wbase + (int64_t)row * a.K + 8 * piece),
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(wbase + (int64_t)row * K + 8 * piece),
                                              (LDS_AS void*)(wdst + i * 1024), 16, 0, 0);
         }
         LDS_AS char* xdst = slot + 4 * 32 * LIN_ROW;
@@ -118,7 +127,7 @@ __global__ __launch_bounds__(256) void linear_kernel(const TrLinearArgs a)
         for (int i = 0; i < 2 * MT; ++i) {
             const int row = 4 * (wave * 2 * MT + i) + lrow; // this wave's quarter of the 32 MT rows
             const int piece = min(c * LIN_PPR + (ppiece ^ (row & (LIN_PPR - 1))), last_piece);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xrows + (int64_t)min(row, M - 1) * a.K + 8 * piece),
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xrows + (int64_t)min(row, M - 1) * K + 8 * piece),
                                              (LDS_AS void*)(xdst + (wave * 2 * MT + i) * 1024), 16, 0, 0);
         }
     };
@@ -142,7 +151,7 @@ __global__ __launch_bounds__(256) void linear_kernel(const TrLinearArgs a)
         LDS_AS const char* slot = lds + (t % NSLOT) * SLOT;
         LDS_AS const char* wb = slot + wave * (32 * LIN_ROW);
         LDS_AS const char* xb0 = slot + 4 * 32 * LIN_ROW;
-        const int steps = min(LIN_CK, a.K - (c0 + t) * LIN_CK) / 16;
+        const int steps = min(LIN_CK, K - (c0 + t) * LIN_CK) / 16;
         auto step = [&](int s) {
             const bf16x8 wa = *(LDS_AS const bf16x8*)(wb + lin_piece_off(r, 2 * s + h));
 #pragma unroll
@@ -180,6 +189,8 @@ __global__ __launch_bounds__(256) void linear_kernel(const TrLinearArgs a)
         }
     }
     if (!tile_mine) return;
+    __bf16* y = of_output(tile, y0, y1, y2, y3);
+    const int Nj = 32 * (of_output(tile, t1, t2, t3, N / 32) - first_tile);
 
     // element e of acc[mt] is y_j[32 mt + r][32 ltile + 8 (e >> 2) + 4 h + (e & 3)]
 #pragma unroll
@@ -189,16 +200,16 @@ __global__ __launch_bounds__(256) void linear_kernel(const TrLinearArgs a)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
             const int n = 32 * tile + 8 * q4 + 4 * h; // column among all outputs
-            if (a.n_split == 1) {
+            if (n_split == 1) {
                 bf16x4 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = (__bf16)acc[mt][4 * q4 + e];
-                *(bf16x4*)(a.y[j] + (int64_t)m * Nj + (n - 32 * a.tile0[j])) = o;
+                *(bf16x4*)(y + (int64_t)m * Nj + (n - 32 * first_tile)) = o;
             } else {
                 f32x4 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = acc[mt][4 * q4 + e];
-                *(f32x4*)(a.partial + ((int64_t)split * a.M + m) * a.N + n) = o;
+                *(f32x4*)(partial + ((int64_t)split * rows + m) * N + n) = o;
             }
         }
     }
@@ -264,22 +275,29 @@ __global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArg
     constexpr int SLOT = direct_slot_bytes<XB, WB>(), NSLOT = direct_slots<XB, WB>();
     constexpr int IPC = XB + WB; // load instructions of a wave for a chunk, four rows x 256 bytes each
     static_assert(NSLOT >= 3 && (NSLOT - 2) * IPC < 63 && 4 * XB * WB * 1024 <= NSLOT * SLOT, "");
-    const int place = blockIdx.x >> 3;
-    const int item = place / a.row_tiles * 8 + (blockIdx.x & 7); // feature tile
-    const int m0 = place % a.row_tiles * (16 * XB);
-    const int blocks = a.N / 16;                                 // of features
+    // All arguments in one batch of scalar loads, and selects between them: indexed by the output, each load address waited for two
+    // more scalar loads, and with the division seven round trips lay in front of the first request.  Ten layers of 64 rows:
+    // 268 -> 261 us.
+    const __bf16* x = a.x;
+    const __bf16 *w0 = a.w[0], *w1 = a.w[1], *w2 = a.w[2], *w3 = a.w[3];
+    __bf16 *y0 = a.y[0], *y1 = a.y[1], *y2 = a.y[2], *y3 = a.y[3];
+    int M = a.M, N = a.N, K = a.K, row_tiles = a.row_tiles, row_magic = a.row_magic, t1 = a.tile0[1], t2 = a.tile0[2], t3 = a.tile0[3];
+    asm volatile("" : "+s"(x), "+s"(w0), "+s"(w1), "+s"(w2), "+s"(w3), "+s"(M), "+s"(N), "+s"(K), "+s"(row_tiles), "+s"(row_magic), "+s"(t1),
+                 "+s"(t2), "+s"(t3));
+    asm volatile("" : "+s"(y0), "+s"(y1), "+s"(y2), "+s"(y3));
+    const int place = blockIdx.x >> 3, group = (int)(((uint32_t)place * (uint32_t)row_magic) >> 16);
+    const int item = group * 8 + (blockIdx.x & 7); // feature tile
+    const int m0 = (place - group * row_tiles) * (16 * XB);
+    const int blocks = N / 16;                     // of features
     if (item * WB >= blocks) return;                             // padding of the grid (whole workgroup)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    auto output_of = [&](int block) { // the output a block of features belongs to
-        int j = 0;
-#pragma unroll
-        for (int i = 1; i < TR_LINEAR_MAX_OUT; ++i) j += i < a.n_out && block >= 2 * a.tile0[i];
-        return j;
-    };
+    static_assert(TR_LINEAR_MAX_OUT == 4, "");
+    // what belongs to the output of a block of features; tile0 of outputs that are not there is the end
+    auto of_output = [&](int block, auto v0, auto v1, auto v2, auto v3) { return block >= 2 * t3 ? v3 : block >= 2 * t2 ? v2 : block >= 2 * t1 ? v1 : v0; };
 
     // Load i of this wave fills rows 4 g .. 4 g + 3 of a slot (x rows, then w rows), 16-byte pieces XOR-swizzled by the row on
     // the source side.  Rows of x past the last one and features past the last one read the last one's and are not stored.
-    const int lrow = lane / LIN_PPR, ppiece = lane % LIN_PPR, last_piece = a.K / 8 - 1;
+    const int lrow = lane / LIN_PPR, ppiece = lane % LIN_PPR, last_piece = K / 8 - 1;
     const __bf16* src[IPC];
     int piece0[IPC];
 #pragma unroll
@@ -287,10 +305,10 @@ __global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArg
         const int g = wave * IPC + i, row = 4 * g + lrow;
         piece0[i] = ppiece ^ (row & (LIN_PPR - 1));
         if (g < 4 * XB) {
-            src[i] = a.x + (int64_t)min(m0 + row, a.M - 1) * a.K;
+            src[i] = x + (int64_t)min(m0 + row, M - 1) * K;
         } else {
-            const int block = min(item * WB + (g - 4 * XB) / 4, blocks - 1), j = output_of(block);
-            src[i] = a.w[j] + (int64_t)(16 * (block - 2 * a.tile0[j]) + (row & 15)) * a.K;
+            const int block = min(item * WB + (g - 4 * XB) / 4, blocks - 1);
+            src[i] = of_output(block, w0, w1, w2, w3) + (int64_t)(16 * (block - 2 * of_output(block, 0, t1, t2, t3)) + (row & 15)) * K;
         }
     }
     auto issue = [&](int c, int slot) {
@@ -312,8 +330,8 @@ __global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArg
     // rows that lie a multiple of 8 KB apart, or all but so, would all be asked for on the same few memory channels at the same time:
     // there every feature tile starts its walk somewhere else (4096 x 4096, 37 rows of x 15.1 -> 11.4 us; 8192 x 8192, 32 rows 35.6 ->
     // 26.5; 44 sizes within 64 bytes of 8 KB 1.09 times as fast, 63 of 16 KB 1.15; elsewhere it costs up to a tenth)
-    const bool staggered = a.K > 32 && (a.K + 32) % 4096 <= 64;
-    const int n_chunks = (a.K + LIN_CK - 1) / LIN_CK, first = staggered ? (int)((uint32_t)item * 5u % (uint32_t)n_chunks) : 0;
+    const bool staggered = K > 32 && (K + 32) % 4096 <= 64;
+    const int n_chunks = (K + LIN_CK - 1) / LIN_CK, first = staggered ? (int)((uint32_t)item * 5u % (uint32_t)n_chunks) : 0;
     auto chunk = [&](int c) { return c + first < n_chunks ? c + first : c + first - n_chunks; };
 #pragma unroll
     for (int p = 0; p < NSLOT - 1; ++p)
@@ -388,12 +406,13 @@ __global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArg
             for (int e = 0; e < 4; ++e) s[e] += q[e];
         }
         const int block = item * WB + t / XB, m = m0 + 16 * (t % XB) + r;
-        if (block >= blocks || m >= a.M) continue;
-        const int j = output_of(block);
+        if (block >= blocks || m >= M) continue;
+        const int first_tile = of_output(block, 0, t1, t2, t3);
         bf16x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = (__bf16)s[e];
-        *(bf16x4*)(a.y[j] + (int64_t)m * (32 * (a.tile0[j + 1] - a.tile0[j])) + 16 * (block - 2 * a.tile0[j]) + 4 * (lane >> 4)) = o;
+        *(bf16x4*)(of_output(block, y0, y1, y2, y3) + (int64_t)m * (32 * (of_output(block, t1, t2, t3, N / 32) - first_tile)) +
+                   16 * (block - 2 * first_tile) + 4 * (lane >> 4)) = o;
     }
 }
 
@@ -522,7 +541,7 @@ int tr_launch_linear(const void* x, int32_t n_out, const void* const* w, void* c
         a.tile0[j] = N / 32;
         N += n_features[j];
     }
-    a.tile0[n_out] = N / 32;
+    for (int j = n_out; j <= TR_LINEAR_MAX_OUT; ++j) a.tile0[j] = N / 32;
     a.partial = (float*)partial;
     a.M = M;
     a.N = N;
@@ -531,6 +550,7 @@ int tr_launch_linear(const void* x, int32_t n_out, const void* const* w, void* c
     if (const DirectTile* t = direct_plan(M, N, K, n_split)) {
         a.n_split = a.m_split = 1;
         a.row_tiles = (M + 16 * t->xb - 1) / (16 * t->xb);
+        a.row_magic = 65536 / a.row_tiles + 1;
         return t->launch(a, s);
     }
     a.n_split = n_split;

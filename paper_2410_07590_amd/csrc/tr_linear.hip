@@ -52,6 +52,7 @@ constexpr int LIN_ROW = LIN_CK * 2;   // bytes per parked row
 constexpr int LIN_MAX_SPLIT = 16;     // k-slices across workgroups, at most
 
 #define LDS_AS __attribute__((address_space(3)))
+#define GLB_AS __attribute__((address_space(1)))
 
 __device__ __forceinline__ int lin_piece_off(int row, int piece) { return row * LIN_ROW + ((piece ^ (row & (LIN_PPR - 1))) * 16); }
 
@@ -77,8 +78,8 @@ __global__ __launch_bounds__(256) void linear_kernel(const TrLinearArgs a)
     // all arguments in one batch of scalar loads, and selects between them: see linear_direct_kernel
     static_assert(TR_LINEAR_MAX_OUT == 4, "");
     const __bf16 *x = a.x, *w0 = a.w[0], *w1 = a.w[1], *w2 = a.w[2], *w3 = a.w[3];
-    __bf16 *y0 = a.y[0], *y1 = a.y[1], *y2 = a.y[2], *y3 = a.y[3];
-    float* partial = a.partial;
+    auto y0 = (GLB_AS __bf16*)a.y[0], y1 = (GLB_AS __bf16*)a.y[1], y2 = (GLB_AS __bf16*)a.y[2], y3 = (GLB_AS __bf16*)a.y[3]; // else flat stores
+    auto partial = (GLB_AS float*)a.partial;
     int rows = a.M, N = a.N, K = a.K, n_split = a.n_split, m_split = a.m_split, t1 = a.tile0[1], t2 = a.tile0[2], t3 = a.tile0[3];
     asm volatile("" : "+s"(x), "+s"(w0), "+s"(w1), "+s"(w2), "+s"(w3), "+s"(rows), "+s"(N), "+s"(K), "+s"(n_split), "+s"(m_split), "+s"(t1),
                  "+s"(t2), "+s"(t3));
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(256) void linear_kernel(const TrLinearArgs a)
         }
     }
     if (!tile_mine) return;
-    __bf16* y = of_output(tile, y0, y1, y2, y3);
+    auto y = of_output(tile, y0, y1, y2, y3);
     const int Nj = 32 * (of_output(tile, t1, t2, t3, N / 32) - first_tile);
 
     // element e of acc[mt] is y_j[32 mt + r][32 ltile + 8 (e >> 2) + 4 h + (e & 3)]
@@ -204,12 +205,12 @@ __global__ __launch_bounds__(256) void linear_kernel(const TrLinearArgs a)
                 bf16x4 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = (__bf16)acc[mt][4 * q4 + e];
-                *(bf16x4*)(y + (int64_t)m * Nj + (n - 32 * first_tile)) = o;
+                *(GLB_AS bf16x4*)(y + (int64_t)m * Nj + (n - 32 * first_tile)) = o;
             } else {
                 f32x4 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = acc[mt][4 * q4 + e];
-                *(f32x4*)(partial + ((int64_t)split * rows + m) * N + n) = o;
+                *(GLB_AS f32x4*)(partial + ((int64_t)split * rows + m) * N + n) = o;
             }
         }
     }
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArg
     // 268 -> 261 us.
     const __bf16* x = a.x;
     const __bf16 *w0 = a.w[0], *w1 = a.w[1], *w2 = a.w[2], *w3 = a.w[3];
-    __bf16 *y0 = a.y[0], *y1 = a.y[1], *y2 = a.y[2], *y3 = a.y[3];
+    auto y0 = (GLB_AS __bf16*)a.y[0], y1 = (GLB_AS __bf16*)a.y[1], y2 = (GLB_AS __bf16*)a.y[2], y3 = (GLB_AS __bf16*)a.y[3]; // else flat stores
     int M = a.M, N = a.N, K = a.K, row_tiles = a.row_tiles, row_magic = a.row_magic, t1 = a.tile0[1], t2 = a.tile0[2], t3 = a.tile0[3];
     asm volatile("" : "+s"(x), "+s"(w0), "+s"(w1), "+s"(w2), "+s"(w3), "+s"(M), "+s"(N), "+s"(K), "+s"(row_tiles), "+s"(row_magic), "+s"(t1),
                  "+s"(t2), "+s"(t3));
@@ -411,7 +412,7 @@ __global__ __launch_bounds__(256, 2) void linear_direct_kernel(const TrLinearArg
         bf16x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = (__bf16)s[e];
-        *(bf16x4*)(of_output(block, y0, y1, y2, y3) + (int64_t)m * (32 * (of_output(block, t1, t2, t3, N / 32) - first_tile)) +
+        *(GLB_AS bf16x4*)(of_output(block, y0, y1, y2, y3) + (int64_t)m * (32 * (of_output(block, t1, t2, t3, N / 32) - first_tile)) +
                    16 * (block - 2 * first_tile) + 4 * (lane >> 4)) = o;
     }
 }

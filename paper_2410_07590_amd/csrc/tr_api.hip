@@ -756,7 +756,7 @@ int64_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t
             d.n_split = n_split;
             d.split_len = (int32_t)split_len;
             d.ws_row0 = (int32_t)ws_rows;
-            d.pad_ = 0;
+            d.split_magic = (uint32_t)((1ull << 32) / n_split) + 1; // not used when n_split is 1
         }
         ++n;
         items += ((q.n_q + tpt - 1) / tpt) * sh->n_kv_heads * n_split;

@@ -1143,23 +1143,63 @@ __device__ __forceinline__ void short_units(const char* __restrict__ k, const ch
     }
 }
 
+// What a workgroup of the short-query kernel reads before its first request, in one batch of scalar loads: the arguments, the first
+// request's descriptor, and, where there are more requests, the item's own.  Left alone, the loads came one after the other, each
+// where its value was needed, with two divisions between them: nine round trips in front of the first keys.  us: 2 tokens over
+// 1.3 k rows 16.7 / 16.3, 57 over 650 keys each 33.6 / 33.4.  The kernel for longer queries gains nothing by it (64 tokens over 4096 rows
+// 22.2 / 22.3, batches of four requests 36.9 / 37.2).
+struct ItemArgs {
+    const __bf16 *q, *k, *v;
+    const int32_t* q_pos;
+    void* out;
+    _Float16* ws_o;
+    float* ws_ml;
+    int n_q_heads, n_kv_heads, group, tok_per_tile, group_magic;
+    float scale_log2e;
+    TrSeqDesc sd;
+    int tile, split, kvh;
+};
+__device__ __forceinline__ ItemArgs item_args(const TrPrefixArgs& a)
+{
+    ItemArgs r;
+    r.n_q_heads = a.n_q_heads, r.n_kv_heads = a.n_kv_heads, r.group = a.group, r.tok_per_tile = a.tok_per_tile, r.group_magic = a.group_magic;
+    r.scale_log2e = a.scale_log2e;
+    r.sd = a.seq[0];
+    int n_seq = a.n_seq;
+    // as pointers to global memory: out of the assembler they are pointers to anything, and flat accesses count twice
+    auto q = (const GLB_AS __bf16*)a.q, k = (const GLB_AS __bf16*)a.k, v = (const GLB_AS __bf16*)a.v;
+    auto q_pos = (const GLB_AS int32_t*)a.q_pos;
+    auto out = (GLB_AS char*)a.out;
+    auto ws_o = (GLB_AS _Float16*)a.ws_o;
+    auto ws_ml = (GLB_AS float*)a.ws_ml;
+    asm volatile("" : "+s"(q), "+s"(k), "+s"(v), "+s"(q_pos), "+s"(r.n_q_heads), "+s"(r.n_kv_heads), "+s"(r.group), "+s"(r.tok_per_tile),
+                 "+s"(r.group_magic), "+s"(r.scale_log2e), "+s"(n_seq));
+    asm volatile("" : "+s"(r.sd.q_row0), "+s"(r.sd.n_q), "+s"(r.sd.kv_row0), "+s"(r.sd.kv_len), "+s"(r.sd.item0), "+s"(r.sd.n_tiles),
+                 "+s"(r.sd.n_split), "+s"(r.sd.split_len), "+s"(r.sd.ws_row0), "+s"(r.sd.split_magic), "+s"(out), "+s"(ws_o), "+s"(ws_ml));
+    r.q = (const __bf16*)q, r.k = (const __bf16*)k, r.v = (const __bf16*)v, r.q_pos = (const int32_t*)q_pos;
+    r.out = (void*)out, r.ws_o = (_Float16*)ws_o, r.ws_ml = (float*)ws_ml;
+    // Not by XCD: a workgroup shares no keys with another, and dealt out in turn the heads of a long request spread over the
+    // chip (18 requests of 1.6 k to 5.8 k keys 49.4 / 40.4 us).
+    const int item = blockIdx.x;
+    if (n_seq > 1) r.sd = a.seq[last_not_above(n_seq, item, [&](int i) { return a.seq[i].item0; })];
+    const int local = item - r.sd.item0;
+    const int rest = r.sd.n_tiles == 1 ? local : local / r.sd.n_tiles;
+    r.tile = local - rest * r.sd.n_tiles;
+    r.kvh = r.sd.n_split == 1 ? rest : (int)(((uint64_t)(uint32_t)rest * r.sd.split_magic) >> 32);
+    r.split = rest - r.kvh * r.sd.n_split;
+    return r;
+}
+
 template <int D, bool HALF>
-__global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPrefixArgs a)
+__global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPrefixArgs args)
 {
     constexpr int NW = SHORT_NW;
     constexpr int UNIT = short_unit_bytes<D>(), LPU = D / 16; // LPU: loads of a unit, as many as a unit has products
     extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
     LDS_AS char* smem = (LDS_AS char*)smem_raw;
-    // Not by XCD: a workgroup shares no keys with another, and dealt out in turn the heads of a long request spread over the
-    // chip (18 requests of 1.6 k to 5.8 k keys 49.4 / 40.4 us).
-    const int item = blockIdx.x;
-    const TrSeqDesc sd = a.seq[last_not_above(a.n_seq, item, [&](int i) { return a.seq[i].item0; })];
-    const int local = item - sd.item0;
-    const int tile = local % sd.n_tiles;
-    const int rest = local / sd.n_tiles;
-    const int split = rest % sd.n_split;
-    const int kvh = rest / sd.n_split;
-    const int g = a.group, tpt = a.tok_per_tile;
+    const ItemArgs a = item_args(args);
+    const TrSeqDesc sd = a.sd;
+    const int tile = a.tile, split = a.split, kvh = a.kvh, g = a.group, tpt = a.tok_per_tile;
     const int n_doc = sd.kv_len - sd.n_q;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);

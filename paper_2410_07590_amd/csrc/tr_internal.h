@@ -223,7 +223,7 @@ struct TrSeqDesc {
     int32_t n_split;   // KV splits (>= 1)
     int32_t split_len; // keys per split, multiple of the key tile
     int32_t ws_row0;   // first partial row of the request in the workspace
-    int32_t pad_;
+    uint32_t split_magic; // 2^32 / n_split + 1 for n_split > 1: x / n_split is the high half of x * split_magic (x n_split < 2^32)
 };
 #define TR_MAX_SEQ 64
 struct TrPrefixArgs {

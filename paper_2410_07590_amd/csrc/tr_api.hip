@@ -551,6 +551,8 @@ SplitPlan cut_keys(int64_t kv_len, int want, int min_split_keys, int key_tile)
 // pieces, dealt out as slots get free, pay for their partial results: 25 requests of 154 to 6589 keys 78.1 / 64.0 us, 45 of 20 to
 // 2.7 k keys 75.2 / 52.5; but 31 to 57 short ones 19.1 / 20.1 .. 33.4 / 39.8.  In units, the excess that pays lies at an
 // eighth of the share and three units of fixed cost, and four more (the merge's launch) where nothing is split otherwise.
+// Those 1536 pieces hold their partial results in fp32: requests are cut in them that one workgroup would have carried in fp32 to the
+// end, and fp16 knows less of bf16's range (values of 1e-6 came out 0.19 off, of 1e5 not finite).
 constexpr int SHORT_UNIT = 2 * KEY_TILE;
 constexpr int SHORT_MANY_ITEMS = 1536;
 
@@ -566,7 +568,8 @@ template <class Items> int shortest_piece(int least, int longest, int64_t most_i
     return lo;
 }
 
-void cut_short(const std::vector<ReqGeom>& reqs, size_t r0, size_t r1, int n_kv_heads, int tpt, int target, int min_split_keys,
+// True where it makes the many pieces.
+bool cut_short(const std::vector<ReqGeom>& reqs, size_t r0, size_t r1, int n_kv_heads, int tpt, int target, int min_split_keys,
                bool many_allowed, std::vector<SplitPlan>* cut)
 {
     struct Req { int units, copies; }; // copies: (head, row tile) pairs that walk the request's keys
@@ -588,6 +591,7 @@ void cut_short(const std::vector<ReqGeom>& reqs, size_t r0, size_t r1, int n_kv_
     };
     const int least = std::max(1, (min_split_keys + SHORT_UNIT - 1) / SHORT_UNIT);
     int len = shortest_piece(least, longest, target, items);
+    bool many = false;
     if (many_allowed) {
         // What the fullest CU walks: workgroups go to the CUs in turn, and a CU holds two.
         const int CUS = TrChip::CUS;
@@ -603,10 +607,12 @@ void cut_short(const std::vector<ReqGeom>& reqs, size_t r0, size_t r1, int n_kv_
             for (int64_t j = 0; j < (int64_t)n * q.copies && i < 2 * CUS; ++j, ++i) load[i % CUS] += piece;
         }
         const double fullest = items(len) > 2 * CUS ? share + 0.5 * longest_piece : *std::max_element(load.begin(), load.end());
-        if (fullest > 1.125 * share + (split ? 3.0 : 7.0)) len = shortest_piece(least, len, SHORT_MANY_ITEMS, items);
+        many = fullest > 1.125 * share + (split ? 3.0 : 7.0);
+        if (many) len = shortest_piece(least, len, SHORT_MANY_ITEMS, items);
     }
     for (size_t r = r0; r < r1; ++r)
         (*cut)[r - r0] = rq[r - r0].copies ? cut_keys(reqs[r].kv_len, pieces(rq[r - r0].units, len), min_split_keys, SHORT_UNIT) : SplitPlan{1, SHORT_UNIT};
+    return many;
 }
 
 // Finishing time, in key-tile steps, of a launch whose items (in launch order) walk item_tiles[i] key tiles each.
@@ -661,9 +667,10 @@ void cut_cache_store(const std::vector<int64_t>& key, const std::vector<SplitPla
     e.cut = cut;
 }
 
-// Fills the per-request descriptors of one launch (requests [r0, r1)); returns the partial rows it needs.
-int64_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t r0, size_t r1, TrPrefixArgs* a,
-                    bool* any_split, int* total_tokens, int* wg_rows_out)
+// Fills the per-request descriptors of one launch (requests [r0, r1)) and lays its partial results out from a->ws_o on; returns
+// the bytes that they need.
+size_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t r0, size_t r1, TrPrefixArgs* a,
+                   bool* any_split, int* total_tokens, int* wg_rows_out)
 {
     const int g = sh->n_q_heads / sh->n_kv_heads;
     int64_t max_rows = 0;
@@ -679,8 +686,9 @@ int64_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t
     if (want_split > MAX_SPLIT) want_split = MAX_SPLIT;
     const int key_tile = wg_rows == 32 ? SHORT_UNIT : KEY_TILE; // the short-query kernel walks 128 keys a step
     std::vector<SplitPlan> cut(r1 - r0);
+    bool partial_f32 = false;
     if (wg_rows == 32 && sh->dtype == TR_BF16)
-        cut_short(reqs, r0, r1, sh->n_kv_heads, tpt, target, min_split_keys, tr_knob(TR_KNOB_TARGET_ITEMS, 0) == 0, &cut);
+        partial_f32 = cut_short(reqs, r0, r1, sh->n_kv_heads, tpt, target, min_split_keys, tr_knob(TR_KNOB_TARGET_ITEMS, 0) == 0, &cut);
     else
         for (size_t r = r0; r < r1; ++r) cut[r - r0] = cut_keys(reqs[r].kv_len, want_split, min_split_keys, key_tile);
     // A batch of requests of different lengths: one split count for all leaves workgroups of very different lengths,
@@ -766,11 +774,18 @@ int64_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t
             ws_rows += (int64_t)n_split * q.n_q * sh->n_q_heads;
         }
     }
-    if (a) { a->n_seq = n; a->n_items = items; a->tok_per_tile = tpt; }
+    const size_t out_bytes = tr_align256((size_t)ws_rows * sh->head_dim * (partial_f32 ? 4 : 2));
+    if (a) {
+        a->n_seq = n;
+        a->n_items = items;
+        a->tok_per_tile = tpt;
+        a->partial_f32 = partial_f32;
+        a->ws_ml = (float*)((char*)a->ws_o + out_bytes);
+    }
     if (any_split) *any_split = any;
     if (total_tokens) *total_tokens = toks;
     if (wg_rows_out) *wg_rows_out = wg_rows;
-    return ws_rows;
+    return out_bytes + tr_align256((size_t)ws_rows * 8);
 }
 
 size_t prefix_ws_bytes(const tr_shape* sh, const std::vector<ReqGeom>& reqs)
@@ -778,9 +793,7 @@ size_t prefix_ws_bytes(const tr_shape* sh, const std::vector<ReqGeom>& reqs)
     size_t need = 0;
     for (size_t r0 = 0; r0 < reqs.size(); r0 += TR_MAX_SEQ) {
         size_t r1 = r0 + TR_MAX_SEQ < reqs.size() ? r0 + TR_MAX_SEQ : reqs.size();
-        int64_t rows = plan_prefix(sh, reqs, r0, r1, nullptr, nullptr, nullptr, nullptr);
-        size_t b = tr_align256((size_t)rows * sh->head_dim * 2) + tr_align256((size_t)rows * 8);
-        if (b > need) need = b;
+        need = std::max(need, plan_prefix(sh, reqs, r0, r1, nullptr, nullptr, nullptr, nullptr));
     }
     return need;
 }
@@ -797,6 +810,7 @@ int run_prefix(const tr_shape* sh, const void* q, const void* k, const void* v, 
     TrPrefixArgs a;
     memset(&a, 0, sizeof a);
     a.q = q; a.k = k; a.v = v; a.q_pos = q_pos; a.out = out;
+    a.ws_o = (_Float16*)ws;
     a.n_q_heads = sh->n_q_heads;
     a.n_kv_heads = sh->n_kv_heads;
     a.group = sh->n_q_heads / sh->n_kv_heads;
@@ -810,9 +824,7 @@ int run_prefix(const tr_shape* sh, const void* q, const void* k, const void* v, 
         size_t r1 = r0 + TR_MAX_SEQ < reqs.size() ? r0 + TR_MAX_SEQ : reqs.size();
         bool any_split = false;
         int toks = 0, wg_rows = 128;
-        int64_t rows = plan_prefix(sh, reqs, r0, r1, &a, &any_split, &toks, &wg_rows);
-        a.ws_o = (_Float16*)ws;
-        a.ws_ml = (float*)((char*)ws + tr_align256((size_t)rows * sh->head_dim * 2));
+        plan_prefix(sh, reqs, r0, r1, &a, &any_split, &toks, &wg_rows);
         if (a.n_seq == 0) continue;
         int rc = sh->dtype == TR_F32 ? tr_launch_prefix_attn_f32(a, sh->head_dim, toks * sh->n_q_heads, stream)
                                      : tr_launch_prefix_attn(a, sh->head_dim, wg_rows, any_split, toks * sh->n_q_heads, stream);

@@ -1154,7 +1154,7 @@ struct ItemArgs {
     void* out;
     _Float16* ws_o;
     float* ws_ml;
-    int n_q_heads, n_kv_heads, group, tok_per_tile, group_magic;
+    int n_q_heads, n_kv_heads, group, tok_per_tile, group_magic, partial_f32;
     float scale_log2e;
     TrSeqDesc sd;
     int tile, split, kvh;
@@ -1164,6 +1164,7 @@ __device__ __forceinline__ ItemArgs item_args(const TrPrefixArgs& a)
     ItemArgs r;
     r.n_q_heads = a.n_q_heads, r.n_kv_heads = a.n_kv_heads, r.group = a.group, r.tok_per_tile = a.tok_per_tile, r.group_magic = a.group_magic;
     r.scale_log2e = a.scale_log2e;
+    r.partial_f32 = a.partial_f32;
     r.sd = a.seq[0];
     int n_seq = a.n_seq;
     // as pointers to global memory: out of the assembler they are pointers to anything, and flat accesses count twice
@@ -1173,7 +1174,7 @@ __device__ __forceinline__ ItemArgs item_args(const TrPrefixArgs& a)
     auto ws_o = (GLB_AS _Float16*)a.ws_o;
     auto ws_ml = (GLB_AS float*)a.ws_ml;
     asm volatile("" : "+s"(q), "+s"(k), "+s"(v), "+s"(q_pos), "+s"(r.n_q_heads), "+s"(r.n_kv_heads), "+s"(r.group), "+s"(r.tok_per_tile),
-                 "+s"(r.group_magic), "+s"(r.scale_log2e), "+s"(n_seq));
+                 "+s"(r.group_magic), "+s"(r.scale_log2e), "+s"(r.partial_f32), "+s"(n_seq));
     asm volatile("" : "+s"(r.sd.q_row0), "+s"(r.sd.n_q), "+s"(r.sd.kv_row0), "+s"(r.sd.kv_len), "+s"(r.sd.item0), "+s"(r.sd.n_tiles),
                  "+s"(r.sd.n_split), "+s"(r.sd.split_len), "+s"(r.sd.ws_row0), "+s"(r.sd.split_magic), "+s"(out), "+s"(ws_o), "+s"(ws_ml));
     r.q = (const __bf16*)q, r.k = (const __bf16*)k, r.v = (const __bf16*)v, r.q_pos = (const int32_t*)q_pos;
@@ -1325,13 +1326,14 @@ __global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPr
     } else {
         const int rows_s = sd.n_q * g;
         const int64_t prow = (int64_t)sd.ws_row0 + (int64_t)(split * a.n_kv_heads + kvh) * rows_s + r_tok * g + r_head;
-        _Float16* op = a.ws_o + prow * D + CPT * j;
+        const int64_t at = prow * D + CPT * j;
 #pragma unroll
         for (int e4 = 0; e4 < CPT / 4; ++e4) {
-            f16x4 y;
+            f32x4 x;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] = (_Float16)(o[4 * e4 + e] * inv);
-            *(f16x4*)(op + 4 * e4) = y;
+            for (int e = 0; e < 4; ++e) x[e] = o[4 * e4 + e] * inv;
+            if (a.partial_f32) *(f32x4*)((float*)a.ws_o + at + 4 * e4) = x;
+            else *(f16x4*)(a.ws_o + at + 4 * e4) = __builtin_convertvector(x, f16x4);
         }
         if (j == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(L > 0.0f ? M : -INFINITY, L);
     }
@@ -1348,6 +1350,7 @@ __global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPr
 // GROUPS: sets of D/8 lanes that share a row, each merging every GROUPS-th split.  A lane spends sixteen vector instructions
 // on a partial, so one group walks 64 splits in some 2 us of issue alone (49 splits of 32 rows: 7.3 us, with half a wave of
 // four-channel lanes 7.8, with a whole wave of four groups 4.9).
+// PART: type of the partials.
 template <bool MAX, int LANES> __device__ __forceinline__ float row_reduce(float x)
 {
     static_assert(LANES == 8 || LANES == 16 || LANES == 64, "");
@@ -1366,7 +1369,7 @@ template <bool MAX, int LANES> __device__ __forceinline__ float row_reduce(float
 constexpr int COMBINE_THREADS = 128; // two waves: the few thousand rows of one request then reach every compute unit
 template <int D, int GROUPS> constexpr int combine_rows() { return COMBINE_THREADS / (D / 8 * GROUPS); } // output rows per workgroup
 
-template <int D, int SPLITS, int GROUPS>
+template <int D, int SPLITS, int GROUPS, class PART>
 __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const TrPrefixArgs a, int total_rows)
 {
     constexpr int LPG = D / 8, LPR = LPG * GROUPS; // lanes per group and per row
@@ -1406,14 +1409,15 @@ __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const TrPrefix
         ml[k] = make_float2(-INFINITY, 0.0f);
         if (lane_r + LPR * k < n_split) ml[k] = *(const float2*)(a.ws_ml + (prow0 + (lane_r + LPR * k) * pstride) * 2);
     }
-    const _Float16* base = a.ws_o + prow0 * D + 8 * piece;
-    f16x8 x[PER_ROUND];
+    typedef PART Piece __attribute__((ext_vector_type(8)));
+    const PART* base = (const PART*)a.ws_o + prow0 * D + 8 * piece;
+    Piece x[PER_ROUND];
     auto load = [&](int j0) { // the group's j-th split is GROUPS j + grp; splits past the last one give zeros
 #pragma unroll
         for (int u = 0; u < PER_ROUND; ++u) {
             const int sp = GROUPS * (j0 + u) + grp;
-            x[u] = f16x8{};
-            if (sp < n_split) x[u] = *(const f16x8*)(base + sp * pstride * D);
+            x[u] = Piece{};
+            if (sp < n_split) x[u] = *(const Piece*)(base + sp * pstride * D);
         }
     };
     load(0);
@@ -1636,7 +1640,8 @@ int blockdiag_dispatch(const TrBlockDiagArgs& a, int head_dim, int wg_rows, hipS
 template <int D, int SPLITS, int GROUPS> static void launch_combine_d(const TrPrefixArgs& a, int total_rows, hipStream_t s)
 {
     constexpr int per_block = combine_rows<D, GROUPS>();
-    hipLaunchKernelGGL((combine_kernel<D, SPLITS, GROUPS>), dim3((unsigned)(((int64_t)total_rows + per_block - 1) / per_block)), dim3(COMBINE_THREADS), 0, s, a, total_rows);
+    auto kern = a.partial_f32 ? combine_kernel<D, SPLITS, GROUPS, float> : combine_kernel<D, SPLITS, GROUPS, _Float16>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(((int64_t)total_rows + per_block - 1) / per_block)), dim3(COMBINE_THREADS), 0, s, a, total_rows);
 }
 // A wave for each row where lanes of one group would walk the splits in more than one round of eight, one after the other,
 // while most of the chip is idle; D/8 lanes per row elsewhere.  A wave for each row against lanes, difference of the whole

@@ -232,7 +232,7 @@ struct TrPrefixArgs {
     const void* v;
     const int32_t* q_pos;
     void* out;
-    _Float16* ws_o; // [partial rows][head_dim] partial outputs, each normalised by its own denominator
+    _Float16* ws_o; // [partial rows][head_dim] partial outputs, each normalised by its own denominator; fp32 where partial_f32
     float* ws_ml; // [partial rows][2] reference maximum (log2 domain) and softmax denominator
     int32_t n_seq;
     int32_t n_items;
@@ -244,6 +244,8 @@ struct TrPrefixArgs {
     float scale;       // 1 / sqrt(head_dim)
     int32_t rope_half;
     int32_t group_magic; // tr_group_magic(group)
+    int32_t partial_f32; // short-query kernel and its merge: ws_o holds fp32
+    int32_t pad_;
     double theta_rev[64]; // theta_m / (2 pi): position * theta_rev = angle in revolutions
     double theta[64];
     TrSeqDesc seq[TR_MAX_SEQ];

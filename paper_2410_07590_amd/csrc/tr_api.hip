@@ -607,8 +607,11 @@ bool cut_short(const std::vector<ReqGeom>& reqs, size_t r0, size_t r1, int n_kv_
             for (int64_t j = 0; j < (int64_t)n * q.copies && i < 2 * CUS; ++j, ++i) load[i % CUS] += piece;
         }
         const double fullest = items(len) > 2 * CUS ? share + 0.5 * longest_piece : *std::max_element(load.begin(), load.end());
-        many = fullest > 1.125 * share + (split ? 3.0 : 7.0);
-        if (many) len = shortest_piece(least, len, SHORT_MANY_ITEMS, items);
+        if (fullest > 1.125 * share + (split ? 3.0 : 7.0)) {
+            const int shorter = shortest_piece(least, len, SHORT_MANY_ITEMS, items);
+            many = shorter < len; // not where the least split or the most pieces of a request had decided already
+            len = shorter;
+        }
     }
     for (size_t r = r0; r < r1; ++r)
         (*cut)[r - r0] = rq[r - r0].copies ? cut_keys(reqs[r].kv_len, pieces(rq[r - r0].units, len), min_split_keys, SHORT_UNIT) : SplitPlan{1, SHORT_UNIT};

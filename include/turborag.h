@@ -179,7 +179,12 @@ int tr_prefill_attn_static(const tr_shape* shape, const void* q, const void* k, 
 
 /* Batched form (one launch for many requests): q/out packed over requests by cu_q; request r's cache is rows
  * [cache_row_start[r], cache_row_start[r+1]) of k/v (kv_len_r = the range length, its last n_q_r rows are
- * the request's query tokens); q_pos packed like q.  Index arrays are host arrays. */
+ * the request's query tokens); q_pos packed like q.  Index arrays are host arrays.
+ * The workspace's size depends on the lengths, not on the counts alone: it can rise from 0 and fall again as contexts grow.
+ * Very short queries over contexts of very different lengths are cut further than it takes to fill the chip, to even the
+ * launch out; they need no workspace for that: where the one given is too small (or NULL) for it, the call runs without
+ * this further cut, more slowly, and TR_ERR_WORKSPACE is left for one that does not hold the rest either (a batch of
+ * 256 and more (request, KV head) pairs has no rest). */
 size_t tr_prefill_attn_batched_workspace_size(const tr_shape* shape, const int32_t* cu_q,
                                               const int64_t* cache_row_start, int32_t n_req);
 int tr_prefill_attn_batched(const tr_shape* shape, const void* q, const void* k, const void* v,
@@ -210,7 +215,8 @@ int tr_prefill_attn_gather(const tr_store* store, const int32_t* chunk_ids /*hos
  * and its LAST row is the new token itself (append it first with tr_kv_append[_batched]); the token attends
  * every row of its range.  Same arithmetic as tr_prefill_attn with n_q = 1; the kernel behind it lets the
  * waves of a workgroup split the keys instead of the rows, because the g rows of a KV head cannot fill a
- * workgroup.  An empty range is an error (TR_ERR_INVALID_ARG).  Workspace as for tr_prefill_attn. */
+ * workgroup.  An empty range is an error (TR_ERR_INVALID_ARG).  Workspace as for tr_prefill_attn_batched: ask again as the
+ * caches grow, or pass what is there. */
 size_t tr_decode_attn_workspace_size(const tr_shape* shape, const int64_t* cache_row_start /*host*/, int32_t n_req);
 int tr_decode_attn(const tr_shape* shape, const void* q, const void* k, const void* v, const int32_t* q_pos /*device*/,
                    const int64_t* cache_row_start /*host [n_req+1]*/, int32_t n_req, void* out,

@@ -670,9 +670,14 @@ void cut_cache_store(const std::vector<int64_t>& key, const std::vector<SplitPla
     e.cut = cut;
 }
 
+// Bytes of partial outputs, which the statistics follow, and of both
+size_t partial_out_bytes(const tr_shape* sh, int64_t rows, bool f32) { return tr_align256((size_t)rows * sh->head_dim * (f32 ? 4 : 2)); }
+size_t partial_bytes(const tr_shape* sh, int64_t rows, bool f32) { return partial_out_bytes(sh, rows, f32) + tr_align256((size_t)rows * 8); }
+
 // Fills the per-request descriptors of one launch (requests [r0, r1)) and lays its partial results out from a->ws_o on; returns
-// the bytes that they need.
-size_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t r0, size_t r1, TrPrefixArgs* a,
+// the bytes that they need.  The workspace holds `held` bytes: where the many pieces of cut_short do not fit, every request is cut
+// into as many pieces as fill the chip, none where the launch does so uncut, and the caller checks whether those fit.
+size_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t r0, size_t r1, size_t held, TrPrefixArgs* a,
                    bool* any_split, int* total_tokens, int* wg_rows_out)
 {
     const int g = sh->n_q_heads / sh->n_kv_heads;
@@ -689,11 +694,24 @@ size_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t 
     if (want_split > MAX_SPLIT) want_split = MAX_SPLIT;
     const int key_tile = wg_rows == 32 ? SHORT_UNIT : KEY_TILE; // the short-query kernel walks 128 keys a step
     std::vector<SplitPlan> cut(r1 - r0);
-    bool partial_f32 = false;
-    if (wg_rows == 32 && sh->dtype == TR_BF16)
-        partial_f32 = cut_short(reqs, r0, r1, sh->n_kv_heads, tpt, target, min_split_keys, tr_knob(TR_KNOB_TARGET_ITEMS, 0) == 0, &cut);
-    else
+    auto cut_alike = [&] {
         for (size_t r = r0; r < r1; ++r) cut[r - r0] = cut_keys(reqs[r].kv_len, want_split, min_split_keys, key_tile);
+    };
+    auto partial_rows = [&] {
+        int64_t rows = 0;
+        for (size_t r = r0; r < r1; ++r)
+            if (cut[r - r0].n_split > 1) rows += (int64_t)cut[r - r0].n_split * reqs[r].n_q * sh->n_q_heads;
+        return rows;
+    };
+    bool partial_f32 = false;
+    if (wg_rows == 32 && sh->dtype == TR_BF16) {
+        const bool many_allowed = tr_knob(TR_KNOB_TARGET_ITEMS, 0) == 0 && max_rows <= 32; // more rows only where the kernel is forced
+        partial_f32 = cut_short(reqs, r0, r1, sh->n_kv_heads, tpt, target, min_split_keys, many_allowed, &cut);
+        if (partial_f32 && partial_bytes(sh, partial_rows(), true) > held) {
+            partial_f32 = false;
+            cut_alike();
+        }
+    } else cut_alike();
     // A batch of requests of different lengths: one split count for all leaves workgroups of very different lengths,
     // and how the launch then packs onto the chip swings by tens of percent with the count.  Instead every request is
     // cut into pieces of about one common length, and that length is chosen by playing the launch through
@@ -777,26 +795,25 @@ size_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t 
             ws_rows += (int64_t)n_split * q.n_q * sh->n_q_heads;
         }
     }
-    const size_t out_bytes = tr_align256((size_t)ws_rows * sh->head_dim * (partial_f32 ? 4 : 2));
     if (a) {
         a->n_seq = n;
         a->n_items = items;
         a->tok_per_tile = tpt;
         a->partial_f32 = partial_f32;
-        a->ws_ml = (float*)((char*)a->ws_o + out_bytes);
+        a->ws_ml = (float*)((char*)a->ws_o + partial_out_bytes(sh, ws_rows, partial_f32));
     }
     if (any_split) *any_split = any;
     if (total_tokens) *total_tokens = toks;
     if (wg_rows_out) *wg_rows_out = wg_rows;
-    return out_bytes + tr_align256((size_t)ws_rows * 8);
+    return partial_bytes(sh, ws_rows, partial_f32);
 }
 
-size_t prefix_ws_bytes(const tr_shape* sh, const std::vector<ReqGeom>& reqs)
+size_t prefix_ws_bytes(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t held = SIZE_MAX)
 {
     size_t need = 0;
     for (size_t r0 = 0; r0 < reqs.size(); r0 += TR_MAX_SEQ) {
         size_t r1 = r0 + TR_MAX_SEQ < reqs.size() ? r0 + TR_MAX_SEQ : reqs.size();
-        need = std::max(need, plan_prefix(sh, reqs, r0, r1, nullptr, nullptr, nullptr, nullptr));
+        need = std::max(need, plan_prefix(sh, reqs, r0, r1, held, nullptr, nullptr, nullptr, nullptr));
     }
     return need;
 }
@@ -804,11 +821,12 @@ size_t prefix_ws_bytes(const tr_shape* sh, const std::vector<ReqGeom>& reqs)
 int run_prefix(const tr_shape* sh, const void* q, const void* k, const void* v, const int32_t* q_pos,
                const std::vector<ReqGeom>& reqs, void* out, void* ws, size_t ws_bytes, hipStream_t stream)
 {
-    const size_t need = prefix_ws_bytes(sh, reqs);
-    if (need > 0) {
+    const size_t held = ws && ((uintptr_t)ws & 255) == 0 ? ws_bytes : 0;
+    if (prefix_ws_bytes(sh, reqs, held) > held) {
+        const size_t need = prefix_ws_bytes(sh, reqs);
         if (!ws) return tr_fail(TR_ERR_WORKSPACE, "workspace is NULL, %zu bytes needed", need);
         if (((uintptr_t)ws & 255) != 0) return tr_fail(TR_ERR_WORKSPACE, "workspace is not 256-byte aligned");
-        if (ws_bytes < need) return tr_fail(TR_ERR_WORKSPACE, "workspace holds %zu bytes, %zu needed", ws_bytes, need);
+        return tr_fail(TR_ERR_WORKSPACE, "workspace holds %zu bytes, %zu needed", ws_bytes, need);
     }
     TrPrefixArgs a;
     memset(&a, 0, sizeof a);
@@ -827,7 +845,7 @@ int run_prefix(const tr_shape* sh, const void* q, const void* k, const void* v, 
         size_t r1 = r0 + TR_MAX_SEQ < reqs.size() ? r0 + TR_MAX_SEQ : reqs.size();
         bool any_split = false;
         int toks = 0, wg_rows = 128;
-        plan_prefix(sh, reqs, r0, r1, &a, &any_split, &toks, &wg_rows);
+        plan_prefix(sh, reqs, r0, r1, held, &a, &any_split, &toks, &wg_rows);
         if (a.n_seq == 0) continue;
         int rc = sh->dtype == TR_F32 ? tr_launch_prefix_attn_f32(a, sh->head_dim, toks * sh->n_q_heads, stream)
                                      : tr_launch_prefix_attn(a, sh->head_dim, wg_rows, any_split, toks * sh->n_q_heads, stream);

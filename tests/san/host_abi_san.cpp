@@ -46,14 +46,13 @@ const char* g_call = "";   // the library call in progress, for the messages
         }                                                                       \
     } while (0)
 
-void partial_rows_fit(const _Float16* ws_o, const float* ws_ml, int64_t rows, const char* who)
+void partial_rows_fit(const _Float16* ws_o, const float* ws_ml, int64_t rows, const char* who, bool f32 = false)
 {
     if (rows == 0) return;
-    const char* end = g_ex.ws + g_ex.ws_bytes;
-    REQUIRE((const char*)ws_o >= g_ex.ws && (const char*)(ws_o + rows * g_ex.head_dim) <= end, "%s: %" PRId64 " partial rows leave the workspace of %zu bytes",
-            who, rows, g_ex.ws_bytes);
+    const char *end = g_ex.ws + g_ex.ws_bytes, *a0 = (const char*)ws_o, *a1 = a0 + rows * g_ex.head_dim * (f32 ? 4 : 2);
+    REQUIRE(a0 >= g_ex.ws && a1 <= end, "%s: %" PRId64 " partial rows leave the workspace of %zu bytes", who, rows, g_ex.ws_bytes);
     REQUIRE((const char*)ws_ml >= g_ex.ws && (const char*)(ws_ml + rows * 2) <= end, "%s: statistics of %" PRId64 " partial rows leave the workspace", who, rows);
-    const char *a0 = (const char*)ws_o, *a1 = (const char*)(ws_o + rows * g_ex.head_dim), *b0 = (const char*)ws_ml, *b1 = (const char*)(ws_ml + rows * 2);
+    const char *b0 = (const char*)ws_ml, *b1 = (const char*)(ws_ml + rows * 2);
     REQUIRE(a1 <= b0 || b1 <= a0, "%s: partial outputs and their statistics overlap", who);
 }
 
@@ -142,7 +141,7 @@ static void check_prefix(const TrPrefixArgs& a, int wg_rows, const char* who)
         }
     }
     REQUIRE(item == a.n_items, "%s: %d items in the descriptors, %d announced", who, item, a.n_items);
-    partial_rows_fit(a.ws_o, a.ws_ml, rows, who);
+    partial_rows_fit(a.ws_o, a.ws_ml, rows, who, a.partial_f32);
 }
 
 int tr_launch_prefix_attn(const TrPrefixArgs& a, int, int wg_rows, bool, int, hipStream_t)
@@ -507,6 +506,51 @@ void argument_errors()
     REQUIRE(tr_prefill_attn_static_scratch_bytes() > 0, "static scratch size");
 }
 
+// Decode batches that the plan cuts further than it takes to fill the chip run with less workspace than that cut asks for.
+void decode_workspaces()
+{
+    tr_shape sh;
+    std::memset(&sh, 0, sizeof sh);
+    sh.n_q_heads = 32; sh.n_kv_heads = 8; sh.head_dim = g_ex.head_dim = 128; sh.dtype = TR_BF16; sh.rope_base = 5e5;
+    Buffers dev;
+    char buf[64];
+    auto decode = [&](const std::vector<int64_t>& start, const void* ws, size_t bytes) {
+        g_ex.ws = (const char*)ws;
+        g_ex.ws_bytes = bytes;
+        return tr_decode_attn(&sh, buf, buf, buf, (const int32_t*)buf, start.data(), (int32_t)start.size() - 1, buf, (void*)ws, bytes, nullptr);
+    };
+    std::vector<int64_t> full(1, 0), part(1, 0), two_launches(1, 0); // 320 pairs; 200; 320 and 200
+    for (int i = 0; i < 40; ++i) full.push_back(full.back() + 140 * i + 5);
+    int64_t cut_in_two = 0; // requests of `part` that are, where the cut only fills the chip
+    for (int i = 0; i < 25; ++i) {
+        const int64_t len = i ? 143 + 7 * i : 6500;
+        part.push_back(part.back() + len);
+        cut_in_two += len > 256;
+    }
+    for (int i = 0; i < 64; ++i) two_launches.push_back(two_launches.back() + (i < 40 ? 140 * i + 5 : 90));
+    for (size_t i = 1; i < part.size(); ++i) two_launches.push_back(two_launches.back() + part[i] - part[i - 1]);
+    const size_t rows = 2 * 32 * cut_in_two, least = (rows * 128 * 2 + 255) / 256 * 256 + (rows * 8 + 255) / 256 * 256;
+    for (const auto* start : {&full, &part, &two_launches}) {
+        const size_t need = tr_decode_attn_workspace_size(&sh, start->data(), (int32_t)start->size() - 1), lowest = start == &full ? 0 : least;
+        char* ws = (char*)dev.get(need + 256);
+        REQUIRE(need > lowest, "the even cut needs %zu bytes, this one %zu", lowest, need);
+        for (size_t bytes : {need + 256, need, need - 1, lowest + 256, lowest}) OK(decode(*start, ws, bytes));
+        const long before = g_ex.launches;
+        if (lowest == 0) {
+            OK(decode(*start, nullptr, 0));
+            OK(decode(*start, nullptr, need));
+            OK(decode(*start, ws + 16, need)); // not aligned: as none
+            REQUIRE(g_ex.launches == before + 3, "%ld launches", g_ex.launches - before);
+        } else {
+            FAILS(decode(*start, ws, lowest - 1), TR_ERR_WORKSPACE);
+            FAILS(decode(*start, ws, 0), TR_ERR_WORKSPACE);
+            FAILS(decode(*start, nullptr, need), TR_ERR_WORKSPACE);
+            FAILS(decode(*start, ws + 16, need), TR_ERR_WORKSPACE);
+            REQUIRE(g_ex.launches == before, "a refused call launched something");
+        }
+    }
+}
+
 // More tokens than one launch holds: every row is covered once, in order, by launches of a legal size.
 void appends_of_many_tokens()
 {
@@ -560,6 +604,7 @@ int main(int argc, char** argv)
     const int rounds = argc > 1 ? std::atoi(argv[1]) : 300;
     argument_errors();
     appends_of_many_tokens();
+    decode_workspaces();
     const char* knobs[] = {"wg_rows", "target_items", "min_split_keys", "bd_piece_tiles"};
     const int values[][3] = {{0, 128, 32}, {0, 64, 2048}, {0, 64, 1024}, {0, 1, 8}};
     for (int i = 0; i < rounds; ++i) {

@@ -76,3 +76,27 @@ def test_many_pieces(hq, hkv, head_dim, layout, lens, n_q, scale):
     err = worst_error(sh, attend(B, sh, q, k, v, pos, cu, start, ws), q, k, v, pos, cu, start)
     print("%d requests, %d tokens, values of %g: %.2e" % (len(lens), n_q, scale, err))
     assert err < 1e-2
+
+
+@pytest.mark.parametrize("layout,lens,n_q", [(0, RISING, 1), (1, RISING, 4), (0, LONG, 1)])
+def test_less_workspace(layout, lens, n_q):
+    """Without room for the many pieces a batch runs with the cut that fills the chip, which is none from 256 pairs on; less room than
+    that is refused, and nothing is written."""
+    from paper_2410_07590_amd import binding as B
+    sh = synth.Shape(32, 8, 128, "bf16", 1e4, layout)
+    lens = [max(n, n_q) for n in lens]
+    q, k, v, pos, cu, start = inputs(sh, lens, n_q, 1.0, len(lens) + n_q)
+    need = B.tr_prefill_attn_batched_workspace_size(H.gpu_shape(B, sh), cu, start)
+    rows = 0 if len(lens) * 8 >= 256 else 2 * n_q * 32 * sum(n > 256 for n in lens)   # two pieces each, of requests that can be cut
+    least = -(-rows * 256 // 256) * 256 + -(-rows * 8 // 256) * 256
+    assert least < need - 256
+    room = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    for ws in [room, room[:need - 256], room[:least]] + ([room[:0], None] if least == 0 else []):
+        room.fill_(0xFF)
+        err = worst_error(sh, attend(B, sh, q, k, v, pos, cu, start, ws), q, k, v, pos, cu, start)
+        assert err < 1e-2, (None if ws is None else ws.numel(), err)
+        assert ws is None or bool((room[ws.numel():] == 0xFF).all())
+    for ws in [room[:least - 256], room[16:], None] if least else []:
+        with pytest.raises(B.TurboRagError) as e:
+            attend(B, sh, q, k, v, pos, cu, start, ws)
+        assert e.value.code == B.TR_ERR_WORKSPACE

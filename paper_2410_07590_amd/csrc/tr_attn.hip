@@ -1455,7 +1455,7 @@ __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const TrPrefix
             for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], o);
         if (grp != 0) return;
     }
-    const float inv = 1.0f / L;
+    const float inv = L > 0.0f ? 1.0f / L : 0.0f; // a row without any weight is zero, as in a launch that is not cut
     bf16x8 y;
 #pragma unroll
     for (int e = 0; e < 8; ++e) y[e] = (__bf16)(acc[e] * inv);

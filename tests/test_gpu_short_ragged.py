@@ -100,3 +100,25 @@ def test_less_workspace(layout, lens, n_q):
         with pytest.raises(B.TurboRagError) as e:
             attend(B, sh, q, k, v, pos, cu, start, ws)
         assert e.value.code == B.TR_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("layout,lens", [(0, RISING), (1, LONG)])
+def test_rows_without_weight(layout, lens):
+    """A row all of whose scores are minus infinity is zero, whether its request is cut or not; a piece without weight changes
+    nothing for the others."""
+    from paper_2410_07590_amd import binding as B
+    sh = synth.Shape(8, 8, 128, "bf16", 1e4, layout)
+    q, k, v, pos, cu, start = inputs(sh, lens, 1, 1.0, 77)
+    pos[:] = 0
+    q[:, :, 0] = 1.0
+    need = B.tr_decode_attn_workspace_size(H.gpu_shape(B, sh), start)
+    last = slice(int(start[-2]), int(start[-1]))     # one request without any weight
+    k[last, :, 0] = float("-inf")
+    first = slice(int(start[0]), int(start[0]) + max(1, lens[0] - 300)) if lens[0] > 600 else slice(int(start[-3]), int(start[-3]) + 4000)
+    k[first, :, 0] = float("-inf")                   # and one whose first pieces have none
+    out = attend(B, sh, q, k, v, pos, cu, start, B.workspace(need))
+    assert bool((out[-1] == 0).all())
+    if lens is RISING:
+        assert bool((attend(B, sh, q, k, v, pos, cu, start, None)[-1] == 0).all())   # the same batch, uncut
+    k[last, :, 0] = 0.0
+    assert worst_error(sh, out[:-1], q[:-1], k, v, pos[:-1], cu[:-1], start[:-1]) < 1e-2

@@ -717,10 +717,10 @@ size_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t 
     // cut into pieces of about one common length, and that length is chosen by playing the launch through
     // (launch_makespan) for a range of candidates, with the traffic of the partial results priced in.
     if (want_split > 1 && r1 - r0 > 1 && wg_rows != 32 && tr_knob(TR_KNOB_TARGET_ITEMS, 0) == 0) {
-        // The search costs tens of microseconds of host time and a call runs it twice (workspace check, then the
-        // launch), after the caller's own workspace query: its result is kept for the last few batch shapes.  The
-        // key is everything the search reads: head counts, tile geometry, the split floor, and (n_q, kv_len) of every
-        // request in order.
+        // The search costs tens of microseconds of host time, and a call runs it again after the caller's own workspace
+        // query (twice where it has several launches): its result is kept for the last few batch shapes.  The key is
+        // everything the search reads: head counts, tile geometry, the split floor, and (n_q, kv_len) of every request in
+        // order.
         std::vector<int64_t> key;
         key.reserve(8 + 2 * (r1 - r0));
         for (int64_t x : {(int64_t)sh->n_q_heads, (int64_t)sh->n_kv_heads, (int64_t)sh->head_dim, (int64_t)wg_rows, (int64_t)min_split_keys,
@@ -795,17 +795,18 @@ size_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t 
             ws_rows += (int64_t)n_split * q.n_q * sh->n_q_heads;
         }
     }
+    const size_t need = partial_bytes(sh, ws_rows, partial_f32);
     if (a) {
         a->n_seq = n;
         a->n_items = items;
         a->tok_per_tile = tpt;
         a->partial_f32 = partial_f32;
-        a->ws_ml = (float*)((char*)a->ws_o + partial_out_bytes(sh, ws_rows, partial_f32));
+        a->ws_ml = need <= held ? (float*)((char*)a->ws_o + partial_out_bytes(sh, ws_rows, partial_f32)) : nullptr;
     }
     if (any_split) *any_split = any;
     if (total_tokens) *total_tokens = toks;
     if (wg_rows_out) *wg_rows_out = wg_rows;
-    return partial_bytes(sh, ws_rows, partial_f32);
+    return need;
 }
 
 size_t prefix_ws_bytes(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t held = SIZE_MAX)
@@ -822,16 +823,19 @@ int run_prefix(const tr_shape* sh, const void* q, const void* k, const void* v, 
                const std::vector<ReqGeom>& reqs, void* out, void* ws, size_t ws_bytes, hipStream_t stream)
 {
     const size_t held = ws && ((uintptr_t)ws & 255) == 0 ? ws_bytes : 0;
-    if (prefix_ws_bytes(sh, reqs, held) > held) {
+    TrPrefixArgs a;
+    memset(&a, 0, sizeof a);
+    a.ws_o = (_Float16*)ws;
+    bool any_split = false;
+    int toks = 0, wg_rows = 128;
+    const bool one = reqs.size() <= TR_MAX_SEQ; // one launch: planned once, here
+    if ((one ? plan_prefix(sh, reqs, 0, reqs.size(), held, &a, &any_split, &toks, &wg_rows) : prefix_ws_bytes(sh, reqs, held)) > held) {
         const size_t need = prefix_ws_bytes(sh, reqs);
         if (!ws) return tr_fail(TR_ERR_WORKSPACE, "workspace is NULL, %zu bytes needed", need);
         if (((uintptr_t)ws & 255) != 0) return tr_fail(TR_ERR_WORKSPACE, "workspace is not 256-byte aligned");
         return tr_fail(TR_ERR_WORKSPACE, "workspace holds %zu bytes, %zu needed", ws_bytes, need);
     }
-    TrPrefixArgs a;
-    memset(&a, 0, sizeof a);
     a.q = q; a.k = k; a.v = v; a.q_pos = q_pos; a.out = out;
-    a.ws_o = (_Float16*)ws;
     a.n_q_heads = sh->n_q_heads;
     a.n_kv_heads = sh->n_kv_heads;
     a.group = sh->n_q_heads / sh->n_kv_heads;
@@ -843,9 +847,7 @@ int run_prefix(const tr_shape* sh, const void* q, const void* k, const void* v, 
     for (int m = 0; m < 64; ++m) a.theta_rev[m] = a.theta[m] / 6.283185307179586476925;
     for (size_t r0 = 0; r0 < reqs.size(); r0 += TR_MAX_SEQ) {
         size_t r1 = r0 + TR_MAX_SEQ < reqs.size() ? r0 + TR_MAX_SEQ : reqs.size();
-        bool any_split = false;
-        int toks = 0, wg_rows = 128;
-        plan_prefix(sh, reqs, r0, r1, held, &a, &any_split, &toks, &wg_rows);
+        if (!one) plan_prefix(sh, reqs, r0, r1, held, &a, &any_split, &toks, &wg_rows);
         if (a.n_seq == 0) continue;
         int rc = sh->dtype == TR_F32 ? tr_launch_prefix_attn_f32(a, sh->head_dim, toks * sh->n_q_heads, stream)
                                      : tr_launch_prefix_attn(a, sh->head_dim, wg_rows, any_split, toks * sh->n_q_heads, stream);

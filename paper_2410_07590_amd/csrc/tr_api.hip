@@ -689,12 +689,11 @@ size_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t 
     const int min_split_keys = std::max(KEY_TILE, tr_knob(TR_KNOB_MIN_SPLIT_KEYS, MIN_SPLIT_KEYS));
     int64_t base_items = 0;
     for (size_t r = r0; r < r1; ++r) base_items += (int64_t)((reqs[r].n_q + tpt - 1) / tpt) * sh->n_kv_heads;
-    int want_split = 1;
+    int want_split = 1; // pieces per request with which the launch fills the chip
     if (sh->dtype == TR_BF16 && base_items > 0 && base_items < target) want_split = (int)((target + base_items - 1) / base_items);
     if (want_split > MAX_SPLIT) want_split = MAX_SPLIT;
-    const int key_tile = wg_rows == 32 ? SHORT_UNIT : KEY_TILE; // the short-query kernel walks 128 keys a step
     std::vector<SplitPlan> cut(r1 - r0);
-    auto cut_alike = [&] {
+    auto cut_alike = [&](int key_tile) {
         for (size_t r = r0; r < r1; ++r) cut[r - r0] = cut_keys(reqs[r].kv_len, want_split, min_split_keys, key_tile);
     };
     auto partial_rows = [&] {
@@ -709,9 +708,9 @@ size_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t 
         partial_f32 = cut_short(reqs, r0, r1, sh->n_kv_heads, tpt, target, min_split_keys, many_allowed, &cut);
         if (partial_f32 && partial_bytes(sh, partial_rows(), true) > held) {
             partial_f32 = false;
-            cut_alike();
+            cut_alike(SHORT_UNIT); // what that kernel walks in a step
         }
-    } else cut_alike();
+    } else cut_alike(KEY_TILE);
     // A batch of requests of different lengths: one split count for all leaves workgroups of very different lengths,
     // and how the launch then packs onto the chip swings by tens of percent with the count.  Instead every request is
     // cut into pieces of about one common length, and that length is chosen by playing the launch through
@@ -723,8 +722,7 @@ size_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t 
         // order.
         std::vector<int64_t> key;
         key.reserve(8 + 2 * (r1 - r0));
-        for (int64_t x : {(int64_t)sh->n_q_heads, (int64_t)sh->n_kv_heads, (int64_t)sh->head_dim, (int64_t)wg_rows, (int64_t)min_split_keys,
-                          (int64_t)key_tile})
+        for (int64_t x : {(int64_t)sh->n_q_heads, (int64_t)sh->n_kv_heads, (int64_t)sh->head_dim, (int64_t)wg_rows, (int64_t)min_split_keys})
             key.push_back(x);
         for (size_t r = r0; r < r1; ++r) {
             key.push_back(reqs[r].n_q);
@@ -746,7 +744,7 @@ size_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t 
             for (size_t r = r0; r < r1; ++r) {
                 const ReqGeom& q = reqs[r];
                 if (q.n_q == 0) continue;
-                const SplitPlan sp = cut_keys(q.kv_len, (int)((double)q.kv_len / keys_per_item + 0.5), min_split_keys, key_tile);
+                const SplitPlan sp = cut_keys(q.kv_len, (int)((double)q.kv_len / keys_per_item + 0.5), min_split_keys, KEY_TILE);
                 cand[r - r0] = sp;
                 const int n_tiles = (q.n_q + tpt - 1) / tpt;
                 const int64_t n_doc = q.kv_len - q.n_q;
@@ -756,7 +754,7 @@ size_t plan_prefix(const tr_shape* sh, const std::vector<ReqGeom>& reqs, size_t 
                             const int64_t sb = (int64_t)sp_i * sp.split_len;
                             const int64_t last_tok = std::min<int64_t>((int64_t)(tile + 1) * tpt, q.n_q) - 1;
                             const int64_t se = std::min<int64_t>(std::min<int64_t>(sb + sp.split_len, q.kv_len), n_doc + last_tok + 1);
-                            item_tiles.push_back(se > sb ? (int)((se - sb + key_tile - 1) / key_tile) : 0);
+                            item_tiles.push_back(se > sb ? (int)((se - sb + KEY_TILE - 1) / KEY_TILE) : 0);
                         }
                 if (sp.n_split > 1) partial_bytes += (double)sp.n_split * q.n_q * sh->n_q_heads * (sh->head_dim * 2 + 8);
             }

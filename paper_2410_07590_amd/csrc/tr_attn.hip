@@ -310,17 +310,17 @@ template <int D> struct Acc {
     }
 };
 
-// Issue this wave's share of the direct global->LDS loads of tile [kt, kt+KROWS): K rows to kdst, V rows to vdst.
+// Issue this wave's share of the direct global->LDS loads of tile [kt, kt+KT): K rows to kdst, V rows to vdst.
 // AUX is the cache policy of the loads: 0 where other workgroups read the same tile soon (the row tiles of a long
 // query), DMA_STREAM (non-temporal) where every key is read exactly once (decode: 114 -> 100 us for 64 x 4096 rows;
 // the same hint on the long-query kernels, whose row tiles share keys through L2, cost 5-8 %).
 constexpr int DMA_STREAM = 2;
-template <int D, int NW, int KROWS = KT, int AUX = 0>
+template <int D, int NW, int AUX = 0>
 __device__ __forceinline__ void issue_tile(const __bf16* __restrict__ k, const __bf16* __restrict__ v, int64_t row_elems,
                                            int head_off, int kt, int key_clamp, LDS_AS char* kdst, LDS_AS char* vdst, int wave, int lane)
 {
     using G = Geo<D>;
-    constexpr int NI = KROWS / G::RPI;
+    constexpr int NI = KT / G::RPI;
     static_assert(NI % NW == 0, "tile loads must divide evenly over the waves");
     const int r_in = lane / G::CPR, pc = lane % G::CPR;
 #pragma unroll
@@ -543,7 +543,7 @@ __device__ __forceinline__ void issue_any(const __bf16* __restrict__ k, const __
 {
     const int64_t off = (int64_t)kt * w.row_elems;
     if (kt + KT - 1 <= w.key_clamp) tl.template tile<NS, AUX>((const char*)(k + off), (const char*)(v + off), stage);
-    else issue_tile<D, NW, KT, AUX>(k, v, w.row_elems, w.head_off, kt, w.key_clamp, smem + ring_k<D>(stage), smem + ring_v<D, NS>(stage), wave, lane);
+    else issue_tile<D, NW, AUX>(k, v, w.row_elems, w.head_off, kt, w.key_clamp, smem + ring_k<D>(stage), smem + ring_v<D, NS>(stage), wave, lane);
 }
 
 // Tiles 0 .. NS-2 in flight.  Stage NS-1 stays free until the tile loop's first iteration has passed its barrier.  Tiles that

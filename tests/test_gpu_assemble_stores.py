@@ -21,7 +21,8 @@ def test_both_sides_of_the_line(dtype, layout, kv_heads, head_dim, by, formed):
     from paper_2410_07590_amd import binding as B
     sh = synth.Shape(kv_heads, kv_heads, head_dim, dtype, 1e6, layout)
     row_bytes = 2 * kv_heads * head_dim * (2 if dtype == "bf16" else 4)
-    rows = -(-formed // row_bytes)
+    rows = formed // row_bytes if formed < THROUGH_MIN else -(-formed // row_bytes)
+    assert (rows * row_bytes >= THROUGH_MIN) == (formed >= THROUGH_MIN) and abs(rows * row_bytes - THROUGH_MIN) <= row_bytes
     lens = [1, 333, 1024, 47, 700]
     ids = []
     while rows - sum(lens[i] for i in ids) > 1024:

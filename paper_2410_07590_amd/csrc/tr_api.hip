@@ -528,6 +528,14 @@ int pick_wg_rows(const tr_shape* sh, int64_t max_rows_per_kv_head)
     return max_rows_per_kv_head >= 512 ? 256 : 128;
 }
 
+// The bf16 attention kernels step through the rows of a tile (64, of the short-query kernel's units 32) with 32-bit byte offsets.
+int check_row_width(const tr_shape* sh, int tile_rows)
+{
+    if (sh->dtype != TR_BF16 || (int64_t)sh->n_kv_heads * sh->head_dim * 2 * tile_rows <= (int64_t)1 << 32) return TR_OK;
+    return tr_fail(TR_ERR_UNSUPPORTED, "attention over rows of %lld bytes, at most %lld", (long long)sh->n_kv_heads * sh->head_dim * 2,
+                   ((long long)1 << 32) / tile_rows);
+}
+
 // How a request's keys are cut: n_split pieces of split_len keys (a multiple of the key tile).
 struct SplitPlan { int n_split; int64_t split_len; };
 
@@ -820,6 +828,9 @@ size_t prefix_ws_bytes(const tr_shape* sh, const std::vector<ReqGeom>& reqs, siz
 int run_prefix(const tr_shape* sh, const void* q, const void* k, const void* v, const int32_t* q_pos,
                const std::vector<ReqGeom>& reqs, void* out, void* ws, size_t ws_bytes, hipStream_t stream)
 {
+    int64_t max_rows = 0;
+    for (const ReqGeom& r : reqs) max_rows = std::max<int64_t>(max_rows, (int64_t)r.n_q * (sh->n_q_heads / sh->n_kv_heads));
+    if (int rc = check_row_width(sh, pick_wg_rows(sh, max_rows) == 32 ? 32 : 64)) return rc;
     const size_t held = ws && ((uintptr_t)ws & 255) == 0 ? ws_bytes : 0;
     TrPrefixArgs a;
     memset(&a, 0, sizeof a);
@@ -1078,6 +1089,7 @@ extern "C" int tr_prefill_attn_gather(const tr_store* store, const int32_t* chun
     if (rc) return rc;
     if (n_q == 0) return TR_OK;
     if (!q || !cache_k || !cache_v || !q_pos || !out) return tr_fail(TR_ERR_INVALID_ARG, "tr_prefill_attn_gather: NULL pointer");
+    if ((rc = check_row_width(sh, KEY_TILE))) return rc;
     if (p.n_doc + n_q > cache_capacity_rows) return tr_fail(TR_ERR_BAD_PLAN, "the cache holds %lld rows, the query tokens end at row %lld", (long long)cache_capacity_rows, (long long)(p.n_doc + n_q));
     const size_t need = gather_ws_bytes(sh, p, n_q);
     if (need > 0) {
@@ -1314,6 +1326,7 @@ extern "C" int tr_sequence_prefill_attn(const tr_shape* shape, const void* q, co
     if (total_tokens == 0) return TR_OK;
     if (!q || !k || !v || !seg_start || !pos || !out) return tr_fail(TR_ERR_INVALID_ARG, "tr_sequence_prefill_attn: NULL pointer");
     if (!k_rot_out) return tr_fail(TR_ERR_INVALID_ARG, "k_rot_out is required (it may alias k)");
+    if ((rc = check_row_width(shape, KEY_TILE))) return rc;
     hipStream_t s = (hipStream_t)stream;
     TrBlockDiagArgs a;
     memset(&a, 0, sizeof a);
@@ -1482,6 +1495,7 @@ extern "C" int tr_chunk_prefill_attn(const tr_shape* shape, const void* q, const
     if (max_chunk_len == 0 || max_chunk_len > total_tokens) return tr_fail(TR_ERR_INVALID_ARG, "max_chunk_len %d must be in [1, total_tokens]", max_chunk_len);
     if (!q || !k || !v || !cu_chunk_lens || !out) return tr_fail(TR_ERR_INVALID_ARG, "tr_chunk_prefill_attn: NULL pointer");
     if (!k_rot_out) return tr_fail(TR_ERR_INVALID_ARG, "k_rot_out is required (it may alias k)");
+    if ((rc = check_row_width(shape, KEY_TILE))) return rc;
     const size_t need = tr_chunk_prefill_attn_workspace_size(shape, total_tokens, max_chunk_len);
     if (!workspace) return tr_fail(TR_ERR_WORKSPACE, "workspace is NULL, %zu bytes needed", need);
     if (((uintptr_t)workspace & 255) != 0) return tr_fail(TR_ERR_WORKSPACE, "workspace is not 256-byte aligned");

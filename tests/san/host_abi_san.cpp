@@ -551,6 +551,40 @@ void decode_workspaces()
     }
 }
 
+// Rows of keys too wide for the kernels' offsets are refused before anything is launched.
+void wide_rows()
+{
+    tr_shape sh;
+    std::memset(&sh, 0, sizeof sh);
+    sh.head_dim = g_ex.head_dim = 128; sh.dtype = TR_BF16; sh.rope_base = 1e4;
+    alignas(256) static char buf[1 << 16];
+    const int32_t* i32 = (const int32_t*)buf;
+    const int64_t start[] = {0, 40};
+    for (int over = 0; over < 2; ++over) {
+        const int rc = over ? TR_ERR_UNSUPPORTED : TR_OK;
+        auto gives = [&](int got, const char* what) { REQUIRE(got == rc, "%s with %d heads returned %d", what, sh.n_kv_heads, got); };
+        const long before = g_ex.launches;
+        sh.n_q_heads = sh.n_kv_heads = (1 << 27) / 256 + over; // 32 rows of them are 4 GiB
+        gives(tr_decode_attn(&sh, buf, buf, buf, i32, start, 1, buf, nullptr, 0, nullptr), "decode");
+        gives(tr_prefill_attn(&sh, buf, buf, buf, i32, 32, 40, buf, nullptr, 0, nullptr), "short prefill");
+        sh.n_q_heads = sh.n_kv_heads = (1 << 26) / 256 + over; // 64 rows
+        gives(tr_prefill_attn(&sh, buf, buf, buf, i32, 33, 40, buf, nullptr, 0, nullptr), "prefill");
+        g_ex.src_rows = g_ex.dst_rows = 40;
+        g_ex.ws = buf;
+        g_ex.ws_bytes = sizeof buf;
+        gives(tr_sequence_prefill_attn(&sh, buf, buf, buf, i32, i32, nullptr, 40, buf, buf, nullptr, 0, nullptr), "sequence");
+        REQUIRE(tr_chunk_prefill_attn_workspace_size(&sh, 40, 40) <= sizeof buf, "scratch of 40 tokens");
+        gives(tr_chunk_prefill_attn(&sh, buf, buf, buf, i32, 1, 40, 40, buf, buf, buf, sizeof buf, nullptr), "chunks");
+        const int64_t rows[] = {0, 32}, off[] = {0, 32};
+        const int32_t id[] = {0};
+        tr_store* st = nullptr;
+        OK(tr_store_create(&sh, buf, buf, rows, 1, &st));
+        gives(tr_prefill_attn_gather(st, id, off, 1, TR_POS_COMPOSITE, buf, buf, buf, i32, 8, 40, buf, nullptr, 0, nullptr), "gather");
+        OK(tr_store_destroy(st));
+        REQUIRE(over == 0 || g_ex.launches == before, "a refused call launched something");
+    }
+}
+
 // More tokens than one launch holds: every row is covered once, in order, by launches of a legal size.
 void appends_of_many_tokens()
 {
@@ -605,6 +639,7 @@ int main(int argc, char** argv)
     argument_errors();
     appends_of_many_tokens();
     decode_workspaces();
+    wide_rows();
     const char* knobs[] = {"wg_rows", "target_items", "min_split_keys", "bd_piece_tiles"};
     const int values[][3] = {{0, 128, 32}, {0, 64, 2048}, {0, 64, 1024}, {0, 1, 8}};
     for (int i = 0; i < rounds; ++i) {

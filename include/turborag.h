@@ -157,7 +157,8 @@ int tr_kv_append_batched(const tr_shape* shape, const void* k_new, const void* v
  * out: device [n_q, n_q_heads, head_dim].  TR_BF16: bf16 MFMA with fp32 accumulation and fp32 softmax;
  * TR_F32: fp32 throughout.
  * workspace: device scratch of at least tr_prefill_attn_workspace_size() bytes, 256-byte aligned, used for
- * split-KV partial results; its contents are undefined afterwards.  n_q == 0 is a no-op.
+ * split-KV partial results; its contents are undefined afterwards.  Where keys are split to fill the chip these are held in
+ * fp16: values of v above 65504 overflow there, and magnitudes below some 1e-4 lose precision.  n_q == 0 is a no-op.
  * Errors: TR_ERR_INVALID_ARG (kv_len < n_q, null pointers), TR_ERR_SHAPE, TR_ERR_WORKSPACE; as in every attention call,
  * TR_ERR_UNSUPPORTED for bf16 rows of k of more than 64 MiB (128 MiB where n_q * n_q_heads / n_kv_heads <= 32). */
 size_t tr_prefill_attn_workspace_size(const tr_shape* shape, int32_t n_q, int64_t kv_len);

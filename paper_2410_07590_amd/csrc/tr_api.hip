@@ -556,9 +556,10 @@ SplitPlan cut_keys(int64_t kv_len, int want, int min_split_keys, int key_tile)
 // more than `target` workgroups.  Its workgroups are bound by the rate of a CU (2.1 us a unit for one of them, 2.6 where all
 // 256 CUs read), so one even piece per CU is best wherever the requests allow it: 17 requests of 7.7 k keys and 4 heads, 272
 // equal workgroups / 248: 67.1 / 53.6 us.  Where the longest piece leaves a CU with much more than its share, 1536 shorter
-// pieces, dealt out as slots get free, pay for their partial results: 25 requests of 154 to 6589 keys 78.1 / 64.0 us, 45 of 20 to
-// 2.7 k keys 75.2 / 52.5; but 31 to 57 short ones 19.1 / 20.1 .. 33.4 / 39.8.  In units, the excess that pays lies at an
-// eighth of the share and three units of fixed cost, and four more (the merge's launch) where nothing is split otherwise.
+// pieces, dealt out as slots get free, pay for their partial results.  us, the former / the latter, 8 heads: 25 requests of 154 to
+// 6589 keys 78.9 / 70.7, 45 of 20 to 2.7 k 70.4 / 53.9, 40 of 100 to 6 k 140 / 94.5, 64 of 1 k to 4 k 134 / 115; but 31 of 650 21.9 / 27.7,
+// 57 of 400 to 900 35.5 / 39.8, 17 of 7.7 k (4 heads) 51.8 / 55.0.  In units, the excess that pays lies at an eighth of the
+// share and three units of fixed cost, and four more (the merge's launch) where nothing is split otherwise.
 // Those 1536 pieces hold their partial results in fp32: requests are cut in them that one workgroup would have carried in fp32 to the
 // end, and fp16 knows less of bf16's range (values of 1e-6 came out 0.19 off, of 1e5 not finite).
 constexpr int SHORT_UNIT = 2 * KEY_TILE;

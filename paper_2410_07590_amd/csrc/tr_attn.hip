@@ -736,7 +736,8 @@ __device__ __forceinline__ void prologue(const __bf16* __restrict__ k, const __b
 // Write the wave's 32 x D accumulator as rows, straight from registers.
 //   PARTIAL = false: out[dst_row][:] = bf16(O / l)       PARTIAL = true: ws_o[dst_row][:] = fp16(O / l)
 // A partial is normalised by its own denominator, so it is a convex combination of V rows and fp16 (11 bits,
-// 8 times finer than the bf16 result) holds it; the merge weighs it with l again.
+// 8 times finer than the bf16 result) holds it where V is in fp16's range, above some 1e-4 and below 65504; the merge weighs it
+// with l again.
 // Lanes c and c + 32 hold alternate groups of four channels of row c.  Two swaps of the vector unit give each of them
 // eight neighbouring channels, so a lane stores 16 bytes and a row receives 32 contiguous bytes per instruction.  An
 // epilogue is pure latency at the end of a workgroup, so what counts is how short its dependent chain is: staging the rows
@@ -1028,14 +1029,17 @@ __global__ __launch_bounds__(64 * GATHER_NW, 2) void gather_attn_kernel(const Tr
 // leave three of four waves idle.  Here all four waves hold the SAME rows and split the keys instead: wave w owns
 // keys [32 w, 32 w + 32) of every 128, and the four partial results are merged through LDS at the end.
 //
-// Bound by the stream of keys and values, whose rate depends on how much of it is on its way: a bare ring of loads over 537 MB
-// reads 5.6 TB/s with 16 KB in flight per CU, 7.1 with 24, 6.7 with 32 and 6.3 with 48 and more, where the requests of 256
-// CUs queue in front of the memory.  So a wave keeps at most SHORT_FLIGHT loads of 1 KB on their way, and refills its own units
-// as soon as their operands are read: no barrier, and no stretch in which nothing is on its way.  (Two stages of a tile
-// shared by the waves, a barrier each: the values' reads waited for every load of the next tile.)  With one unit of K and
-// one of V per wave two workgroups fit a CU, and one reads while the other starts or merges.  64 tokens over 4096 keys each
-// (539 MB): 94.3 us with the shared stages, 82.5 / 84.2 / 86.4 / 91.6 with 5 / 6 / 7 / 8 loads; 5 tokens over 300 to 3000
-// keys 18.3, then 17.6 / 17.5 / 17.3 / 17.2; between 6 and 5 lie 2 to 4 % at most sizes between those.
+// Bound by the stream of keys and values, whose rate depends on how much of it is on its way: a bare ring of loads over 537 MB in
+// these rows' order reads 5.6 / 6.7 / 7.1 / 6.8 / 6.4 TB/s with 12 / 16 / 20 / 24 / 32 KB and more in flight per CU
+// (profiles/load_rates.md).  So a wave refills its own units as soon as their operands are read, with at most SHORT_FLIGHT loads of
+// 1 KB on their way: no barrier, and no stretch in which nothing is on its way.  (The first units, 2 D / 16 loads, leave together:
+// nothing else would be asked for while the queries are rotated.  Two stages of a tile shared by the waves, a barrier
+// each: the values' reads waited for every load of the next tile.)  With one unit of K and one of V per wave two workgroups
+// fit a CU, and one reads while the other starts or merges.
+// us with 5 / 6 / 7 / 8 loads: 64 tokens over 4096 keys each (539 MB; 94.3 with the shared stages) 82.5 / 84.4 / 86.5 / 90.6, 32
+// over 8192 (8 heads) 154.5 / 158.3 / 162.0 / 170.2, but 32 over 1000 to 3000 56.5 / 53.7 / 53.7 / 54.2, 12 over 600 to 6000 40.2 /
+// 38.9 / 39.3 / 40.4, and no clear difference where launch and prologue are most of the call or the pieces many.  Six is within
+// 2.5 % of the best at these, five and seven are not.
 constexpr int SHORT_NW = 4, SHORT_KT = 32 * SHORT_NW;
 constexpr int SHORT_FLIGHT = 6;
 template <int D> constexpr int short_unit_bytes() { return 32 * D * 2; }
@@ -1327,13 +1331,17 @@ __global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPr
         const int rows_s = sd.n_q * g;
         const int64_t prow = (int64_t)sd.ws_row0 + (int64_t)(split * a.n_kv_heads + kvh) * rows_s + r_tok * g + r_head;
         const int64_t at = prow * D + CPT * j;
+        f32x4 x[CPT / 4];
 #pragma unroll
-        for (int e4 = 0; e4 < CPT / 4; ++e4) {
-            f32x4 x;
+        for (int e4 = 0; e4 < CPT / 4; ++e4)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = o[4 * e4 + e] * inv;
-            if (a.partial_f32) *(f32x4*)((float*)a.ws_o + at + 4 * e4) = x;
-            else *(f16x4*)(a.ws_o + at + 4 * e4) = __builtin_convertvector(x, f16x4);
+            for (int e = 0; e < 4; ++e) x[e4][e] = o[4 * e4 + e] * inv;
+        if (a.partial_f32) {
+#pragma unroll
+            for (int e4 = 0; e4 < CPT / 4; ++e4) *(f32x4*)((float*)a.ws_o + at + 4 * e4) = x[e4];
+        } else {
+#pragma unroll
+            for (int e4 = 0; e4 < CPT / 4; ++e4) *(f16x4*)(a.ws_o + at + 4 * e4) = __builtin_convertvector(x[e4], f16x4);
         }
         if (j == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(L > 0.0f ? M : -INFINITY, L);
     }

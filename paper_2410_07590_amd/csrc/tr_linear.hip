@@ -244,8 +244,9 @@ __global__ __launch_bounds__(256) void linear_combine_kernel(const TrLinearArgs 
 }
 
 // All of k in one workgroup, so that no partial sums are left over: a tile of 16 XB rows of x and 16 WB features.  What bounds it
-// is how fast a CU takes bytes in through the direct loads, from HBM or L2 alike: 46 .. 51 GB/s over launches of 12 to 16 us with
-// nothing but the loads in them, 57 .. 62 without the 2.5 us of an empty launch.  A workgroup asks for (XB + WB) * 16 rows of K
+// is how fast a CU takes bytes in through the direct loads, from HBM or L2 alike: with nothing but the loads and the exchange left
+// (profiles/load_rates.md) 4608 x 3584 and 3584 x 3584 at 64 rows take 13.5 and 11.2 us of their 14.2 and 11.9, 41 .. 43 GB/s
+// per CU, some 50 without an empty launch.  A workgroup asks for (XB + WB) * 16 rows of K
 // values, and the best tile is the one that keeps the largest share per CU small.  The row tiles of one feature tile run on the same
 // XCD, whose L2 serves the weights to all but the first of them.
 // k is walked in chunks of 128 values through a ring of LDS slots; of a chunk each of the four waves multiplies 32 values (one

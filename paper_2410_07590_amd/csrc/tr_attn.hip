@@ -1358,7 +1358,7 @@ __global__ __launch_bounds__(64 * SHORT_NW, 2) void short_attn_kernel(const TrPr
 // GROUPS: sets of D/8 lanes that share a row, each merging every GROUPS-th split.  A lane spends sixteen vector instructions
 // on a partial, so one group walks 64 splits in some 2 us of issue alone (49 splits of 32 rows: 7.3 us, with half a wave of
 // four-channel lanes 7.8, with a whole wave of four groups 4.9).
-// PART: type of the partials.
+// F32: the partials are fp32, not fp16.
 template <bool MAX, int LANES> __device__ __forceinline__ float row_reduce(float x)
 {
     static_assert(LANES == 8 || LANES == 16 || LANES == 64, "");
@@ -1377,7 +1377,7 @@ template <bool MAX, int LANES> __device__ __forceinline__ float row_reduce(float
 constexpr int COMBINE_THREADS = 128; // two waves: the few thousand rows of one request then reach every compute unit
 template <int D, int GROUPS> constexpr int combine_rows() { return COMBINE_THREADS / (D / 8 * GROUPS); } // output rows per workgroup
 
-template <int D, int SPLITS, int GROUPS, class PART>
+template <int D, int SPLITS, int GROUPS, bool F32>
 __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const TrPrefixArgs a, int total_rows)
 {
     constexpr int LPG = D / 8, LPR = LPG * GROUPS; // lanes per group and per row
@@ -1417,6 +1417,7 @@ __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const TrPrefix
         ml[k] = make_float2(-INFINITY, 0.0f);
         if (lane_r + LPR * k < n_split) ml[k] = *(const float2*)(a.ws_ml + (prow0 + (lane_r + LPR * k) * pstride) * 2);
     }
+    typedef std::conditional_t<F32, float, _Float16> PART;
     typedef PART Piece __attribute__((ext_vector_type(8)));
     const PART* base = (const PART*)a.ws_o + prow0 * D + 8 * piece;
     Piece x[PER_ROUND];
@@ -1648,7 +1649,7 @@ int blockdiag_dispatch(const TrBlockDiagArgs& a, int head_dim, int wg_rows, hipS
 template <int D, int SPLITS, int GROUPS> static void launch_combine_d(const TrPrefixArgs& a, int total_rows, hipStream_t s)
 {
     constexpr int per_block = combine_rows<D, GROUPS>();
-    auto kern = a.partial_f32 ? combine_kernel<D, SPLITS, GROUPS, float> : combine_kernel<D, SPLITS, GROUPS, _Float16>;
+    auto kern = a.partial_f32 ? combine_kernel<D, SPLITS, GROUPS, true> : combine_kernel<D, SPLITS, GROUPS, false>;
     hipLaunchKernelGGL(kern, dim3((unsigned)(((int64_t)total_rows + per_block - 1) / per_block)), dim3(COMBINE_THREADS), 0, s, a, total_rows);
 }
 // A wave for each row where lanes of one group would walk the splits in more than one round of eight, one after the other,

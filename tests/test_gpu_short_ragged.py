@@ -122,3 +122,18 @@ def test_rows_without_weight(layout, lens):
         assert bool((attend(B, sh, q, k, v, pos, cu, start, None)[-1] == 0).all())   # the same batch, uncut
     k[last, :, 0] = 0.0
     assert worst_error(sh, out[:-1], q[:-1], k, v, pos[:-1], cu[:-1], start[:-1]) < 1e-2
+
+
+def test_static_array_holds_the_many_pieces():
+    """One request whose pairs leave CUs idle (96 heads of up to 256 CUs, 24 MB of partials): the library's own array, same bits."""
+    from paper_2410_07590_amd import binding as B
+    sh = synth.Shape(96, 96, 128, "bf16", 1e4, 0)
+    q, k, v, pos, cu, start = inputs(sh, [8192], 32, 1e-6, 5)
+    need = B.tr_prefill_attn_workspace_size(H.gpu_shape(B, sh), 32, 8192)
+    assert 256 * 32 * (128 * 2 + 8) < need <= B.tr_prefill_attn_static_scratch_bytes()
+    want = attend(B, sh, q, k, v, pos, cu, start, B.workspace(need))
+    assert worst_error(sh, want, q, k, v, pos, cu, start) < 1e-2
+    got = torch.full_like(q, float("nan"))
+    B.tr_prefill_attn_static(H.gpu_shape(B, sh), q, k, v, torch.from_numpy(pos.astype(np.int32)).cuda(), 8192, got)
+    torch.cuda.synchronize()
+    assert torch.equal(H.bits_t(got), H.bits_t(want))
